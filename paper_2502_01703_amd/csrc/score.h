@@ -1,0 +1,41 @@
+// Shared between the scoring kernels (score.hip, score_wide.hip).
+#pragma once
+#include "common.h"
+
+namespace qless {
+
+struct ScoreArgs {
+    const unsigned char *tc[QLESS_MAX_CHECKPOINTS];
+    const unsigned char *vc[QLESS_MAX_CHECKPOINTS];
+    const float *tr[QLESS_MAX_CHECKPOINTS];
+    const float *vr[QLESS_MAX_CHECKPOINTS];
+    float eta[QLESS_MAX_CHECKPOINTS];
+    int C;
+    int64_t N;
+    int32_t M, k;                              // bfloat16 rows: k is their length in bytes
+    float *score, *full;
+};
+
+__device__ inline float neg_inf() { return __uint_as_float(0xFF800000u); }
+// unsigned keys that order like the fp32 values; 0 lies below every value's key
+__device__ inline unsigned int f32_order_key(float f) {
+    const unsigned int u = __float_as_uint(f);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+__device__ inline float f32_from_order_key(unsigned int k) {
+    return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
+}
+
+constexpr size_t kLdsPerCU = 160 * 1024;       // LDS of one compute unit
+int compute_units();                           // of the current device (256 on MI355X)
+
+// score.hip: score[i] = the value of key smax[i], keys cleared
+void launch_score_finish(unsigned int *smax, int64_t N, float *score, hipStream_t st);
+
+// score_wide.hip: 8- and 4-bit codes and bfloat16 rows (bits = 16) against more than 64 validation vectors.
+size_t wide_workspace(int64_t N, int32_t M, int64_t row_bytes, int C);
+// prepare = false: the workspace still holds the pre-pass of an earlier launch with the same validation
+// side, laid out for plan_rows >= a.N train rows (the finish kernel leaves the row maxima cleared)
+qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st, bool prepare = true, int64_t plan_rows = 0);
+
+}  // namespace qless

@@ -18,24 +18,9 @@
 // The popcount kernels give a workgroup a block of train rows and walk it over all validation
 // tiles with the running row maximum in registers; the MFMA kernel gives every (train tile, val
 // tile) pair its own workgroup and combines the row maxima with an exact integer atomicMax.
-#include "common.h"
-#include <atomic>
+#include "score.h"
 
 namespace qless {
-
-struct ScoreArgs {
-    const unsigned char *tc[QLESS_MAX_CHECKPOINTS];
-    const unsigned char *vc[QLESS_MAX_CHECKPOINTS];
-    const float *tr[QLESS_MAX_CHECKPOINTS];
-    const float *vr[QLESS_MAX_CHECKPOINTS];
-    float eta[QLESS_MAX_CHECKPOINTS];
-    int C;
-    int64_t N;
-    int32_t M, k;
-    float *score, *full;
-};
-
-__device__ inline float neg_inf() { return __uint_as_float(0xFF800000u); }
 
 // ------------------------------------------------------------------------------------------
 // 1-bit / 2-bit: popcount kernel.  Thread grid TY x TX; thread (ty, tx) owns train rows
@@ -250,14 +235,6 @@ struct ScorePrep {                             // workspace views (device pointe
     int32_t vrow;                              // bytes per expanded validation row: kp, or kp / 2 for 1-bit (FP4 codes)
 };
 
-__device__ inline unsigned int f32_order_key(float f) {
-    const unsigned int u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ inline float f32_from_order_key(unsigned int k) {
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
-}
-
 // position p (0..kp) of an expanded val row -> element index of the code vector
 template <int BITS>
 __device__ inline int val_source_element(int p) {
@@ -358,6 +335,12 @@ __global__ void score_finish_kernel(unsigned int *smax, int64_t N, float *score)
         score[i] = f32_from_order_key(smax[i]);
         smax[i] = 0u;
     }
+}
+
+void launch_score_finish(unsigned int *smax, int64_t N, float *score, hipStream_t st) {
+    int64_t blocks = (N + 255) / 256;
+    if (blocks > 4096) blocks = 4096;
+    hipLaunchKernelGGL(score_finish_kernel, dim3((unsigned)blocks), dim3(256), 0, st, smax, N, score);
 }
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -1121,16 +1104,9 @@ struct MfmaShape {
 // to the matrix core are eight bfloat16 values for v_mfma_f32_32x32x16_bf16 (same bytes, same
 // addresses as the int8 operands), the accumulator is fp32 and the epilogue is acc += eta * D:
 // the 16-bit LESS comparator (Eq.(2),(3)) on pre-normalised rows.
-// AGG: instead of score / full the kernel writes, per train row, the maximum or the left-to-right fp32
-// mean of acc over each group of consecutive validation columns (gout[N][T]).  One workgroup then takes a
-// train tile through all validation tiles in order; after each tile the sums go through LDS (the stage
-// ring is idle then) to one thread per train row, which walks the tile's columns in order and carries
-// the running value of the open group in a register.
-struct AggArgs { GroupEnds ge; int T, mean; float *gout; };
-
-template <int BITS, int WR, int WC, int WX, int NW, bool F16 = false, bool VH = false, bool AGG = false>
+template <int BITS, int WR, int WC, int WX, int NW, bool F16 = false, bool VH = false>
 __global__ void __launch_bounds__(64 * NW, (WR == 1 ? 4 : 2))
-score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles, AggArgs ag) {
+score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles) {
     static_assert(!F16 || BITS == 8, "bfloat16 rows use the byte geometry of the 8-bit codes");
     using Sh = MfmaShape<BITS, WR, WC, WX, NW, VH>;
     constexpr int kMT = Sh::MT;
@@ -1145,9 +1121,8 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles, AggArgs ag) 
     const int64_t id = blockIdx.x;
     const int xcd = (int)(id & 7);
     const int64_t j = id >> 3;
-    const int vt_first = AGG ? 0 : (int)(j % vtiles);
-    const int vt_end = AGG ? vtiles : vt_first + 1;
-    const int64_t tt = AGG ? id : (j / vtiles) * 8 + xcd;
+    const int vt = (int)(j % vtiles);
+    const int64_t tt = (j / vtiles) * 8 + xcd;
     if (tt >= ttiles) return;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1156,7 +1131,7 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles, AggArgs ag) 
     const int wy = wave / WX, wx = wave % WX;
     const int trow = wy * 32 * WR, vcol = wx * 32 * WC;   // this wave's corner inside the tile
     const int64_t row0 = tt * kMT;
-    int v0 = vt_first * VT;                             // advanced per validation tile (AGG)
+    const int v0 = vt * VT;
     const int64_t cb = (int64_t)a.k * BITS / 8;
     const int nstages = (a.k + KE - 1) / KE;            // <= kp / KE: the expanded val rows cover every stage
     if (tid < kMT) s_rowmax[tid] = 0u;
@@ -1223,13 +1198,6 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles, AggArgs ag) 
         else b_base[c] = TRAIN_BYTES + Rv * Sh::VROWB + (sw >> 1) * 32 + ((half ^ (sw & 1)) * 16);
     }
 
-    // AGG: thread t < kMT owns train row t of the tile: index and running value of its open group
-    int ag_group = 0;
-    float ag_run = 0.0f;
-    static_assert(!AGG || (!Sh::VPACKED && !VH), "group aggregation runs on the wide tiles");
-
-  for (int vt = vt_first; vt < vt_end; ++vt) {
-    v0 = vt * VT;
     float facc[WR][WC][16];
 #pragma unroll
     for (int b = 0; b < WR; ++b)
@@ -1414,52 +1382,6 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles, AggArgs ag) 
                                 acc[b][c] = mfma_fp4(af[b], bf[c], acc[b][c]);
                     }
                 }
-            } else if constexpr (!Sh::NARROW) {
-                // int8 (or bfloat16) operands, wide tiles: the fragments of K step ks + 1 are requested before the
-                // matrix instructions of step ks (scheduling barriers keep that order)
-                i32x4 aq[WR], bq[WC], an[WR], bn[WC];
-                auto load_step = [&](int ks, i32x4 (&fa)[WR], i32x4 (&fb)[WC]) {
-#pragma unroll
-                    for (int b = 0; b < WR; ++b) {
-                        if (BITS == 8) {
-                            fa[b] = *(const i32x4 *)(sb + (a_base[b] ^ (ks << 5)));
-                        } else {
-                            const uint2 pa = *(const uint2 *)(sb + (a_base[b] ^ (ks << 4)));
-                            fa[b] = i32x4{(int)pa.x, (int)pa.y, 0, 0};
-                        }
-                    }
-#pragma unroll
-                    for (int c = 0; c < WC; ++c) fb[c] = *(const i32x4 *)(sb + (b_base[c] ^ (ks << 5)));
-                };
-                load_step(0, aq, bq);
-#pragma unroll
-                for (int ks = 0; ks < KE / 32; ++ks) {
-                    if (ks + 1 < KE / 32) load_step(ks + 1, an, bn);
-                    __builtin_amdgcn_sched_barrier(0);
-                    i32x4 af[WR];
-#pragma unroll
-                    for (int b = 0; b < WR; ++b) {
-                        if (BITS == 8) {
-                            af[b] = aq[b];
-                        } else {
-                            const unsigned int px = (unsigned int)aq[b][0], py = (unsigned int)aq[b][1];
-                            af[b][0] = (int)((px << 4) & 0xF0F0F0F0u); af[b][1] = (int)(px & 0xF0F0F0F0u);
-                            af[b][2] = (int)((py << 4) & 0xF0F0F0F0u); af[b][3] = (int)(py & 0xF0F0F0F0u);
-                        }
-                    }
-#pragma unroll
-                    for (int b = 0; b < WR; ++b)
-#pragma unroll
-                        for (int c = 0; c < WC; ++c)
-                            acc[b][c] = mfma_step<F16>(af[b], bq[c], acc[b][c]);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (ks + 1 < KE / 32) {
-#pragma unroll
-                        for (int b = 0; b < WR; ++b) aq[b] = an[b];
-#pragma unroll
-                        for (int c = 0; c < WC; ++c) bq[c] = bn[c];
-                    }
-                }
             } else {
 #pragma unroll
                 for (int ks = 0; ks < KE / 32; ++ks) {
@@ -1518,39 +1440,6 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles, AggArgs ag) 
                 }
             }
     }
-    if constexpr (AGG) {
-        // the tile's sums go to LDS as [kMT][VT + 1] floats (odd stride: a wavefront's rows fall in different
-        // banks); every copy of the tile has landed and every wavefront has read its last stage by now
-        constexpr int LD = VT + 1;
-        float *tile = (float *)smem;
-        __syncthreads();
-#pragma unroll
-        for (int b = 0; b < WR; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int rloc = trow + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-#pragma unroll
-                for (int c = 0; c < WC; ++c) tile[rloc * LD + vcol + 32 * c + l32] = facc[b][c][v];
-            }
-        __syncthreads();
-        if (tid < kMT && row0 + tid < a.N) {
-            const float *trowp = tile + tid * LD;
-            const int ncol = a.M - v0 < VT ? a.M - v0 : VT;
-            for (int jc = 0; jc < ncol; ++jc) {
-                const int col = v0 + jc;
-                const int g0 = ag_group ? ag.ge.end[ag_group - 1] : 0, g1 = ag.ge.end[ag_group];
-                const float x = trowp[jc];
-                if (ag.mean) ag_run = __fadd_rn(col == g0 ? 0.0f : ag_run, x);
-                else ag_run = (col == g0 || x > ag_run) ? x : ag_run;
-                if (col == g1 - 1) {
-                    ag.gout[(row0 + tid) * ag.T + ag_group] = ag.mean ? __fdiv_rn(ag_run, (float)(g1 - g0)) : ag_run;
-                    ++ag_group;
-                }
-            }
-        }
-        __syncthreads();                             // the next tile's copies overwrite the buffer
-        continue;
-    }
     // tile epilogue: optional full matrix, row maxima over this val tile
 #pragma unroll
     for (int b = 0; b < WR; ++b)
@@ -1577,13 +1466,11 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles, AggArgs ag) 
         __syncthreads();
         if (tid < kMT && row0 + tid < a.N && s_rowmax[tid] != 0u) atomicMax(&w.smax[row0 + tid], s_rowmax[tid]);
     }
-  }
 }
 
-constexpr size_t kLdsPerCU = 160 * 1024;       // LDS of one compute unit
 constexpr size_t kStaticLds = 1024;            // s_rowmax
 // Compute units of the current device (256 on MI355X).
-static int compute_units() {
+int compute_units() {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
@@ -1592,12 +1479,12 @@ static int compute_units() {
 }
 
 struct MfmaPlan { int32_t vt, Mp, kp; size_t off_vw, off_vbias, off_smax, total; };
-static MfmaPlan mfma_plan(int64_t N, int32_t M, int32_t k, int bits, int C, bool wide128 = false) {
+static MfmaPlan mfma_plan(int64_t N, int32_t M, int32_t k, int bits, int C) {
     MfmaPlan p{};
-    p.vt = (M > 64 || wide128) ? 128 : (M > 32 ? 64 : 32);
+    p.vt = M > 64 ? 128 : (M > 32 ? 64 : 32);
     // sign codes: 512 x 96 tiles (64 x 96 per wave) where 96-wide tiles pad the validation set less than
     // 128-wide ones (M = 285: 288 instead of 384 columns)
-    if (!wide128 && bits == 1 && M > 64 && (M + 95) / 96 * 96 < (M + 127) / 128 * 128) p.vt = 96;
+    if (bits == 1 && M > 64 && (M + 95) / 96 * 96 < (M + 127) / 128 * 128) p.vt = 96;
     p.Mp = (M + p.vt - 1) / p.vt * p.vt;
     const int ke = narrow_stage_elements(bits, p.vt);                 // MfmaShape::KE of the shape used
     p.kp = (k + ke - 1) / ke * ke;
@@ -1610,6 +1497,13 @@ static MfmaPlan mfma_plan(int64_t N, int32_t M, int32_t k, int bits, int C, bool
     p.off_smax = o; o += (size_t)(N > 0 ? N : 1) * 4;
     p.total = o;
     return p;
+}
+// Workspace of the tile kernels (bfloat16 rows: bits = 8 and k their length in bytes): 8- and 4-bit codes and
+// bfloat16 rows against more than 64 validation vectors go to score_wide.hip, which lays it out differently.
+static size_t tiles_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
+    const size_t t = mfma_plan(N, M, k, bits, C).total;
+    const size_t w = bits >= 4 && M > 64 ? wide_workspace(N, M, (int64_t)k * bits / 8, C) : 0;
+    return t > w ? t : w;
 }
 // The bit planes are copied in 16-byte chunks: k must be a multiple of 128 for the 1-/2-bit codes.
 // With at most 8 validation vectors those codes never take this path (and never need its
@@ -1639,31 +1533,8 @@ static qless_status launch_mfma_shape(const ScoreArgs &a, const ScorePrep &w, in
     const int64_t grid = 8 * (int64_t)vtiles * ((ttiles + 7) / 8);
     if (grid > 0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
     hipLaunchKernelGGL((score_mfma_kernel<BITS, WR, WC, WX, NW, F16, VH>), dim3((unsigned)grid), dim3(64 * NW), lds, st, a, w,
-                       (int)ttiles, vtiles, AggArgs{});
+                       (int)ttiles, vtiles);
     return QLESS_OK;
-}
-
-// Wide tiles with the group aggregation in the epilogue: one workgroup per train tile.
-template <int BITS>
-static qless_status launch_mfma_groups(const ScoreArgs &a, void *ws, const AggArgs &ag, hipStream_t st) {
-    using Sh = MfmaShape<BITS, 2, 2, 2, 8, false>;
-    const MfmaPlan p = mfma_plan(a.N, a.M, a.k, BITS, a.C, true);               // 128-wide validation tiles
-    ScorePrep w{};
-    unsigned char *base = (unsigned char *)ws;
-    w.vexp = (int8_t *)base; w.vw = (float *)(base + p.off_vw); w.vbias = (int32_t *)(base + p.off_vbias);
-    w.smax = (unsigned int *)(base + p.off_smax); w.Mp = p.Mp; w.kp = p.kp;
-    w.vrow = BITS <= 2 ? p.kp / 2 : p.kp;
-    hipLaunchKernelGGL((score_prepare_kernel<BITS, false>), dim3((unsigned)p.Mp, (unsigned)a.C), dim3(256), 0, st, a, w);
-    constexpr int kMaxDynamic = (int)kLdsPerCU - 4 * Sh::MT;
-    QLESS_LDS_KERNEL((score_mfma_kernel<BITS, 2, 2, 2, 8, false, false, true>), kMaxDynamic);
-    size_t lds = (size_t)Sh::NBUF * Sh::BUF;
-    const size_t tile = (size_t)Sh::MT * (Sh::VT + 1) * sizeof(float);
-    if (tile > lds) lds = tile;
-    if (lds > (size_t)kMaxDynamic) return QLESS_ERR_DEVICE;
-    const int64_t ttiles = (a.N + Sh::MT - 1) / Sh::MT;
-    hipLaunchKernelGGL((score_mfma_kernel<BITS, 2, 2, 2, 8, false, false, true>), dim3((unsigned)ttiles), dim3(64 * 8), lds, st,
-                       a, w, (int)ttiles, p.Mp / Sh::VT, ag);
-    return launch_status();
 }
 
 // Few validation vectors: every workgroup streams its train rows at the same pace, so the launch
@@ -1697,14 +1568,15 @@ static NarrowChoice choose_narrow(int64_t N) {
 template <int BITS, bool F16 = false>
 static qless_status launch_mfma(const ScoreArgs &a, void *ws, hipStream_t st, bool prepare = true, int64_t plan_rows = 0) {
     const MfmaPlan p = mfma_plan(plan_rows > 0 ? plan_rows : a.N, a.M, a.k, BITS, a.C);
-    ScorePrep w{};
-    unsigned char *base = (unsigned char *)ws;
-    w.vexp = (int8_t *)base; w.vw = (float *)(base + p.off_vw); w.vbias = (int32_t *)(base + p.off_vbias);
-    w.smax = (unsigned int *)(base + p.off_smax); w.Mp = p.Mp; w.kp = p.kp;
     // a small datastore leaves most compute units without a 256 x 128 tile: 128 x 64 tiles fill four times as
     // many (the expanded validation rows are the same for both shapes; the sign codes' narrow shape stages the
     // packed validation rows itself)
     const bool small = !F16 && p.vt == 128 && ((a.N + 255) / 256) * (p.Mp / 128) * 2 <= compute_units();
+    if (BITS >= 4 && p.vt == 128 && !small) return launch_wide(a, F16 ? 16 : BITS, ws, st, prepare, plan_rows);
+    ScorePrep w{};
+    unsigned char *base = (unsigned char *)ws;
+    w.vexp = (int8_t *)base; w.vw = (float *)(base + p.off_vw); w.vbias = (int32_t *)(base + p.off_vbias);
+    w.smax = (unsigned int *)(base + p.off_smax); w.Mp = p.Mp; w.kp = p.kp;
     w.vrow = BITS == 1 ? (p.vt > 64 && !small ? p.kp / 2 : 0) : (BITS == 2 ? p.kp / 2 : p.kp);
     if (prepare)
         hipLaunchKernelGGL((score_prepare_kernel<BITS, F16>), dim3((unsigned)p.Mp, (unsigned)a.C), dim3(256), 0, st, a, w);
@@ -1713,7 +1585,8 @@ static qless_status launch_mfma(const ScoreArgs &a, void *ws, hipStream_t st, bo
         if constexpr (BITS == 1) rc = launch_mfma_shape<BITS, 2, 3, 1, 8, F16>(a, w, 0, st);
         else rc = QLESS_ERR_UNSUPPORTED;
     } else if (p.vt == 128) {
-        if (small) rc = launch_mfma_shape<BITS, 1, 2, 1, 4, F16>(a, w, 0, st);
+        if constexpr (BITS >= 4) rc = launch_mfma_shape<BITS, 1, 2, 1, 4, F16>(a, w, 0, st);
+        else if (small) rc = launch_mfma_shape<BITS, 1, 2, 1, 4, F16>(a, w, 0, st);
         else rc = launch_mfma_shape<BITS, 2, 2, 2, 8, F16>(a, w, 0, st);
     }
     else if (p.vt == 64) {
@@ -1731,11 +1604,7 @@ static qless_status launch_mfma(const ScoreArgs &a, void *ws, hipStream_t st, bo
         else rc = launch_mfma_shape<BITS, 1, 1, 1, 4, F16>(a, w, c.per_cu, st);
     }
     if (rc != QLESS_OK) return rc;
-    if (a.score) {
-        int64_t blocks = (a.N + 255) / 256;
-        if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(score_finish_kernel, dim3((unsigned)blocks), dim3(256), 0, st, w.smax, a.N, a.score);
-    }
+    if (a.score) launch_score_finish(w.smax, a.N, a.score, st);
     return launch_status();
 }
 
@@ -1980,7 +1849,7 @@ static MixedPlan mixed_plan(int64_t N, int32_t M, int32_t k, int C) {
     size_t o = (size_t)C * (size_t)p.rows * (size_t)k * 2;
     o = (o + 255) & ~(size_t)255;
     p.off_tiles = o;
-    p.total = o + mfma_plan(p.rows, M, 2 * k, 8, C).total;
+    p.total = o + tiles_workspace(p.rows, M, 2 * k, 8, C);
     return p;
 }
 
@@ -2051,7 +1920,7 @@ extern "C" size_t qless_score_workspace(int64_t N, int32_t M, int32_t k, int bit
         if (perm > need) need = perm;
     }
     if (!use_mfma_path(bits, M, k)) return need;
-    const size_t tiles = mfma_plan(N, M, k, bits, C).total;
+    const size_t tiles = tiles_workspace(N, M, k, bits, C);
     return tiles > need ? tiles : need;
 }
 
@@ -2090,7 +1959,7 @@ extern "C" qless_status qless_score(const void *const *train_codes, const float 
         return launch_stream_mfma32(a, ws, st);
     }
     if (use_mfma_path(bits, M, k)) {
-        const size_t need = mfma_plan(N, M, k, bits, C).total;
+        const size_t need = tiles_workspace(N, M, k, bits, C);
         if (!ws || ws_bytes < need) return QLESS_ERR_WORKSPACE;
         if ((uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
         if (N > (int64_t)0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
@@ -2114,16 +1983,23 @@ extern "C" qless_status qless_score(const void *const *train_codes, const float 
     return launch_status();
 }
 
-// Influence aggregated over groups of validation columns without the N x M matrix in memory.
-static bool groups_fused(int32_t M, int32_t k, int bits) { return M > 64 && (bits >= 4 || k % 128 == 0); }
+// Influence aggregated over groups of validation columns: the matrix passes through the workspace, at most
+// kGroupsMatrix bytes of it at a time.  (One workgroup walking a train tile through all validation tiles, with the
+// aggregation as its epilogue, avoids the matrix but leaves the chip to whole rounds of 256-row tiles:
+// 270 000 x 285 at 4 bits 4.7 ms, of which the matrix, written and read once, would be 0.15 ms.)
+constexpr size_t kGroupsMatrix = (size_t)2 << 30;
+// train rows per block: a multiple of every tile height and of what keeps the code pointers 16-byte aligned
+static int64_t groups_block_rows(int64_t N, int32_t M) {
+    const int64_t fit = (int64_t)(kGroupsMatrix / ((size_t)M * sizeof(float))) / 1536 * 1536;
+    const int64_t rows = fit < 1536 ? 1536 : fit;
+    return N < rows ? N : rows;
+}
+static size_t groups_matrix_bytes(int64_t rows, int32_t M) { return ((size_t)rows * (size_t)M * sizeof(float) + 255) & ~(size_t)255; }
 
 extern "C" size_t qless_score_groups_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
     if (N < 0 || M < 1 || k <= 0 || C < 1 || !valid_bits(bits)) return 0;
-    if (groups_fused(M, k, bits)) return mfma_plan(N, M, k, bits, C, true).total;
-    // few validation vectors (or bit planes that are not whole 16-byte chunks): the matrix is small; it is
-    // written to the workspace by the ordinary paths and aggregated from there
-    size_t full = ((size_t)N * (size_t)M * sizeof(float) + 255) & ~(size_t)255;
-    return full + qless_score_workspace(N, M, k, bits, C) + 16;
+    const int64_t rows = groups_block_rows(N, M);
+    return groups_matrix_bytes(rows, M) + qless_score_workspace(rows, M, k, bits, C) + 16;
 }
 
 extern "C" qless_status qless_score_groups(const void *const *train_codes, const float *const *train_rnorm,
@@ -2137,49 +2013,44 @@ extern "C" qless_status qless_score_groups(const void *const *train_codes, const
     if (T > QLESS_MAX_GROUPS) return QLESS_ERR_UNSUPPORTED;
     if (C > QLESS_MAX_CHECKPOINTS || !valid_bits(bits) || k % 64 != 0 || k > 65536) return QLESS_ERR_UNSUPPORTED;
     if (N > (int64_t)0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
-    AggArgs ag{};
+    GroupEnds ge{};
     for (int t = 0; t < T; ++t) {
         const int32_t g0 = t ? group_end[t - 1] : 0;
         if (group_end[t] <= g0 || group_end[t] > M) return QLESS_ERR_INVALID_ARG;
-        ag.ge.end[t] = group_end[t];
+        ge.end[t] = group_end[t];
     }
     if (group_end[T - 1] != M) return QLESS_ERR_INVALID_ARG;
     if (N == 0) return QLESS_OK;
     if (!out) return QLESS_ERR_INVALID_ARG;
     const size_t need = qless_score_groups_workspace(N, M, k, bits, C);
     if (!ws || ws_bytes < need || (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
-    hipStream_t st = (hipStream_t)stream;
-    ag.T = T; ag.mean = mode == QLESS_AGG_MEAN ? 1 : 0; ag.gout = out;
-    if (!groups_fused(M, k, bits)) {
+    const int64_t block = groups_block_rows(N, M);
+    const size_t full_bytes = groups_matrix_bytes(block, M);
+    const int64_t cb = (int64_t)k * bits / 8;
+    for (int64_t r0 = 0; r0 < N; r0 += block) {
+        const int64_t rows = N - r0 < block ? N - r0 : block;
+        const void *tc[QLESS_MAX_CHECKPOINTS];
+        const float *tr[QLESS_MAX_CHECKPOINTS];
+        for (int i = 0; i < C; ++i) {
+            if (!train_codes[i] || !train_rnorm[i]) return QLESS_ERR_INVALID_ARG;
+            tc[i] = (const unsigned char *)train_codes[i] + r0 * cb;
+            tr[i] = train_rnorm[i] + r0;
+        }
         float *full = (float *)ws;
-        const size_t full_bytes = ((size_t)N * (size_t)M * sizeof(float) + 255) & ~(size_t)255;
-        const qless_status rc = qless_score(train_codes, train_rnorm, val_codes, val_rnorm, eta, C, N, M, k, bits,
-                                            nullptr, full, (unsigned char *)ws + full_bytes, ws_bytes - full_bytes, stream);
+        // (its argument checks come before any launch, so a bad pointer is reported by the first block with out untouched)
+        const qless_status rc = qless_score(tc, tr, val_codes, val_rnorm, eta, C, rows, M, k, bits, nullptr, full,
+                                            (unsigned char *)ws + full_bytes, ws_bytes - full_bytes, stream);
         if (rc != QLESS_OK) return rc;
-        return aggregate_rows(full, N, M, ag.ge, T, ag.mean, out, st);
+        const qless_status ra = aggregate_rows(full, rows, M, ge, T, mode == QLESS_AGG_MEAN ? 1 : 0, out + r0 * T, (hipStream_t)stream);
+        if (ra != QLESS_OK) return ra;
     }
-    ScoreArgs a{};
-    for (int i = 0; i < C; ++i) {
-        if (!val_codes[i] || !val_rnorm[i] || !train_codes[i] || !train_rnorm[i]) return QLESS_ERR_INVALID_ARG;
-        if ((uintptr_t)val_codes[i] % 16 || (uintptr_t)train_codes[i] % 16) return QLESS_ERR_INVALID_ARG;
-        a.tc[i] = (const unsigned char *)train_codes[i]; a.vc[i] = (const unsigned char *)val_codes[i];
-        a.tr[i] = train_rnorm[i]; a.vr[i] = val_rnorm[i]; a.eta[i] = eta[i];
-    }
-    a.C = C; a.N = N; a.M = M; a.k = k; a.score = nullptr; a.full = nullptr;
-    const qless_status ready = device_ready();
-    if (ready != QLESS_OK) return ready;
-    switch (bits) {
-        case 8: return launch_mfma_groups<8>(a, ws, ag, st);
-        case 4: return launch_mfma_groups<4>(a, ws, ag, st);
-        case 2: return launch_mfma_groups<2>(a, ws, ag, st);
-        default: return launch_mfma_groups<1>(a, ws, ag, st);
-    }
+    return QLESS_OK;
 }
 
 // 16-bit LESS comparator: bfloat16 rows scored by the 8-bit kernel geometry on 2k bytes per row.
 extern "C" size_t qless_score16_workspace(int64_t N, int32_t M, int32_t k, int C) {
     if (N < 0 || M < 1 || k <= 0 || k > 32768 || C < 1) return 0;
-    return mfma_plan(N, M, 2 * k, 8, C).total;
+    return tiles_workspace(N, M, 2 * k, 8, C);
 }
 
 extern "C" qless_status qless_score16(const void *const *train16, const void *const *val16, const float *eta,
@@ -2199,7 +2070,7 @@ extern "C" qless_status qless_score16(const void *const *train16, const void *co
     }
     a.C = C; a.N = N; a.M = M; a.k = 2 * k; a.score = score; a.full = full;     // k in bytes from here on
     if (N == 0) return QLESS_OK;
-    const size_t need = mfma_plan(N, M, a.k, 8, C).total;
+    const size_t need = tiles_workspace(N, M, a.k, 8, C);
     if (!ws || ws_bytes < need) return QLESS_ERR_WORKSPACE;
     if ((uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
     const qless_status ready = device_ready();
