@@ -5,10 +5,14 @@
 // coordinates, contraction over the gradient dimension d (huge).  One workgroup of 8 waves
 // owns a 64 (rows) x 1024 (coordinates) output tile for one slice of d; each wave owns
 // 64 x 128 of it as 2 x 4 MFMA 32x32 accumulators.  Gaussian projections of batches that
-// fill 128-row tiles take 128 x 512 tiles instead (4 x 2 accumulators per wave): every
-// generated fragment of the random operand then feeds four matrix instructions instead of two.  The gradient tile is staged through LDS; partial tiles of
-// the d-slices go to the workspace and are summed in a fixed order by a second kernel, so
-// results are run-to-run identical.
+// fill 128-row tiles take 128 x 512 tiles (4 x 2 accumulators per wave): every
+// generated fragment of the random operand then feeds four matrix instructions instead of two.
+// Other batches take tiles of 16, 32 or 48 rows on 16 x 16 matrix instructions (project_narrow_kernel);
+// make_plans() chooses the shape and the number of d-slices by what they cost.  The gradient tile is
+// staged through LDS; partial tiles of the d-slices go to the workspace and are summed in a fixed
+// order by a second kernel, so results are run-to-run identical.
+// Measured, before (64-row tiles for every batch) -> now: 16 x 2^19 bf16 -> 8192 350 -> 189 us, 32 x 2^20 642 -> 444 us,
+// 1 x 2^20 631 -> 318 us; 37 x 1 000 017 at odd row offsets -> 4096 468 -> 348 us; 1024 x 16384 fp32 -> 512 43.7 -> 35.1 us.
 //
 // Random operand: lanes 0..31 of a wave take one 32-column word of R for their row m, lanes
 // 32..63 the next word; the 32 sign bits of a word feed four MFMA K-steps of 8 columns each.
@@ -23,6 +27,7 @@ namespace qless {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kWaves = 8;
 constexpr int kStageD = 128;                   // gradient columns per LDS stage
@@ -37,37 +42,61 @@ template <int NB> struct ProjShape {
     static constexpr int kStageBytes = kTileRows * kLdsStride;
     static constexpr int kDirectStageBytes = kTileRows * kStageD * 2;
 };
-// 128-row tiles for the Gaussian family (whose operand generation, one table look-up per element,
-// is what bounds the kernel) when they cover the batch with no more padding rows than 64-row tiles
-// would.  The Rademacher kernel gains nothing from them: it already runs at the matrix-core rate the
-// chip sustains.
-static int tile_row_blocks(int64_t n, bool gauss) {
-    return (gauss && n > 64 && (n + 127) / 128 * 128 <= (n + 63) / 64 * 64) ? 4 : 2;
-}
+// Tile shapes (rows x projected coordinates of a workgroup) and what one costs: microseconds per 128 gradient columns with a
+// workgroup on every slot of the chip, measured at 2^20 columns, k = 8192 (bf16 and fp32 input of the Rademacher family --
+// fp32 is converted while it is staged; Gaussian: bound by the table look-ups, which a fragment costs whatever it
+// feeds), how many workgroups a compute unit holds, and microseconds a round costs whatever its length (the narrow 512-wide
+// tiles join two groups' sums in LDS).
+enum ProjectTile { kTile128, kTile64, kTile48, kTile48x512, kTile32x512, kTile16x512, kTiles };
+struct TileCost { int rows, cols, per_cu; double bf16, fp32, gauss, fixed; };
+constexpr TileCost kTileCost[kTiles] = {
+    {128, 512, 1, 2.60, 3.30, 4.60, 4}, {64, 1024, 1, 2.60, 3.27, 6.10, 4}, {48, 1024, 1, 2.21, 2.73, 6.10, 4},
+    {48, 512, 1, 1.12, 1.81, 3.05, 8}, {32, 512, 1, 0.90, 1.41, 2.95, 8}, {16, 512, 2, 1.28, 1.50, 5.80, 8}};
 
 struct ProjectPlan {
+    int shape;
     int64_t ntiles, ktiles, nsplit, stages_per_split, slices, grid;
     size_t ws_bytes;
 };
 
-static ProjectPlan make_plan(int64_t n, int64_t d_len, int32_t k, bool gauss) {
-    ProjectPlan p{};
-    const int nb = tile_row_blocks(n, gauss);
-    const int kTileRows = 32 * nb, kTileCols = kWaves * 32 * (8 / nb);
-    p.ntiles = (n + kTileRows - 1) / kTileRows;
-    p.ktiles = (k + kTileCols - 1) / kTileCols;
-    int64_t stages = (d_len + kStageD - 1) / kStageD;
-    if (n <= 0 || d_len <= 0) { p.nsplit = 0; p.ws_bytes = 0; return p; }
-    int64_t tiles = p.ntiles * p.ktiles;
-    int64_t want = (2048 / kWaves + tiles - 1) / tiles;   // about eight waves per CU
-    if (want > stages) want = stages;
-    if (want < 1) want = 1;
-    p.stages_per_split = (stages + want - 1) / want;
-    p.nsplit = (stages + p.stages_per_split - 1) / p.stages_per_split;
-    p.slices = p.ntiles * p.nsplit;
-    p.grid = p.ktiles * 8 * ((p.slices + 7) / 8);
-    p.ws_bytes = (size_t)p.nsplit * (size_t)n * (size_t)k * sizeof(float);
-    return p;
+// The plans of the four kinds of input (bf16, fp32, Gaussian bf16, Gaussian fp32), in one pass: it runs on every call.
+constexpr int kPlanKinds = 4;
+static int plan_kind(bool gauss, bool fp32) { return 2 * gauss + fp32; }
+static void make_plans(int64_t n, int64_t d_len, int32_t k, ProjectPlan (&p)[kPlanKinds]) {
+    for (ProjectPlan &q : p) q = ProjectPlan{};
+    if (n <= 0 || d_len <= 0) return;
+    const int64_t stages = (d_len + kStageD - 1) / kStageD;
+    // Over the shapes and the numbers of d-slices: rounds of workgroups times a workgroup's columns, plus the round's fixed
+    // share, plus the partial sums' way through memory (written and read once, 4 TB/s).  A (row tile, d-slice)
+    // runs on one XCD with all its column tiles, so the rounds are those of the XCD with the most of them (416 x 2 020 480 ->
+    // 8256: 28 slices x 9 column tiles are 252 workgroups, but 36 of them on four of the XCDs: 19.3 against 15.6 ms).
+    double least[kPlanKinds] = {0, 0, 0, 0};
+    const double plane = (double)n * k * 8 / 4e6;
+    for (int t = 0; t < kTiles; ++t) {
+        const TileCost &c = kTileCost[t];
+        const int64_t nt = (n + c.rows - 1) / c.rows, kt = (k + c.cols - 1) / c.cols, slots = 32 * c.per_cu;     // per XCD
+        for (int rounds = 1; rounds <= 2; ++rounds) {
+            int64_t w = rounds * slots / kt * 8 / nt;         // the most d-slices that fit these rounds
+            if (w < 1) w = 1;
+            if (w > stages) w = stages;
+            const int64_t per = (stages + w - 1) / w, splits = (stages + per - 1) / per;
+            const int64_t r = ((nt * splits + 7) / 8 * kt + slots - 1) / slots;
+            const int64_t cols = t >= kTile48x512 ? (per + 1) / 2 * 2 : per;                  // two groups of wavefronts, alternate columns
+            for (int v = 0; v < kPlanKinds; ++v) {
+                const double cost = v >= 2 ? c.gauss : (v == 1 ? c.fp32 : c.bf16);
+                const double us = (double)r * ((double)cols * cost + c.fixed) + (double)splits * plane;
+                if (least[v] == 0 || us < least[v]) { least[v] = us; p[v].shape = t; p[v].stages_per_split = per; p[v].nsplit = splits; }
+            }
+        }
+    }
+    for (ProjectPlan &q : p) {
+        const TileCost &c = kTileCost[q.shape];
+        q.ntiles = (n + c.rows - 1) / c.rows;
+        q.ktiles = (k + c.cols - 1) / c.cols;
+        q.slices = q.ntiles * q.nsplit;
+        q.grid = q.ktiles * 8 * ((q.slices + 7) / 8);
+        q.ws_bytes = (size_t)q.nsplit * (size_t)n * (size_t)k * sizeof(float);
+    }
 }
 
 struct ProjectArgs {
@@ -83,61 +112,67 @@ struct ProjectArgs {
 
 struct GaussTable { uint16_t v[256]; };
 
-__device__ inline uint32_t pack_bf16_rne(float a, float b) {
-    uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    ua += 0x7FFFu + ((ua >> 16) & 1u);
-    ub += 0x7FFFu + ((ub >> 16) & 1u);
-    return (ua >> 16) | (ub & 0xFFFF0000u);
+// How gradient tiles reach LDS: asynchronous copies (bf16, 16-byte aligned rows, a length of whole stages), or through
+// registers (fp32, any alignment, any length).
+enum ProjectInput { kDirectBf16, kStagedBf16, kStagedF32 };
+
+// 16 bytes from any element boundary (a wide load has no alignment of its own to keep: rows at odd element offsets take as
+// many load instructions as aligned ones; eight 2-byte loads instead made 37 x 1 000 017 bf16 -> 4096 30 % slower)
+__device__ inline uint4 load_any(const void *p) {
+    struct __attribute__((packed, aligned(2))) Bytes { uint4 v; };
+    return ((const Bytes *)p)->v;
+}
+__device__ inline uint32_t pack2_bf16(float a, float b) {          // round to nearest even (v_cvt_pk_bf16_f32)
+    bf16x2 r;
+    r[0] = (__bf16)a; r[1] = (__bf16)b;
+    return __builtin_bit_cast(uint32_t, r);
 }
 
 // Loads 8 consecutive gradient elements (row, col..col+7) as packed bf16; elements outside
 // [0, n) x [0, c_end) read as zero.
-template <bool IN_F32, bool ALIGNED>
+template <ProjectInput IN>
 __device__ inline uint4 load_chunk(const ProjectArgs &a, int64_t row, int64_t col, int64_t c_end) {
-    uint4 out = make_uint4(0, 0, 0, 0);
-    if (row >= a.n || col >= c_end) return out;
-    if (IN_F32) {
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (row >= a.n || col >= c_end) return v;
+    if (IN == kStagedF32) {
         const float *p = (const float *)a.G + row * a.ldG + col;
-        float f[8];
-        if (ALIGNED && col + 8 <= c_end) {
-            float4 lo = *(const float4 *)p, hi = *(const float4 *)(p + 4);
-            f[0] = lo.x; f[1] = lo.y; f[2] = lo.z; f[3] = lo.w;
-            f[4] = hi.x; f[5] = hi.y; f[6] = hi.z; f[7] = hi.w;
+        if (col + 8 <= c_end) {
+            const uint4 lo = load_any(p), hi = load_any(p + 4);
+            v.x = pack2_bf16(__uint_as_float(lo.x), __uint_as_float(lo.y)); v.y = pack2_bf16(__uint_as_float(lo.z), __uint_as_float(lo.w));
+            v.z = pack2_bf16(__uint_as_float(hi.x), __uint_as_float(hi.y)); v.w = pack2_bf16(__uint_as_float(hi.z), __uint_as_float(hi.w));
         } else {
+            float f[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) f[e] = (col + e < c_end) ? p[e] : 0.0f;
+            for (int e = 0; e < 8; ++e) f[e] = col + e < c_end ? p[e] : 0.0f;
+            v.x = pack2_bf16(f[0], f[1]); v.y = pack2_bf16(f[2], f[3]); v.z = pack2_bf16(f[4], f[5]); v.w = pack2_bf16(f[6], f[7]);
         }
-        out.x = pack_bf16_rne(f[0], f[1]); out.y = pack_bf16_rne(f[2], f[3]);
-        out.z = pack_bf16_rne(f[4], f[5]); out.w = pack_bf16_rne(f[6], f[7]);
     } else {
         const uint16_t *p = (const uint16_t *)a.G + row * a.ldG + col;
-        if (ALIGNED && col + 8 <= c_end) {
-            out = *(const uint4 *)p;
+        if (col + 8 <= c_end) {
+            v = load_any(p);
         } else {
             uint32_t h[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = (col + e < c_end) ? p[e] : 0u;
-            out.x = h[0] | (h[1] << 16); out.y = h[2] | (h[3] << 16);
-            out.z = h[4] | (h[5] << 16); out.w = h[6] | (h[7] << 16);
+            for (int e = 0; e < 8; ++e) h[e] = col + e < c_end ? p[e] : 0u;
+            v.x = h[0] | (h[1] << 16); v.y = h[2] | (h[3] << 16); v.z = h[4] | (h[5] << 16); v.w = h[6] | (h[7] << 16);
         }
     }
-    return out;
+    return v;
 }
 
 union Frag { bf16x8 v; bf16x2 p[4]; uint4 u; uint32_t w[4]; uint16_t h[8]; };
 
 // DIRECT: gradient tiles go global -> LDS asynchronously (no VGPR staging) into a ring of kRing
-// unpadded, XOR-swizzled stage buffers, three stages ahead of the MFMAs.  It needs bf16 input,
-// 16-byte aligned rows and a gradient length that is a multiple of the stage width; every other
-// case stages through registers into two padded buffers.
+// unpadded, XOR-swizzled stage buffers, three stages ahead of the MFMAs; the other inputs are staged
+// through registers into two padded buffers.
 constexpr int kRing = 4;
 constexpr int kGaussCopies = 32;                // copies of the Gaussian table in LDS
 constexpr int kProjectMaxLds = kRing * 128 * kStageD * 2 + 256 * kGaussCopies * 2;   // largest request of any shape (128-row tiles)
 
-template <bool IN_F32, bool ALIGNED, bool GAUSS, bool DIRECT, int NB>
+template <ProjectInput IN, bool GAUSS, int NB>
 __global__ void __launch_bounds__(kWaves * 64, 2)
 project_kernel(ProjectArgs a, GaussTable gt) {
-    static_assert(!DIRECT || (!IN_F32 && ALIGNED), "direct LDS copies move bf16 rows as they are");
+    constexpr bool DIRECT = IN == kDirectBf16;
     using Sh = ProjShape<NB>;
     constexpr int KB = Sh::KB, kTileRows = Sh::kTileRows, kWaveCols = Sh::kWaveCols, kTileCols = Sh::kTileCols;
     constexpr int kStageBytes = Sh::kStageBytes, kDirectStageBytes = Sh::kDirectStageBytes;
@@ -199,7 +234,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
         for (int i = 0; i < kChunksPerThread; ++i) {
             int c = tid + kThreads * i;
             int r = c >> 4, cc = c & 15;
-            stage_regs[DIRECT ? 0 : i] = load_chunk<IN_F32, ALIGNED>(a, row0 + r, cs + cc * 8, c_end);
+            stage_regs[DIRECT ? 0 : i] = load_chunk<IN>(a, row0 + r, cs + cc * 8, c_end);
         }
     };
     auto commit = [&](int buf) {
@@ -345,20 +380,265 @@ project_kernel(ProjectArgs a, GaussTable gt) {
         }
 }
 
-// P = (accumulate ? P : 0) + ((p_0 + p_1) + p_2) + ...   fixed order over the d-slices
+// ------------------------------------------------------------------------------------------
+// Batches that do not fill 64-row tiles, and few projected coordinates: tiles of 16 NR rows (NR = 1 .. 4).
+//
+// The same product with v_mfma_f32_16x16x32_bf16: a fragment of the random operand is 16 coordinates x 32 columns and
+// feeds NR matrix instructions of 16 cycles, so a batch of 16 pays for 16 rows and not for 64.  Bound there: vector
+// ALU, about 8.5 operations per fragment (34 cycles against 16 NR of the matrix cores).  A lane (coordinate
+// lane % 16, group lane / 16) takes word 4 s + lane / 16 of its row for sub-stage s of 128 columns; the word's four
+// bytes-of-columns are the lane's 8 columns of the four K steps, on both operands.
+//   NX wavefronts side by side cover 128 NX coordinates; NK = 8 / NX groups of them take alternate sub-stages of the
+//   workgroup's d-slice (k <= 512: all eight wavefronts have work although the tile is 512 wide) and join their
+//   sums in LDS at the end.
+// ------------------------------------------------------------------------------------------
+constexpr int kNarrowCols = 128;                // coordinates per wavefront
+template <int NR, int NX> struct NarrowShape {
+    static constexpr int NK = kWaves / NX, kRows = 16 * NR, kCols = kNarrowCols * NX;
+    static constexpr int kSubBytes = kRows * kStageD * 2;         // a sub-stage: kRows x 256 bytes, chunk c of row r at c ^ (r % 16)
+    static constexpr int kStage = NK * kSubBytes;
+    static constexpr int kRingN = 4;                               // stages in the ring (asynchronous copies), 2 when staged
+    static constexpr int kJoin = (NK - 1) * kRows * kCols * 4;     // sums of the other groups, after the last stage
+    static constexpr int kLdsMax = (kRingN * kStage > kJoin ? kRingN * kStage : kJoin) + 256 * kGaussCopies * 2;
+    static_assert(kLdsMax <= 160 * 1024, "LDS of one compute unit");
+};
+
+template <ProjectInput IN, bool GAUSS, int NR, int NX>
+__global__ void __launch_bounds__(kWaves * 64, 2)
+project_narrow_kernel(ProjectArgs a, GaussTable gt) {
+    using Sh = NarrowShape<NR, NX>;
+    constexpr int NK = Sh::NK, KB = kNarrowCols / 16, kSubBytes = Sh::kSubBytes, kStage = Sh::kStage;
+    constexpr bool DIRECT = IN == kDirectBf16;
+    constexpr int RING = DIRECT ? Sh::kRingN : 2;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    // XCD-aware decode as in project_kernel
+    const int64_t id = blockIdx.x, t = id >> 3;
+    const int kt = (int)(t % a.ktiles);
+    const int64_t slice = (t / a.ktiles) * 8 + (id & 7);
+    if (slice >= a.slices) return;
+    const int64_t ntile = slice / a.nsplit;
+    const int split = (int)(slice % a.nsplit);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lg = lane >> 4;
+    const int wx = wave % NX, wk = wave / NX;
+    const int64_t row0 = ntile * Sh::kRows;
+    const int64_t c_begin = (int64_t)split * a.stages_per_split * kStageD;
+    int64_t c_end = c_begin + a.stages_per_split * kStageD;
+    if (c_end > a.d_len) c_end = a.d_len;
+    const int nsub = (int)((c_end - c_begin + kStageD - 1) / kStageD), nstages = (nsub + NK - 1) / NK;
+
+    uint16_t *gtab = (uint16_t *)(smem + RING * kStage);
+    if (GAUSS)
+        for (int i = tid; i < 256 * kGaussCopies; i += kWaves * 64) gtab[i] = gt.v[i / kGaussCopies];
+
+    const int mbase = kt * Sh::kCols + wx * kNarrowCols;
+    RowKey key[KB];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+        key[kb] = row_key(a.sk, (uint32_t)(mbase + 16 * kb + l16));
+        if (!GAUSS) key[kb].a += (uint32_t)lg * kGold;
+    }
+    f32x4 acc[NR][KB];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) acc[r][kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // ---- staging through registers: 16-byte chunks of the stage, [sub-stage][row][chunk]
+    constexpr int kThreads = kWaves * 64, kChunks = kStage / 16, kPer = (kChunks + kThreads - 1) / kThreads;
+    uint4 regs[DIRECT ? 1 : kPer];
+    auto fetch = [&](int s) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int c = tid + kThreads * i;
+            const int sub = c / (kSubBytes / 16), r = c / 16 % Sh::kRows, cc = c & 15;
+            const int64_t row = row0 + r, col = c_begin + ((int64_t)s * NK + sub) * kStageD + cc * 8;
+            const uint4 v = c < kChunks ? load_chunk<IN>(a, row, col, c_end) : make_uint4(0, 0, 0, 0);
+            regs[DIRECT ? 0 : i] = v;
+        }
+    };
+    auto commit = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int c = tid + kThreads * i, r = c >> 4, cc = c & 15;         // r counts rows over all sub-stages: r % 16 is the row's
+            if (c < kChunks) *(uint4 *)(smem + buf * kStage + r * 256 + ((cc ^ (r & 15)) << 4)) = regs[DIRECT ? 0 : i];
+        }
+    };
+    // ---- asynchronous copies of 1 KB (4 rows); past the end of a stage a wavefront repeats its last copy, past the end
+    // of the slice (an odd number of sub-stages) a group that has no sub-stage left re-reads the last one
+    constexpr int kCp = kStage / 1024, kCopies = (kCp + kWaves - 1) / kWaves;
+    const unsigned lds0 = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)smem);
+    const unsigned char *cptr[kCopies];
+    unsigned cdst[kCopies];
+    int csub[kCopies];
+    if (DIRECT) {
+#pragma unroll
+        for (int u = 0; u < kCopies; ++u) {
+            const int q = wave * kCopies + u < kCp ? wave * kCopies + u : kCp - 1;
+            csub[u] = q / (kSubBytes / 1024);
+            const int r = 4 * (q % (kSubBytes / 1024)) + (lane >> 4);
+            int64_t grow = row0 + r;
+            if (grow > a.n - 1) grow = a.n - 1;                                 // never stored
+            cptr[u] = (const unsigned char *)a.G + (grow * a.ldG + c_begin) * 2 + (((lane & 15) ^ (r & 15)) << 4);
+            cdst[u] = (unsigned)q * 1024u;
+        }
+    }
+    auto issue = [&](int s) {
+        const unsigned buf = lds0 + (unsigned)(s % RING) * kStage;
+#pragma unroll
+        for (int u = 0; u < kCopies; ++u) {
+            const int sub = s * NK + csub[u] < nsub ? s * NK + csub[u] : nsub - 1;   // wave-uniform
+            global_to_lds16(cptr[u] + (int64_t)sub * (kStageD * 2), buf + cdst[u]);
+        }
+    };
+    if (DIRECT) {
+#pragma unroll
+        for (int s = 0; s < RING - 1; ++s)
+            if (s < nstages) issue(s);
+    } else {
+        fetch(0);
+        commit(0);
+        __syncthreads();
+    }
+
+    const uint16_t *gl = gtab + (lane & (kGaussCopies - 1));
+    uint32_t fp4_one = 0x22222222u;                // eight FP4 codes of +1.0
+    asm volatile("" : "+v"(fp4_one));
+    for (int s = 0; s < nstages; ++s) {
+        const int buf = DIRECT ? s % RING : (s & 1);
+        if (DIRECT) {
+            if (s + RING - 2 < nstages) wait_vmcnt<(RING - 2) * kCopies>(); else wait_vmcnt<0>();
+            __syncthreads();
+            if (s + RING - 1 < nstages) issue(s + RING - 1);
+        } else if (s + 1 < nstages) {
+            fetch(s + 1);
+        }
+        const int sub = s * NK + wk;
+        if (sub < nsub) {                                                       // wave-uniform
+            const unsigned char *sb = smem + buf * kStage + wk * kSubBytes + l16 * 256;
+            Frag af[NR][4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+                for (int r = 0; r < NR; ++r) af[r][ks].u = *(const uint4 *)(sb + r * 4096 + (((4 * lg + ks) ^ l16) << 4));
+            const uint32_t wstage = a.wbase + (uint32_t)((c_begin + (int64_t)sub * kStageD) >> 5);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                uint32_t h = 0;
+                if (!GAUSS) h = key_word(key[kb], wstage * kGold);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    Frag bf;
+                    if (!GAUSS) {
+                        uint32_t x;
+                        asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(x) : "v"(h << ks), "s"(0x88888888u), "v"(fp4_one));
+                        bf.p[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 0);
+                        bf.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 1);
+                        bf.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 2);
+                        bf.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 3);
+                    } else {
+                        const uint32_t w4 = (wstage + (uint32_t)lg) * 8u + 2u * ks;
+                        const uint32_t h0 = key_word(key[kb], w4 * kGold + kSaltStride), h1 = key_word(key[kb], (w4 + 1u) * kGold + kSaltStride);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            bf.h[e] = gl[((h0 >> (8 * e)) & 0xFF) * kGaussCopies];
+                            bf.h[4 + e] = gl[((h1 >> (8 * e)) & 0xFF) * kGaussCopies];
+                        }
+                    }
+#pragma unroll
+                    for (int r = 0; r < NR; ++r)
+                        acc[r][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[r][ks].v, bf.v, acc[r][kb], 0, 0, 0);
+                }
+            }
+        }
+        if (!DIRECT) {
+            if (s + 1 < nstages) commit(buf ^ 1);
+            __syncthreads();
+        }
+    }
+    if (NK > 1) {
+        // the other groups' sums pass through LDS ([group][row][column]; every copy has landed), added in group order
+        float *join = (float *)smem;
+        __syncthreads();
+        if (wk > 0) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        join[((wk - 1) * Sh::kRows + 16 * r + 4 * lg + v) * Sh::kCols + wx * kNarrowCols + 16 * kb + l16] = acc[r][kb][v];
+        }
+        __syncthreads();
+        if (wk > 0) return;
+#pragma unroll
+        for (int z = 1; z < NK; ++z)
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[r][kb][v] += join[((z - 1) * Sh::kRows + 16 * r + 4 * lg + v) * Sh::kCols + wx * kNarrowCols + 16 * kb + l16];
+    }
+    // partial tile -> workspace [split][n][k];  D[i][j]: j = lane % 16, i = 4 (lane / 16) + v
+    float *wsp = a.ws + (size_t)split * (size_t)a.n * (size_t)a.k;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+        const int m = mbase + 16 * kb + l16;
+        if (mbase + 16 * kb >= a.k) continue;                                   // wave-uniform (k is a multiple of 64)
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int64_t row = row0 + 16 * r + 4 * lg + v;
+                if (row < a.n) wsp[(size_t)row * a.k + m] = acc[r][kb][v];
+            }
+    }
+}
+
+// P = (accumulate ? P : 0) + ((p_0 + p_1) + p_2) + ...   fixed order over the d-slices; four elements of a row per thread,
+// eight planes in flight (bound: memory; 16 x 8192 with 32 planes 9.8 us with one 4-byte load at a time)
 __global__ void __launch_bounds__(256)
 project_reduce_kernel(const float *ws, int nsplit, int64_t n, int32_t k, int accumulate,
-                      float *P, int64_t ldP) {
+                      float *P, int64_t ldP, int vec) {
     const int64_t total = n * (int64_t)k;
-    const size_t plane = (size_t)total;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (int sp = 0; sp < nsplit; ++sp) s += ws[(size_t)sp * plane + (size_t)i];
-        const int64_t row = i / k, m = i - row * k;
-        float *dst = P + row * ldP + m;
-        *dst = accumulate ? (*dst + s) : s;
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= total) return;
+    const float4 *src = (const float4 *)(ws + i);
+    const size_t plane = (size_t)total / 4;                   // k is a multiple of 64
+    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    int sp = 0;
+    for (; sp + 8 <= nsplit; sp += 8) {
+        float4 t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = src[(size_t)(sp + u) * plane];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
     }
+    for (; sp < nsplit; ++sp) {
+        const float4 t = src[(size_t)sp * plane];
+        s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+    }
+    const int64_t row = i / k, m = i - row * k;
+    float *dst = P + row * ldP + m;
+    if (vec) {
+        if (accumulate) {
+            const float4 o = *(const float4 *)dst;
+            s.x = o.x + s.x; s.y = o.y + s.y; s.z = o.z + s.z; s.w = o.w + s.w;
+        }
+        *(float4 *)dst = s;
+    } else {
+        const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dst[e] = accumulate ? dst[e] + v[e] : v[e];
+    }
+}
+static void launch_reduce(const float *ws, int nsplit, int64_t n, int32_t k, int accumulate, float *P, int64_t ldP, hipStream_t st) {
+    const int64_t blocks = (n * (int64_t)k / 4 + 255) / 256;
+    const int vec = (uintptr_t)P % 16 == 0 && ldP % 4 == 0;
+    hipLaunchKernelGGL(project_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, ws, nsplit, n, k, accumulate, P, ldP, vec);
 }
 
 __global__ void generator_words_kernel(SeedKeys sk, uint32_t m0, int32_t nrows, uint32_t w0,
@@ -377,9 +657,39 @@ using namespace qless;
 
 extern "C" size_t qless_project_workspace(int64_t n, int64_t d_len, int32_t k) {
     if (n <= 0 || d_len <= 0 || k <= 0) return 0;
-    // enough for either matrix family (their tile shapes, hence their d-splits, may differ)
-    const size_t r = make_plan(n, d_len, k, false).ws_bytes, g = make_plan(n, d_len, k, true).ws_bytes;
-    return r > g ? r : g;
+    // enough for either matrix family and input type (their tile shapes, hence their d-splits, may differ)
+    ProjectPlan p[kPlanKinds];
+    make_plans(n, d_len, k, p);
+    size_t most = 0;
+    for (const ProjectPlan &q : p) most = q.ws_bytes > most ? q.ws_bytes : most;
+    return most;
+}
+
+template <ProjectInput IN, bool GAUSS, int NR, int NX>
+static void launch_narrow_shape(dim3 grid, hipStream_t st, const ProjectArgs &a, const GaussTable &gt) {
+    using Sh = NarrowShape<NR, NX>;
+    QLESS_LDS_KERNEL((project_narrow_kernel<IN, GAUSS, NR, NX>), Sh::kLdsMax);
+    size_t lds = (size_t)(IN == kDirectBf16 ? Sh::kRingN : 2) * Sh::kStage + (GAUSS ? 256 * kGaussCopies * 2 : 0);
+    if (lds < (size_t)Sh::kJoin) lds = Sh::kJoin;
+    hipLaunchKernelGGL((project_narrow_kernel<IN, GAUSS, NR, NX>), grid, dim3(kWaves * 64), lds, st, a, gt);
+}
+template <ProjectInput IN, bool GAUSS, int NB>
+static void launch_project_shape(dim3 grid, hipStream_t st, const ProjectArgs &a, const GaussTable &gt) {
+    QLESS_LDS_KERNEL((project_kernel<IN, GAUSS, NB>), kProjectMaxLds);
+    const size_t lds = (IN == kDirectBf16 ? (size_t)kRing * (32 * NB) * kStageD * 2 : (size_t)2 * (32 * NB) * kLdsStride) +
+                       (GAUSS ? (size_t)256 * kGaussCopies * 2 : 0);
+    hipLaunchKernelGGL((project_kernel<IN, GAUSS, NB>), grid, dim3(kWaves * 64), lds, st, a, gt);
+}
+template <ProjectInput IN, bool GAUSS>
+static void launch_project(const ProjectPlan &p, dim3 grid, hipStream_t st, const ProjectArgs &a, const GaussTable &gt) {
+    switch (p.shape) {
+        case kTile128: launch_project_shape<IN, GAUSS, 4>(grid, st, a, gt); break;
+        case kTile64: launch_project_shape<IN, GAUSS, 2>(grid, st, a, gt); break;
+        case kTile48: launch_narrow_shape<IN, GAUSS, 3, 8>(grid, st, a, gt); break;
+        case kTile48x512: launch_narrow_shape<IN, GAUSS, 3, 4>(grid, st, a, gt); break;
+        case kTile32x512: launch_narrow_shape<IN, GAUSS, 2, 4>(grid, st, a, gt); break;
+        default: launch_narrow_shape<IN, GAUSS, 1, 4>(grid, st, a, gt); break;
+    }
 }
 
 // Validates the projection arguments shared by both entry points and launches the split-d
@@ -398,7 +708,9 @@ static qless_status project_partials(const void *G, qless_dtype dt, int64_t n, i
     if (kind == QLESS_GAUSSIAN && d_offset + d_len > ((int64_t)1 << 34)) return QLESS_ERR_UNSUPPORTED;
     if (n > ((int64_t)1 << 31)) return QLESS_ERR_UNSUPPORTED;
     if (n == 0) return QLESS_OK;
-    ProjectPlan plan = make_plan(n, d_len, k, kind == QLESS_GAUSSIAN);
+    ProjectPlan plans[kPlanKinds];
+    make_plans(n, d_len, k, plans);
+    const ProjectPlan &plan = plans[plan_kind(kind == QLESS_GAUSSIAN, dt == QLESS_F32)];
     if (plan.ws_bytes > 0 && (!ws || ws_bytes < plan.ws_bytes || (uintptr_t)ws % 16 != 0)) return QLESS_ERR_WORKSPACE;
     if (plan.grid > 0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
     if (plan.nsplit == 0) return QLESS_OK;
@@ -411,32 +723,16 @@ static qless_status project_partials(const void *G, qless_dtype dt, int64_t n, i
     GaussTable gt{};
     const bool gauss = kind == QLESS_GAUSSIAN;
     if (gauss) { const uint16_t *t = gaussian_table_bf16(); for (int i = 0; i < 256; ++i) gt.v[i] = t[i]; }
-    const size_t esz = dt == QLESS_F32 ? 4 : 2;
-    const bool aligned = ((uintptr_t)G % 16 == 0) && ((ldG * esz) % 16 == 0);
-    const bool direct = dt == QLESS_BF16 && aligned && d_len % kStageD == 0;
-    const int nb = tile_row_blocks(n, gauss);
-    const size_t lds = (direct ? (size_t)kRing * (32 * nb) * kStageD * 2 : (size_t)2 * (32 * nb) * kLdsStride) +
-                       (gauss ? (size_t)256 * kGaussCopies * 2 : 0);
-    dim3 grid((unsigned)plan.grid), block(kWaves * 64);
-    if (lds > (size_t)kProjectMaxLds) return QLESS_ERR_DEVICE;
+    const bool direct = dt == QLESS_BF16 && (uintptr_t)G % 16 == 0 && (ldG * 2) % 16 == 0 && d_len % kStageD == 0;
+    const ProjectInput in = direct ? kDirectBf16 : (dt == QLESS_F32 ? kStagedF32 : kStagedBf16);
     const qless_status ready = device_ready();     // more than 64 KB of dynamic LDS has to be allowed per kernel
     if (ready != QLESS_OK) return ready;
-#define QLESS_LAUNCH_NB(F32, AL, GA, DI, NBLK) do { \
-        QLESS_LDS_KERNEL((project_kernel<F32, AL, GA, DI, NBLK>), kProjectMaxLds); \
-        hipLaunchKernelGGL((project_kernel<F32, AL, GA, DI, NBLK>), grid, block, lds, st, a, gt); } while (0)
-#define QLESS_LAUNCH(F32, AL, GA, DI) do { \
-        if (nb == 4) QLESS_LAUNCH_NB(F32, AL, GA, DI, 4); else QLESS_LAUNCH_NB(F32, AL, GA, DI, 2); } while (0)
-    if (dt == QLESS_F32) {
-        if (aligned) { if (gauss) QLESS_LAUNCH(true, true, true, false); else QLESS_LAUNCH(true, true, false, false); }
-        else         { if (gauss) QLESS_LAUNCH(true, false, true, false); else QLESS_LAUNCH(true, false, false, false); }
-    } else if (direct) {
-        if (gauss) QLESS_LAUNCH(false, true, true, true); else QLESS_LAUNCH(false, true, false, true);
-    } else {
-        if (aligned) { if (gauss) QLESS_LAUNCH(false, true, true, false); else QLESS_LAUNCH(false, true, false, false); }
-        else         { if (gauss) QLESS_LAUNCH(false, false, true, false); else QLESS_LAUNCH(false, false, false, false); }
+    const dim3 grid((unsigned)plan.grid);
+    switch (in) {
+        case kDirectBf16: gauss ? launch_project<kDirectBf16, true>(plan, grid, st, a, gt) : launch_project<kDirectBf16, false>(plan, grid, st, a, gt); break;
+        case kStagedBf16: gauss ? launch_project<kStagedBf16, true>(plan, grid, st, a, gt) : launch_project<kStagedBf16, false>(plan, grid, st, a, gt); break;
+        default: gauss ? launch_project<kStagedF32, true>(plan, grid, st, a, gt) : launch_project<kStagedF32, false>(plan, grid, st, a, gt); break;
     }
-#undef QLESS_LAUNCH
-#undef QLESS_LAUNCH_NB
     if (launch_status() != QLESS_OK) return QLESS_ERR_DEVICE;
     *nsplit_out = (int)plan.nsplit;
     return QLESS_OK;
@@ -453,11 +749,7 @@ extern "C" qless_status qless_project(const void *G, qless_dtype dt, int64_t n, 
                                              st, &nsplit);
     if (rc != QLESS_OK || n == 0) return rc;
     if (nsplit == 0 && accumulate) return QLESS_OK;       // nothing to add
-    const int64_t total = n * (int64_t)k;
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(project_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
-                       (const float *)ws, nsplit, n, k, accumulate, P, ldP);
+    launch_reduce((const float *)ws, nsplit, n, k, accumulate, P, ldP, st);
     return launch_status();
 }
 
@@ -517,8 +809,7 @@ extern "C" qless_status qless_project_quantize_slice(const void *G, qless_dtype 
     const bool fused = last && nsplit > 0 && k <= 16384;
     if (!fused) {
         if (nsplit > 0 || first)
-            hipLaunchKernelGGL(project_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
-                               (const float *)ws, nsplit, n, k, first ? 0 : 1, P, ldP);
+            launch_reduce((const float *)ws, nsplit, n, k, first ? 0 : 1, P, ldP, st);
         if (!last) return launch_status();
         if (P_other)
             hipLaunchKernelGGL(add_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, P, ldP, P_other, ldO, n, k);
