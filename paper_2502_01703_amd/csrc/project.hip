@@ -50,8 +50,8 @@ template <int NB> struct ProjShape {
 enum ProjectTile { kTile128, kTile64, kTile48, kTile48x512, kTile32x512, kTile16x512, kTiles };
 struct TileCost { int rows, cols, per_cu; double bf16, fp32, gauss, fixed; };
 constexpr TileCost kTileCost[kTiles] = {
-    {128, 512, 1, 2.60, 3.30, 4.60, 4}, {64, 1024, 1, 2.60, 3.27, 6.10, 4}, {48, 1024, 1, 2.21, 2.73, 6.10, 4},
-    {48, 512, 1, 1.12, 1.81, 3.05, 8}, {32, 512, 1, 0.90, 1.41, 2.95, 8}, {16, 512, 2, 1.28, 1.50, 5.80, 8}};
+    {128, 512, 1, 2.60, 3.30, 4.15, 4}, {64, 1024, 1, 2.60, 3.27, 5.75, 4}, {48, 1024, 1, 2.21, 2.73, 5.30, 4},
+    {48, 512, 1, 1.12, 1.81, 2.60, 8}, {32, 512, 1, 0.90, 1.41, 2.40, 8}, {16, 512, 2, 1.28, 1.50, 4.70, 8}};
 
 struct ProjectPlan {
     int shape;
@@ -166,17 +166,50 @@ union Frag { bf16x8 v; bf16x2 p[4]; uint4 u; uint32_t w[4]; uint16_t h[8]; };
 // unpadded, XOR-swizzled stage buffers, three stages ahead of the MFMAs; the other inputs are staged
 // through registers into two padded buffers.
 constexpr int kRing = 4;
-constexpr int kGaussCopies = 32;                // copies of the Gaussian table in LDS
-constexpr int kProjectMaxLds = kRing * 128 * kStageD * 2 + 256 * kGaussCopies * 2;   // largest request of any shape (128-row tiles)
+constexpr int kProjectMaxLds = 160 * 1024;      // largest request of any shape (Gaussian, 128-row tiles)
+
+// Gaussian table in LDS, at offset 0: entry i for lane l is the dword at byte 256 i + 4 l, holding the bfloat16 value in its
+// upper half.  Every lane looks up in a column of its own, so no lookup conflicts with another, and the address
+// is one byte permute of the hash (its byte above the lane's constant); the lower element of a pair is read as the
+// dword's upper 16 bits and the two halves are joined by an OR.  Twelve vector-ALU operations per fragment beside the two
+// hashes; 32 copies of 2 bytes, whose addresses took a shift, a mask and an addition, took more than twice that
+// (128 x 2^18 -> 8192: 569 -> 531 us, 64 x 2^19 835 -> 743, 1 x 2^19 811 -> 553 with the 16-row tiles).
+constexpr int kGaussBytes = 256 * 256;
+__device__ inline void gauss_fill(unsigned char *tab, const GaussTable &gt) {
+    for (int i = threadIdx.x; i < kGaussBytes / 4; i += kWaves * 64) ((uint32_t *)tab)[i] = (uint32_t)gt.v[i >> 6] << 16;
+}
+// A fragment's eight entries (two hash words): requested one fragment ahead of their use.  The LDS addresses are formed as such: the table is
+// the first thing in a kernel's dynamic LDS, which starts at 0 (no static LDS), and a pointer into the array would
+// cost an addition of that 0 per lookup.
+struct GaussRaw { uint32_t lo[4], hi[4]; };
+__device__ inline void gauss_request(RowKey key, uint32_t counter, uint32_t lane4, GaussRaw &r) {
+    typedef __attribute__((address_space(3))) const uint16_t *lds16;
+    typedef __attribute__((address_space(3))) const uint32_t *lds32;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const uint32_t h = key_word(key, counter + (uint32_t)e * kGold);
+        r.lo[2 * e] = ((lds16)(uintptr_t)__builtin_amdgcn_perm(h, lane4, 0x0C0C0400u))[1];
+        r.hi[2 * e] = *(lds32)(uintptr_t)__builtin_amdgcn_perm(h, lane4, 0x0C0C0500u);
+        r.lo[2 * e + 1] = ((lds16)(uintptr_t)__builtin_amdgcn_perm(h, lane4, 0x0C0C0600u))[1];
+        r.hi[2 * e + 1] = *(lds32)(uintptr_t)__builtin_amdgcn_perm(h, lane4, 0x0C0C0700u);
+    }
+}
+__device__ inline Frag gauss_join(const GaussRaw &r) {
+    Frag f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f.w[i] = r.lo[i] | r.hi[i];
+    return f;
+}
 
 template <ProjectInput IN, bool GAUSS, int NB>
 __global__ void __launch_bounds__(kWaves * 64, 2)
 project_kernel(ProjectArgs a, GaussTable gt) {
     constexpr bool DIRECT = IN == kDirectBf16;
+    constexpr int RING = GAUSS && NB == 4 ? 3 : kRing;         // next to the table three stages of 128 rows fit
     using Sh = ProjShape<NB>;
     constexpr int KB = Sh::KB, kTileRows = Sh::kTileRows, kWaveCols = Sh::kWaveCols, kTileCols = Sh::kTileCols;
     constexpr int kStageBytes = Sh::kStageBytes, kDirectStageBytes = Sh::kDirectStageBytes;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     // XCD-aware decode: consecutive workgroup ids land on different XCDs, so the ktiles
     // workgroups that share one gradient slice are given ids 8 apart (same XCD, same L2).
     const int64_t id = blockIdx.x;
@@ -196,13 +229,9 @@ project_kernel(ProjectArgs a, GaussTable gt) {
     if (c_end > a.d_len) c_end = a.d_len;
     const int nstages = (int)((c_end - c_begin + kStageD - 1) / kStageD);
 
-    uint16_t *gtab = (uint16_t *)(smem + (DIRECT ? kRing * kDirectStageBytes : 2 * kStageBytes));
-    // Gaussian table in LDS, 32 copies side by side: entry i for lane l at halfword 32 i + l % 32, so
-    // the 32 lanes that look up together use 16 different banks whatever their indices are (a single
-    // copy makes them collide on the 128 dwords of the table)
-    if (GAUSS) {
-        for (int i = tid; i < 256 * kGaussCopies; i += kWaves * 64) gtab[i] = gt.v[i / kGaussCopies];
-    }
+    unsigned char *smem = lds + (GAUSS ? kGaussBytes : 0);          // the stage ring
+    const uint32_t lane4 = (uint32_t)lane * 4u;
+    if (GAUSS) gauss_fill(lds, gt);
 
     // row keys of this lane's KB 32-row blocks of the random matrix
     const int mbase = kt * kTileCols + wave * kWaveCols;
@@ -213,7 +242,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
         int m = mbase + 32 * kb + l32;
         live[kb] = (mbase + 32 * kb) < a.k;            // wave-uniform (k is a multiple of 64)
         key[kb] = row_key(a.sk, (uint32_t)m);
-        if (!GAUSS) key[kb].a += (uint32_t)half * kGold;   // upper half-wave reads the next word
+        key[kb].a += (uint32_t)half * (GAUSS ? 8u * kGold : kGold);   // upper half-wave reads the next word (eight words)
     }
 
     f32x16 acc[NB][KB];
@@ -266,8 +295,8 @@ project_kernel(ProjectArgs a, GaussTable gt) {
             cdst[u] = (unsigned)q * 1024u;
         }
     }
-    auto issue = [&](int s) {                      // start the copies of stage s (ring slot s % kRing)
-        const unsigned buf = lds0 + (unsigned)(s % kRing) * kDirectStageBytes;
+    auto issue = [&](int s) {                      // start the copies of stage s (ring slot s % RING)
+        const unsigned buf = lds0 + (unsigned)(s % RING) * kDirectStageBytes;
 #pragma unroll
         for (int u = 0; u < kCopies; ++u) {
             global_to_lds16(cptr[u], buf + cdst[u]);
@@ -286,7 +315,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
 
     if (DIRECT) {
 #pragma unroll
-        for (int s = 0; s < kRing - 1; ++s)
+        for (int s = 0; s < RING - 1; ++s)
             if (s < nstages) issue(s);
     } else {
         fetch(0);
@@ -294,21 +323,55 @@ project_kernel(ProjectArgs a, GaussTable gt) {
         __syncthreads();
     }
 
-    const uint16_t *gl = gtab + (lane & (kGaussCopies - 1));   // this lane's copy of the table
     uint32_t fp4_one = 0x22222222u;                // eight FP4 codes of +1.0
     asm volatile("" : "+v"(fp4_one));              // keep it in a vector register
+    GaussRaw raw;                                  // Gaussian: the next fragment's entries
     for (int s = 0; s < nstages; ++s) {
-        const int buf = DIRECT ? s % kRing : (s & 1);
+        const int buf = DIRECT ? s % RING : (s & 1);
         if (DIRECT) {
             // stage s is the oldest copy group in flight; two younger ones may stay outstanding
-            if (s + kRing - 2 < nstages) wait_vmcnt<(kRing - 2) * kCopies>(); else wait_vmcnt<0>();
+            if (s + RING - 2 < nstages) wait_vmcnt<(RING - 2) * kCopies>(); else wait_vmcnt<0>();
             __syncthreads();                       // stage s visible to all waves; slot of stage s-1 free
-            if (s + kRing - 1 < nstages) issue(s + kRing - 1);
+            if (s + RING - 1 < nstages) issue(s + RING - 1);
         } else {
             if (s + 1 < nstages) fetch(s + 1);
         }
         const int64_t cs = c_begin + (int64_t)s * kStageD;       // multiple of 128
         const uint32_t wstage = a.wbase + (uint32_t)(cs >> 5);
+        if constexpr (GAUSS) {
+            // Fragment f = (K step f / KB, coordinate block f % KB): its entries are joined, then the matrix instructions
+            // of its NB row blocks are issued with a share of the next fragment's hashes and look-ups behind each (that of
+            // the next stage's first fragment too: the generator does not wait for gradients); the next K step's
+            // gradient fragments are read during the last block of this one.
+            constexpr int F = 8 * KB;
+            Frag ag[2][NB];
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) ag[0][nb].u = read_a(buf, nb, 0, 0);
+            if (s == 0) gauss_request(key[0], wstage * 8u * kGold + kSaltStride, lane4, raw);
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const int ks = f / KB, kb = f % KB, fn = f + 1, kn = fn / KB;
+                const Frag bf = gauss_join(raw);
+                __builtin_amdgcn_sched_barrier(0);
+                // word of K step ks: 16 (ks / 4) + 2 (ks % 4) from the stage's first
+                const uint32_t wn = fn < F ? wstage * 8u + 16u * (uint32_t)(kn >> 2) + 2u * (uint32_t)(kn & 3) : (wstage + 4u) * 8u;
+                gauss_request(key[fn % KB], wn * kGold + kSaltStride, lane4, raw);
+                if (kb == KB - 1 && fn < F) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) ag[kn & 1][nb].u = read_a(buf, nb, kn >> 2, kn & 3);
+                }
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[ks & 1][nb].v, bf.v, acc[nb][kb], 0, 0, 0);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 26 / NB + 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 12 / NB, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else
 #pragma unroll
         for (int bp = 0; bp < 2; ++bp) {
             // A fragments: rows 32*nb + l32, columns 64*bp + 32*half + 8*ks .. +7
@@ -322,7 +385,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
                 // row blocks past k (last k-tile only) are computed and dropped in the epilogue
-                if (!GAUSS) {
+                {
                     const uint32_t h = key_word(key[kb], wpair * kGold);
 #pragma unroll
                     for (int ks = 0; ks < 4; ++ks) {
@@ -335,22 +398,6 @@ project_kernel(ProjectArgs a, GaussTable gt) {
                         bf.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 1);
                         bf.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 2);
                         bf.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 3);
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb)
-                            acc[nb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[nb][ks].v, bf.v, acc[nb][kb], 0, 0, 0);
-                    }
-                } else {
-                    // Gaussian-like entries: 4 columns per word, one table byte per column
-                    const uint32_t w4 = (wpair + (uint32_t)half) * 8u;   // word of column 32*(...)
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) {
-                        const uint32_t h0 = key_word(key[kb], (w4 + 2u * ks) * kGold + kSaltStride);
-                        const uint32_t h1 = key_word(key[kb], (w4 + 2u * ks + 1u) * kGold + kSaltStride);
-                        Frag bf;
-                        bf.h[0] = gl[(h0 & 0xFF) * kGaussCopies];         bf.h[1] = gl[((h0 >> 8) & 0xFF) * kGaussCopies];
-                        bf.h[2] = gl[((h0 >> 16) & 0xFF) * kGaussCopies]; bf.h[3] = gl[(h0 >> 24) * kGaussCopies];
-                        bf.h[4] = gl[(h1 & 0xFF) * kGaussCopies];         bf.h[5] = gl[((h1 >> 8) & 0xFF) * kGaussCopies];
-                        bf.h[6] = gl[((h1 >> 16) & 0xFF) * kGaussCopies]; bf.h[7] = gl[(h1 >> 24) * kGaussCopies];
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb)
                             acc[nb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[nb][ks].v, bf.v, acc[nb][kb], 0, 0, 0);
@@ -397,10 +444,14 @@ template <int NR, int NX> struct NarrowShape {
     static constexpr int NK = kWaves / NX, kRows = 16 * NR, kCols = kNarrowCols * NX;
     static constexpr int kSubBytes = kRows * kStageD * 2;         // a sub-stage: kRows x 256 bytes, chunk c of row r at c ^ (r % 16)
     static constexpr int kStage = NK * kSubBytes;
-    static constexpr int kRingN = 4;                               // stages in the ring (asynchronous copies), 2 when staged
+    // stages in the ring (asynchronous copies; 2 when staged); Gaussian: two, so that two workgroups of 16-row tiles fit
+    static constexpr int ring(bool gauss) { return gauss ? 2 : 4; }
     static constexpr int kJoin = (NK - 1) * kRows * kCols * 4;     // sums of the other groups, after the last stage
-    static constexpr int kLdsMax = (kRingN * kStage > kJoin ? kRingN * kStage : kJoin) + 256 * kGaussCopies * 2;
-    static_assert(kLdsMax <= 160 * 1024, "LDS of one compute unit");
+    static constexpr int lds(bool direct, bool gauss) {
+        const int r = (direct ? ring(gauss) : 2) * kStage;
+        return (r > kJoin ? r : kJoin) + (gauss ? kGaussBytes : 0);
+    }
+    static_assert(lds(true, false) <= kProjectMaxLds && lds(true, true) <= kProjectMaxLds, "LDS of one compute unit");
 };
 
 template <ProjectInput IN, bool GAUSS, int NR, int NX>
@@ -409,8 +460,8 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
     using Sh = NarrowShape<NR, NX>;
     constexpr int NK = Sh::NK, KB = kNarrowCols / 16, kSubBytes = Sh::kSubBytes, kStage = Sh::kStage;
     constexpr bool DIRECT = IN == kDirectBf16;
-    constexpr int RING = DIRECT ? Sh::kRingN : 2;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int RING = DIRECT ? Sh::ring(GAUSS) : 2;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     // XCD-aware decode as in project_kernel
     const int64_t id = blockIdx.x, t = id >> 3;
     const int kt = (int)(t % a.ktiles);
@@ -428,16 +479,16 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
     if (c_end > a.d_len) c_end = a.d_len;
     const int nsub = (int)((c_end - c_begin + kStageD - 1) / kStageD), nstages = (nsub + NK - 1) / NK;
 
-    uint16_t *gtab = (uint16_t *)(smem + RING * kStage);
-    if (GAUSS)
-        for (int i = tid; i < 256 * kGaussCopies; i += kWaves * 64) gtab[i] = gt.v[i / kGaussCopies];
+    unsigned char *smem = lds + (GAUSS ? kGaussBytes : 0);
+    const uint32_t lane4 = (uint32_t)lane * 4u;
+    if (GAUSS) gauss_fill(lds, gt);
 
     const int mbase = kt * Sh::kCols + wx * kNarrowCols;
     RowKey key[KB];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
         key[kb] = row_key(a.sk, (uint32_t)(mbase + 16 * kb + l16));
-        if (!GAUSS) key[kb].a += (uint32_t)lg * kGold;
+        key[kb].a += (uint32_t)lg * (GAUSS ? 8u * kGold : kGold);
     }
     f32x4 acc[NR][KB];
 #pragma unroll
@@ -502,9 +553,9 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
         __syncthreads();
     }
 
-    const uint16_t *gl = gtab + (lane & (kGaussCopies - 1));
     uint32_t fp4_one = 0x22222222u;                // eight FP4 codes of +1.0
     asm volatile("" : "+v"(fp4_one));
+    GaussRaw raw;
     for (int s = 0; s < nstages; ++s) {
         const int buf = DIRECT ? s % RING : (s & 1);
         if (DIRECT) {
@@ -538,13 +589,11 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
                         bf.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 2);
                         bf.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 3);
                     } else {
-                        const uint32_t w4 = (wstage + (uint32_t)lg) * 8u + 2u * ks;
-                        const uint32_t h0 = key_word(key[kb], w4 * kGold + kSaltStride), h1 = key_word(key[kb], (w4 + 1u) * kGold + kSaltStride);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            bf.h[e] = gl[((h0 >> (8 * e)) & 0xFF) * kGaussCopies];
-                            bf.h[4 + e] = gl[((h1 >> (8 * e)) & 0xFF) * kGaussCopies];
-                        }
+                        // requested one fragment ahead, in the order of use
+                        if (kb == 0 && ks == 0) gauss_request(key[0], wstage * 8u * kGold + kSaltStride, lane4, raw);
+                        bf = gauss_join(raw);
+                        const int fn = 4 * kb + ks + 1;
+                        if (fn < 4 * KB) gauss_request(key[fn >> 2], (wstage * 8u + 2u * (uint32_t)(fn & 3)) * kGold + kSaltStride, lane4, raw);
                     }
 #pragma unroll
                     for (int r = 0; r < NR; ++r)
@@ -668,16 +717,16 @@ extern "C" size_t qless_project_workspace(int64_t n, int64_t d_len, int32_t k) {
 template <ProjectInput IN, bool GAUSS, int NR, int NX>
 static void launch_narrow_shape(dim3 grid, hipStream_t st, const ProjectArgs &a, const GaussTable &gt) {
     using Sh = NarrowShape<NR, NX>;
-    QLESS_LDS_KERNEL((project_narrow_kernel<IN, GAUSS, NR, NX>), Sh::kLdsMax);
-    size_t lds = (size_t)(IN == kDirectBf16 ? Sh::kRingN : 2) * Sh::kStage + (GAUSS ? 256 * kGaussCopies * 2 : 0);
-    if (lds < (size_t)Sh::kJoin) lds = Sh::kJoin;
+    constexpr int lds = Sh::lds(IN == kDirectBf16, GAUSS);
+    QLESS_LDS_KERNEL((project_narrow_kernel<IN, GAUSS, NR, NX>), lds);
     hipLaunchKernelGGL((project_narrow_kernel<IN, GAUSS, NR, NX>), grid, dim3(kWaves * 64), lds, st, a, gt);
 }
 template <ProjectInput IN, bool GAUSS, int NB>
 static void launch_project_shape(dim3 grid, hipStream_t st, const ProjectArgs &a, const GaussTable &gt) {
     QLESS_LDS_KERNEL((project_kernel<IN, GAUSS, NB>), kProjectMaxLds);
-    const size_t lds = (IN == kDirectBf16 ? (size_t)kRing * (32 * NB) * kStageD * 2 : (size_t)2 * (32 * NB) * kLdsStride) +
-                       (GAUSS ? (size_t)256 * kGaussCopies * 2 : 0);
+    constexpr size_t ring = GAUSS && NB == 4 ? 3 : kRing;
+    constexpr size_t lds = (IN == kDirectBf16 ? ring * (32 * NB) * kStageD * 2 : (size_t)2 * (32 * NB) * kLdsStride) + (GAUSS ? kGaussBytes : 0);
+    static_assert(lds <= (size_t)kProjectMaxLds, "LDS of one compute unit");
     hipLaunchKernelGGL((project_kernel<IN, GAUSS, NB>), grid, dim3(kWaves * 64), lds, st, a, gt);
 }
 template <ProjectInput IN, bool GAUSS>
