@@ -77,11 +77,36 @@ qless_status device_ready() {
     return QLESS_OK;
 }
 
+// Short groups: one thread per (train example, group), its entries visited in column order.  Neighbouring lanes read
+// neighbouring groups of a row, so up to about eight columns a group their loads share lines (46 483 x 62, 55 groups:
+// 25 us with scoring, 43 us by the kernel below, whose wavefronts take 64 rows x 32 columns whatever M is).
+__global__ void __launch_bounds__(256)
+aggregate_short_kernel(const float *full, int64_t N, int32_t M, GroupEnds ge, int T, int mean, float *out) {
+    const int64_t total = N * (int64_t)T;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t z = i / T;
+        const int t = (int)(i - z * T);
+        const int32_t g0 = t ? ge.end[t - 1] : 0, g1 = ge.end[t];
+        const float *row = full + z * (int64_t)M;
+        float r;
+        if (mean) {
+            float s = 0.0f;
+            for (int32_t j = g0; j < g1; ++j) s = __fadd_rn(s, row[j]);
+            r = __fdiv_rn(s, (float)(g1 - g0));
+        } else {
+            r = row[g0];
+            for (int32_t j = g0 + 1; j < g1; ++j) { const float v = row[j]; if (v > r) r = v; }
+        }
+        out[i] = r;
+    }
+}
+
 // One wavefront per 64 rows and range of groups: blocks of 64 rows x 32 columns are read as whole 128-byte pieces of the
 // rows (the next block's loads in flight while this one is reduced), transposed through LDS (rows 33 floats apart: no bank
 // conflicts), and every lane walks the columns of its row in order, so the mean is the same sequence of fp32 additions for
-// every launch shape.  Bound: memory, 4 N M bytes (270 000 x 285, 57 groups: one thread per (row, group), whose lanes
-// read lines of 64 different rows, took 0.6 ms).
+// every launch shape.  Bound: memory, 4 N M bytes (one thread per (row, group) reads lines of 64
+// different rows when groups are long: 18 326 x 504, 20 groups, 8 bits 1.69 -> 0.60 ms with scoring).
 constexpr int kAggCols = 32;
 __global__ void __launch_bounds__(256)
 aggregate_kernel(const float *full, int64_t N, int32_t M, GroupEnds ge, int T, int mean, float *out) {
@@ -130,6 +155,12 @@ aggregate_kernel(const float *full, int64_t N, int32_t M, GroupEnds ge, int T, i
 
 qless_status aggregate_rows(const float *full, int64_t N, int32_t M, const GroupEnds &ge, int T, int mean,
                             float *out, hipStream_t st) {
+    if (M < 32 || M <= 8 * T) {
+        int64_t short_blocks = (N * (int64_t)T + 255) / 256;
+        if (short_blocks > 65536) short_blocks = 65536;
+        hipLaunchKernelGGL(aggregate_short_kernel, dim3((unsigned)short_blocks), dim3(256), 0, st, full, N, M, ge, T, mean, out);
+        return launch_status();
+    }
     const int64_t blocks = (N + 255) / 256;
     if (blocks > 0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
     // few rows: the groups are shared out as well, until about eight wavefronts per SIMD have work (37 237 x 228, 56 groups: 165 us of scoring and aggregation with two, 154 with eight)

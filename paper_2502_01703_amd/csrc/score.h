@@ -38,4 +38,10 @@ size_t wide_workspace(int64_t N, int32_t M, int64_t row_bytes, int C);
 // side, laid out for plan_rows >= a.N train rows (the finish kernel leaves the row maxima cleared)
 qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st, bool prepare = true, int64_t plan_rows = 0);
 
+// score_split.hip: few pairs (bits = 16: bfloat16 rows).  use_split: whether the path serves a call faster than the others.
+// Rows hold at least 16 bytes (16 per plane for the ternary codes).
+bool use_split(int64_t N, int32_t M, int64_t row_bytes, int bits, int C);
+size_t split_workspace(int64_t N, int32_t M, int64_t row_bytes, int bits, int C);
+qless_status launch_split(const ScoreArgs &a, int bits, void *ws, hipStream_t st);
+
 }  // namespace qless

@@ -1910,8 +1910,8 @@ extern "C" qless_status qless_score_mixed(const void *const *train_codes, const 
     return launch_status();
 }
 
-extern "C" size_t qless_score_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
-    if (N < 0 || M < 1 || k <= 0 || C < 1 || !valid_bits(bits)) return 0;
+// Workspace of the paths other than score_split.hip's.
+static size_t score_base_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
     size_t need = 0;
     if (bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0)      // checkpoint groups hand their sums on through the workspace
         need = stream_mfma_partial_bytes(stream_mfma_plan(M, k, bits, C), N, C);
@@ -1922,6 +1922,17 @@ extern "C" size_t qless_score_workspace(int64_t N, int32_t M, int32_t k, int bit
     if (!use_mfma_path(bits, M, k)) return need;
     const size_t tiles = tiles_workspace(N, M, k, bits, C);
     return tiles > need ? tiles : need;
+}
+// (it reads 16 bytes of a row or bit plane at a time, so k = 64 is too short at 1 and 2 bits)
+static bool score_splits(int64_t N, int32_t M, int32_t k, int bits, int C) {
+    return N > 0 && (bits >= 4 || k >= 128) && use_split(N, M, (int64_t)k * bits / 8, bits, C);
+}
+
+extern "C" size_t qless_score_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
+    if (N < 0 || M < 1 || k <= 0 || C < 1 || !valid_bits(bits)) return 0;
+    const size_t need = score_base_workspace(N, M, k, bits, C);
+    const size_t split = score_splits(N, M, k, bits, C) ? split_workspace(N, M, (int64_t)k * bits / 8, bits, C) : 0;
+    return split > need ? split : need;
 }
 
 extern "C" qless_status qless_score(const void *const *train_codes, const float *const *train_rnorm,
@@ -1945,6 +1956,14 @@ extern "C" qless_status qless_score(const void *const *train_codes, const float 
     hipStream_t st = (hipStream_t)stream;
     const qless_status ready = device_ready();            // LDS limits of the kernels, once per device
     if (ready != QLESS_OK) return ready;
+    if (score_splits(N, M, k, bits, C)) {
+        if (ws && ws_bytes >= split_workspace(N, M, (int64_t)k * bits / 8, bits, C) && (uintptr_t)ws % 16 == 0)
+            return launch_split(a, bits, ws, st);
+        // a configuration whose other path needs no workspace is served by it without one
+        const StreamMfmaPlan sp = stream_mfma_plan(M, k, bits, C);
+        const bool streams = bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0 && sp.nb >= 2;
+        if (streams ? stream_mfma_partial_bytes(sp, N, C) > 0 : score_base_workspace(N, M, k, bits, C) > 0) return QLESS_ERR_WORKSPACE;
+    }
     if (bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0) {
         const StreamMfmaPlan sp = stream_mfma_plan(M, k, bits, C);
         if (sp.nb >= 2) {
@@ -2050,7 +2069,9 @@ extern "C" qless_status qless_score_groups(const void *const *train_codes, const
 // 16-bit LESS comparator: bfloat16 rows scored by the 8-bit kernel geometry on 2k bytes per row.
 extern "C" size_t qless_score16_workspace(int64_t N, int32_t M, int32_t k, int C) {
     if (N < 0 || M < 1 || k <= 0 || k > 32768 || C < 1) return 0;
-    return tiles_workspace(N, M, 2 * k, 8, C);
+    const size_t tiles = tiles_workspace(N, M, 2 * k, 8, C);
+    const size_t split = N > 0 && use_split(N, M, 2 * (int64_t)k, 16, C) ? split_workspace(N, M, 2 * (int64_t)k, 16, C) : 0;
+    return split > tiles ? split : tiles;
 }
 
 extern "C" qless_status qless_score16(const void *const *train16, const void *const *val16, const float *eta,
@@ -2070,10 +2091,11 @@ extern "C" qless_status qless_score16(const void *const *train16, const void *co
     }
     a.C = C; a.N = N; a.M = M; a.k = 2 * k; a.score = score; a.full = full;     // k in bytes from here on
     if (N == 0) return QLESS_OK;
-    const size_t need = tiles_workspace(N, M, a.k, 8, C);
+    const size_t need = qless_score16_workspace(N, M, k, C);
     if (!ws || ws_bytes < need) return QLESS_ERR_WORKSPACE;
     if ((uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
     const qless_status ready = device_ready();
     if (ready != QLESS_OK) return ready;
+    if (use_split(N, M, a.k, 16, C)) return launch_split(a, 16, ws, (hipStream_t)stream);
     return launch_mfma<8, true>(a, ws, (hipStream_t)stream);
 }

@@ -1,0 +1,81 @@
+"""Scoring of few pairs (K and the checkpoints shared out over workgroups) against the oracle: tiles of 64 x 64 with every kind
+of remainder, rows that end inside a 16-byte chunk or a pair of chunks, one part and many, and the paths that it stands next to."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2502_01703_amd import binding as Q
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _say(msg):
+    print("[case] " + msg, flush=True)
+
+
+def _bits(a):
+    return np.ascontiguousarray(a, dtype=np.float32).view(np.uint32)
+
+
+def _store(rows, k, C, bits, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    out = [Q.quantize(torch.randn(rows, k, generator=g, device=DEV), bits) for _ in range(C)]
+    return [o[0] for o in out], [o[2] for o in out]
+
+
+def _eta(C):
+    return [(-0.75) ** i for i in range(C)]
+
+
+# k: 8192 (whole chunks), 8256 / 4160 / 1984 (1-/2-bit rows end inside a chunk, 4 bits inside a pair), 128 and 192 (shorter than
+# a part); (1, 1) .. (129, 130): every remainder of the 64 x 64 tiles; 16 checkpoints
+@pytest.mark.parametrize("bits", [8, 4, 2, 1])
+@pytest.mark.parametrize("N,M,k,C", [(64, 512, 8192, 4), (1, 1, 8192, 4), (65, 70, 8256, 2), (129, 130, 4160, 3), (63, 20, 1984, 6),
+                                     (40, 300, 128, 16), (7, 640, 192, 16), (100, 9, 16384, 2), (300, 33, 1024, 4)])
+def test_split_codes_bit_exact(bits, N, M, k, C):
+    _say("split bits=%d N=%d M=%d k=%d C=%d" % (bits, N, M, k, C))
+    tc, tr = _store(N, k, C, bits, N + k)
+    vc, vr = _store(M, k, C, bits, M + 1)
+    got, full = Q.score(tc, tr, vc, vr, _eta(C), k, bits, want_full=True)
+    host = lambda ts: [t.cpu().numpy() for t in ts]
+    ref, ref_full = oracle.score(host(tc), host(tr), host(vc), host(vr), _eta(C), k, bits, want_full=True)
+    np.testing.assert_array_equal(_bits(full.cpu().numpy()), _bits(ref_full))
+    np.testing.assert_array_equal(_bits(got.cpu().numpy()), _bits(ref))
+    assert torch.equal(Q.score(tc, tr, vc, vr, _eta(C), k, bits), got)
+
+
+@pytest.mark.parametrize("N,M,k,C", [(64, 100, 8192, 4), (1, 3, 4096, 2), (130, 65, 192, 16), (33, 9, 16384, 1)])
+def test_split_bfloat16(N, M, k, C):
+    _say("split bfloat16 N=%d M=%d k=%d C=%d" % (N, M, k, C))
+    g = torch.Generator(device=DEV)
+    g.manual_seed(N)
+    t16 = [Q.normalize16(torch.randn(N, k, generator=g, device=DEV)) for _ in range(C)]
+    v16 = [Q.normalize16(torch.randn(M, k, generator=g, device=DEV)) for _ in range(C)]
+    got, full = Q.score16(t16, v16, _eta(C), want_full=True)
+    raw = lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)
+    ref, ref_full = oracle.less16_score([raw(t) for t in t16], [raw(v) for v in v16], _eta(C), want_full=True)
+    # at most k / 16 chained fp32 additions of exact products of unit rows: far inside C 2^-17
+    assert np.abs(full.cpu().numpy() - ref_full).max() <= C * 2.0 ** -17
+    assert np.abs(got.cpu().numpy() - ref).max() <= C * 2.0 ** -17
+    assert torch.equal(Q.score16(t16, v16, _eta(C)), got)              # parts are added in a fixed order
+
+
+def test_without_a_workspace_where_none_was_needed():
+    """At most eight validation vectors and bit-plane codes: served without a workspace as well, with the same bits."""
+    N, M, k, C, bits = 64, 8, 8192, 4, 1
+    _say("no workspace, bits=1 N=64 M=8")
+    tc, tr = _store(N, k, C, bits, 1)
+    vc, vr = _store(M, k, C, bits, 2)
+    with_ws = Q.score(tc, tr, vc, vr, _eta(C), k, bits)
+    out = torch.empty(N, dtype=torch.float32, device=DEV)
+    arr = lambda ts: (ctypes.c_void_p * C)(*[t.data_ptr() for t in ts])
+    eta = (ctypes.c_float * C)(*_eta(C))
+    rc = Q.lib().qless_score(arr(tc), arr(tr), arr(vc), arr(vr), ctypes.cast(eta, ctypes.c_void_p), C, N, M, k, bits,
+                             ctypes.c_void_p(out.data_ptr()), None, None, 0, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    assert torch.equal(out, with_ws)
