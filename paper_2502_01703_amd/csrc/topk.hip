@@ -5,7 +5,7 @@
 // keys are distinct and "larger key" is exactly "selected earlier".  Steps:
 //   1. radix-select the k_sel-th largest key in passes of 8 bits (keys are formed on the fly from
 //   the scores); the passes stop as soon as the bucket that holds the k_sel-th key is selected as a
-//   whole.  Up to 32768 scores one workgroup does all (up to 8) passes in a single launch (a launch
+//   whole.  Up to 16384 scores one workgroup does all (up to 8) passes in a single launch (a launch
 //   costs more than such a pass; beyond that size the ~50 instructions per key and pass are too
 //   many for one compute unit).  Above that, one histogram launch for each of the four digits of
 //   the score, whose workgroups each first pick the digit of the pass before from its finished
@@ -27,7 +27,7 @@ namespace qless {
 constexpr int kSortBlock = 4096;   // keys sorted per workgroup in LDS (32 KB)
 constexpr int kSortOne = 16384;    // most (padded) selected keys that are ordered by rank instead of sorted
 constexpr int kPasses = 4;         // 8-bit digits of the score half of the keys (histogram launches)
-constexpr int64_t kSelectSmallMax = 32768;   // scores one workgroup selects from in a single launch
+constexpr int64_t kSelectSmallMax = 16384;   // scores one workgroup selects from in a single launch (top 5 % of 32768: 41 us, by the launches 33)
 
 struct TopkPlan {
     int64_t padded;                // power of two >= k_sel (>= kSortBlock)
@@ -304,8 +304,9 @@ topk_tie_scan_kernel(const SelectState *state, unsigned int *ties, int64_t chunk
 // with a whole bucket; otherwise score above the threshold score T, or equal to it and among the
 // first `remaining` such examples in array order (`ties` holds how many precede each group).
 __global__ void __launch_bounds__(256)
-topk_compact_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *ties,
+topk_compact_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *ties, int scanned,
                     unsigned long long *sel, unsigned int *rank, int64_t k_sel, int64_t padded) {
+    __shared__ unsigned int before[4];
     __shared__ unsigned int offs[4 * kCompactPer + 1];
     __shared__ unsigned int toffs[4 * kCompactPer];
     const SelectState fin = state[kPasses];
@@ -339,9 +340,17 @@ topk_compact_kernel(const float *score, int64_t N, SelectState *state, const uns
                 tmask[u] = __ballot(tie[u]);
                 if (lane == 0) toffs[u * 4 + wave] = (unsigned int)__popcll(tmask[u]);
             }
+            // ties in the groups before this one: from the scan, or summed here
+            if (!scanned && c0 < N) {
+                unsigned int mine = 0;
+                for (int64_t g = threadIdx.x; g < c0 / kChunk; g += 256) mine += ties[g];
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
+                if (lane == 0) before[wave] = mine;
+            }
             __syncthreads();
             if (threadIdx.x == 0) {
-                unsigned int run = c0 < N ? ties[c0 / kChunk] : 0u;
+                unsigned int run = c0 >= N ? 0u : (scanned ? ties[c0 / kChunk] : before[0] + before[1] + before[2] + before[3]);
                 for (int q = 0; q < 4 * kCompactPer; ++q) { const unsigned int v = toffs[q]; toffs[q] = run; run += v; }
             }
             __syncthreads();
@@ -394,11 +403,12 @@ topk_rank_kernel(const unsigned long long *sel, int64_t k_sel, int64_t seg, unsi
     const int64_t j0 = (int64_t)blockIdx.y * seg;
     const int64_t j1 = j0 + seg < k_sel ? j0 + seg : k_sel;
     for (int64_t jb = j0; jb < j1; jb += 1024) {
+        const int n = j1 - jb < 1024 ? (int)(j1 - jb) : 1024, up = (n + 15) & ~15;
         __syncthreads();
-        for (int t = threadIdx.x; t < 1024; t += 256) tile[t] = jb + t < j1 ? sel[jb + t] : 0ull;   // 0 is below every key
+        for (int t = threadIdx.x; t < up; t += 256) tile[t] = t < n ? sel[jb + t] : 0ull;   // 0 is below every key
         __syncthreads();
 #pragma unroll 8
-        for (int t = 0; t < 1024; t += 2) {
+        for (int t = 0; t < up; t += 2) {
             const ulonglong2 pr = *(const ulonglong2 *)&tile[t];
 #pragma unroll
             for (int e = 0; e < kRankPer; ++e) cnt[e] += (pr.x > mine[e]) + (pr.y > mine[e]);
@@ -518,19 +528,25 @@ static qless_status topk_run(const float *score, int64_t N, int64_t k_sel, int64
     const int64_t span = N > p.padded ? N : p.padded;
     int64_t cblocks = (span + kChunk - 1) / kChunk;
     if (cblocks > 2048) cblocks = 2048;
+    // up to 2^22 scores (4096 groups of 1024) the compaction sums the counts of the groups before its own itself: a launch less
+    const bool scan = p.chunks > 4096;
     if (!small) {
         int64_t tblocks = (N + kChunk - 1) / kChunk;
         if (tblocks > 2048) tblocks = 2048;
         hipLaunchKernelGGL(topk_tie_count_kernel, dim3((unsigned)tblocks), dim3(256), 0, st, score, N, state,
                            (const unsigned int *)hist, ties);
-        hipLaunchKernelGGL(topk_tie_scan_kernel, dim3(1), dim3(1024), 0, st, (const SelectState *)state, ties, p.chunks);
+        if (scan) hipLaunchKernelGGL(topk_tie_scan_kernel, dim3(1), dim3(1024), 0, st, (const SelectState *)state, ties, p.chunks);
     }
     hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)cblocks), dim3(256), 0, st, score, N, state,
-                       (const unsigned int *)ties, sel, rank, k_sel, p.padded);
+                       (const unsigned int *)ties, scan ? 1 : 0, sel, rank, k_sel, p.padded);
     if (p.padded <= kSortOne) {
         // few selected keys: rank every key among all of them, then write in rank order
         const unsigned kb = (unsigned)((k_sel + 255) / 256);
-        const int64_t seg = 1024;
+        // keys per workgroup and segment: a segment is one chain of LDS broadcasts (1024 keys: 13 us), so few selected keys are
+        // cut into short segments, down to 64 keys, as long as there are not far more workgroups than the chip holds
+        // (409 of 8192: 13 -> 2 us, 3276 of 65536: 14 -> 4 us); many keys keep 1024 and fewer atomics
+        int64_t seg = 1024;
+        while (seg > 64 && ((k_sel + 255) / 256) * ((k_sel + seg / 2 - 1) / (seg / 2)) <= 1024) seg >>= 1;
         const unsigned rb = (unsigned)((k_sel + 256 * kRankPer - 1) / (256 * kRankPer));
         hipLaunchKernelGGL(topk_rank_kernel, dim3(rb, (unsigned)((k_sel + seg - 1) / seg)), dim3(256), 0, st,
                            (const unsigned long long *)sel, k_sel, seg, rank);
