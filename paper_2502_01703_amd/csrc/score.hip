@@ -235,26 +235,22 @@ struct ScorePrep {                             // workspace views (device pointe
     int32_t vrow;                              // bytes per expanded validation row: kp, or kp / 2 for 1-bit (FP4 codes)
 };
 
-// position p (0..kp) of an expanded val row -> element index of the code vector
-template <int BITS>
-__device__ inline int val_source_element(int p) {
-    if (BITS == 8) return p;
-    if (BITS == 4) {
-        // inside a half K-step of 16: [0,2,4,6,1,3,5,7,8,10,12,14,9,11,13,15]
-        const int i = p & 15, base = p & ~15;
-        const int d = i >> 2, b = i & 3;               // dword d, byte b
-        return base + 8 * (d >> 1) + 2 * b + (d & 1);
-    }
-    // FP4 codes (1- and 2-bit), stages of 512 elements = 16 words of 32 codes per row.  K step ks of a
-    // stage (64 positions), half h: the train lane reads the 16-byte chunk 2 (ks / 4) + h and uses its
-    // dword ks % 4, i.e. word 4 (2 (ks / 4) + h) + ks % 4 of the stage; FP4 dword j, nibble n of the
-    // expansion is bit 4 n + 3 - j of that word.
-    const int g = p >> 6, h = (p >> 5) & 1, j = (p >> 3) & 3, n = p & 7;
-    const int stage = g >> 3, ks = g & 7;
-    const int word = 16 * stage + 4 * (2 * (ks >> 2) + h) + (ks & 3);
-    return 32 * word + 4 * n + 3 - j;
-}
-
+// The expanded validation rows, 16 bytes (a word of 32 bit-plane codes, 16 codes of 8 or 4 bits) per thread and round; the form
+// that took a byte or two codes at a time cost 21 us of the 157 us of a tile launch at 8192 x 256, k = 16384, 2 bits.
+// Order of the codes in a row:
+//   8 bits  as stored
+//   4 bits  inside a half K-step of 16: [0,2,4,6,1,3,5,7,8,10,12,14,9,11,13,15] (the even, then the odd nibbles of a dword)
+//   1, 2    FP4 codes, stages of 512 elements = 16 words of 32 codes: K step ks of a stage (64 positions), half h: the train lane
+//           reads the 16-byte chunk 2 (ks / 4) + h and uses its dword ks % 4, i.e. word 4 (2 (ks / 4) + h) + ks % 4 of
+//           the stage; FP4 dword j, nibble n of the expansion is bit 4 n + 3 - j of that word.
+//   1 bit on wide tiles: the train side feeds FP4 dword j of a word as the word's bits 4 n + 3 - j left in place (no shift),
+//           i.e. as 2 s, s, s / 2 for j = 1, 2, 3 with s = 1 for a negative code a = 1 - 2 s; the validation code b of such
+//           a position is stored as -b, -2 b, -4 b, so that every product is -2 s b = a b - b, and the sum of b over
+//           these positions is added back after the dot product (vbias).  j = 0 keeps +-1 on both sides.  (Few validation
+//           vectors: vrow == 0, the main kernel stages the packed codes itself.)
+//   2 bits  the train side leaves its "non-zero" bit of dwords 1, 2, 3 in place (FP4 2, 1, 1/2): the validation magnitudes are
+//           1/2, 1, 2 there, so that every product is a b.
+// Codes past the end of the vector, and rows past M, are 0.
 template <int BITS, bool F16 = false>        // F16: rows are bfloat16 bytes, no code norms (see score_mfma_kernel)
 __global__ void __launch_bounds__(256)
 score_prepare_kernel(ScoreArgs a, ScorePrep w) {
@@ -263,41 +259,28 @@ score_prepare_kernel(ScoreArgs a, ScorePrep w) {
     const bool live = row < a.M;
     const unsigned char *src = a.vc[ci] + (int64_t)(live ? row : 0) * ((int64_t)a.k * BITS / 8);
     if (BITS <= 2) {
-        // two FP4 codes per byte: 0x2 = +1.0, 0xA = -1.0, 0x0 = 0 (2-bit zeros, and past the end of the
-        // vector).  1-bit with few validation vectors (vrow == 0): the main kernel stages the packed codes itself.
-        // 1-bit on wide tiles: the train side feeds FP4 dword jd of a word as the word's bits 4 n + 3 - jd
-        // left in place (no shift), i.e. as 2 s, s, s / 2 for jd = 1, 2, 3 with s = 1 for a negative code
-        // a = 1 - 2 s; the validation code b of such a position is stored as -b, -2 b, -4 b, so that every
-        // product is -2 s b = a b - b, and the sum of b over these positions is added back after the
-        // dot product (vbias).  jd = 0 keeps +-1 on both sides.
         int bias = 0;
-        for (int bi = threadIdx.x; bi < w.vrow; bi += 256) {
-            unsigned byte = 0;
+        const int words = w.vrow / 16;
+        for (int t = threadIdx.x; t < words; t += 256) {
+            const int stage = t >> 4, ks = (t >> 1) & 7, h = t & 1;          // 16 bytes t of the row: K step 8 stage + ks, half h
+            const int wi = 16 * stage + 4 * (2 * (ks >> 2) + h) + (ks & 3);  // source word (rows and planes are whole words)
+            uint32_t d[4] = {0, 0, 0, 0};
+            if (live && wi * 32 < a.k) {
+                const uint32_t sg = ((const uint32_t *)(src + (BITS == 2 ? a.k / 8 : 0)))[wi];
+                const uint32_t nz = BITS == 2 ? ((const uint32_t *)src)[wi] : 0u;
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const int p = 2 * bi + e;
-                const int m = val_source_element<BITS>(p);               // source elements past k: code 0
-                if (live && m < a.k) {
-                    unsigned nz = 1u, neg;
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t s = (sg >> (3 - j)) & 0x11111111u;
                     if (BITS == 2) {
-                        nz = (src[m >> 3] >> (m & 7)) & 1u;
-                        neg = (src[a.k / 8 + (m >> 3)] >> (m & 7)) & 1u;
-                        // the train side leaves its "non-zero" bit of dwords 1, 2, 3 in place (FP4 2, 1, 1/2):
-                        // the validation magnitudes are 1/2, 1, 2 there, so that every product is a b
-                        const int jd = (p >> 3) & 3;
-                        const unsigned mag = jd == 1 ? 0x1u : (jd == 3 ? 0x4u : 0x2u);
-                        byte |= (nz ? (mag | (neg << 3)) : 0u) << (4 * e);
+                        const uint32_t x = (nz >> (3 - j)) & 0x11111111u;
+                        d[j] = x * (j == 1 ? 1u : (j == 3 ? 4u : 2u)) | ((x & s) << 3);
                     } else {
-                        neg = (src[m >> 3] >> (m & 7)) & 1u;
-                        const int jd = (p >> 3) & 3;
-                        const unsigned mag = jd == 3 ? 0x6u : (jd == 2 ? 0x4u : 0x2u);     // 4.0, 2.0, 1.0
-                        const unsigned sgn = jd == 0 ? neg : neg ^ 1u;
-                        byte |= (mag | (sgn << 3)) << (4 * e);
-                        if (jd != 0) bias += neg ? -1 : 1;
+                        d[j] = (j == 3 ? 0x66666666u : (j == 2 ? 0x44444444u : 0x22222222u)) | ((j == 0 ? s : s ^ 0x11111111u) << 3);
+                        if (j != 0) bias += 8 - 2 * (int)__popc(s);
                     }
                 }
             }
-            dst[bi] = (int8_t)byte;
+            *(uint4 *)(dst + 16 * t) = make_uint4(d[0], d[1], d[2], d[3]);
         }
         if (BITS == 1 && w.vrow > 0) {
             __shared__ int sh_bias;
@@ -308,14 +291,21 @@ score_prepare_kernel(ScoreArgs a, ScorePrep w) {
             if (threadIdx.x == 0) w.vbias[ci * w.Mp + row] = sh_bias;
         }
     } else {
-        for (int p = threadIdx.x; p < w.kp; p += 256) {
-            int q = 0;
-            if (live && p < a.k) {
-                const int m = val_source_element<BITS>(p);
-                if (BITS == 8) q = (int8_t)src[m];
-                else { q = (src[m >> 1] >> (4 * (m & 1))) & 0xF; if (q & 8) q -= 16; }
+        for (int t = threadIdx.x; t < w.kp / 16; t += 256) {
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (live && 16 * t < a.k) {
+                if (BITS == 8) {
+                    v = *(const uint4 *)(src + 16 * t);
+                } else {
+                    const uint2 p = *(const uint2 *)(src + 8 * t);
+                    auto widen = [](uint32_t x) {                             // nibbles in the low halves of the bytes, sign-extended
+                        x = (x & 0x0F0F0F0Fu) ^ 0x08080808u;
+                        return ((x | 0x80808080u) - 0x08080808u) ^ 0x80808080u;
+                    };
+                    v = make_uint4(widen(p.x), widen(p.x >> 4), widen(p.y), widen(p.y >> 4));
+                }
             }
-            dst[p] = (int8_t)q;
+            *(uint4 *)(dst + 16 * t) = v;
         }
     }
     if (threadIdx.x == 0)
