@@ -79,6 +79,7 @@ qless_status qless_init(void);
  *   ws         device workspace, 16-byte aligned, of at least qless_project_workspace(n, d_len, k) bytes
  * Arithmetic: gradient values enter as bfloat16 (fp32 input is rounded to nearest-even),
  * products are exact, sums are fp32 in a fixed order (results are run-to-run identical).
+ * A workspace of the size for some n and d_len serves every smaller n and d_len as well.
  * n == 0 or d_len == 0 is valid (P is zero-filled unless accumulating).
  * ------------------------------------------------------------------------------------------- */
 size_t qless_project_workspace(int64_t n, int64_t d_len, int32_t k);
@@ -181,10 +182,12 @@ qless_status qless_project_quantize_slice(const void *G, qless_dtype dt, int64_t
  *   full       device, N x M fp32 row-major receiving acc, or NULL (at least one of the two)
  *   ws         device workspace, 16-byte aligned, of at least qless_score_workspace(N, M, k, bits, C)
  *              bytes (0 for the configurations that need none).  It holds the validation codes
- *              expanded for the tiled matrix-core path and the running row maxima; for sign codes
+ *              as the tiled matrix-core paths stage them and the running row maxima; for sign codes
  *              against 17 .. 192 validation vectors a bit-permuted copy of the validation codes and
- *              their per-row counts; the path that streams bit-plane codes against at most 16
- *              validation vectors leaves it untouched, unless the checkpoints are scored in groups of
+ *              their per-row counts; for few pairs partial dot products (at most 256 MB; a workspace
+ *              laid out for more train rows serves such a call by the other paths if it cannot hold them);
+ *              the path that streams bit-plane codes against at most 16 validation vectors leaves it
+ *              untouched, unless the checkpoints are scored in groups of
  *              launches (their validation rows do not all fit in LDS): then it carries N x 16 fp32
  *              sums from one launch to the next.
  * N == 0 is valid; M >= 1.  Whichever kernels a shape selects, the results are the same bits.  With
@@ -292,9 +295,8 @@ qless_status qless_aggregate(const float *full, int64_t N, int32_t M, const int3
 /* ---------------------------------------------------------------------------------------------
  * qless_score and qless_aggregate in one call: out[z][t] = maximum or mean, as defined for
  * qless_aggregate, of acc(z, z') of qless_score over the validation columns of group t -- the same bits
- * as the two calls, without the N x M matrix in memory (with more than 64 validation vectors the
- * aggregation is the epilogue of the scoring kernel; below that the matrix is small and passes through
- * the workspace).  Arguments as for qless_score and qless_aggregate;
+ * as the two calls.  The matrix passes through the workspace in blocks of train rows, at most 2 GiB of it
+ * at a time.  Arguments as for qless_score and qless_aggregate;
  *   out   device, N x T fp32 row-major
  *   ws    device workspace, 16-byte aligned, of at least qless_score_groups_workspace(N, M, k, bits, C) bytes
  * ------------------------------------------------------------------------------------------- */

@@ -704,14 +704,19 @@ __global__ void generator_words_kernel(SeedKeys sk, uint32_t m0, int32_t nrows, 
 
 using namespace qless;
 
+// Enough for every kind of input and for every smaller batch or gradient length (the plans of those may cut d into more
+// slices, and a program that lays its workspace out for its largest batch uses it for the last one too): a batch
+// of n rows in tiles of r takes at most the slices of two rounds, shared by its row tiles.
 extern "C" size_t qless_project_workspace(int64_t n, int64_t d_len, int32_t k) {
     if (n <= 0 || d_len <= 0 || k <= 0) return 0;
-    // enough for either matrix family and input type (their tile shapes, hence their d-splits, may differ)
-    ProjectPlan p[kPlanKinds];
-    make_plans(n, d_len, k, p);
-    size_t most = 0;
-    for (const ProjectPlan &q : p) most = q.ws_bytes > most ? q.ws_bytes : most;
-    return most;
+    int64_t rows = 0;                                              // n times d-slices, at most
+    for (const TileCost &c : kTileCost) {
+        const int64_t kt = (k + c.cols - 1) / c.cols, w = 2 * (32 * c.per_cu) / kt * 8, r = (n < c.rows ? n : c.rows) * w;
+        rows = r > rows ? r : rows;
+    }
+    const int64_t stages = (d_len + kStageD - 1) / kStageD;
+    if (stages < rows && n * stages < rows) rows = n * stages;
+    return (size_t)(rows > n ? rows : n) * (size_t)k * sizeof(float);
 }
 
 template <ProjectInput IN, bool GAUSS, int NR, int NX>

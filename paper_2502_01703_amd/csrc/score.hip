@@ -3,7 +3,8 @@
 // reduced by max over validation examples.
 //
 // Integer dot products are exact; how they are formed depends on the code width:
-//   8-/4-bit: int8 x int8 -> int32 MFMA (v_mfma_i32_32x32x32_i8) on codes unpacked in registers
+//   8-/4-bit: int8 x int8 -> int32 MFMA (v_mfma_i32_32x32x32_i8) on codes unpacked in registers; against
+//           more than 64 validation vectors by the kernels of score_wide.hip
 //   2-/1-bit: the codes {-1, 0, +1} are exactly representable as FP4 (E2M1) values; the scaled FP4
 //           matrix-core instructions multiply them and sum in fp32, which is exact for these integers
 //           (|D| <= k <= 65536 < 2^24): v_mfma_scale_f32_32x32x64_f8f6f4 in score_mfma_kernel, and for at
@@ -194,7 +195,8 @@ score_popcount_kernel(ScoreArgs a) {
 constexpr int kStreamVal = 8;                  // bit-plane codes against at most this many val vectors never take the tile kernel (no workspace)
 
 // ------------------------------------------------------------------------------------------
-// Matrix-core kernel for all four code widths.
+// Matrix-core kernel for the 2-/1-bit codes, and for the 8-/4-bit codes against few validation vectors or in
+// small datastores.
 //
 // A small pre-pass expands the validation codes of every checkpoint to int8 rows (8-/4-bit) or
 // FP4 rows (2-/1-bit), padded to the tile size and in the K order in which the train operand is
@@ -1046,7 +1048,7 @@ score_stream_mfma32_kernel(ScoreArgs a, const int8_t *vexp, const int32_t *vsum,
 // Shape of the NW waves of a workgroup: WX waves across the val tile, NW / WX down the train
 // rows; each wave owns WR x WC accumulators of 32 x 32.  Train tile height MT = 32 WR NW / WX, val
 // tile width VT = 32 WC WX:
-//   M > 64: <2, 2, 2, 8> (64 x 64 per wave, 256 x 128 per workgroup), or for sign codes <2, 3, 1, 8>
+//   M > 64 (2-/1-bit): <2, 2, 2, 8> (64 x 64 per wave, 256 x 128 per workgroup), or for sign codes <2, 3, 1, 8>
 //   (64 x 96 per wave, 512 x 96 per workgroup) when that pads M less;  M <= 64: <1, 2, 1, 8> (256 x 64);
 //   M <= 32: <1, 1, 1, 8> (256 x 32) or <1, 1, 1, 4> (128 x 32), whichever fills the chip more evenly.
 template <int BITS, int WR, int WC, int WX, int NW, bool VH = false>
@@ -1946,14 +1948,9 @@ extern "C" qless_status qless_score(const void *const *train_codes, const float 
     hipStream_t st = (hipStream_t)stream;
     const qless_status ready = device_ready();            // LDS limits of the kernels, once per device
     if (ready != QLESS_OK) return ready;
-    if (score_splits(N, M, k, bits, C)) {
-        if (ws && ws_bytes >= split_workspace(N, M, (int64_t)k * bits / 8, bits, C) && (uintptr_t)ws % 16 == 0)
-            return launch_split(a, bits, ws, st);
-        // a configuration whose other path needs no workspace is served by it without one
-        const StreamMfmaPlan sp = stream_mfma_plan(M, k, bits, C);
-        const bool streams = bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0 && sp.nb >= 2;
-        if (streams ? stream_mfma_partial_bytes(sp, N, C) > 0 : score_base_workspace(N, M, k, bits, C) > 0) return QLESS_ERR_WORKSPACE;
-    }
+    // (a workspace laid out for a larger call may be too small for the parts: the other paths serve that as well)
+    if (score_splits(N, M, k, bits, C) && ws && (uintptr_t)ws % 16 == 0 && ws_bytes >= qless_score_workspace(N, M, k, bits, C))
+        return launch_split(a, bits, ws, st);
     if (bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0) {
         const StreamMfmaPlan sp = stream_mfma_plan(M, k, bits, C);
         if (sp.nb >= 2) {
@@ -2031,10 +2028,10 @@ extern "C" qless_status qless_score_groups(const void *const *train_codes, const
     if (group_end[T - 1] != M) return QLESS_ERR_INVALID_ARG;
     if (N == 0) return QLESS_OK;
     if (!out) return QLESS_ERR_INVALID_ARG;
-    const size_t need = qless_score_groups_workspace(N, M, k, bits, C);
-    if (!ws || ws_bytes < need || (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
     const int64_t block = groups_block_rows(N, M);
     const size_t full_bytes = groups_matrix_bytes(block, M);
+    const size_t need = full_bytes + score_base_workspace(block, M, k, bits, C) + 16;    // (qless_score does without its parts)
+    if (!ws || ws_bytes < need || (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
     const int64_t cb = (int64_t)k * bits / 8;
     for (int64_t r0 = 0; r0 < N; r0 += block) {
         const int64_t rows = N - r0 < block ? N - r0 : block;
@@ -2081,11 +2078,11 @@ extern "C" qless_status qless_score16(const void *const *train16, const void *co
     }
     a.C = C; a.N = N; a.M = M; a.k = 2 * k; a.score = score; a.full = full;     // k in bytes from here on
     if (N == 0) return QLESS_OK;
-    const size_t need = qless_score16_workspace(N, M, k, C);
-    if (!ws || ws_bytes < need) return QLESS_ERR_WORKSPACE;
+    if (!ws || ws_bytes < tiles_workspace(N, M, a.k, 8, C)) return QLESS_ERR_WORKSPACE;
     if ((uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
     const qless_status ready = device_ready();
     if (ready != QLESS_OK) return ready;
-    if (use_split(N, M, a.k, 16, C)) return launch_split(a, 16, ws, (hipStream_t)stream);
+    // (a workspace laid out for a larger call may be too small for the parts: the tile kernels serve that as well)
+    if (use_split(N, M, a.k, 16, C) && ws_bytes >= split_workspace(N, M, a.k, 16, C)) return launch_split(a, 16, ws, (hipStream_t)stream);
     return launch_mfma<8, true>(a, ws, (hipStream_t)stream);
 }

@@ -262,7 +262,7 @@ bool use_split(int64_t N, int32_t M, int64_t row_bytes, int bits, int C) {
     const double tiles = (double)((N + kSplitTile - 1) / kSplitTile) * (double)((M + kSplitTile - 1) / kSplitTile);
     // (the second kernel takes a workgroup per row: 1.2 ns each)
     double here = 12 + tiles * kSplitTile * kSplitTile * (double)row_bytes / 32 / 6e6 * C + (double)N * 1.2e-3;
-    if (here >= there || tiles > 65536) return false;
+    if (here >= there || tiles > 65535) return false;       // (a grid takes 65535 val tiles)
     const SplitPlan p = split_plan(N, M, row_bytes, bits, C);
     here += (double)p.bytes * 2 / 4e6;
     return here < there && p.bytes <= ((size_t)256 << 20) && C * p.parts <= 65535;

@@ -11,8 +11,9 @@
 //   the score, whose workgroups each first pick the digit of the pass before from its finished
 //   histogram (a 256-bin scan, cheaper than a launch of its own); if the threshold score T is then
 //   shared by more examples than are still to be taken, the r with the smallest indices are the
-//   first r in array order: a count of the examples with score T per 1024 examples and an exclusive
-//   scan of these counts give every such example its position among them;
+//   first r in array order: a count of the examples with score T per 1024 examples and the sum of the
+//   counts before them (taken by the compaction itself, above 4096 such groups by a scan launch) give
+//   every such example its position among them;
 //   2. compact all selected keys (exactly k_sel of them; one atomic per workgroup and 1024 examples);
 //   3. order them, descending: up to 16384 selected keys by rank (every key counts the larger ones
 //   among all of them, k_sel^2 comparisons spread over the whole chip, and is written to the slot of

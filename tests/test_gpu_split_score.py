@@ -79,3 +79,31 @@ def test_without_a_workspace_where_none_was_needed():
                              ctypes.c_void_p(out.data_ptr()), None, None, 0, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
     assert rc == 0
     assert torch.equal(out, with_ws)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 4, 8, 16])
+def test_workspace_laid_out_for_a_larger_call(bits):
+    """A program lays its workspace out for the whole datastore and scores a few rows with it: the partial dot products of the few
+    pairs need more (1000 x 597 here), and the call is served all the same, with the same integers in the same epilogue."""
+    n, N, M, k, C = 1000, 94753, 597, 6080 if bits < 16 else 1920, 2
+    _say("workspace of a larger call, bits=%d" % bits)
+    arr = lambda ts: (ctypes.c_void_p * C)(*[t.data_ptr() for t in ts])
+    eta = ctypes.cast((ctypes.c_float * C)(*_eta(C)), ctypes.c_void_p)
+    out = torch.empty(n, dtype=torch.float32, device=DEV)
+    stream = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    L, ptr = Q.lib(), lambda t: ctypes.c_void_p(t.data_ptr())
+    if bits == 16:
+        g = torch.Generator(device=DEV)
+        g.manual_seed(3)
+        t16 = [Q.normalize16(torch.randn(n, k, generator=g, device=DEV)) for _ in range(C)]
+        v16 = [Q.normalize16(torch.randn(M, k, generator=g, device=DEV)) for _ in range(C)]
+        ws = torch.empty(L.qless_score16_workspace(N, M, k, C), dtype=torch.uint8, device=DEV)
+        assert L.qless_score16(arr(t16), arr(v16), eta, C, n, M, k, ptr(out), None, ptr(ws), ws.numel(), stream) == 0
+        # two sums of at most k / 16 chained fp32 additions of exact products of unit rows
+        assert (out - Q.score16(t16, v16, _eta(C))).abs().max() <= C * 2.0 ** -16
+        return
+    tc, tr = _store(n, k, C, bits, 1)
+    vc, vr = _store(M, k, C, bits, 2)
+    ws = torch.empty(L.qless_score_workspace(N, M, k, bits, C) + 16, dtype=torch.uint8, device=DEV)
+    assert L.qless_score(arr(tc), arr(tr), arr(vc), arr(vr), eta, C, n, M, k, bits, ptr(out), None, ptr(ws), ws.numel(), stream) == 0
+    assert torch.equal(out, Q.score(tc, tr, vc, vr, _eta(C), k, bits))
