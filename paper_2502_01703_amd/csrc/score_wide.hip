@@ -83,10 +83,31 @@ struct WideShape {
     static_assert((NBUF - 1) * LPW < 64, "vmcnt is a 6-bit counter");
 };
 
+// Where the copies of train rows read, in bytes from the tile's first row (and the stage's 128 q bytes into it): copy q takes
+// rows 8 q + lane / 8, chunk (lane % 8) ^ ((row / 2) % 8).
+//   wide_lane_offset     the lane's part beside the wave-uniform 8 q cb.  Chunks past a row's end read on into the rows
+//                        after it (the validation bytes there are zero).
+//   wide_reads_past      whether that leaves the store: its last rows are shorter than a stage, and one row of 32 bytes
+//                        (4 bits, k = 64) reaches three rows on, so this can be the tile before the last one as well.
+//   wide_clamped_offset  for such tiles: rows past N re-read the last row (masked later), chunks past the row end its last
+//                        16 bytes.  over: bytes of this stage past the end of a row.
+__host__ __device__ inline unsigned wide_lane_offset(unsigned lane, int q, int cb) {
+    return (lane >> 3) * (unsigned)cb + (((lane & 7) ^ ((4u * (unsigned)q + (lane >> 4)) & 7)) << 4);
+}
+__host__ __device__ inline bool wide_reads_past(int64_t row0, int MT, int64_t N, int cb, int nst) {
+    return (row0 + MT - 1) * cb + (int64_t)nst * 128 > N * cb;
+}
+__host__ __device__ inline unsigned wide_clamped_offset(unsigned lane, int q, int64_t row0, int64_t N, int cb, int over) {
+    const int64_t r = row0 + q * 8 + (int)(lane >> 3), gr = r < N ? r : N - 1;
+    int at = (int)(((lane & 7) ^ ((4u * (unsigned)q + (lane >> 4)) & 7)) << 4);
+    if (over > 0 && at > 112 - over) at = 112 - over;
+    return (unsigned)((gr - row0) * cb) + (unsigned)at;
+}
+
 // EDGE = false: every tile has MT rows that exist (the last one starts at N - MT and repeats rows of the tile before
 // it, with the same results) and rows are whole stages.  EDGE = true: fewer train rows than a tile, or rows that
-// end inside a stage, which the last tile may not read past; the branch this takes per copy costs 10 % in the 256 x 128
-// shape (2.42 against 2.20 ms, bfloat16 65536 x 512).
+// end inside a stage, whose last tiles may not read past the store; the branch this takes per copy costs 10 % in the
+// 256 x 128 shape (2.42 against 2.20 ms, bfloat16 65536 x 512).
 template <class Sh, bool EDGE>
 __global__ void __launch_bounds__(64 * Sh::NW, Sh::NW / 4)
 score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
@@ -114,12 +135,11 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
     // and a spilled register is read back through the same counter as the copies.
     const int T = a.C * w.nst;                            // stages of all checkpoints, one pipeline
     const int over = EDGE ? w.nst * 128 - w.cb : 0;       // bytes of the last stage past the end of a train row
-    const bool last_tile = EDGE && tt == ttiles - 1;
+    const bool clamped = EDGE && wide_reads_past(row0, MT, a.N, w.cb, w.nst);
     const int q0 = wave * TU, v0 = wave * VU < VCP ? wave * VU : VCP - 1;     // first copy of either side
     unsigned train_lane[2];                               // of copies of even and odd distance from q0
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
-        train_lane[e] = (unsigned)((lane >> 3) * w.cb + (((lane & 7) ^ ((4 * (q0 + e) + (lane >> 4)) & 7)) << 4));
+    for (int e = 0; e < 2; ++e) train_lane[e] = wide_lane_offset((unsigned)lane, q0 + e, w.cb);
     const unsigned val_lane = (unsigned)(lane * 16);
     int i_it = 0, i_ci = 0, i_s = 0, i_buf = 0;           // the next stage to request
     const unsigned char *tb = a.tc[0] + row0 * w.cb;
@@ -132,19 +152,12 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
         }
         const int q = q0 + u;
         const unsigned lds = lds0 + (unsigned)(i_buf * BUF + q * 1024);
-        if (!last_tile) {
-            // chunk (lane % 8) ^ ((r / 2) % 8) of row r = 8 q + lane / 8; past the row end this is the next row (the
-            // validation bytes there are zero)
+        if (!clamped) {
             global_to_lds16(tb + (unsigned)(q * 8 * w.cb), train_lane[u & 1], lds);
         } else {
-            // rows past N re-read the last row (masked later), chunks past the row end its last 16 bytes; the lane
-            // number is made opaque so that this stays in its branch
-            unsigned l = (unsigned)lane;
+            unsigned l = (unsigned)lane;                  // opaque, so that this stays in its branch
             asm volatile("" : "+v"(l));
-            const int64_t r = row0 + q * 8 + (int)(l >> 3), gr = r < a.N ? r : a.N - 1;
-            int at = (int)(((l & 7) ^ ((4u * (unsigned)q + (l >> 4)) & 7)) << 4);
-            if (over > 0 && i_s == w.nst - 1 && at > 112 - over) at = 112 - over;
-            global_to_lds16(tb, (unsigned)((gr - row0) * w.cb) + (unsigned)at, lds);
+            global_to_lds16(tb, wide_clamped_offset(l, q, row0, a.N, w.cb, i_s == w.nst - 1 ? over : 0), lds);
         }
     };
     auto copy_next = [&]() {
@@ -391,4 +404,37 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
     return launch_status();
 }
 
+template <class Sh>
+static int64_t wide_reach(int64_t N, int cb) {
+    const int nst = (cb + 127) / 128, over = nst * 128 - cb;
+    const int64_t ttiles = (N + Sh::MT - 1) / Sh::MT;
+    const bool edge = !(N >= Sh::MT && cb % 128 == 0);
+    int64_t most = 0;
+    for (int64_t tt = ttiles > 3 ? ttiles - 3 : 0; tt < ttiles; ++tt) {
+        const int64_t row0 = edge || tt * Sh::MT + Sh::MT <= N ? tt * Sh::MT : N - Sh::MT;
+        const bool clamped = edge && wide_reads_past(row0, Sh::MT, N, cb, nst);
+        for (int s = 0; s < nst; ++s)
+            for (int q = 0; q < Sh::TCP; ++q)
+                for (unsigned lane = 0; lane < 64; ++lane) {
+                    const int64_t off = clamped ? (int64_t)wide_clamped_offset(lane, q, row0, N, cb, s == nst - 1 ? over : 0)
+                                                : (int64_t)q * 8 * cb + wide_lane_offset(lane, q, cb);
+                    const int64_t end = row0 * cb + (int64_t)s * 128 + off + 16;
+                    most = end > most ? end : most;
+                }
+    }
+    return most;
+}
+
 }  // namespace qless
+
+// For the tests, host only: the end of the last byte of the train rows that any copy of tile shape `shape` reads (at most
+// N * row_bytes), from the kernel's own address arithmetic.
+extern "C" int64_t qless_internal_wide_reach(int64_t N, int row_bytes, int shape) {
+    using namespace qless;
+    switch (shape) {
+        case 0: return wide_reach<WideShape<8, 3, 2, 2, 4, 2>>(N, row_bytes);
+        case 1: return wide_reach<WideShape<8, 2, 3, 4, 2, 2>>(N, row_bytes);
+        case 2: return wide_reach<WideShape<8, 2, 2, 4, 2, 3>>(N, row_bytes);
+        default: return wide_reach<WideShape<8, 2, 3, 8, 1, 2>>(N, row_bytes);
+    }
+}

@@ -102,3 +102,22 @@ def test_score_groups_blocks_of_rows(bits):
     got = Q.score_groups(tc, tr, vc, vr, ETA[:C], k, bits, ends, Q.AGG_MEAN)
     full = Q.score(tc, tr, vc, vr, ETA[:C], k, bits, want_score=False, want_full=True)
     assert torch.equal(got.view(torch.int32), Q.aggregate(full, ends, Q.AGG_MEAN).view(torch.int32))
+
+
+# (N, M): the last tile holds one or two rows, in each of the four tile shapes; its rows of 32 bytes are shorter than a stage by
+# three rows
+@pytest.mark.parametrize("N,M", [(30145, 513), (30146, 513), (30209, 257), (30210, 257), (30209, 129), (30210, 129), (32769, 257),
+                                 (32770, 257)])
+def test_wide_rows_shorter_than_a_stage(N, M):
+    k, bits = 64, 4
+    _say("wide bits=4 k=64 N=%d M=%d" % (N, M))
+    tc, tr = _store(N, k, 1, bits, N)
+    vc, vr = _store(M, k, 1, bits, M)
+    got, full = Q.score(tc, tr, vc, vr, ETA[:1], k, bits, want_full=True)
+    at = _rows(N)
+    pick = torch.from_numpy(at).to(DEV)
+    ref, ref_full = oracle.score([tc[0][pick].cpu().numpy()], [tr[0][pick].cpu().numpy()], [vc[0].cpu().numpy()],
+                                 [vr[0].cpu().numpy()], ETA[:1], k, bits, want_full=True)
+    np.testing.assert_array_equal(_bits(got[pick].cpu().numpy()), _bits(ref))
+    np.testing.assert_array_equal(_bits(full[pick].cpu().numpy()), _bits(ref_full))
+    assert torch.equal(full.amax(1), got)
