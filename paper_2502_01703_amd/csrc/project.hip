@@ -653,39 +653,40 @@ __global__ void __launch_bounds__(256)
 project_reduce_kernel(const float *ws, int nsplit, int64_t n, int32_t k, int accumulate,
                       float *P, int64_t ldP, int vec) {
     const int64_t total = n * (int64_t)k;
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= total) return;
-    const float4 *src = (const float4 *)(ws + i);
     const size_t plane = (size_t)total / 4;                   // k is a multiple of 64
-    float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    int sp = 0;
-    for (; sp + 8 <= nsplit; sp += 8) {
-        float4 t[8];
+    for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < total; i += (int64_t)gridDim.x * 1024) {
+        const float4 *src = (const float4 *)(ws + i);
+        float4 s = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        int sp = 0;
+        for (; sp + 8 <= nsplit; sp += 8) {
+            float4 t[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = src[(size_t)(sp + u) * plane];
+            for (int u = 0; u < 8; ++u) t[u] = src[(size_t)(sp + u) * plane];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
-    }
-    for (; sp < nsplit; ++sp) {
-        const float4 t = src[(size_t)sp * plane];
-        s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-    }
-    const int64_t row = i / k, m = i - row * k;
-    float *dst = P + row * ldP + m;
-    if (vec) {
-        if (accumulate) {
-            const float4 o = *(const float4 *)dst;
-            s.x = o.x + s.x; s.y = o.y + s.y; s.z = o.z + s.z; s.w = o.w + s.w;
+            for (int u = 0; u < 8; ++u) { s.x += t[u].x; s.y += t[u].y; s.z += t[u].z; s.w += t[u].w; }
         }
-        *(float4 *)dst = s;
-    } else {
-        const float v[4] = {s.x, s.y, s.z, s.w};
+        for (; sp < nsplit; ++sp) {
+            const float4 t = src[(size_t)sp * plane];
+            s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
+        }
+        const int64_t row = i / k, m = i - row * k;
+        float *dst = P + row * ldP + m;
+        if (vec) {
+            if (accumulate) {
+                const float4 o = *(const float4 *)dst;
+                s.x = o.x + s.x; s.y = o.y + s.y; s.z = o.z + s.z; s.w = o.w + s.w;
+            }
+            *(float4 *)dst = s;
+        } else {
+            const float v[4] = {s.x, s.y, s.z, s.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dst[e] = accumulate ? dst[e] + v[e] : v[e];
+            for (int e = 0; e < 4; ++e) dst[e] = accumulate ? dst[e] + v[e] : v[e];
+        }
     }
 }
 static void launch_reduce(const float *ws, int nsplit, int64_t n, int32_t k, int accumulate, float *P, int64_t ldP, hipStream_t st) {
-    const int64_t blocks = (n * (int64_t)k / 4 + 255) / 256;
+    int64_t blocks = (n * (int64_t)k / 4 + 255) / 256;
+    if (blocks > 1 << 20) blocks = 1 << 20;                   // a launch takes fewer than 2^32 threads (n k of 2^34 and more)
     const int vec = (uintptr_t)P % 16 == 0 && ldP % 4 == 0;
     hipLaunchKernelGGL(project_reduce_kernel, dim3((unsigned)blocks), dim3(256), 0, st, ws, nsplit, n, k, accumulate, P, ldP, vec);
 }
