@@ -361,14 +361,16 @@ static qless_status launch_wide_shape(const ScoreArgs &a, WidePrep w, bool prepa
 
 // The shape with the least padded work: rounds of one workgroup per compute unit, times the tile's pairs, times what a
 // pair costs in the shape (measured at N = 270 000, M = 285 and 1024, 8 and 4 bits, relative to the 96 x 64 wavefronts:
-// 256 x 128 6 %, 512 x 96 16 % more per pair -- more operand bytes per product).
+// 256 x 128 6 %, 512 x 96 16 % more per pair -- more operand bytes per product).  The validation tiles of a train tile run
+// on one XCD, so the rounds are those of the XCD with the most train tiles: 25 316 x 773 in tiles of 256 x 192 is 495
+// workgroups, but 65 of them on three of the XCDs, a third round (6016 codes of 4 bits: 202 us; 256 x 128: 169).
 static int choose_shape(int64_t N, int32_t M) {
     static const struct { int mt, vt; double cost; } s[4] = {{192, 256, 1.0}, {256, 192, 1.0}, {256, 128, 1.06}, {512, 96, 1.16}};
-    const int64_t cus = compute_units();
+    const int64_t cus = (compute_units() + 7) / 8;                   // per XCD
     int best = 0;
     double least = 0;
     for (int i = 0; i < 4; ++i) {
-        const int64_t tiles = ((N + s[i].mt - 1) / s[i].mt) * ((M + s[i].vt - 1) / s[i].vt);
+        const int64_t ttiles = (N + s[i].mt - 1) / s[i].mt, tiles = (ttiles + 7) / 8 * ((M + s[i].vt - 1) / s[i].vt);
         const double c = (double)((tiles + cus - 1) / cus) * s[i].mt * s[i].vt * s[i].cost;
         if (i == 0 || c < least) { best = i; least = c; }
     }
@@ -438,3 +440,6 @@ extern "C" int64_t qless_internal_wide_reach(int64_t N, int row_bytes, int shape
         default: return wide_reach<WideShape<8, 2, 3, 8, 1, 2>>(N, row_bytes);
     }
 }
+
+// For the tests, host only: the tile shape that a call with N train rows and M validation vectors takes.
+extern "C" int qless_internal_wide_shape(int64_t N, int32_t M) { return qless::choose_shape(N, M); }
