@@ -891,3 +891,13 @@ extern "C" qless_status qless_generator_words(uint64_t seed, uint32_t m0, int32_
                        (hipStream_t)stream, seed_keys(seed), m0, nrows, w0, nwords, salt, out);
     return launch_status();
 }
+
+// For the tests, host only: {rows and coordinates of the tile, d-slices, 128-column stages per d-slice, workspace bytes} of a
+// projection's plan.
+extern "C" void qless_internal_project_plan(int64_t n, int64_t d_len, int32_t k, int gauss, int fp32, int64_t *out) {
+    ProjectPlan plans[kPlanKinds];
+    make_plans(n, d_len, k, plans);
+    const ProjectPlan &p = plans[plan_kind(gauss != 0, fp32 != 0)];
+    out[0] = kTileCost[p.shape].rows; out[1] = kTileCost[p.shape].cols;
+    out[2] = p.nsplit; out[3] = p.stages_per_split; out[4] = (int64_t)p.ws_bytes;
+}

@@ -1,6 +1,9 @@
-"""Projection of batches that do not fill 64-row tiles, against the oracle: row counts at the edges of the 16-, 32- and 48-row
-tiles, coordinate counts at the edges of the 512- and 1024-wide ones, gradient lengths that leave the second group of wavefronts
-without columns or end inside a 16-byte chunk, rows at every alignment, and the whole path's determinism."""
+"""Projection against the oracle in every tile shape: test_every_tile names the shape that each of its sizes takes and asks the library
+for it -- full tiles and one row less, remainders of rows and coordinates, d-slices with an odd number of 128-column stages (the second
+group of wavefronts is left without columns), for every input; the other tests go over row counts, coordinate counts, short
+lengths and alignments whatever tile they take, and compare the copies through registers with the asynchronous ones."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -33,6 +36,43 @@ def _check(G, k, kind, seed):
     # bf16: exact products, fp32 sums; fp32 input is rounded to bf16 first (2^-9 per entry, random signs)
     assert err.max() <= (1e-4 if G.dtype == torch.bfloat16 else 1e-2), err.max()
     return got
+
+
+def _tile(n, d, k, kind, dtype):
+    plan = Q.lib().qless_internal_project_plan
+    plan.restype, plan.argtypes = None, [Q._i64, Q._i64, Q._i32, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    out = (ctypes.c_int64 * 5)()
+    plan(n, d, k, int(kind == Q.GAUSSIAN), int(dtype == torch.float32), ctypes.cast(out, ctypes.c_void_p))
+    return out[0], out[1]
+
+
+# (tile) -> {(kind, fp32): [(n, stages of 128 columns, k), ...]}
+TILES = {
+    (128, 512): {(Q.RADEMACHER, 0): [(129, 257, 64)], (Q.RADEMACHER, 1): [(127, 513, 64)],
+                 (Q.GAUSSIAN, 0): [(128, 513, 64), (129, 257, 64), (127, 17, 8256)], (Q.GAUSSIAN, 1): [(127, 513, 64), (129, 257, 64)]},
+    (64, 1024): {(Q.RADEMACHER, 1): [(63, 513, 64), (64, 513, 64), (257, 49, 64)], (Q.GAUSSIAN, 0): [(49, 25, 8256)]},
+    (48, 1024): {(Q.RADEMACHER, 0): [(47, 513, 64), (48, 513, 64), (49, 257, 448), (47, 3, 1088)],
+                 (Q.RADEMACHER, 1): [(48, 513, 64), (49, 257, 448)],
+                 (Q.GAUSSIAN, 0): [(1, 9, 8256), (17, 9, 8256), (49, 33, 8256)], (Q.GAUSSIAN, 1): [(16, 9, 8256)]},
+    (48, 512): {(Q.RADEMACHER, 0): [(47, 801, 64), (48, 801, 64), (47, 25, 8256)], (Q.RADEMACHER, 1): [(48, 2049, 64), (193, 25, 1088)],
+                (Q.GAUSSIAN, 0): [(47, 801, 64), (48, 801, 64), (47, 25, 8256)], (Q.GAUSSIAN, 1): [(48, 801, 64), (193, 193, 448)]},
+    (32, 512): {(Q.RADEMACHER, 0): [(31, 801, 64), (32, 801, 64), (129, 33, 1088), (31, 17, 8256)],
+                (Q.RADEMACHER, 1): [(32, 801, 64), (129, 193, 448)],
+                (Q.GAUSSIAN, 0): [(31, 801, 64), (32, 801, 64), (97, 65, 1088), (31, 25, 8256)], (Q.GAUSSIAN, 1): [(32, 801, 64)]},
+    (16, 512): {(Q.RADEMACHER, 0): [(1, 801, 64), (15, 1025, 64), (16, 2049, 64)], (Q.RADEMACHER, 1): [(16, 1025, 64), (65, 385, 448)],
+                (Q.GAUSSIAN, 0): [(1, 801, 64), (16, 2561, 64), (15, 193, 4160)], (Q.GAUSSIAN, 1): [(1, 801, 64), (16, 2561, 64)]}}
+
+
+@pytest.mark.parametrize("tile", sorted(TILES))
+def test_every_tile(tile):
+    for (kind, fp32), sizes in TILES[tile].items():
+        dtype = torch.float32 if fp32 else torch.bfloat16
+        for n, stages, k in sizes:
+            # whole stages (bf16: asynchronous copies), the same from odd row offsets (through registers), an end inside a chunk
+            for d, pad, lead in ((128 * stages, 0, 0), (128 * stages, 3, 1), (128 * stages - 5, 0, 0))[fp32:]:
+                _say("projection tile %dx%d kind=%d %s n=%d d=%d k=%d pad=%d" % (tile + (kind, dtype, n, d, k, pad)))
+                assert _tile(n, d, k, kind, dtype) == tile
+                _check(_gradients(n, d, pad, lead, dtype, n + d), k, kind, 7)
 
 
 @pytest.mark.parametrize("kind", [Q.RADEMACHER, Q.GAUSSIAN])
