@@ -1,16 +1,33 @@
-"""Host-side: a projection workspace serves every smaller batch and gradient length of the same projection."""
+"""Host-side: a projection workspace serves every smaller batch and gradient length of the same projection, whatever the plans of
+those take."""
+import ctypes
 import random
 
 from paper_2502_01703_amd import binding as Q
 
 
+def _plan_bytes(n, d, k):
+    """The most that the plans of the four kinds of input take."""
+    plan = Q.lib().qless_internal_project_plan
+    plan.restype, plan.argtypes = None, [Q._i64, Q._i64, Q._i32, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
+    out = (ctypes.c_int64 * 5)()
+    most = 0
+    for gauss in (0, 1):
+        for fp32 in (0, 1):
+            plan(n, d, k, gauss, fp32, ctypes.cast(out, ctypes.c_void_p))
+            assert out[2] * out[3] * 128 >= d > (out[2] - 1) * out[3] * 128          # the slices cover the columns, none is empty
+            most = max(most, out[4])
+    return most
+
+
 def test_workspace_serves_smaller_batches_and_lengths():
     rng = random.Random(5)
-    for _ in range(2000):
-        k = 64 * rng.choice([1, 8, 42, 52, 128, 256])
-        n = rng.randint(1, 1024) if rng.random() < 0.5 else rng.randint(1, 64)
+    for _ in range(3000):
+        k = 64 * rng.choice([1, 8, 42, 52, 128, 256, 1024])
+        n = rng.choice([rng.randint(1, 1024), rng.randint(1, 64), rng.randint(1, 20000)])
         d = int(2 ** rng.uniform(0, 27))
         most = Q.project_workspace(n, d, k)
         assert most >= n * k * 4
-        for n2, d2 in ((rng.randint(1, n), d), (n, rng.randint(1, d)), (rng.randint(1, n), rng.randint(1, d))):
+        for n2, d2 in ((n, d), (rng.randint(1, n), d), (n, rng.randint(1, d)), (rng.randint(1, n), rng.randint(1, d)), (min(n, 16), d)):
+            assert _plan_bytes(n2, d2, k) <= most, (n, d, k, n2, d2)
             assert Q.project_workspace(n2, d2, k) <= most, (n, d, k, n2, d2)
