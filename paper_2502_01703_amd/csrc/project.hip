@@ -46,7 +46,9 @@ template <int NB> struct ProjShape {
 // workgroup on every slot of the chip, measured at 2^20 columns, k = 8192 (bf16 and fp32 input of the Rademacher family --
 // fp32 is converted while it is staged; Gaussian: bound by the table look-ups, which a fragment costs whatever it
 // feeds), how many workgroups a compute unit holds, and microseconds a round costs whatever its length (the narrow 512-wide
-// tiles join two groups' sums in LDS).
+// tiles join two groups' sums in LDS).  The Gaussian 16-row tiles take 3.5 with both workgroups resident; their entry stays at what
+// one workgroup a compute unit took, because with the lower one outputs of few coordinates are cut into up to 500 d-slices,
+// whose addition costs more than the tile saves (6 x 107 136 fp32 -> 512 with codes 36.7 -> 54.8 us).
 enum ProjectTile { kTile128, kTile64, kTile48, kTile48x512, kTile32x512, kTile16x512, kTiles };
 struct TileCost { int rows, cols, per_cu; double bf16, fp32, gauss, fixed; };
 constexpr TileCost kTileCost[kTiles] = {
@@ -173,7 +175,7 @@ constexpr int kProjectMaxLds = 160 * 1024;      // largest request of any shape 
 // is one byte permute of the hash (its byte above the lane's constant); the lower element of a pair is read as the
 // dword's upper 16 bits and the two halves are joined by an OR.  Twelve vector-ALU operations per fragment beside the two
 // hashes; 32 copies of 2 bytes, whose addresses took a shift, a mask and an addition, took more than twice that
-// (128 x 2^18 -> 8192: 569 -> 531 us, 64 x 2^19 835 -> 743, 1 x 2^19 811 -> 553 with the 16-row tiles).
+// (128 x 2^18 -> 8192: 569 -> 531 us, 64 x 2^19 835 -> 743, 1 x 2^19 811 -> 463 with the 16-row tiles).
 constexpr int kGaussBytes = 256 * 256;
 __device__ inline void gauss_fill(unsigned char *tab, const GaussTable &gt) {       // (16 bytes a store: 128 x 896 -> 128 17.1 us with 4, now 14.3)
 #pragma unroll
@@ -451,12 +453,17 @@ template <int NR, int NX> struct NarrowShape {
     static constexpr int kStage = NK * kSubBytes;
     // stages in the ring (asynchronous copies; 2 when staged); Gaussian: two, so that two workgroups of 16-row tiles fit
     static constexpr int ring(bool gauss) { return gauss ? 2 : 4; }
-    static constexpr int kJoin = (NK - 1) * kRows * kCols * 4;     // sums of the other groups, after the last stage
+    static constexpr int kJoin = (NK - 1) * kRows * kCols * 4;     // sums of the other groups, after the last stage: over everything else
     static constexpr int lds(bool direct, bool gauss) {
-        const int r = (direct ? ring(gauss) : 2) * kStage;
-        return (r > kJoin ? r : kJoin) + (gauss ? kGaussBytes : 0);
+        const int r = (direct ? ring(gauss) : 2) * kStage + (gauss ? kGaussBytes : 0);
+        return r > kJoin ? r : kJoin;
     }
     static_assert(lds(true, false) <= kProjectMaxLds && lds(true, true) <= kProjectMaxLds, "LDS of one compute unit");
+    // as many workgroups on a compute unit as the plan counts: two of 16-row tiles, 81 920 bytes each when Gaussian (with the
+    // sums beside the table 98 304, one workgroup: 1 x 2^19 -> 8192 553 us, now 463; 4 x 194 560 fp32 280, now 202)
+    static constexpr int kPerCU = NX == 8 ? kTileCost[kTile48].per_cu
+        : kTileCost[NR == 3 ? kTile48x512 : (NR == 2 ? kTile32x512 : kTile16x512)].per_cu;
+    static_assert(kPerCU * lds(true, false) <= kProjectMaxLds && kPerCU * lds(true, true) <= kProjectMaxLds, "the plan's workgroups fit");
 };
 
 template <ProjectInput IN, bool GAUSS, int NR, int NX>
@@ -612,8 +619,9 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
         }
     }
     if (NK > 1) {
-        // the other groups' sums pass through LDS ([group][row][column]; every copy has landed), added in group order
-        float *join = (float *)smem;
+        // the other groups' sums pass through LDS ([group][row][column], over the ring and the table: every copy has landed and
+        // every look-up returned before the barrier), added in group order
+        float *join = (float *)lds;
         __syncthreads();
         if (wk > 0) {
 #pragma unroll
