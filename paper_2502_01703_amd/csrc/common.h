@@ -73,13 +73,15 @@ template <int N> __device__ inline void wait_vmcnt() {
 // kernel is entered in a list while the library is loaded (no HIP call is made then);
 // device_ready() raises the limit of every listed kernel on the current device, once per device,
 // and is called by qless_init() and at the top of every entry point that launches one of them.
-bool register_lds_kernel(const void *fn, int bytes);
+// A kernel that forms addresses into its dynamic LDS from 0 is listed as such: device_ready() refuses the device if the
+// kernel was built with static LDS, which would come first.
+bool register_lds_kernel(const void *fn, int bytes, bool from_zero);
 qless_status device_ready();
-template <auto Fn, int BYTES> struct LdsKernel {
-    static inline const bool listed = register_lds_kernel((const void *)Fn, BYTES);
+template <auto Fn, int BYTES, bool FROM_ZERO = false> struct LdsKernel {
+    static inline const bool listed = register_lds_kernel((const void *)Fn, BYTES, FROM_ZERO);
 };
 // names a kernel's list entry so that the entry exists in the loaded library
-#define QLESS_LDS_KERNEL(fn, bytes) ((void)qless::LdsKernel<&fn, (bytes)>::listed)
+#define QLESS_LDS_KERNEL(fn, ...) ((void)qless::LdsKernel<&fn, __VA_ARGS__>::listed)
 
 // topk.hip: device address of the current GPU's scratch array of qless_topk_noalloc (looked up once
 // per device)

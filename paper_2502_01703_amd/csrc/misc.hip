@@ -39,7 +39,7 @@ static const uint16_t kGaussianTable[256] = {
 
 const uint16_t *gaussian_table_bf16() { return kGaussianTable; }
 
-struct LdsEntry { const void *fn; int bytes; };
+struct LdsEntry { const void *fn; int bytes; bool from_zero; };
 static std::vector<LdsEntry> &lds_kernels() {
     static std::vector<LdsEntry> list;            // built by static initialisers of the other files
     return list;
@@ -48,11 +48,11 @@ static std::mutex &ready_mutex() {
     static std::mutex m;
     return m;
 }
-bool register_lds_kernel(const void *fn, int bytes) {
+bool register_lds_kernel(const void *fn, int bytes, bool from_zero) {
     std::lock_guard<std::mutex> lock(ready_mutex());
     for (LdsEntry &e : lds_kernels())
-        if (e.fn == fn) { if (bytes > e.bytes) e.bytes = bytes; return true; }
-    lds_kernels().push_back(LdsEntry{fn, bytes});
+        if (e.fn == fn) { if (bytes > e.bytes) e.bytes = bytes; e.from_zero |= from_zero; return true; }
+    lds_kernels().push_back(LdsEntry{fn, bytes, from_zero});
     return true;
 }
 
@@ -65,11 +65,15 @@ qless_status device_ready() {
     if (ready[dev].load(std::memory_order_acquire)) return QLESS_OK;
     std::lock_guard<std::mutex> lock(ready_mutex());
     if (ready[dev].load(std::memory_order_relaxed)) return QLESS_OK;
-    for (const LdsEntry &e : lds_kernels())
-        if (hipFuncSetAttribute(e.fn, hipFuncAttributeMaxDynamicSharedMemorySize, e.bytes) != hipSuccess) {
+    for (const LdsEntry &e : lds_kernels()) {
+        hipFuncAttributes attr{};
+        if (hipFuncSetAttribute(e.fn, hipFuncAttributeMaxDynamicSharedMemorySize, e.bytes) != hipSuccess ||
+            (e.from_zero && hipFuncGetAttributes(&attr, e.fn) != hipSuccess)) {
             (void)hipGetLastError();
             return QLESS_ERR_DEVICE;
         }
+        if (e.from_zero && attr.sharedSizeBytes != 0) return QLESS_ERR_DEVICE;
+    }
     void *scratch = nullptr;
     const qless_status rs = topk_scratch_address(&scratch);
     if (rs != QLESS_OK) return rs;

@@ -186,8 +186,8 @@ __device__ inline void gauss_fill(unsigned char *tab, const GaussTable &gt) {   
     }
 }
 // A fragment's eight entries (two hash words): requested one fragment ahead of their use.  The LDS addresses are formed as such: the table is
-// the first thing in a kernel's dynamic LDS, which starts at 0 (no static LDS), and a pointer into the array would
-// cost an addition of that 0 per lookup.
+// the first thing in a kernel's dynamic LDS, which starts at 0 (no static LDS: checked at run time, QLESS_LDS_KERNEL), and a
+// pointer into the array would cost an addition of that 0 per lookup.
 struct GaussRaw { uint32_t lo[4], hi[4]; };
 __device__ inline void gauss_request(RowKey key, uint32_t counter, uint32_t lane4, GaussRaw &r) {
     typedef __attribute__((address_space(3))) const uint16_t *lds16;
@@ -737,12 +737,12 @@ template <ProjectInput IN, bool GAUSS, int NR, int NX>
 static void launch_narrow_shape(dim3 grid, hipStream_t st, const ProjectArgs &a, const GaussTable &gt) {
     using Sh = NarrowShape<NR, NX>;
     constexpr int lds = Sh::lds(IN == kDirectBf16, GAUSS);
-    QLESS_LDS_KERNEL((project_narrow_kernel<IN, GAUSS, NR, NX>), lds);
+    QLESS_LDS_KERNEL((project_narrow_kernel<IN, GAUSS, NR, NX>), lds, GAUSS);
     hipLaunchKernelGGL((project_narrow_kernel<IN, GAUSS, NR, NX>), grid, dim3(kWaves * 64), lds, st, a, gt);
 }
 template <ProjectInput IN, bool GAUSS, int NB>
 static void launch_project_shape(dim3 grid, hipStream_t st, const ProjectArgs &a, const GaussTable &gt) {
-    QLESS_LDS_KERNEL((project_kernel<IN, GAUSS, NB>), kProjectMaxLds);
+    QLESS_LDS_KERNEL((project_kernel<IN, GAUSS, NB>), kProjectMaxLds, GAUSS);
     constexpr size_t ring = GAUSS && NB == 4 ? 3 : kRing;
     constexpr size_t lds = (IN == kDirectBf16 ? ring * (32 * NB) * kStageD * 2 : (size_t)2 * (32 * NB) * kLdsStride) + (GAUSS ? kGaussBytes : 0);
     static_assert(lds <= (size_t)kProjectMaxLds, "LDS of one compute unit");
