@@ -190,7 +190,10 @@ qless_status qless_project_quantize_slice(const void *G, qless_dtype dt, int64_t
  *              untouched, unless the checkpoints are scored in groups of
  *              launches (their validation rows do not all fit in LDS): then it carries N x 16 fp32
  *              sums from one launch to the next.
- * N == 0 is valid; M >= 1.  Whichever kernels a shape selects, the results are the same bits.  With
+ * N == 0 is valid; M >= 1.  Whichever kernels a shape selects, the results are the same bits.  (Norms that are
+ * not finite: a sum that is NaN is passed over by the maximum, and a row none of whose sums lies above -infinity scores
+ * -infinity on the streaming and popcount paths and a NaN of all ones on the tiled paths; which of them is
+ * fixed by bits, M, k and C, not by N.)  With
  * more than 64 validation vectors a call may consist of several launches that update score in
  * place: score and full are complete once the stream has run the whole call.
  * ------------------------------------------------------------------------------------------- */
@@ -210,7 +213,7 @@ qless_status qless_score(const void *const *train_codes, const float *const *tra
  *     out  device, n x k bfloat16 (dense rows)
  * qless_score16:  acc(z, z') = sum_{i<C} eta[i] * <y_{z,i}, y_{z',i}> over the stored rows, products exact,
  *   sums in fp32 on the matrix cores (order unspecified: results agree with an fp64 evaluation to
- *   about 1e-5, not bit for bit);  score[z] = max_{z'} acc(z, z').
+ *   about 1e-5, not bit for bit);  score[z] = max_{z'} acc(z, z') (a NaN for a row without a sum above -infinity).
  *     train16, val16  host arrays of C device pointers to N (resp. M) bfloat16 rows of k, 16-byte aligned
  *     eta             host, C weights;  k a multiple of 64, at most 32768
  *     score, full, ws, ws_bytes, stream   as for qless_score; workspace from qless_score16_workspace

@@ -1,4 +1,4 @@
-// Shared between the scoring kernels (score.hip, score_wide.hip).
+// Shared between the scoring kernels (score.hip, score_wide.hip, score_split.hip).
 #pragma once
 #include "common.h"
 
@@ -22,6 +22,7 @@ __device__ inline unsigned int f32_order_key(float f) {
     const unsigned int u = __float_as_uint(f);
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
+inline float nan_below_all() { return __builtin_bit_cast(float, 0xFFFFFFFFu); }      // the value of key 0
 __device__ inline float f32_from_order_key(unsigned int k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
@@ -42,6 +43,7 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
 // Rows hold at least 16 bytes (16 per plane for the ternary codes).
 bool use_split(int64_t N, int32_t M, int64_t row_bytes, int bits, int C);
 size_t split_workspace(int64_t N, int32_t M, int64_t row_bytes, int bits, int C);
-qless_status launch_split(const ScoreArgs &a, int bits, void *ws, hipStream_t st);
+// none: the score of a row none of whose sums lies above -infinity
+qless_status launch_split(const ScoreArgs &a, int bits, float none, void *ws, hipStream_t st);
 
 }  // namespace qless

@@ -1902,7 +1902,19 @@ extern "C" qless_status qless_score_mixed(const void *const *train_codes, const 
     return launch_status();
 }
 
-// Workspace of the paths other than score_split.hip's.
+// The paths other than score_split.hip's.
+enum ScorePath { kScoreStream, kScoreStream32, kScoreStreamI8, kScoreTiles, kScorePopcount };
+static ScorePath score_path(int bits, int32_t M, int32_t k, int C) {
+    if (bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0 && stream_mfma_plan(M, k, bits, C).nb >= 2) return kScoreStream;
+    if (bits == 1 && M <= kStream32MaxVal && k % 512 == 0 && stream_mfma32_plan(1, 2, 64, k, C).nb >= 2) return kScoreStream32;
+    if (use_mfma_path(bits, M, k)) return use_stream_i8(bits, M, k, C) ? kScoreStreamI8 : kScoreTiles;
+    return kScorePopcount;
+}
+// What a row scores none of whose sums lies above -infinity (norms that are not finite): the tile kernels leave its key
+// cleared, which reads as a NaN that no score is below; the others reduce from -infinity.
+static float no_score(ScorePath p) { return p == kScoreTiles ? nan_below_all() : -__builtin_inff(); }
+
+// Workspace of those paths.
 static size_t score_base_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
     size_t need = 0;
     if (bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0)      // checkpoint groups hand their sums on through the workspace
@@ -1950,30 +1962,31 @@ extern "C" qless_status qless_score(const void *const *train_codes, const float 
     if (ready != QLESS_OK) return ready;
     // (a workspace laid out for a larger call may be too small for the parts: the other paths serve that as well)
     if (score_splits(N, M, k, bits, C) && ws && (uintptr_t)ws % 16 == 0 && ws_bytes >= qless_score_workspace(N, M, k, bits, C))
-        return launch_split(a, bits, ws, st);
-    if (bits <= 2 && M <= kStreamMfmaVal && k % 128 == 0) {
-        const StreamMfmaPlan sp = stream_mfma_plan(M, k, bits, C);
-        if (sp.nb >= 2) {
+        return launch_split(a, bits, no_score(score_path(bits, M, k, C)), ws, st);
+    switch (score_path(bits, M, k, C)) {
+        case kScoreStream: {
+            const StreamMfmaPlan sp = stream_mfma_plan(M, k, bits, C);
             const size_t need = stream_mfma_partial_bytes(sp, N, C);
             if (need && (!ws || ws_bytes < need)) return QLESS_ERR_WORKSPACE;
             if (need && (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
             return launch_stream_mfma(a, bits, sp, (float *)ws, st);
         }
-    }
-    if (bits == 1 && M <= kStream32MaxVal && k % 512 == 0 && stream_mfma32_plan(1, 2, 64, k, C).nb >= 2) {
-        if (!ws || ws_bytes < perm_plan(M, k, C).total || (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
-        return launch_stream_mfma32(a, ws, st);
-    }
-    if (use_mfma_path(bits, M, k)) {
-        const size_t need = tiles_workspace(N, M, k, bits, C);
-        if (!ws || ws_bytes < need) return QLESS_ERR_WORKSPACE;
-        if ((uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
-        if (N > (int64_t)0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
-        if (use_stream_i8(bits, M, k, C)) return bits == 8 ? launch_stream_i8<8>(a, ws, st) : launch_stream_i8<4>(a, ws, st);
-        if (bits == 8) return launch_mfma<8>(a, ws, st);
-        if (bits == 4) return launch_mfma<4>(a, ws, st);
-        if (bits == 2) return launch_mfma<2>(a, ws, st);
-        return launch_mfma<1>(a, ws, st);
+        case kScoreStream32:
+            if (!ws || ws_bytes < perm_plan(M, k, C).total || (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
+            return launch_stream_mfma32(a, ws, st);
+        case kScoreStreamI8:
+        case kScoreTiles: {
+            const size_t need = tiles_workspace(N, M, k, bits, C);
+            if (!ws || ws_bytes < need) return QLESS_ERR_WORKSPACE;
+            if ((uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
+            if (N > (int64_t)0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
+            if (use_stream_i8(bits, M, k, C)) return bits == 8 ? launch_stream_i8<8>(a, ws, st) : launch_stream_i8<4>(a, ws, st);
+            if (bits == 8) return launch_mfma<8>(a, ws, st);
+            if (bits == 4) return launch_mfma<4>(a, ws, st);
+            if (bits == 2) return launch_mfma<2>(a, ws, st);
+            return launch_mfma<1>(a, ws, st);
+        }
+        case kScorePopcount: break;
     }
     // bit-plane codes with rows that are not multiples of 16 bytes, or a handful of val vectors whose
     // codes do not fit in LDS: popcount kernels
@@ -2083,6 +2096,6 @@ extern "C" qless_status qless_score16(const void *const *train16, const void *co
     const qless_status ready = device_ready();
     if (ready != QLESS_OK) return ready;
     // (a workspace laid out for a larger call may be too small for the parts: the tile kernels serve that as well)
-    if (use_split(N, M, a.k, 16, C) && ws_bytes >= split_workspace(N, M, a.k, 16, C)) return launch_split(a, 16, ws, (hipStream_t)stream);
+    if (use_split(N, M, a.k, 16, C) && ws_bytes >= split_workspace(N, M, a.k, 16, C)) return launch_split(a, 16, no_score(kScoreTiles), ws, (hipStream_t)stream);
     return launch_mfma<8, true>(a, ws, (hipStream_t)stream);
 }

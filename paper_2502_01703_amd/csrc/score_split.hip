@@ -173,7 +173,7 @@ score_split_kernel(ScoreArgs a, int cb, int parts, int per, uint32_t *planes) {
 
 // One workgroup per train row: the parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.
 __global__ void __launch_bounds__(256)
-score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf16) {
+score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf16, float none) {
     __shared__ float wave_best[4];
     const int64_t z = blockIdx.x;
     const size_t plane = (size_t)a.N * (size_t)a.M;
@@ -204,7 +204,10 @@ score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf
     for (int o = 32; o > 0; o >>= 1) best = fmaxf(best, __shfl_xor(best, o, 64));
     if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = best;
     __syncthreads();
-    if (threadIdx.x == 0) a.score[z] = fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
+    if (threadIdx.x == 0) {
+        best = fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
+        a.score[z] = best > neg_inf() ? best : none;
+    }
 }
 
 struct SplitPlan { int parts, per; size_t bytes; };
@@ -230,7 +233,7 @@ static void launch_split_bits(const ScoreArgs &a, int cb, const SplitPlan &p, ui
     const dim3 grid((unsigned)((a.N + kSplitTile - 1) / kSplitTile), (unsigned)((a.M + kSplitTile - 1) / kSplitTile), (unsigned)(a.C * p.parts));
     hipLaunchKernelGGL((score_split_kernel<BITS>), grid, dim3(64 * kSplitWaves), lds, st, a, cb, p.parts, p.per, ws);
 }
-qless_status launch_split(const ScoreArgs &a, int bits, void *ws, hipStream_t st) {
+qless_status launch_split(const ScoreArgs &a, int bits, float none, void *ws, hipStream_t st) {
     const int cb = bits == 16 ? a.k : a.k * bits / 8;
     const SplitPlan p = split_plan(a.N, a.M, cb, bits, a.C);
     uint32_t *w = (uint32_t *)ws;
@@ -241,7 +244,7 @@ qless_status launch_split(const ScoreArgs &a, int bits, void *ws, hipStream_t st
         case 2: launch_split_bits<2>(a, cb, p, w, st); break;
         default: launch_split_bits<1>(a, cb, p, w, st); break;
     }
-    hipLaunchKernelGGL(score_split_finish_kernel, dim3((unsigned)a.N), dim3(256), 0, st, a, p.parts, (const uint32_t *)ws, bits == 16);
+    hipLaunchKernelGGL(score_split_finish_kernel, dim3((unsigned)a.N), dim3(256), 0, st, a, p.parts, (const uint32_t *)ws, bits == 16, none);
     return launch_status();
 }
 

@@ -107,3 +107,35 @@ def test_workspace_laid_out_for_a_larger_call(bits):
     ws = torch.empty(L.qless_score_workspace(N, M, k, bits, C) + 16, dtype=torch.uint8, device=DEV)
     assert L.qless_score(arr(tc), arr(tr), arr(vc), arr(vr), eta, C, n, M, k, bits, ptr(out), None, ptr(ws), ws.numel(), stream) == 0
     assert torch.equal(out, Q.score(tc, tr, vc, vr, _eta(C), k, bits))
+
+
+# 4 bits and 81 validation vectors: streamed or tiled by k; 1 and 2 bits: streamed, popcounts (k % 128 != 0), tiled (M > 192)
+@pytest.mark.parametrize("bits,M,k", [(8, 20, 4096), (8, 200, 4096), (4, 81, 8192), (4, 81, 8256), (2, 9, 8192), (2, 40, 8192),
+                                      (2, 40, 1984), (1, 9, 8192), (1, 100, 8192), (1, 300, 8192), (1, 40, 1984), (16, 20, 2048),
+                                      (16, 200, 2048)])
+def test_norms_that_are_not_finite(bits, M, k):
+    """The few pairs of a batch score what the same rows score in a large store, also where a norm is NaN or infinite."""
+    n, N, C = 65, 40000, 2
+    _say("norms that are not finite, bits=%d M=%d k=%d" % (bits, M, k))
+    if bits == 16:
+        g = torch.Generator(device=DEV)
+        g.manual_seed(3)
+        t16 = [Q.normalize16(torch.randn(N, k, generator=g, device=DEV)) for _ in range(C)]
+        v16 = [Q.normalize16(torch.randn(M, k, generator=g, device=DEV)) for _ in range(C)]
+        t16[0][7, 11] = float("nan")
+        t16[1][64] = float("nan")
+        few = Q.score16([t[:n].contiguous() for t in t16], v16, _eta(C))
+        many = Q.score16(t16, v16, _eta(C))[:n]
+        for z in range(n):
+            assert bool(few[z].isnan()) == bool(many[z].isnan()) == (z in (7, 64)), z
+        assert (few - many)[~many.isnan()].abs().max() <= C * 2.0 ** -16
+        return
+    tc, tr = _store(N, k, C, bits, 5)
+    vc, vr = _store(M, k, C, bits, 6)
+    tr[0][7] = float("nan")
+    tr[1][64] = float("nan")
+    tr[1][13] = float("inf")
+    vr[0][M - 1] = float("nan")
+    few = Q.score([t[:n] for t in tc], [r[:n] for r in tr], vc, vr, _eta(C), k, bits)
+    many = Q.score(tc, tr, vc, vr, _eta(C), k, bits)[:n]
+    np.testing.assert_array_equal(_bits(few.cpu().numpy()), _bits(many.cpu().numpy()))
