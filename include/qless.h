@@ -299,9 +299,11 @@ qless_status qless_aggregate(const float *full, int64_t N, int32_t M, const int3
  * qless_score and qless_aggregate in one call: out[z][t] = maximum or mean, as defined for
  * qless_aggregate, of acc(z, z') of qless_score over the validation columns of group t -- the same bits
  * as the two calls.  The matrix passes through the workspace in blocks of train rows, at most 2 GiB of it
- * at a time.  Arguments as for qless_score and qless_aggregate;
+ * (or 16 rows, where those are more) at a time.  Arguments as for qless_score and qless_aggregate;
  *   out   device, N x T fp32 row-major
- *   ws    device workspace, 16-byte aligned, of at least qless_score_groups_workspace(N, M, k, bits, C) bytes
+ *   ws    device workspace, 16-byte aligned, of qless_score_groups_workspace(N, M, k, bits, C) bytes.  A smaller
+ *         one, down to the size for 16 rows, qless_score_groups_workspace(16, M, k, bits, C), is served as well, in blocks of
+ *         fewer rows: the same bits, more launches
  * ------------------------------------------------------------------------------------------- */
 size_t qless_score_groups_workspace(int64_t N, int32_t M, int32_t k, int bits, int C);
 qless_status qless_score_groups(const void *const *train_codes, const float *const *train_rnorm,

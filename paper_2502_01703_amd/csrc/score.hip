@@ -2003,21 +2003,23 @@ extern "C" qless_status qless_score(const void *const *train_codes, const float 
 }
 
 // Influence aggregated over groups of validation columns: the matrix passes through the workspace, at most
-// kGroupsMatrix bytes of it at a time.  (One workgroup walking a train tile through all validation tiles, with the
+// kGroupsMatrix bytes of it at a time (a block less costs 1 to 2 %: 270 000 x 1024 x 4, 8 bits 9.0 ms in one block of 1.1 GB,
+// 9.4 in five; a caller that is short of memory passes less and gets more blocks).  (One workgroup walking a train tile through all validation tiles, with the
 // aggregation as its epilogue, avoids the matrix but leaves the chip to whole rounds of 256-row tiles:
 // 270 000 x 285 at 4 bits 4.7 ms, of which the matrix, written and read once, would be 0.15 ms.)
 constexpr size_t kGroupsMatrix = (size_t)2 << 30;
-// train rows per block: a multiple of every tile height and of what keeps the code pointers 16-byte aligned
-static int64_t groups_block_rows(int64_t N, int32_t M) {
-    const int64_t fit = (int64_t)(kGroupsMatrix / ((size_t)M * sizeof(float))) / 1536 * 1536;
-    const int64_t rows = fit < 1536 ? 1536 : fit;
+// Train rows per block of at most `bytes` of the matrix: a multiple of every tile height where that many fit, and always of what
+// keeps the code pointers 16-byte aligned; at least 16.
+static int64_t groups_block_rows(int64_t N, int32_t M, size_t bytes) {
+    const int64_t fit = (int64_t)(bytes / ((size_t)M * sizeof(float)));
+    const int64_t rows = fit >= 1536 ? fit / 1536 * 1536 : (fit >= 16 ? fit / 16 * 16 : 16);
     return N < rows ? N : rows;
 }
 static size_t groups_matrix_bytes(int64_t rows, int32_t M) { return ((size_t)rows * (size_t)M * sizeof(float) + 255) & ~(size_t)255; }
 
 extern "C" size_t qless_score_groups_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
     if (N < 0 || M < 1 || k <= 0 || C < 1 || !valid_bits(bits)) return 0;
-    const int64_t rows = groups_block_rows(N, M);
+    const int64_t rows = groups_block_rows(N, M, kGroupsMatrix);
     return groups_matrix_bytes(rows, M) + qless_score_workspace(rows, M, k, bits, C) + 16;
 }
 
@@ -2041,10 +2043,15 @@ extern "C" qless_status qless_score_groups(const void *const *train_codes, const
     if (group_end[T - 1] != M) return QLESS_ERR_INVALID_ARG;
     if (N == 0) return QLESS_OK;
     if (!out) return QLESS_ERR_INVALID_ARG;
-    const int64_t block = groups_block_rows(N, M);
-    const size_t full_bytes = groups_matrix_bytes(block, M);
-    const size_t need = full_bytes + score_base_workspace(block, M, k, bits, C) + 16;    // (qless_score does without its parts)
-    if (!ws || ws_bytes < need || (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
+    if (!ws || (uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
+    int64_t block = groups_block_rows(N, M, kGroupsMatrix);
+    size_t full_bytes;
+    for (;;) {
+        full_bytes = groups_matrix_bytes(block, M);
+        if (ws_bytes >= full_bytes + score_base_workspace(block, M, k, bits, C) + 16) break;    // (qless_score does without its parts)
+        if (block <= 16) return QLESS_ERR_WORKSPACE;
+        block = groups_block_rows(block, M, (size_t)(block / 2) * (size_t)M * sizeof(float));
+    }
     const int64_t cb = (int64_t)k * bits / 8;
     for (int64_t r0 = 0; r0 < N; r0 += block) {
         const int64_t rows = N - r0 < block ? N - r0 : block;
