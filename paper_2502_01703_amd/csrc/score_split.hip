@@ -84,9 +84,11 @@ __device__ inline void split_products(const SplitChunk<BITS> (&t)[2], const Spli
     }
 }
 
-// grid (train tiles, val tiles, C * parts); part p of a checkpoint takes chunk steps [p * per, (p + 1) * per)
+// grid (train tiles, val tiles, C * parts); part p of a checkpoint takes chunk steps [p * per, (p + 1) * per).  Two wavefronts
+// per SIMD, so that two workgroups share a compute unit as split_plan counts them (left free, the compiler took 198 + 64 registers for
+// the ternary codes, one workgroup: 256 x 256 x 4, k = 16384 26.9 us, now 23.8).
 template <int BITS>
-__global__ void __launch_bounds__(64 * kSplitWaves)
+__global__ void __launch_bounds__(64 * kSplitWaves, 2)
 score_split_kernel(ScoreArgs a, int cb, int parts, int per, uint32_t *planes) {
     constexpr int DEPTH = BITS == 2 ? 2 : 4, NPL = BITS == 2 ? 2 : 1;
     extern __shared__ __attribute__((aligned(16))) uint32_t join[];             // [wavefront][64 rows][64 columns]
