@@ -82,7 +82,7 @@ qless_status device_ready() {
 }
 
 // Short groups: one thread per (train example, group), its entries visited in column order.  Neighbouring lanes read
-// neighbouring groups of a row, so up to about eight columns a group their loads share lines (46 483 x 62, 55 groups:
+// neighbouring groups of a row, so up to about ten columns a group their loads share lines (46 483 x 62, 55 groups:
 // 25 us with scoring, 43 us by the kernel below, whose wavefronts take 64 rows x 32 columns whatever M is).
 __global__ void __launch_bounds__(256)
 aggregate_short_kernel(const float *full, int64_t N, int32_t M, GroupEnds ge, int T, int mean, float *out) {
@@ -159,7 +159,12 @@ aggregate_kernel(const float *full, int64_t N, int32_t M, GroupEnds ge, int T, i
 
 qless_status aggregate_rows(const float *full, int64_t N, int32_t M, const GroupEnds &ge, int T, int mean,
                             float *out, hipStream_t st) {
-    if (M < 32 || M <= 8 * T) {
+    // Where the two kernels cross, in columns a group (after the scoring that wrote the matrix, M = 33 .. 1000, T = 1 .. 64): 270 000 x 285
+    // in 28 groups 319 us with scoring short, 347 long, in 20 groups 346 and 316; rows that begin on cache lines favour the
+    // long form (270 000 x 128 in 12 groups 110 and 87); few rows do not fill the chip with wavefronts of 64 of them (10 000 x 200 in 16
+    // groups 16.2 and 16.9, 10 000 x 285 in 20 groups 33.3 and 31.4; 1000 x 512 in 24 groups 12.3 and 14.2).
+    const bool few = N <= 16384;
+    if (M < 32 || M <= (N <= 2048 ? 24 : (few ? 14 : (M % 32 == 0 ? 8 : 11))) * T) {
         int64_t short_blocks = (N * (int64_t)T + 255) / 256;
         if (short_blocks > 65536) short_blocks = 65536;
         hipLaunchKernelGGL(aggregate_short_kernel, dim3((unsigned)short_blocks), dim3(256), 0, st, full, N, M, ge, T, mean, out);
@@ -167,8 +172,11 @@ qless_status aggregate_rows(const float *full, int64_t N, int32_t M, const Group
     }
     const int64_t blocks = (N + 255) / 256;
     if (blocks > 0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
-    // few rows: the groups are shared out as well, until about eight wavefronts per SIMD have work (37 237 x 228, 56 groups: 165 us of scoring and aggregation with two, 154 with eight)
+    // The groups are shared out as well, until about eight wavefronts per SIMD have work (37 237 x 228, 56 groups: 165 us of scoring and
+    // aggregation with two, 154 with eight), but shares of less than the 32 columns of a line are not worth the lines that they
+    // read twice (100 000 x 33 in 4 groups 31 us with scoring in four shares, 24 in two), unless there are few rows.
     int64_t gy = (2048 + blocks - 1) / blocks;
+    if (!few && gy > (M + 31) / 32) gy = (M + 31) / 32;
     if (gy > T) gy = T;
     hipLaunchKernelGGL(aggregate_kernel, dim3((unsigned)blocks, (unsigned)gy), dim3(256), 0, st, full, N, M, ge, T, mean, out);
     return launch_status();

@@ -77,8 +77,10 @@ def test_wide_bfloat16(N, M, k, C):
     assert torch.equal(full.amax(1), got)
 
 
-# rows: one wavefront's 64 and its neighbours; columns: the 32-column blocks; groups shared out over wavefronts (few rows) or not
-@pytest.mark.parametrize("N,M,T", [(1, 1, 1), (63, 33, 5), (64, 32, 2), (65, 64, 64), (1000, 285, 57), (140001, 40, 3)])
+# rows: one wavefront's 64 and its neighbours; columns: the 32-column blocks; groups shared out over wavefronts (few rows: up to one
+# each, many rows: a line of columns each) or not; both kernels on either side of the line between them
+@pytest.mark.parametrize("N,M,T", [(1, 1, 1), (63, 33, 5), (64, 32, 2), (64, 33, 1), (65, 64, 64), (1000, 285, 57), (2049, 290, 20),
+                                   (16385, 67, 6), (16385, 66, 6), (20000, 300, 20), (20000, 256, 32), (140001, 40, 3)])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_aggregate_edges(N, M, T, mode):
     _say("aggregate N=%d M=%d T=%d mode=%d" % (N, M, T, mode))
