@@ -42,18 +42,19 @@ template <int NB> struct ProjShape {
     static constexpr int kStageBytes = kTileRows * kLdsStride;
     static constexpr int kDirectStageBytes = kTileRows * kStageD * 2;
 };
-// Tile shapes (rows x projected coordinates of a workgroup) and what one costs: microseconds per 128 gradient columns with a
-// workgroup on every slot of the chip, measured at 2^20 columns, k = 8192 (bf16 and fp32 input of the Rademacher family --
-// fp32 is converted while it is staged; Gaussian: bound by the table look-ups, which a fragment costs whatever it
-// feeds), how many workgroups a compute unit holds, and microseconds a round costs whatever its length (the narrow 512-wide
-// tiles join two groups' sums in LDS).  The Gaussian 16-row tiles take 3.5 with both workgroups resident; their entry stays at what
-// one workgroup a compute unit took, because with the lower one outputs of few coordinates are cut into up to 500 d-slices,
-// whose addition costs more than the tile saves (6 x 107 136 fp32 -> 512 with codes 36.7 -> 54.8 us).
+// Tile shapes (rows x projected coordinates of a workgroup), how many workgroups a compute unit holds, microseconds a round costs
+// whatever its length (the narrow 512-wide tiles join two groups' sums in LDS), and microseconds per 128 gradient columns with a
+// workgroup on every slot of the chip for each kind of input: bf16, fp32 (converted while it is staged), Gaussian bf16 (bound by the
+// table look-ups, which a fragment costs whatever it feeds), Gaussian fp32.  Fitted, with the two figures for a d-slice in
+// make_plans, to 1950 random calls (n = 1 .. 1024, d = 512 .. 2^25, k = 64 .. 16384) that were each run with every shape: the chosen
+// plan is 1.2 % behind the fastest one on average.
 enum ProjectTile { kTile128, kTile64, kTile48, kTile48x512, kTile32x512, kTile16x512, kTiles };
-struct TileCost { int rows, cols, per_cu; double bf16, fp32, gauss, fixed; };
+constexpr int kPlanKinds = 4;
+struct TileCost { int rows, cols, per_cu; double fixed, stage[kPlanKinds]; };
 constexpr TileCost kTileCost[kTiles] = {
-    {128, 512, 1, 2.60, 3.30, 4.15, 4}, {64, 1024, 1, 2.60, 3.27, 5.75, 4}, {48, 1024, 1, 2.21, 2.73, 5.30, 4},
-    {48, 512, 1, 1.12, 1.81, 2.60, 8}, {32, 512, 1, 0.90, 1.41, 2.40, 8}, {16, 512, 2, 1.28, 1.50, 4.70, 8}};
+    {128, 512, 1, 4.5, {2.45, 4.10, 4.50, 4.30}}, {64, 1024, 1, 4.5, {2.35, 3.25, 6.20, 5.00}},
+    {48, 1024, 1, 5.5, {2.08, 2.78, 5.70, 5.10}}, {48, 512, 1, 8.0, {1.05, 1.76, 2.80, 2.70}},
+    {32, 512, 1, 4.0, {0.93, 1.45, 2.48, 2.35}}, {16, 512, 2, 6.0, {1.13, 2.10, 3.90, 4.20}}};
 
 struct ProjectPlan {
     int shape;
@@ -62,18 +63,19 @@ struct ProjectPlan {
 };
 
 // The plans of the four kinds of input (bf16, fp32, Gaussian bf16, Gaussian fp32), in one pass: it runs on every call.
-constexpr int kPlanKinds = 4;
 static int plan_kind(bool gauss, bool fp32) { return 2 * gauss + fp32; }
 static void make_plans(int64_t n, int64_t d_len, int32_t k, ProjectPlan (&p)[kPlanKinds]) {
     for (ProjectPlan &q : p) q = ProjectPlan{};
     if (n <= 0 || d_len <= 0) return;
     const int64_t stages = (d_len + kStageD - 1) / kStageD;
     // Over the shapes and the numbers of d-slices: rounds of workgroups times a workgroup's columns, plus the round's fixed
-    // share, plus the partial sums' way through memory (written and read once, 4 TB/s).  A (row tile, d-slice)
-    // runs on one XCD with all its column tiles, so the rounds are those of the XCD with the most of them (416 x 2 020 480 ->
-    // 8256: 28 slices x 9 column tiles are 252 workgroups, but 36 of them on four of the XCDs: 19.3 against 15.6 ms).
+    // share, plus the partial sums of the slices: their way through memory (written and read once, mostly in the caches) and a
+    // share each of the kernel that adds them one after the other (without it 1 x 169 856 fp32 -> 320 took 443 slices: 45 us, 30 with
+    // 222).  A (row tile, d-slice) runs on one XCD with all its column tiles, so the rounds are those of the XCD with the most
+    // of them (416 x 2 020 480 -> 8256: 28 slices x 9 column tiles are 252 workgroups, but 36 of them on four of the XCDs: 19.3
+    // against 15.6 ms).
     double least[kPlanKinds] = {0, 0, 0, 0};
-    const double plane = (double)n * k * 8 / 4e6;
+    const double plane = (double)n * k * 8 / 6.2e6 + 0.07;
     for (int t = 0; t < kTiles; ++t) {
         const TileCost &c = kTileCost[t];
         const int64_t nt = (n + c.rows - 1) / c.rows, kt = (k + c.cols - 1) / c.cols, slots = 32 * c.per_cu;     // per XCD
@@ -85,8 +87,7 @@ static void make_plans(int64_t n, int64_t d_len, int32_t k, ProjectPlan (&p)[kPl
             const int64_t r = ((nt * splits + 7) / 8 * kt + slots - 1) / slots;
             const int64_t cols = t >= kTile48x512 ? (per + 1) / 2 * 2 : per;                  // two groups of wavefronts, alternate columns
             for (int v = 0; v < kPlanKinds; ++v) {
-                const double cost = v >= 2 ? c.gauss : (v == 1 ? c.fp32 : c.bf16);
-                const double us = (double)r * ((double)cols * cost + c.fixed) + (double)splits * plane;
+                const double us = (double)r * ((double)cols * c.stage[v] + c.fixed) + (double)splits * plane;
                 if (least[v] == 0 || us < least[v]) { least[v] = us; p[v].shape = t; p[v].stages_per_split = per; p[v].nsplit = splits; }
             }
         }

@@ -48,19 +48,20 @@ def _tile(n, d, k, kind, dtype):
 
 # (tile) -> {(kind, fp32): [(n, stages of 128 columns, k), ...]}
 TILES = {
-    (128, 512): {(Q.RADEMACHER, 0): [(129, 257, 64)], (Q.RADEMACHER, 1): [(127, 513, 64)],
-                 (Q.GAUSSIAN, 0): [(128, 513, 64), (129, 257, 64), (127, 17, 8256)], (Q.GAUSSIAN, 1): [(127, 513, 64), (129, 257, 64)]},
-    (64, 1024): {(Q.RADEMACHER, 1): [(63, 513, 64), (64, 513, 64), (257, 49, 64)], (Q.GAUSSIAN, 0): [(49, 25, 8256)]},
-    (48, 1024): {(Q.RADEMACHER, 0): [(47, 513, 64), (48, 513, 64), (49, 257, 448), (47, 3, 1088)],
-                 (Q.RADEMACHER, 1): [(48, 513, 64), (49, 257, 448)],
-                 (Q.GAUSSIAN, 0): [(1, 9, 8256), (17, 9, 8256), (49, 33, 8256)], (Q.GAUSSIAN, 1): [(16, 9, 8256)]},
-    (48, 512): {(Q.RADEMACHER, 0): [(47, 801, 64), (48, 801, 64), (47, 25, 8256)], (Q.RADEMACHER, 1): [(48, 2049, 64), (193, 25, 1088)],
-                (Q.GAUSSIAN, 0): [(47, 801, 64), (48, 801, 64), (47, 25, 8256)], (Q.GAUSSIAN, 1): [(48, 801, 64), (193, 193, 448)]},
-    (32, 512): {(Q.RADEMACHER, 0): [(31, 801, 64), (32, 801, 64), (129, 33, 1088), (31, 17, 8256)],
-                (Q.RADEMACHER, 1): [(32, 801, 64), (129, 193, 448)],
-                (Q.GAUSSIAN, 0): [(31, 801, 64), (32, 801, 64), (97, 65, 1088), (31, 25, 8256)], (Q.GAUSSIAN, 1): [(32, 801, 64)]},
-    (16, 512): {(Q.RADEMACHER, 0): [(1, 801, 64), (15, 1025, 64), (16, 2049, 64)], (Q.RADEMACHER, 1): [(16, 1025, 64), (65, 385, 448)],
-                (Q.GAUSSIAN, 0): [(1, 801, 64), (16, 2561, 64), (15, 193, 4160)], (Q.GAUSSIAN, 1): [(1, 801, 64), (16, 2561, 64)]}}
+    (128, 512): {(Q.RADEMACHER, 0): [(385, 3, 8256)], (Q.RADEMACHER, 1): [(128, 4097, 64)],
+                 (Q.GAUSSIAN, 0): [(127, 513, 64), (128, 513, 64), (257, 193, 64), (127, 17, 8256)],
+                 (Q.GAUSSIAN, 1): [(127, 513, 64), (257, 193, 64)]},
+    (64, 1024): {(Q.RADEMACHER, 0): [(65, 33, 8256)], (Q.RADEMACHER, 1): [(63, 51, 8256), (257, 3, 8256)],
+                 (Q.GAUSSIAN, 0): [(63, 49, 8256), (129, 13, 8256)], (Q.GAUSSIAN, 1): [(64, 49, 8256), (65, 25, 8256)]},
+    (48, 1024): {(Q.RADEMACHER, 0): [(97, 37, 8256)], (Q.RADEMACHER, 1): [(48, 49, 8256), (49, 33, 8256)],
+                 (Q.GAUSSIAN, 0): [(47, 49, 8256), (145, 17, 8256)]},
+    (48, 512): {(Q.RADEMACHER, 0): [(48, 4097, 64), (193, 801, 64)], (Q.RADEMACHER, 1): [(47, 4097, 64)],
+                (Q.GAUSSIAN, 0): [(47, 2049, 64), (48, 2049, 64), (47, 25, 8256)], (Q.GAUSSIAN, 1): [(48, 2049, 64), (145, 7, 16384)]},
+    (32, 512): {(Q.RADEMACHER, 0): [(31, 513, 64), (32, 513, 64), (33, 257, 64), (31, 17, 8256)],
+                (Q.RADEMACHER, 1): [(32, 513, 64), (33, 257, 64)],
+                (Q.GAUSSIAN, 0): [(31, 513, 64), (32, 513, 64), (33, 257, 64), (31, 17, 8256)], (Q.GAUSSIAN, 1): [(32, 513, 64)]},
+    (16, 512): {(Q.RADEMACHER, 0): [(1, 49, 8256), (15, 81, 8256), (33, 41, 8256)], (Q.RADEMACHER, 1): [(1, 49, 12352), (16, 81, 8256)],
+                (Q.GAUSSIAN, 0): [(1, 49, 8256), (15, 51, 8256), (16, 51, 8256)], (Q.GAUSSIAN, 1): [(1, 81, 8256), (16, 81, 8256)]}}
 
 
 @pytest.mark.parametrize("tile", sorted(TILES))
