@@ -11,8 +11,8 @@
 // make_plans() chooses the shape and the number of d-slices by what they cost.  The gradient tile is
 // staged through LDS; partial tiles of the d-slices go to the workspace and are summed in a fixed
 // order by a second kernel, so results are run-to-run identical.
-// Measured, before (64-row tiles for every batch) -> now: 16 x 2^19 bf16 -> 8192 350 -> 189 us, 32 x 2^20 642 -> 444 us,
-// 1 x 2^20 631 -> 318 us; 37 x 1 000 017 at odd row offsets -> 4096 468 -> 348 us; 1024 x 16384 fp32 -> 512 43.7 -> 35.1 us.
+// Measured, before (64-row tiles for every batch) -> now: 16 x 2^19 bf16 -> 8192 326 -> 166 us, 32 x 2^20 637 -> 432 us,
+// 1 x 2^20 623 -> 317 us; 37 x 1 000 017 at odd row offsets -> 4096 439 -> 293 us; 1024 x 16384 fp32 -> 512 42.6 -> 33.7 us.
 //
 // Random operand: lanes 0..31 of a wave take one 32-column word of R for their row m, lanes
 // 32..63 the next word; the 32 sign bits of a word feed four MFMA K-steps of 8 columns each.
@@ -176,7 +176,7 @@ constexpr int kProjectMaxLds = 160 * 1024;      // largest request of any shape 
 // is one byte permute of the hash (its byte above the lane's constant); the lower element of a pair is read as the
 // dword's upper 16 bits and the two halves are joined by an OR.  Twelve vector-ALU operations per fragment beside the two
 // hashes; 32 copies of 2 bytes, whose addresses took a shift, a mask and an addition, took more than twice that
-// (128 x 2^18 -> 8192: 569 -> 531 us, 64 x 2^19 835 -> 743, 1 x 2^19 811 -> 463 with the 16-row tiles).
+// (128 x 2^18 -> 8192: 570 -> 516 us, 64 x 2^19 801 -> 675, 1 x 2^19 796 -> 457 with the 16-row tiles).
 constexpr int kGaussBytes = 256 * 256;
 __device__ inline void gauss_fill(unsigned char *tab, const GaussTable &gt) {       // (16 bytes a store: 128 x 896 -> 128 17.1 us with 4, now 14.3)
 #pragma unroll
@@ -440,7 +440,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
 //
 // The same product with v_mfma_f32_16x16x32_bf16: a fragment of the random operand is 16 coordinates x 32 columns and
 // feeds NR matrix instructions of 16 cycles, so a batch of 16 pays for 16 rows and not for 64.  Bound there: vector
-// ALU, about 8.5 operations per fragment (34 cycles against 16 NR of the matrix cores).  A lane (coordinate
+// ALU, 8.4 operations per fragment (33 cycles beside 16 NR of the matrix cores; 16 rows: 67 % and 32 % of all cycles).  A lane (coordinate
 // lane % 16, group lane / 16) takes word 4 s + lane / 16 of its row for sub-stage s of 128 columns; the word's four
 // bytes-of-columns are the lane's 8 columns of the four K steps, on both operands.
 //   NX wavefronts side by side cover 128 NX coordinates; NK = 8 / NX groups of them take alternate sub-stages of the

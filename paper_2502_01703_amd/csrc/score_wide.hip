@@ -3,11 +3,12 @@
 //
 // Bound: the matrix cores under the card's power limit.  At 270 000 x 1024 x 4 checkpoints, k = 8192, 8 bits, the
 // matrix instructions alone (random operands) take 4.8 ms at 2.0 GHz; LDS operand reads add 1.6 ms, the
-// copies into LDS 2 ms -- and most of that as clock (the card falls to 1.5 - 1.8 GHz while the matrix pipes
-// are busy 57 % of the cycles), so what counts is bytes moved per product, then latency at the barriers.
+// copies into LDS 2 ms -- and most of that as clock (the card falls to 1.7 - 1.8 GHz while the matrix pipes
+// are busy 54 % of the cycles), so what counts is bytes moved per product, then latency at the barriers.
 //   * Tiles of 192 x 256, 256 x 192, 256 x 128 or 512 x 96 (train x validation), eight wavefronts of 96 x 64,
 //     64 x 96 or 64 x 64: the fp32 checkpoint sums and the accumulators of a larger tile do not fit in
-//     registers next to each other.  choose_shape() picks by padded work.
+//     registers next to each other.  choose_shape() picks by padded work.  (The 4-bit kernels of 256 x 192 and 512 x 96
+//     tiles spill 5 - 9 registers, 24 - 40 bytes of scratch a lane; the others none.)
 //   * A stage is 128 bytes (a whole cache line) of every train and validation row of the tile, copied
 //     global -> LDS asynchronously into a ring of two or three stages.  The pre-pass lays the validation rows out
 //     stage by stage as they lie in LDS, so their copies are linear.

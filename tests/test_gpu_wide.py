@@ -37,7 +37,7 @@ def _rows(N):
     return np.array(sorted(r))
 
 
-# N, M: 33001 x 129 / 33001 x 513 / 33001 x 65 / 33001 x 257 take the four tile shapes; 49152 rows are whole tiles of each;
+# N, M: 33001 x 129 / 513 / 97 / 257 take tiles of 192, 256, 256 and 512 rows; 49152 rows are whole tiles of each;
 # k: rows of half a stage, of whole stages plus 32 and 64 bytes, of whole stages (8 bits: k bytes, 4 bits: k / 2)
 @pytest.mark.parametrize("bits", [8, 4])
 @pytest.mark.parametrize("N,M,k,C", [(33001, 129, 64, 1), (33001, 513, 192, 2), (33001, 257, 320, 2), (33001, 97, 1024, 3),
