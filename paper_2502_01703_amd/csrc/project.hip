@@ -186,16 +186,25 @@ __device__ inline void gauss_fill(unsigned char *tab, const GaussTable &gt) {   
         ((uint4 *)tab)[i] = make_uint4(e, e, e, e);
     }
 }
-// A fragment's eight entries (two hash words): requested one fragment ahead of their use.  The LDS addresses are formed as such: the table is
+// A fragment's eight entries come from two hash words, in three steps that are spread over three fragments: the words of fragment
+// f + 2 are hashed and the entries of fragment f + 1 requested while the matrix instructions of fragment f run, and joined
+// behind them.  The LDS addresses are formed as such: the table is
 // the first thing in a kernel's dynamic LDS, which starts at 0 (no static LDS: checked at run time, QLESS_LDS_KERNEL), and a
 // pointer into the array would cost an addition of that 0 per lookup.
+struct GaussWords { uint32_t h[2]; };
 struct GaussRaw { uint32_t lo[4], hi[4]; };
-__device__ inline void gauss_request(RowKey key, uint32_t counter, uint32_t lane4, GaussRaw &r) {
+__device__ inline GaussWords gauss_words(RowKey key, uint32_t counter) {
+    GaussWords w;
+    w.h[0] = key_word(key, counter);
+    w.h[1] = key_word(key, counter + kGold);
+    return w;
+}
+__device__ inline void gauss_request(const GaussWords &w, uint32_t lane4, GaussRaw &r) {
     typedef __attribute__((address_space(3))) const uint16_t *lds16;
     typedef __attribute__((address_space(3))) const uint32_t *lds32;
 #pragma unroll
     for (int e = 0; e < 2; ++e) {
-        const uint32_t h = key_word(key, counter + (uint32_t)e * kGold);
+        const uint32_t h = w.h[e];
         r.lo[2 * e] = ((lds16)(uintptr_t)__builtin_amdgcn_perm(h, lane4, 0x0C0C0400u))[1];
         r.hi[2 * e] = *(lds32)(uintptr_t)__builtin_amdgcn_perm(h, lane4, 0x0C0C0500u);
         r.lo[2 * e + 1] = ((lds16)(uintptr_t)__builtin_amdgcn_perm(h, lane4, 0x0C0C0600u))[1];
@@ -303,8 +312,8 @@ project_kernel(ProjectArgs a, GaussTable gt) {
             cdst[u] = (unsigned)q * 1024u;
         }
     }
-    auto issue = [&](int s) {                      // start the copies of stage s (ring slot s % RING)
-        const unsigned buf = lds0 + (unsigned)(s % RING) * kDirectStageBytes;
+    auto issue = [&](int slot) {                   // start the copies of the next stage into a slot of the ring
+        const unsigned buf = lds0 + (unsigned)slot * kDirectStageBytes;
 #pragma unroll
         for (int u = 0; u < kCopies; ++u) {
             global_to_lds16(cptr[u], buf + cdst[u]);
@@ -321,6 +330,84 @@ project_kernel(ProjectArgs a, GaussTable gt) {
                                 (64 * bp + 32 * half + 8 * ks) * 2);
     };
 
+    if constexpr (GAUSS) {
+        // Fragment f of a stage (K step f / KB, coordinate block f % KB): its NB matrix instructions, behind the first of them the
+        // look-ups of the next fragment and then the hashes of the one after that, the join last, so that neither the
+        // look-ups' latency nor the chain of a hash is waited for.  The gradient fragments of a K step are read during the
+        // first block of the one before, those of the next stage too: the stage's only barrier stands behind the first matrix
+        // instruction of its last fragment, where every read of its slot has returned, and the slot is filled again
+        // at once.  (128 x 2^18 -> 8192 609 -> 531 us, 64 x 2^20 1460 -> 1317, 128 x 2^22 -> 16384 16.5 -> 15.3 ms; entries requested
+        // two fragments ahead instead of one are no faster.)
+        constexpr int F = 8 * KB;
+        auto word = [&](int s, int f) -> uint32_t {              // counter of fragment f of stage s (f may reach into the next)
+            const int ks = f / KB % 8;
+            const uint32_t w = a.wbase + (uint32_t)((c_begin + ((int64_t)s + f / F) * kStageD) >> 5);
+            return (w * 8u + 16u * (uint32_t)(ks >> 2) + 2u * (uint32_t)(ks & 3)) * kGold + kSaltStride;
+        };
+        if (DIRECT) {
+#pragma unroll
+            for (int s = 0; s < RING; ++s)
+                if (s < nstages) issue(s);
+            if (nstages >= RING) wait_vmcnt<(RING - 1) * kCopies>(); else wait_vmcnt<0>();
+        } else {
+            fetch(0);
+            commit(0);
+        }
+        __syncthreads();                           // stage 0 and the table visible to all waves
+        Frag ag[2][NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) ag[0][nb].u = read_a(0, nb, 0, 0);
+        GaussRaw raw;
+        GaussWords next = gauss_words(key[0], word(0, 0));
+        gauss_request(next, lane4, raw);
+        next = gauss_words(key[1], word(0, 1));
+        Frag bf = gauss_join(raw);
+        for (int s = 0, buf = 0; s < nstages; ++s) {
+            const int nbuf = buf + 1 < (DIRECT ? RING : 2) ? buf + 1 : 0;
+            if (!DIRECT && s + 1 < nstages) fetch(s + 1);
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const int ks = f / KB, kb = f % KB, kn = ks + 1;
+                __builtin_amdgcn_sched_barrier(0);
+                acc[0][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[ks & 1][0].v, bf.v, acc[0][kb], 0, 0, 0);
+                if (f == F - 1) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (DIRECT) {
+                        // stage s + 1 is the oldest copy group in flight; RING - 2 younger ones may stay outstanding
+                        if (s + RING - 1 < nstages) wait_vmcnt<(RING - 2) * kCopies>(); else wait_vmcnt<0>();
+                    } else if (s + 1 < nstages) {
+                        commit(nbuf);
+                    }
+                    __syncthreads();
+                    if (DIRECT && s + RING < nstages) issue(buf);
+                    // (after the last stage: in bounds, not used)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) ag[0][nb].u = read_a(nbuf, nb, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                gauss_request(next, lane4, raw);
+                if (kb == 0 && kn < 8) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) ag[kn & 1][nb].u = read_a(buf, nb, kn >> 2, kn & 3);
+                }
+                next = gauss_words(key[(f + 2) % KB], word(s, f + 2));
+#pragma unroll
+                for (int nb = 1; nb < NB; ++nb)
+                    acc[nb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[ks & 1][nb].v, bf.v, acc[nb][kb], 0, 0, 0);
+                bf = gauss_join(raw);
+                // order: look-ups right behind the first matrix instruction, the hashes between the others
+                if (f != F - 1) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+#pragma unroll
+                for (int nb = 1; nb < NB; ++nb) {
+                    __builtin_amdgcn_sched_group_barrier(0x002, NB == 2 ? 16 : 4, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                }
+            }
+            buf = nbuf;
+        }
+    } else {
     if (DIRECT) {
 #pragma unroll
         for (int s = 0; s < RING - 1; ++s)
@@ -333,53 +420,18 @@ project_kernel(ProjectArgs a, GaussTable gt) {
 
     uint32_t fp4_one = 0x22222222u;                // eight FP4 codes of +1.0
     asm volatile("" : "+v"(fp4_one));              // keep it in a vector register
-    GaussRaw raw;                                  // Gaussian: the next fragment's entries
     for (int s = 0; s < nstages; ++s) {
         const int buf = DIRECT ? s % RING : (s & 1);
         if (DIRECT) {
             // stage s is the oldest copy group in flight; two younger ones may stay outstanding
             if (s + RING - 2 < nstages) wait_vmcnt<(RING - 2) * kCopies>(); else wait_vmcnt<0>();
             __syncthreads();                       // stage s visible to all waves; slot of stage s-1 free
-            if (s + RING - 1 < nstages) issue(s + RING - 1);
+            if (s + RING - 1 < nstages) issue((s + RING - 1) % RING);
         } else {
             if (s + 1 < nstages) fetch(s + 1);
         }
         const int64_t cs = c_begin + (int64_t)s * kStageD;       // multiple of 128
         const uint32_t wstage = a.wbase + (uint32_t)(cs >> 5);
-        if constexpr (GAUSS) {
-            // Fragment f = (K step f / KB, coordinate block f % KB): its entries are joined, then the matrix instructions
-            // of its NB row blocks are issued with a share of the next fragment's hashes and look-ups behind each (that of
-            // the next stage's first fragment too: the generator does not wait for gradients); the next K step's
-            // gradient fragments are read during the last block of this one.
-            constexpr int F = 8 * KB;
-            Frag ag[2][NB];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) ag[0][nb].u = read_a(buf, nb, 0, 0);
-            if (s == 0) gauss_request(key[0], wstage * 8u * kGold + kSaltStride, lane4, raw);
-#pragma unroll
-            for (int f = 0; f < F; ++f) {
-                const int ks = f / KB, kb = f % KB, fn = f + 1, kn = fn / KB;
-                const Frag bf = gauss_join(raw);
-                __builtin_amdgcn_sched_barrier(0);
-                // word of K step ks: 16 (ks / 4) + 2 (ks % 4) from the stage's first
-                const uint32_t wn = fn < F ? wstage * 8u + 16u * (uint32_t)(kn >> 2) + 2u * (uint32_t)(kn & 3) : (wstage + 4u) * 8u;
-                gauss_request(key[fn % KB], wn * kGold + kSaltStride, lane4, raw);
-                if (kb == KB - 1 && fn < F) {
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) ag[kn & 1][nb].u = read_a(buf, nb, kn >> 2, kn & 3);
-                }
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-                    acc[nb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ag[ks & 1][nb].v, bf.v, acc[nb][kb], 0, 0, 0);
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 26 / NB + 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x100, 12 / NB, 0);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else
 #pragma unroll
         for (int bp = 0; bp < 2; ++bp) {
             // A fragments: rows 32*nb + l32, columns 64*bp + 32*half + 8*ks .. +7
@@ -417,6 +469,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
             if (s + 1 < nstages) commit(buf ^ 1);
             __syncthreads();
         }
+    }
     }
 
     // partial tile -> workspace [split][n][k];  D[i][j]: j = lane%32, i = 8*(v/4) + 4*(lane/32) + v%4
@@ -569,6 +622,7 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
     uint32_t fp4_one = 0x22222222u;                // eight FP4 codes of +1.0
     asm volatile("" : "+v"(fp4_one));
     GaussRaw raw;
+    GaussWords next;
     for (int s = 0; s < nstages; ++s) {
         const int buf = DIRECT ? s % RING : (s & 1);
         if (DIRECT) {
@@ -602,11 +656,17 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
                         bf.p[2] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 2);
                         bf.p[3] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(x, 1.0f, 3);
                     } else {
-                        // requested one fragment ahead, in the order of use
-                        if (kb == 0 && ks == 0) gauss_request(key[0], wstage * 8u * kGold + kSaltStride, lane4, raw);
+                        // hashed two fragments ahead, requested one ahead, in the order of use
+                        auto words = [&](int f) { return gauss_words(key[f >> 2], (wstage * 8u + 2u * (uint32_t)(f & 3)) * kGold + kSaltStride); };
+                        const int f = 4 * kb + ks;
+                        if (f == 0) {
+                            next = words(0);
+                            gauss_request(next, lane4, raw);
+                            next = words(1);
+                        }
                         bf = gauss_join(raw);
-                        const int fn = 4 * kb + ks + 1;
-                        if (fn < 4 * KB) gauss_request(key[fn >> 2], (wstage * 8u + 2u * (uint32_t)(fn & 3)) * kGold + kSaltStride, lane4, raw);
+                        if (f + 1 < 4 * KB) gauss_request(next, lane4, raw);
+                        if (f + 2 < 4 * KB) next = words(f + 2);
                     }
 #pragma unroll
                     for (int r = 0; r < NR; ++r)

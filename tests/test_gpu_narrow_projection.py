@@ -76,6 +76,16 @@ def test_every_tile(tile):
                 _check(_gradients(n, d, pad, lead, dtype, n + d), k, kind, 7)
 
 
+@pytest.mark.parametrize("n,stages,per,tile", [(1000, 1, 1, (128, 512)), (1000, 2, 2, (128, 512)), (1000, 3, 3, (128, 512)),
+                                               (1000, 4, 4, (128, 512)), (1000, 5, 5, (128, 512)), (640, 6, 3, (64, 1024))])
+def test_gaussian_ring(n, stages, per, tile):
+    """Slices of fewer, as many and more stages than the ring holds: its first fill, its last stages and the look-ups past the end."""
+    _say("Gaussian ring n=%d stages=%d" % (n, stages))
+    assert _tile(n, 128 * stages, 8256, Q.GAUSSIAN, torch.bfloat16) == tile
+    for dtype, d, pad, lead in ((torch.bfloat16, 128 * stages, 0, 0), (torch.float32, 128 * stages - 3, 1, 0)):
+        _check(_gradients(n, d, pad, lead, dtype, n + d), 8256, Q.GAUSSIAN, 11)
+
+
 @pytest.mark.parametrize("kind", [Q.RADEMACHER, Q.GAUSSIAN])
 @pytest.mark.parametrize("n,d,k", [(1, 40001, 512), (15, 33280, 576), (16, 70000, 1024), (17, 40960, 512), (32, 30080, 1088),
                                    (33, 40003, 512), (47, 25600, 1024), (48, 50000, 448), (49, 20000, 960), (96, 20480, 1024),
