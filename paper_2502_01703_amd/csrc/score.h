@@ -33,11 +33,15 @@ int compute_units();                           // of the current device (256 on 
 // score.hip: score[i] = the value of key smax[i], keys cleared
 void launch_score_finish(unsigned int *smax, int64_t N, float *score, hipStream_t st);
 
-// score_wide.hip: 8- and 4-bit codes and bfloat16 rows (bits = 16) against more than 64 validation vectors.
+// score_wide.hip: 8-bit codes and bfloat16 rows (bits = 16) against more than 64 validation vectors.
 size_t wide_workspace(int64_t N, int32_t M, int64_t row_bytes, int C);
 // prepare = false: the workspace still holds the pre-pass of an earlier launch with the same validation
 // side, laid out for plan_rows >= a.N train rows (the finish kernel leaves the row maxima cleared)
 qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st, bool prepare = true, int64_t plan_rows = 0);
+
+// score_codes.hip: 4-bit codes against more than 64 validation vectors.
+size_t codes_workspace(int64_t N, int32_t M, int64_t row_bytes, int C);
+qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st);
 
 // score_split.hip: few pairs (bits = 16: bfloat16 rows).  use_split: whether the path serves a call faster than the others.
 // Rows hold at least 16 bytes (16 per plane for the ternary codes).

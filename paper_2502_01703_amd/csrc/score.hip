@@ -1490,11 +1490,11 @@ static MfmaPlan mfma_plan(int64_t N, int32_t M, int32_t k, int bits, int C) {
     p.total = o;
     return p;
 }
-// Workspace of the tile kernels (bfloat16 rows: bits = 8 and k their length in bytes): 8- and 4-bit codes and
-// bfloat16 rows against more than 64 validation vectors go to score_wide.hip, which lays it out differently.
+// Workspace of the tile kernels (bfloat16 rows: bits = 8 and k their length in bytes): 8-bit codes and bfloat16 rows against more
+// than 64 validation vectors go to score_wide.hip, 4-bit codes to score_codes.hip, which lay it out differently.
 static size_t tiles_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
     const size_t t = mfma_plan(N, M, k, bits, C).total;
-    const size_t w = bits >= 4 && M > 64 ? wide_workspace(N, M, (int64_t)k * bits / 8, C) : 0;
+    const size_t w = bits < 4 || M <= 64 ? 0 : (bits == 4 ? codes_workspace(N, M, k / 2, C) : wide_workspace(N, M, (int64_t)k * bits / 8, C));
     return t > w ? t : w;
 }
 // The bit planes are copied in 16-byte chunks: k must be a multiple of 128 for the 1-/2-bit codes.
@@ -1564,7 +1564,8 @@ static qless_status launch_mfma(const ScoreArgs &a, void *ws, hipStream_t st, bo
     // many (the expanded validation rows are the same for both shapes; the sign codes' narrow shape stages the
     // packed validation rows itself)
     const bool small = !F16 && p.vt == 128 && ((a.N + 255) / 256) * (p.Mp / 128) * 2 <= compute_units();
-    if (BITS >= 4 && p.vt == 128 && !small) return launch_wide(a, F16 ? 16 : BITS, ws, st, prepare, plan_rows);
+    if (BITS == 4 && p.vt == 128 && !small) return launch_codes(a, ws, st);
+    if (BITS == 8 && p.vt == 128 && !small) return launch_wide(a, F16 ? 16 : BITS, ws, st, prepare, plan_rows);
     ScorePrep w{};
     unsigned char *base = (unsigned char *)ws;
     w.vexp = (int8_t *)base; w.vw = (float *)(base + p.off_vw); w.vbias = (int32_t *)(base + p.off_vbias);

@@ -1,5 +1,5 @@
 // qless_score / qless_score16 / qless_score_mixed against more than 64 validation vectors: the tile kernel of
-// the 8- and 4-bit codes (int8 products) and of bfloat16 rows.
+// the 8-bit codes (int8 products) and of bfloat16 rows.
 //
 // Bound: the matrix cores under the card's power limit.  At 270 000 x 1024 x 4 checkpoints, k = 8192, 8 bits, the
 // matrix instructions alone (random operands) take 4.8 ms at 2.0 GHz; LDS operand reads add 1.6 ms, the
@@ -7,8 +7,7 @@
 // are busy 54 % of the cycles), so what counts is bytes moved per product, then latency at the barriers.
 //   * Tiles of 192 x 256, 256 x 192, 256 x 128 or 512 x 96 (train x validation), eight wavefronts of 96 x 64,
 //     64 x 96 or 64 x 64: the fp32 checkpoint sums and the accumulators of a larger tile do not fit in
-//     registers next to each other.  choose_shape() picks by padded work.  (The 4-bit kernels of 256 x 192 and 512 x 96
-//     tiles spill 5 - 9 registers, 24 - 40 bytes of scratch a lane; the others none.)
+//     registers next to each other.  choose_shape() picks by padded work.
 //   * A stage is 128 bytes (a whole cache line) of every train and validation row of the tile, copied
 //     global -> LDS asynchronously into a ring of two or three stages.  The pre-pass lays the validation rows out
 //     stage by stage as they lie in LDS, so their copies are linear.
@@ -16,13 +15,11 @@
 //     registers by then, so the copies of the stage after the ring and the operand reads of the next stage
 //     start behind it while the remaining instructions run, and no wavefront waits for its first operands
 //     after a barrier (the kernel before: barrier, then reads, then instructions).
-//   * Every matrix instruction is followed by one operand read, copy or unpacking step of the next K step.
+//   * Every matrix instruction is followed by one operand read or copy of the next K step.
 //   * 16-byte chunk c of row r lies at position c ^ ((r / 2) % 8): 16 consecutive rows read together use all 64
 //     banks (c ^ (r % 8), conflict-free for 32 banks, cost 5 %).
-//   * 4-bit codes stay packed in LDS on both sides (half the copies and reads) and are unpacked in registers to
-//     16 q (three operations per dword pair), so an accumulator holds 256 D; |256 D| <= 256 * 49 * 65536 < 2^31.
-// Measured, same card, N = 270 000, k = 8192, C = 4 (before -> now): 8 bits, M = 1024: 10.0 -> 8.5 ms; 4 bits, M = 1024:
-// 8.7 -> 7.0 ms, M = 285: 3.36 -> 2.63 ms; bfloat16 65536 x 512: 2.51 -> 2.15 ms.
+// Measured, same card, N = 270 000, k = 8192, C = 4 (before -> now): 8 bits, M = 1024: 10.0 -> 8.5 ms; bfloat16 65536 x 512:
+// 2.51 -> 2.15 ms.
 #include "score.h"
 
 namespace qless {
@@ -115,7 +112,6 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
     constexpr bool BF16 = Sh::BITS == 16;
     constexpr int WR = Sh::WR, WC = Sh::WC, WX = Sh::WX, NBUF = Sh::NBUF, NW = Sh::NW, MT = Sh::MT, VT = Sh::VT;
     constexpr int TBYTES = Sh::TBYTES, VBYTES = Sh::VBYTES, BUF = Sh::BUF, VCP = Sh::VCP, TU = Sh::TU, VU = Sh::VU, LPW = Sh::LPW;
-    constexpr int SUB = Sh::BITS == 4 ? 2 : 1;            // matrix K steps per 16-byte chunk of a lane
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ unsigned int s_rowmax[MT];
     // XCD-aware decode: the vtiles workgroups of one train tile get ids 8 apart (same XCD, same L2)
@@ -180,10 +176,6 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
     auto load_b = [&](int c, int slot, int buf, int ks) {
         fb[slot][c] = *(const i32x4 *)(smem + ((lane_base ^ (ks << 5)) + (unsigned)(buf * BUF) + b_base) + c * 4096);
     };
-    auto unpack = [](i32x4 x, int sub) {                  // 4 bits: codes 16 sub .. of the chunk as bytes 16 q
-        const unsigned px = (unsigned)x[2 * sub], py = (unsigned)x[2 * sub + 1];
-        return i32x4{(int)((px << 4) & 0xF0F0F0F0u), (int)(px & 0xF0F0F0F0u), (int)((py << 4) & 0xF0F0F0F0u), (int)(py & 0xF0F0F0F0u)};
-    };
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };   // keeps the order below
 
     float facc[WR][WC][16];
@@ -226,46 +218,39 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
             for (int ks = 0; ks < 4; ++ks) {
                 const int cur = ks & 1, nxt = cur ^ 1;
                 const int lbuf = ks < 3 ? buf : next, lks = (ks + 1) & 3;
-                constexpr int K0 = SUB == 1 ? WC - 1 : WR * WC - 1;            // instruction of the last step before the barrier
-                constexpr int SLOTS = SUB * WR * WC - K0;                       // instructions the copies are spread over
+                constexpr int K0 = WC - 1;                                      // instruction of the last step before the barrier
+                constexpr int SLOTS = WR * WC - K0;                             // instructions the copies are spread over
 #pragma unroll
-                for (int sub = 0; sub < SUB; ++sub) {
-                    i32x4 ub[WC];
+                for (int b = 0; b < WR; ++b) {
 #pragma unroll
-                    for (int c = 0; c < WC; ++c) ub[c] = SUB == 2 ? unpack(fb[cur][c], sub) : fb[cur][c];
+                    for (int c = 0; c < WC; ++c) {
+                        pin();
+                        acc[b][c] = wide_mma<BF16>(fa[b], fb[cur][c], acc[b][c]);
+                        pin();
+                        if (ks < 3 && b == 0) load_b(c, nxt, lbuf, lks);
+                        const int i = b * WC + c;
+                        if (ks == 3 && more && i >= K0) {
+                            if (i == K0) {
+                                // this wavefront's reads of the stage have returned and its share of the next
+                                // stage has landed; the barrier says so of all wavefronts
+                                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                                if (refill) wait_vmcnt<(NBUF - 2) * LPW>(); else wait_vmcnt<0>();
+                                __builtin_amdgcn_s_barrier();
+                                asm volatile("" ::: "memory");
+                                pin();
 #pragma unroll
-                    for (int b = 0; b < WR; ++b) {
-                        const i32x4 ua = SUB == 2 ? unpack(fa[b], sub) : fa[b];
+                                for (int q = 0; q < WC; ++q) load_b(q, nxt, lbuf, lks);
+                                pin();
+                            }
+                            if (refill) {
 #pragma unroll
-                        for (int c = 0; c < WC; ++c) {
-                            pin();
-                            acc[b][c] = wide_mma<BF16>(ua, ub[c], acc[b][c]);
-                            pin();
-                            if (ks < 3 && sub == 0 && b == 0) load_b(c, nxt, lbuf, lks);
-                            const int i = (sub * WR + b) * WC + c;
-                            if (ks == 3 && more && i >= K0) {
-                                if (i == K0) {
-                                    // this wavefront's reads of the stage have returned and its share of the next
-                                    // stage has landed; the barrier says so of all wavefronts
-                                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                                    if (refill) wait_vmcnt<(NBUF - 2) * LPW>(); else wait_vmcnt<0>();
-                                    __builtin_amdgcn_s_barrier();
-                                    asm volatile("" ::: "memory");
-                                    pin();
-#pragma unroll
-                                    for (int q = 0; q < WC; ++q) load_b(q, nxt, lbuf, lks);
-                                    pin();
-                                }
-                                if (refill) {
-#pragma unroll
-                                    for (int u = 0; u < LPW; ++u)
-                                        if (u * SLOTS / LPW == i - K0) copy(u);
-                                }
+                                for (int u = 0; u < LPW; ++u)
+                                    if (u * SLOTS / LPW == i - K0) copy(u);
                             }
                         }
-                        pin();
-                        if (sub == SUB - 1 && (ks < 3 || more)) load_a(b, lbuf, lks);
                     }
+                    pin();
+                    if (ks < 3 || more) load_a(b, lbuf, lks);
                 }
             }
             if (refill) copy_next();
@@ -295,7 +280,7 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
                 const float rt = __shfl(rt_lane[b >> 1], 32 * (b & 1) + 8 * (v >> 2) + row_lane + (v & 3), 64);
 #pragma unroll
                 for (int c = 0; c < WC; ++c) {
-                    const float D = Sh::BITS == 4 ? (float)((int)acc[b][c][v] >> 8) : (float)acc[b][c][v];
+                    const float D = (float)acc[b][c][v];
                     facc[b][c][v] = __fadd_rn(facc[b][c][v], __fmul_rn(__fmul_rn(D, rt), wv[c]));
                 }
             }
@@ -361,7 +346,7 @@ static qless_status launch_wide_shape(const ScoreArgs &a, WidePrep w, bool prepa
 }
 
 // The shape with the least padded work: rounds of one workgroup per compute unit, times the tile's pairs, times what a
-// pair costs in the shape (measured at N = 270 000, M = 285 and 1024, 8 and 4 bits, relative to the 96 x 64 wavefronts:
+// pair costs in the shape (measured at N = 270 000, M = 285 and 1024, relative to the 96 x 64 wavefronts:
 // 256 x 128 6 %, 512 x 96 16 % more per pair -- more operand bytes per product).  The validation tiles of a train tile run
 // on one XCD, so the rounds are those of the XCD with the most train tiles: 25 316 x 773 in tiles of 256 x 192 is 495
 // workgroups, but 65 of them on three of the XCDs, a third round (6016 codes of 4 bits: 202 us; 256 x 128: 169).
@@ -400,8 +385,7 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
     const int shape = choose_shape(rows, a.M);            // of plan_rows: the pre-pass is laid out for it
     qless_status rc;
     if (bits == 16) rc = launch_wide_bits<16>(a, w, shape, prepare, st);
-    else if (bits == 8) rc = launch_wide_bits<8>(a, w, shape, prepare, st);
-    else rc = launch_wide_bits<4>(a, w, shape, prepare, st);
+    else rc = launch_wide_bits<8>(a, w, shape, prepare, st);
     if (rc != QLESS_OK) return rc;
     if (a.score) launch_score_finish(w.smax, a.N, a.score, st);
     return launch_status();
