@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libqless.so")
-SOURCES = ["project.hip", "quantize.hip", "score.hip", "score_wide.hip", "score_codes.hip", "score_split.hip", "topk.hip", "misc.hip"]
+SOURCES = ["project.hip", "quantize.hip", "score.hip", "score_wide.hip", "score_codes.hip", "score_fp4.hip", "score_split.hip", "topk.hip", "misc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -43,11 +43,20 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
 size_t codes_workspace(int64_t N, int32_t M, int64_t row_bytes, int C);
 qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st);
 
+// score_fp4.hip: 1- and 2-bit codes (k a multiple of 128) against more than 64 validation vectors.
+// use_fp4: whether it serves a call faster than the 128 x 64 tiles of score.hip; share: with the planes of a call whose checkpoints
+// are shared out over workgroups
+bool use_fp4(int64_t N, int32_t M, int32_t k, int bits, int C);
+size_t fp4_workspace(int64_t N, int32_t M, int32_t k, int bits, int C, bool share);
+qless_status launch_fp4(const ScoreArgs &a, int bits, void *ws, size_t ws_bytes, hipStream_t st);
+
 // score_split.hip: few pairs (bits = 16: bfloat16 rows).  use_split: whether the path serves a call faster than the others.
 // Rows hold at least 16 bytes (16 per plane for the ternary codes).
 bool use_split(int64_t N, int32_t M, int64_t row_bytes, int bits, int C);
 size_t split_workspace(int64_t N, int32_t M, int64_t row_bytes, int bits, int C);
 // none: the score of a row none of whose sums lies above -infinity
+// launch_split_finish: joins planes [C * parts][N][M] of partial dot products (int32, or fp32 of bfloat16 rows)
+qless_status launch_split_finish(const ScoreArgs &a, int parts, const uint32_t *planes, bool bf16, float none, hipStream_t st);
 qless_status launch_split(const ScoreArgs &a, int bits, float none, void *ws, hipStream_t st);
 
 }  // namespace qless

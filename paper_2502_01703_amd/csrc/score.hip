@@ -19,7 +19,7 @@
 // The popcount kernels give a workgroup a block of train rows and walk it over all validation
 // tiles with the running row maximum in registers; the MFMA kernel gives every (train tile, val
 // tile) pair its own workgroup and combines the row maxima with an exact integer atomicMax.
-#include "score.h"
+#include "score_tile.h"
 
 namespace qless {
 
@@ -231,7 +231,7 @@ constexpr int log2c(int x) { return x <= 1 ? 0 : 1 + log2c(x / 2); }
 struct ScorePrep {                             // workspace views (device pointers)
     int8_t *vexp;                              // [C][Mp][kp]
     float *vw;                                 // [C][Mp]
-    int32_t *vbias;                            // [C][Mp] sign codes on wide tiles: what the scaled validation codes leave to add to a dot product
+    int32_t *vbias;                            // [C][M] streaming sign codes: numbers of negative codes outside dword 0
     unsigned int *smax;                        // [N] order-preserving keys of the row maxima
     int32_t Mp, kp;                            // padded validation rows / elements per row
     int32_t vrow;                              // bytes per expanded validation row: kp, or kp / 2 for 1-bit (FP4 codes)
@@ -242,14 +242,10 @@ struct ScorePrep {                             // workspace views (device pointe
 // Order of the codes in a row:
 //   8 bits  as stored
 //   4 bits  inside a half K-step of 16: [0,2,4,6,1,3,5,7,8,10,12,14,9,11,13,15] (the even, then the odd nibbles of a dword)
-//   1, 2    FP4 codes, stages of 512 elements = 16 words of 32 codes: K step ks of a stage (64 positions), half h: the train lane
+//   2       FP4 codes, stages of 512 elements = 16 words of 32 codes: K step ks of a stage (64 positions), half h: the train lane
 //           reads the 16-byte chunk 2 (ks / 4) + h and uses its dword ks % 4, i.e. word 4 (2 (ks / 4) + h) + ks % 4 of
 //           the stage; FP4 dword j, nibble n of the expansion is bit 4 n + 3 - j of that word.
-//   1 bit on wide tiles: the train side feeds FP4 dword j of a word as the word's bits 4 n + 3 - j left in place (no shift),
-//           i.e. as 2 s, s, s / 2 for j = 1, 2, 3 with s = 1 for a negative code a = 1 - 2 s; the validation code b of such
-//           a position is stored as -b, -2 b, -4 b, so that every product is -2 s b = a b - b, and the sum of b over
-//           these positions is added back after the dot product (vbias).  j = 0 keeps +-1 on both sides.  (Few validation
-//           vectors: vrow == 0, the main kernel stages the packed codes itself.)
+//   1 bit   vrow == 0: the main kernel stages the packed codes itself
 //   2 bits  the train side leaves its "non-zero" bit of dwords 1, 2, 3 in place (FP4 2, 1, 1/2): the validation magnitudes are
 //           1/2, 1, 2 there, so that every product is a b.
 // Codes past the end of the vector, and rows past M, are 0.
@@ -261,36 +257,20 @@ score_prepare_kernel(ScoreArgs a, ScorePrep w) {
     const bool live = row < a.M;
     const unsigned char *src = a.vc[ci] + (int64_t)(live ? row : 0) * ((int64_t)a.k * BITS / 8);
     if (BITS <= 2) {
-        int bias = 0;
-        const int words = w.vrow / 16;
+        const int words = BITS == 2 ? w.vrow / 16 : 0;
         for (int t = threadIdx.x; t < words; t += 256) {
             const int stage = t >> 4, ks = (t >> 1) & 7, h = t & 1;          // 16 bytes t of the row: K step 8 stage + ks, half h
             const int wi = 16 * stage + 4 * (2 * (ks >> 2) + h) + (ks & 3);  // source word (rows and planes are whole words)
             uint32_t d[4] = {0, 0, 0, 0};
             if (live && wi * 32 < a.k) {
-                const uint32_t sg = ((const uint32_t *)(src + (BITS == 2 ? a.k / 8 : 0)))[wi];
-                const uint32_t nz = BITS == 2 ? ((const uint32_t *)src)[wi] : 0u;
+                const uint32_t sg = ((const uint32_t *)(src + a.k / 8))[wi], nz = ((const uint32_t *)src)[wi];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
-                    const uint32_t s = (sg >> (3 - j)) & 0x11111111u;
-                    if (BITS == 2) {
-                        const uint32_t x = (nz >> (3 - j)) & 0x11111111u;
-                        d[j] = x * (j == 1 ? 1u : (j == 3 ? 4u : 2u)) | ((x & s) << 3);
-                    } else {
-                        d[j] = (j == 3 ? 0x66666666u : (j == 2 ? 0x44444444u : 0x22222222u)) | ((j == 0 ? s : s ^ 0x11111111u) << 3);
-                        if (j != 0) bias += 8 - 2 * (int)__popc(s);
-                    }
+                    const uint32_t s = (sg >> (3 - j)) & 0x11111111u, x = (nz >> (3 - j)) & 0x11111111u;
+                    d[j] = x * (j == 1 ? 1u : (j == 3 ? 4u : 2u)) | ((x & s) << 3);
                 }
             }
             *(uint4 *)(dst + 16 * t) = make_uint4(d[0], d[1], d[2], d[3]);
-        }
-        if (BITS == 1 && w.vrow > 0) {
-            __shared__ int sh_bias;
-            if (threadIdx.x == 0) sh_bias = 0;
-            __syncthreads();
-            if (bias) atomicAdd(&sh_bias, bias);
-            __syncthreads();
-            if (threadIdx.x == 0) w.vbias[ci * w.Mp + row] = sh_bias;
         }
     } else {
         for (int t = threadIdx.x; t < w.kp / 16; t += 256) {
@@ -1048,8 +1028,7 @@ score_stream_mfma32_kernel(ScoreArgs a, const int8_t *vexp, const int32_t *vsum,
 // Shape of the NW waves of a workgroup: WX waves across the val tile, NW / WX down the train
 // rows; each wave owns WR x WC accumulators of 32 x 32.  Train tile height MT = 32 WR NW / WX, val
 // tile width VT = 32 WC WX:
-//   M > 64 (2-/1-bit): <2, 2, 2, 8> (64 x 64 per wave, 256 x 128 per workgroup), or for sign codes <2, 3, 1, 8>
-//   (64 x 96 per wave, 512 x 96 per workgroup) when that pads M less;  M <= 64: <1, 2, 1, 8> (256 x 64);
+//   M <= 64: <1, 2, 1, 8> (256 x 64), and <1, 2, 1, 4> (128 x 64) for M > 64 and few train rows;
 //   M <= 32: <1, 1, 1, 8> (256 x 32) or <1, 1, 1, 4> (128 x 32), whichever fills the chip more evenly.
 template <int BITS, int WR, int WC, int WX, int NW, bool VH = false>
 struct MfmaShape {
@@ -1064,14 +1043,12 @@ struct MfmaShape {
     // Code elements per stage: a stage should bring 128 bytes of every train row (whole cache lines
     // when the codes are streamed from HBM) as far as the expanded validation rows leave room in LDS:
     // the shapes for few validation vectors take 256 elements (4- and 2-bit) or 512 (1-bit).
-    static constexpr bool NARROW = WR == 1;              // the shapes for at most 64 validation vectors
     static constexpr int KE = narrow_stage_elements(BITS, 32 * WC * WX);
     static constexpr bool FP4 = BITS <= 2;               // sign / ternary codes go to the matrix core as FP4 +-1.0, 0
     static constexpr int TB = KE * BITS / 8;             // train bytes per row per stage
     static constexpr int TCPR = TB / 16;                 // 16-byte chunks per train row
-    // val bytes per row per stage: int8-expanded; for the sign codes FP4-expanded by the pre-pass (wide
-    // tiles, where the VALU has no room to expand both operands), or the packed signs themselves
-    static constexpr bool VPACKED = BITS == 1 && NARROW;
+    // val bytes per row per stage: int8-expanded, FP4-expanded (ternary codes), or the packed signs themselves
+    static constexpr bool VPACKED = BITS == 1;
     static constexpr int VROWB = VPACKED ? KE / 8 : (FP4 ? KE / 2 : KE);
     static constexpr int VCPR = VROWB / 16;              // 16-byte chunks per expanded val row
     // rows whose chunks share a bank group are 16 / CPR apart: the swizzle key is (row >> SH) % CPR
@@ -1081,13 +1058,14 @@ struct MfmaShape {
     static constexpr int NINST = (TCH + VCH) / 64;       // wavefront-wide copies per stage
     static constexpr int LPW = (NINST + NW - 1) / NW;    // per wave
     static constexpr int BUF = TRAIN_BYTES + VAL_BYTES + 1024;   // + 1 KB landing zone for padding copies
-    // LDS ring depth.  The narrow shapes serve few validation vectors, where scoring streams the
-    // train codes from HBM: two stages per workgroup and several workgroups per compute unit,
+    // LDS ring depth.  The shapes serve few validation vectors, where scoring streams the
+    // train codes from HBM (or few rows): two stages per workgroup and several workgroups per compute unit,
     // whose barriers and epilogues then overlap each other's copies.
-    static constexpr int NBUF = NARROW ? 2 : ((158 * 1024) / BUF >= 4 ? 4 : (158 * 1024) / BUF);
+    static constexpr int NBUF = 2;
     static constexpr int PLANES = BITS == 2 ? 2 : 1;     // separately stored bit planes of a train row
     static constexpr int PCH = TCPR / PLANES;            // chunks per plane and stage
     static constexpr int TSTEP = TB / PLANES;            // bytes a plane's source advances per stage
+    static_assert(WR == 1 && WX == 1, "32 rows per wavefront");
     static_assert(WY * WX == NW && TCH % 64 == 0 && (TCH + VCH) % 64 == 0, "whole wavefront copies");
     static_assert(NBUF >= 2 && NBUF * BUF <= 158 * 1024, "a ring of at least two stages fits in LDS");
 };
@@ -1242,69 +1220,8 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles) {
             __syncthreads();                         // stage g visible to all; buffer of stage g-1 free
             if (g + NBUF - 1 < total) issue(g + NBUF - 1);
             const unsigned char *sb = smem + (g % NBUF) * BUF;
-            if constexpr (BITS == 1 && !Sh::VPACKED) {
-                // sign codes as FP4: one 64-element K step per matrix-core instruction.  A lane reads 16
-                // bytes of its row (chunk 2 q + half: four words of 32 signs) per four K steps; word j
-                // becomes four dwords of FP4 codes, dword jd = bits 3 - jd of every nibble, left where they
-                // are: (w & 0x88888888) | 0x22222222 = +-1.0, then w & 0x44444444, w & 0x22222222,
-                // w & 0x11111111 = 2 s, s, s / 2 (four operations per word; the pre-pass scaled the
-                // validation codes of those positions to match, see score_prepare_kernel).  The pre-expanded
-                // validation rows follow the same order and are zero past the end of the vectors.
-                // The validation fragments of K step ks + 1 and the train words of the next four steps are
-                // requested before the matrix instructions of step ks (scheduling barriers keep that
-                // order), so a wave waits for LDS once per stage instead of once per step; the train
-                // fragments of step ks + 1 are expanded between the matrix instructions of step ks, each
-                // instruction followed by its share of the expansions (scheduling groups).
-                i32x4 wq[KE / 256][WR], bq[WC], bn[WC];
-#pragma unroll
-                for (int b = 0; b < WR; ++b) wq[0][b] = *(const i32x4 *)(sb + a_base[b]);
-#pragma unroll
-                for (int c = 0; c < WC; ++c) bq[c] = *(const i32x4 *)(sb + b_base[c]);
-                auto expand = [&](unsigned int wd) {
-                    i32x8 r = {0, 0, 0, 0, 0, 0, 0, 0};
-                    r[0] = (int)sign_bits_or(wd, ones); r[1] = (int)(wd & 0x44444444u);
-                    r[2] = (int)(wd & 0x22222222u); r[3] = (int)(wd & 0x11111111u);
-                    return r;
-                };
-                i32x8 afc[WR], afn[WR];
-#pragma unroll
-                for (int b = 0; b < WR; ++b) afc[b] = expand((unsigned int)wq[0][b][0]);
-#pragma unroll
-                for (int ks = 0; ks < KE / 64; ++ks) {
-                    const int q = ks >> 2, j = ks & 3;
-                    if (ks + 1 < KE / 64) {
-#pragma unroll
-                        for (int c = 0; c < WC; ++c) bn[c] = *(const i32x4 *)(sb + (b_base[c] ^ ((ks + 1) << 5)));
-                    }
-                    if (j == 1 && q + 1 < KE / 256) {
-#pragma unroll
-                        for (int b = 0; b < WR; ++b) wq[q + 1][b] = *(const i32x4 *)(sb + (a_base[b] ^ ((q + 1) << 5)));
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    i32x8 bf[WC];
-#pragma unroll
-                    for (int c = 0; c < WC; ++c) bf[c] = i32x8{bq[c][0], bq[c][1], bq[c][2], bq[c][3], 0, 0, 0, 0};
-#pragma unroll
-                    for (int b = 0; b < WR; ++b)
-#pragma unroll
-                        for (int c = 0; c < WC; ++c) acc[b][c] = mfma_fp4(afc[b], bf[c], acc[b][c]);
-                    if (ks + 1 < KE / 64) {
-#pragma unroll
-                        for (int b = 0; b < WR; ++b) afn[b] = expand((unsigned int)wq[(ks + 1) >> 2][b][(ks + 1) & 3]);
-                    }
-#pragma unroll
-                    for (int i = 0; i < WR * WC; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one matrix instruction
-                        __builtin_amdgcn_sched_group_barrier(0x002, 4 / WC > 0 ? 4 / WC : 1, 0);   // its share of the 4 WR expansion operations
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int c = 0; c < WC; ++c) bq[c] = bn[c];
-#pragma unroll
-                    for (int b = 0; b < WR; ++b) afc[b] = afn[b];
-                }
-            } else if constexpr (BITS == 1) {
-                // few validation vectors: both operands are packed rows, read as 4-byte words (K step ks:
+            if constexpr (BITS == 1) {
+                // both operands are packed rows, read as 4-byte words (K step ks:
                 // word 2 ks + half) and expanded in registers.  K steps of the last stage that start past
                 // the end of the vectors are skipped (k % 64 == 0).
                 const int ksteps = (a.k - s * KE) / 64 < KE / 64 ? (a.k - s * KE) / 64 : KE / 64;
@@ -1406,13 +1323,8 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles) {
         // gives one (mixed precision: rows of integer codes with their 1 / ||q||)
         const float rt_lane = (F16 && !a.tr[ci]) ? 1.0f : a.tr[ci][myrow];
         float wv[WC];
-        int vbias[WC];
 #pragma unroll
-        for (int c = 0; c < WC; ++c) {
-            const int col = v0 + vcol + 32 * c + l32;               // < Mp (padded)
-            wv[c] = w.vw[ci * w.Mp + col];
-            vbias[c] = (BITS == 1 && !Sh::VPACKED) ? w.vbias[ci * w.Mp + col] : 0;
-        }
+        for (int c = 0; c < WC; ++c) wv[c] = w.vw[ci * w.Mp + v0 + vcol + 32 * c + l32];       // column < Mp (padded)
 #pragma unroll
         for (int b = 0; b < WR; ++b)
 #pragma unroll
@@ -1424,36 +1336,14 @@ score_mfma_kernel(ScoreArgs a, ScorePrep w, int ttiles, int vtiles) {
                     if (F16) {
                         t = __fmul_rn(__fmul_rn((float)acc[b][c][v], rt), wv[c]);     // rt = 1: the product is acc itself
                     } else {
-                        int D = BITS == 4 ? ((int)acc[b][c][v] >> 4) : (int)acc[b][c][v];   // 1-/2-bit: an exact integer in fp32
-                        if (BITS == 1 && !Sh::VPACKED) D += vbias[c];
+                        const int D = BITS == 4 ? ((int)acc[b][c][v] >> 4) : (int)acc[b][c][v];   // 1-/2-bit: an exact integer in fp32
                         t = __fmul_rn(__fmul_rn((float)D, rt), wv[c]);
                     }
                     facc[b][c][v] = __fadd_rn(facc[b][c][v], t);
                 }
             }
     }
-    // tile epilogue: optional full matrix, row maxima over this val tile
-#pragma unroll
-    for (int b = 0; b < WR; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int rloc = trow + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-            const int64_t r = row0 + rloc;
-            float m = neg_inf();
-#pragma unroll
-            for (int c = 0; c < WC; ++c) {
-                const int col = v0 + vcol + 32 * c + l32;
-                if (col < a.M) {
-                    m = fmaxf(m, facc[b][c][v]);
-                    if (a.full && r < a.N) a.full[r * a.M + col] = facc[b][c][v];
-                }
-            }
-            if (a.score) {
-#pragma unroll
-                for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-                if (l32 == 0 && m > neg_inf()) atomicMax(&s_rowmax[rloc], f32_order_key(m));
-            }
-        }
+    tile_finish<WR, WC>(a, facc, row0, trow, v0 + vcol, s_rowmax);
     if (a.score) {
         __syncthreads();
         if (tid < kMT && row0 + tid < a.N && s_rowmax[tid] != 0u) atomicMax(&w.smax[row0 + tid], s_rowmax[tid]);
@@ -1474,9 +1364,6 @@ struct MfmaPlan { int32_t vt, Mp, kp; size_t off_vw, off_vbias, off_smax, total;
 static MfmaPlan mfma_plan(int64_t N, int32_t M, int32_t k, int bits, int C) {
     MfmaPlan p{};
     p.vt = M > 64 ? 128 : (M > 32 ? 64 : 32);
-    // sign codes: 512 x 96 tiles (64 x 96 per wave) where 96-wide tiles pad the validation set less than
-    // 128-wide ones (M = 285: 288 instead of 384 columns)
-    if (bits == 1 && M > 64 && (M + 95) / 96 * 96 < (M + 127) / 128 * 128) p.vt = 96;
     p.Mp = (M + p.vt - 1) / p.vt * p.vt;
     const int ke = narrow_stage_elements(bits, p.vt);                 // MfmaShape::KE of the shape used
     p.kp = (k + ke - 1) / ke * ke;
@@ -1494,7 +1381,8 @@ static MfmaPlan mfma_plan(int64_t N, int32_t M, int32_t k, int bits, int C) {
 // than 64 validation vectors go to score_wide.hip, 4-bit codes to score_codes.hip, which lay it out differently.
 static size_t tiles_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
     const size_t t = mfma_plan(N, M, k, bits, C).total;
-    const size_t w = bits < 4 || M <= 64 ? 0 : (bits == 4 ? codes_workspace(N, M, k / 2, C) : wide_workspace(N, M, (int64_t)k * bits / 8, C));
+    const size_t w = M <= 64 ? 0 : (bits <= 2 ? fp4_workspace(N, M, k, bits, C, false) : (bits == 4 ? codes_workspace(N, M, k / 2, C)
+                                                                                     : wide_workspace(N, M, (int64_t)k * bits / 8, C)));
     return t > w ? t : w;
 }
 // The bit planes are copied in 16-byte chunks: k must be a multiple of 128 for the 1-/2-bit codes.
@@ -1558,30 +1446,22 @@ static NarrowChoice choose_narrow(int64_t N) {
 // prepare = false: the workspace still holds the pre-pass of an earlier launch with the same validation
 // side and at least as many train rows (the finish kernel leaves the row maxima cleared)
 template <int BITS, bool F16 = false>
-static qless_status launch_mfma(const ScoreArgs &a, void *ws, hipStream_t st, bool prepare = true, int64_t plan_rows = 0) {
+static qless_status launch_mfma(const ScoreArgs &a, void *ws, size_t ws_bytes, hipStream_t st, bool prepare = true, int64_t plan_rows = 0) {
     const MfmaPlan p = mfma_plan(plan_rows > 0 ? plan_rows : a.N, a.M, a.k, BITS, a.C);
-    // a small datastore leaves most compute units without a 256 x 128 tile: 128 x 64 tiles fill four times as
-    // many (the expanded validation rows are the same for both shapes; the sign codes' narrow shape stages the
-    // packed validation rows itself)
+    // a small datastore leaves most compute units without a 256 x 128 tile: 128 x 64 tiles fill four times as many
     const bool small = !F16 && p.vt == 128 && ((a.N + 255) / 256) * (p.Mp / 128) * 2 <= compute_units();
+    if (BITS <= 2 && a.M > 64 && use_fp4(a.N, a.M, a.k, BITS, a.C)) return launch_fp4(a, BITS, ws, ws_bytes, st);
     if (BITS == 4 && p.vt == 128 && !small) return launch_codes(a, ws, st);
     if (BITS == 8 && p.vt == 128 && !small) return launch_wide(a, F16 ? 16 : BITS, ws, st, prepare, plan_rows);
     ScorePrep w{};
     unsigned char *base = (unsigned char *)ws;
     w.vexp = (int8_t *)base; w.vw = (float *)(base + p.off_vw); w.vbias = (int32_t *)(base + p.off_vbias);
     w.smax = (unsigned int *)(base + p.off_smax); w.Mp = p.Mp; w.kp = p.kp;
-    w.vrow = BITS == 1 ? (p.vt > 64 && !small ? p.kp / 2 : 0) : (BITS == 2 ? p.kp / 2 : p.kp);
+    w.vrow = BITS == 1 ? 0 : (BITS == 2 ? p.kp / 2 : p.kp);
     if (prepare)
         hipLaunchKernelGGL((score_prepare_kernel<BITS, F16>), dim3((unsigned)p.Mp, (unsigned)a.C), dim3(256), 0, st, a, w);
     qless_status rc;
-    if (p.vt == 96) {
-        if constexpr (BITS == 1) rc = launch_mfma_shape<BITS, 2, 3, 1, 8, F16>(a, w, 0, st);
-        else rc = QLESS_ERR_UNSUPPORTED;
-    } else if (p.vt == 128) {
-        if constexpr (BITS >= 4) rc = launch_mfma_shape<BITS, 1, 2, 1, 4, F16>(a, w, 0, st);
-        else if (small) rc = launch_mfma_shape<BITS, 1, 2, 1, 4, F16>(a, w, 0, st);
-        else rc = launch_mfma_shape<BITS, 2, 2, 2, 8, F16>(a, w, 0, st);
-    }
+    if (p.vt == 128) rc = launch_mfma_shape<BITS, 1, 2, 1, 4, F16>(a, w, 0, st);
     else if (p.vt == 64) {
         const NarrowChoice c = choose_narrow<BITS, 2>(a.N);
         if (c.nw == 8) rc = launch_mfma_shape<BITS, 1, 2, 1, 8, F16>(a, w, c.per_cu, st);
@@ -1897,7 +1777,7 @@ extern "C" qless_status qless_score_mixed(const void *const *train_codes, const 
         a.C = C; a.N = rows; a.M = M; a.k = 2 * k;                    // k in bytes from here on
         a.score = score ? score + r0 : nullptr;
         a.full = full ? full + r0 * (int64_t)M : nullptr;
-        const qless_status rc = launch_mfma<8, true>(a, (unsigned char *)ws + mp.off_tiles, st, r0 == 0, mp.rows);
+        const qless_status rc = launch_mfma<8, true>(a, (unsigned char *)ws + mp.off_tiles, ws_bytes - mp.off_tiles, st, r0 == 0, mp.rows);
         if (rc != QLESS_OK) return rc;
     }
     return launch_status();
@@ -1936,7 +1816,8 @@ static bool score_splits(int64_t N, int32_t M, int32_t k, int bits, int C) {
 extern "C" size_t qless_score_workspace(int64_t N, int32_t M, int32_t k, int bits, int C) {
     if (N < 0 || M < 1 || k <= 0 || C < 1 || !valid_bits(bits)) return 0;
     const size_t need = score_base_workspace(N, M, k, bits, C);
-    const size_t split = score_splits(N, M, k, bits, C) ? split_workspace(N, M, (int64_t)k * bits / 8, bits, C) : 0;
+    size_t split = score_splits(N, M, k, bits, C) ? split_workspace(N, M, (int64_t)k * bits / 8, bits, C) : 0;
+    if (!split && N > 0 && bits <= 2 && M > 64 && score_path(bits, M, k, C) == kScoreTiles) split = fp4_workspace(N, M, k, bits, C, true);
     return split > need ? split : need;
 }
 
@@ -1982,10 +1863,10 @@ extern "C" qless_status qless_score(const void *const *train_codes, const float 
             if ((uintptr_t)ws % 16) return QLESS_ERR_WORKSPACE;
             if (N > (int64_t)0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
             if (use_stream_i8(bits, M, k, C)) return bits == 8 ? launch_stream_i8<8>(a, ws, st) : launch_stream_i8<4>(a, ws, st);
-            if (bits == 8) return launch_mfma<8>(a, ws, st);
-            if (bits == 4) return launch_mfma<4>(a, ws, st);
-            if (bits == 2) return launch_mfma<2>(a, ws, st);
-            return launch_mfma<1>(a, ws, st);
+            if (bits == 8) return launch_mfma<8>(a, ws, ws_bytes, st);
+            if (bits == 4) return launch_mfma<4>(a, ws, ws_bytes, st);
+            if (bits == 2) return launch_mfma<2>(a, ws, ws_bytes, st);
+            return launch_mfma<1>(a, ws, ws_bytes, st);
         }
         case kScorePopcount: break;
     }
@@ -2105,5 +1986,5 @@ extern "C" qless_status qless_score16(const void *const *train16, const void *co
     if (ready != QLESS_OK) return ready;
     // (a workspace laid out for a larger call may be too small for the parts: the tile kernels serve that as well)
     if (use_split(N, M, a.k, 16, C) && ws_bytes >= split_workspace(N, M, a.k, 16, C)) return launch_split(a, 16, no_score(kScoreTiles), ws, (hipStream_t)stream);
-    return launch_mfma<8, true>(a, ws, (hipStream_t)stream);
+    return launch_mfma<8, true>(a, ws, ws_bytes, (hipStream_t)stream);
 }

@@ -22,14 +22,13 @@
 //     during the one before.
 // Measured, same card, N = 270 000, k = 8192, C = 4 (int8 form -> now): M = 1024 6.92 -> 5.78 ms, M = 285 2.53 -> 1.96 ms;
 // 65536 x 512 0.95 -> 0.80 ms.  Without the copies (what the rings hold, any numbers) M = 1024 takes 4.8 ms.
-#include "score.h"
+#include "score_tile.h"
 
 namespace qless {
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(2))) int i32x2;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 struct CodesPrep {                             // workspace views (device pointers)
     unsigned char *vexp;                       // [C][val tile][half line][VBYTES]
@@ -334,49 +333,10 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
             next_train();
             tslot = tnext;
         }
-        // checkpoint epilogue.  acc[b][c][v] = D / 64: train row 32 b + 8 (v / 4) + 4 half + v % 4, val column 32 c + l32.
-        // Lane L holds rnorm of train row trow + L; rows are fetched by shuffle.
-        int64_t r = row0 + trow + lane;
-        if (r > a.N - 1) r = a.N - 1;
-        const float rt_lane = a.tr[ci][r];
-        int row_lane = 4 * half;                          // opaque: the 16 lane numbers below are formed here, not kept over the loop
-        asm volatile("" : "+v"(row_lane));
-        float wv[WC];
-#pragma unroll
-        for (int c = 0; c < WC; ++c) wv[c] = w.vw[ci * w.Mp + vt * VT + vcol + 32 * c + l32];
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float rt = __shfl(rt_lane, 32 * b + 8 * (v >> 2) + row_lane + (v & 3), 64);
-#pragma unroll
-                for (int c = 0; c < WC; ++c)
-                    facc[b][c][v] = __fadd_rn(facc[b][c][v], __fmul_rn(__fmul_rn(64.0f * acc[b][c][v], rt), wv[c]));
-            }
+        tile_add_checkpoint<2, WC>(acc, 64.0f, a.tr[ci], row0 + trow, a.N, w.vw + ci * w.Mp + vt * VT + vcol, facc);      // acc = D / 64
     }
     wait_vmcnt<0>();                                      // no copy is under way when the workgroup gives its LDS back
-    // tile epilogue: optional full matrix, row maxima over this val tile
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int rloc = trow + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-            const int64_t r = row0 + rloc;
-            float m = neg_inf();
-#pragma unroll
-            for (int c = 0; c < WC; ++c) {
-                const int col = vt * VT + vcol + 32 * c + l32;
-                if (col < a.M) {
-                    m = fmaxf(m, facc[b][c][v]);
-                    if (a.full && r < a.N) a.full[r * a.M + col] = facc[b][c][v];
-                }
-            }
-            if (a.score) {
-#pragma unroll
-                for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-                if (l32 == 0 && m > neg_inf()) atomicMax(&s_rowmax[rloc], f32_order_key(m));
-            }
-        }
+    tile_finish<2, WC>(a, facc, row0, trow, vt * VT + vcol, s_rowmax);
     if (a.score) {
         __syncthreads();
         for (int i = tid; i < MT; i += 64 * NW)

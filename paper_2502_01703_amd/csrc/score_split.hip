@@ -173,14 +173,18 @@ score_split_kernel(ScoreArgs a, int cb, int parts, int per, uint32_t *planes) {
     }
 }
 
-// One workgroup per train row: the parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.
+// The parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.  ROWS train rows per workgroup of four
+// wavefronts: one each, or (more than 256 columns) all on one row.
+template <int ROWS>
 __global__ void __launch_bounds__(256)
 score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf16, float none) {
     __shared__ float wave_best[4];
-    const int64_t z = blockIdx.x;
+    const int wave = threadIdx.x >> 6;
+    const int64_t z = ROWS == 1 ? blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
     const size_t plane = (size_t)a.N * (size_t)a.M;
+    if (ROWS > 1 && z >= a.N) return;                // (no barrier below then)
     float best = neg_inf();
-    for (int c = threadIdx.x; c < a.M; c += 256) {
+    for (int c = ROWS == 1 ? threadIdx.x : threadIdx.x & 63; c < a.M; c += ROWS == 1 ? 256 : 64) {
         float acc = 0.0f;
         const uint32_t *p = planes + (size_t)z * a.M + c;
         for (int ci = 0; ci < a.C; ++ci) {
@@ -204,12 +208,19 @@ score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf
     if (!a.score) return;                            // uniform
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) best = fmaxf(best, __shfl_xor(best, o, 64));
-    if ((threadIdx.x & 63) == 0) wave_best[threadIdx.x >> 6] = best;
-    __syncthreads();
-    if (threadIdx.x == 0) {
+    if (ROWS == 1) {
+        if ((threadIdx.x & 63) == 0) wave_best[wave] = best;
+        __syncthreads();
         best = fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
-        a.score[z] = best > neg_inf() ? best : none;
     }
+    if (threadIdx.x == (ROWS == 1 ? 0 : wave * 64)) a.score[z] = best > neg_inf() ? best : none;
+}
+qless_status launch_split_finish(const ScoreArgs &a, int parts, const uint32_t *planes, bool bf16, float none, hipStream_t st) {
+    if (a.M <= 256 && a.N >= 1024)
+        hipLaunchKernelGGL(score_split_finish_kernel<4>, dim3((unsigned)((a.N + 3) / 4)), dim3(256), 0, st, a, parts, planes, bf16, none);
+    else
+        hipLaunchKernelGGL(score_split_finish_kernel<1>, dim3((unsigned)a.N), dim3(256), 0, st, a, parts, planes, bf16, none);
+    return launch_status();
 }
 
 struct SplitPlan { int parts, per; size_t bytes; };
@@ -246,8 +257,7 @@ qless_status launch_split(const ScoreArgs &a, int bits, float none, void *ws, hi
         case 2: launch_split_bits<2>(a, cb, p, w, st); break;
         default: launch_split_bits<1>(a, cb, p, w, st); break;
     }
-    hipLaunchKernelGGL(score_split_finish_kernel, dim3((unsigned)a.N), dim3(256), 0, st, a, p.parts, (const uint32_t *)ws, bits == 16, none);
-    return launch_status();
+    return launch_split_finish(a, p.parts, w, bits == 16, none, st);
 }
 
 // The other paths walk their stages one after the other whatever the number of pairs (measured with few pairs: about a
