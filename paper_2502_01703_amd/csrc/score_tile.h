@@ -1,4 +1,4 @@
-// What the tile kernels of score_codes.hip and score_fp4.hip share: the epilogues of a wavefront that owns WR x WC accumulators of
+// What the tile kernels share: the epilogues of a wavefront that owns WR x WC accumulators of
 // 32 x 32 (train rows x validation columns).  acc[b][c][v]: train row 32 b + 8 (v / 4) + 4 half + v % 4, column 32 c + lane % 32.
 #pragma once
 #include "score.h"
@@ -8,9 +8,9 @@ namespace qless {
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // Checkpoint epilogue: facc += ((unit acc) rnorm) w', rounded after every operation.  row_first: the wavefront's first train row,
-// vw: weights of its first column on.  Lane L holds rnorm of train rows 64 q + L; rows are fetched by shuffle.
-template <int WR, int WC>
-__device__ inline void tile_add_checkpoint(const f32x16 (&acc)[WR][WC], float unit, const float *rnorm, int64_t row_first, int64_t N,
+// vw: weights of its first column on; rnorm may be null (1).  Lane L holds rnorm of train rows 64 q + L; rows are fetched by shuffle.
+template <int WR, int WC, class Acc>
+__device__ inline void tile_add_checkpoint(const Acc (&acc)[WR][WC], float unit, const float *rnorm, int64_t row_first, int64_t N,
                                            const float *vw, float (&facc)[WR][WC][16]) {
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     float rt_lane[(WR + 1) / 2];
@@ -18,7 +18,7 @@ __device__ inline void tile_add_checkpoint(const f32x16 (&acc)[WR][WC], float un
     for (int q = 0; q < (WR + 1) / 2; ++q) {
         int64_t r = row_first + 64 * q + lane;
         if (r > N - 1) r = N - 1;
-        rt_lane[q] = rnorm[r];
+        rt_lane[q] = rnorm ? rnorm[r] : 1.0f;
     }
     int row_lane = 4 * half;                              // opaque: the 16 lane numbers below are formed here, not kept over the loop
     asm volatile("" : "+v"(row_lane));
@@ -31,8 +31,10 @@ __device__ inline void tile_add_checkpoint(const f32x16 (&acc)[WR][WC], float un
         for (int v = 0; v < 16; ++v) {
             const float rt = __shfl(rt_lane[b >> 1], 32 * (b & 1) + 8 * (v >> 2) + row_lane + (v & 3), 64);
 #pragma unroll
-            for (int c = 0; c < WC; ++c)
-                facc[b][c][v] = __fadd_rn(facc[b][c][v], __fmul_rn(__fmul_rn(unit == 1.0f ? acc[b][c][v] : unit * acc[b][c][v], rt), wv[c]));
+            for (int c = 0; c < WC; ++c) {
+                const float D = unit == 1.0f ? (float)acc[b][c][v] : unit * (float)acc[b][c][v];
+                facc[b][c][v] = __fadd_rn(facc[b][c][v], __fmul_rn(__fmul_rn(D, rt), wv[c]));
+            }
         }
 }
 

@@ -8,32 +8,28 @@
 //   * Tiles of 192 x 256, 256 x 192, 256 x 128 or 512 x 96 (train x validation), eight wavefronts of 96 x 64,
 //     64 x 96 or 64 x 64: the fp32 checkpoint sums and the accumulators of a larger tile do not fit in
 //     registers next to each other.  choose_shape() picks by padded work.
-//   * A stage is 128 bytes (a whole cache line) of every train and validation row of the tile, copied
-//     global -> LDS asynchronously into a ring of two or three stages.  The pre-pass lays the validation rows out
-//     stage by stage as they lie in LDS, so their copies are linear.
-//   * One barrier per stage, between the matrix instructions of its last K step: everything of the stage is in
-//     registers by then, so the copies of the stage after the ring and the operand reads of the next stage
-//     start behind it while the remaining instructions run, and no wavefront waits for its first operands
-//     after a barrier (the kernel before: barrier, then reads, then instructions).
-//   * Every matrix instruction is followed by one operand read or copy of the next K step.
-//   * 16-byte chunk c of row r lies at position c ^ ((r / 2) % 8): 16 consecutive rows read together use all 64
-//     banks (c ^ (r % 8), conflict-free for 32 banks, cost 5 %).
-// Measured, same card, N = 270 000, k = 8192, C = 4 (before -> now): 8 bits, M = 1024: 10.0 -> 8.5 ms; bfloat16 65536 x 512:
-// 2.51 -> 2.15 ms.
-#include "score.h"
+//   * Two rings, as in score_codes.hip: lines (128 bytes) of every train row in a ring of three (512 rows: two), half lines of every
+//     validation row in a ring of three; the pre-pass lays the validation rows out in the order in which the lanes read them.  One ring
+//     of two whole-line stages of both had every copy start behind one barrier and land before the next.
+//   * One barrier per half line, behind the second matrix instruction of its last K step: everything of the half line is in
+//     registers by then.  Validation fragments are requested again as soon as their last instruction is issued, train fragments
+//     of the next K step go to registers of their own.
+// Measured, same card, k = 8192, C = 4 (one ring of whole-line stages, row maxima by shuffles -> now): 8 bits, N = 270 000, M = 1024 8.63 -> 7.86 ms,
+// M = 285 3.43 -> 3.19; 30 000 x 285 x 3, k = 4160 184 -> 155 us; bfloat16 65 536 x 512 2.16 -> 2.02 ms, 65 536 x 285, k = 4096 848 -> 750 us.
+// Rings of four half lines: the same.
+#include "score_tile.h"
 
 namespace qless {
 
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(16))) int i32x16;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 
 struct WidePrep {                              // workspace views (device pointers)
-    unsigned char *vexp;                       // [C][val tile][stage][VT rows x 128 bytes], zero past the rows and their ends
+    unsigned char *vexp;                       // [C][val tile][half line][2 K steps][2 halves][VT rows][16 bytes], zero past the rows and their ends
     float *vw;                                 // [C][Mp] eta * rnorm'
     unsigned int *smax;                        // [N] order-preserving keys of the row maxima
-    int32_t Mp, cb, nst;                       // padded validation rows, bytes per row, stages per row
+    int32_t Mp, cb, nst;                       // padded validation rows, bytes and lines per row
 };
 
 template <bool BF16> struct WideAcc { typedef i32x16 type; };
@@ -47,72 +43,63 @@ __device__ inline f32x16 wide_mma<true>(i32x4 a, i32x4 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
 }
 
-// One workgroup per (padded validation row, checkpoint); the first checkpoint's also clear the row-maximum keys.
+// grid (32 padded validation rows, checkpoint, part of the row): a thread takes one row's 16-byte chunks j, j + 8, .. of the part; the first
+// checkpoint's workgroups clear the row-maximum keys.
 __global__ void __launch_bounds__(256)
 score_wide_prepare_kernel(ScoreArgs a, WidePrep w, int VT, int bf16) {
-    const int row = blockIdx.x, ci = blockIdx.y, vt = row / VT, r = row % VT;
-    unsigned char *dst = w.vexp + ((size_t)ci * w.Mp + (size_t)vt * VT) * (size_t)w.nst * 128 + (size_t)r * 128;
+    const int ci = blockIdx.y, rl = threadIdx.x & 31, j = threadIdx.x >> 5, row = (int)blockIdx.x * 32 + rl, r = row % VT;
+    // chunk t: half line t / 4; 2 * (K step) + half = t % 4
+    unsigned char *dst = w.vexp + ((size_t)ci * w.Mp + row - r) * (size_t)w.nst * 128;
     const unsigned char *src = a.vc[ci] + (int64_t)(row < a.M ? row : 0) * w.cb;
-    for (int t = threadIdx.x; t < w.nst * 8; t += 256) {
-        const int st = t >> 3, c = t & 7;
+    const int chunks = w.cb / 16, per = (w.nst + (int)gridDim.z - 1) / (int)gridDim.z * 8, t0 = (int)blockIdx.z * per;
+    for (int t = t0 + j; t < t0 + per && t < w.nst * 8; t += 8) {
         uint4 v = make_uint4(0, 0, 0, 0);
-        if (row < a.M && st * 128 + c * 16 < w.cb) v = *(const uint4 *)(src + st * 128 + c * 16);
-        *(uint4 *)(dst + (size_t)st * VT * 128 + ((c ^ ((r >> 1) & 7)) << 4)) = v;
+        if (row < a.M && t < chunks) v = *(const uint4 *)(src + t * 16);
+        *(uint4 *)(dst + ((size_t)t * VT + r) * 16) = v;
     }
-    if (threadIdx.x == 0) w.vw[ci * w.Mp + row] = row < a.M ? (bf16 ? a.eta[ci] : __fmul_rn(a.eta[ci], a.vr[ci][row])) : 0.0f;
+    if (blockIdx.z == 0 && j == 0) w.vw[ci * w.Mp + row] = row < a.M ? (bf16 ? a.eta[ci] : __fmul_rn(a.eta[ci], a.vr[ci][row])) : 0.0f;
     if (ci == 0) {
-        const int64_t per = (a.N + gridDim.x - 1) / gridDim.x, lo = (int64_t)row * per;
-        for (int64_t i = lo + threadIdx.x; i < lo + per && i < a.N; i += 256) w.smax[i] = 0u;
+        const int64_t groups = (int64_t)gridDim.x * gridDim.z, g = (int64_t)blockIdx.z * gridDim.x + blockIdx.x;
+        const int64_t share = (a.N + groups - 1) / groups, lo = g * share;
+        for (int64_t i = lo + threadIdx.x; i < lo + share && i < a.N; i += 256) w.smax[i] = 0u;
     }
 }
 
 // A wavefront owns WR x WC accumulators of 32 x 32, WY x WX wavefronts make a tile of 32 WR WY train rows x 32 WC WX
-// validation rows; NBUF stages in the ring.
-template <int BITS_, int WR_, int WC_, int WY_, int WX_, int NBUF_>
+// validation rows; NT lines of train rows and NV half lines of validation rows in the rings.
+template <int BITS_, int WR_, int WC_, int WY_, int WX_, int NT_, int NV_>
 struct WideShape {
-    static constexpr int BITS = BITS_, WR = WR_, WC = WC_, WY = WY_, WX = WX_, NBUF = NBUF_, NW = WY * WX;
+    static constexpr int BITS = BITS_, WR = WR_, WC = WC_, WY = WY_, WX = WX_, NT = NT_, NV = NV_, NW = WY * WX;
     static constexpr int MT = 32 * WR * WY, VT = 32 * WC * WX;
-    static constexpr int TBYTES = MT * 128, VBYTES = VT * 128, BUF = TBYTES + VBYTES;
-    static constexpr int TCP = TBYTES / 1024, VCP = VBYTES / 1024;              // 1 KB copies per stage
-    static constexpr int TU = (TCP + NW - 1) / NW, VU = (VCP + NW - 1) / NW, LPW = TU + VU;      // per wavefront
-    static_assert(TCP % NW == 0, "a copy's parity follows from its number");
-    static constexpr int LDS = NBUF * BUF;
-    static_assert(NBUF >= 2 && LDS + 4 * MT <= (int)kLdsPerCU, "the ring and the row maxima fit in LDS");
-    static_assert((NBUF - 1) * LPW < 64, "vmcnt is a 6-bit counter");
+    static constexpr int TBYTES = MT * 128, VBYTES = VT * 64;
+    static constexpr int TCP = TBYTES / 1024, VCP = VBYTES / 1024;              // 1 KB copies
+    static constexpr int TU = TCP / NW, VU = (VCP + NW - 1) / NW;               // per wavefront
+    static constexpr int LDS = NT * TBYTES + NV * VBYTES;
+    static_assert(TCP % NW == 0 && VBYTES % 1024 == 0, "whole copies");
+    static_assert((NT == 2 || NT == 3) && NV >= 3 && LDS + 4 * MT <= (int)kLdsPerCU, "the rings and the row maxima fit in LDS");
+    static_assert((NV - 1) * VU + 2 * TU < 64, "vmcnt is a 6-bit counter");
 };
 
-// Where the copies of train rows read, in bytes from the tile's first row (and the stage's 128 q bytes into it): copy q takes
-// rows 8 q + lane / 8, chunk (lane % 8) ^ ((row / 2) % 8).
-//   wide_lane_offset     the lane's part beside the wave-uniform 8 q cb.  Chunks past a row's end read on into the rows
-//                        after it (the validation bytes there are zero).
-//   wide_reads_past      whether that leaves the store: its last rows are shorter than a stage, and one row of 32 bytes
-//                        (4 bits, k = 64) reaches three rows on, so this can be the tile before the last one as well.
-//   wide_clamped_offset  for such tiles: rows past N re-read the last row (masked later), chunks past the row end its last
-//                        16 bytes.  over: bytes of this stage past the end of a row.
-__host__ __device__ inline unsigned wide_lane_offset(unsigned lane, int q, int cb) {
-    return (lane >> 3) * (unsigned)cb + (((lane & 7) ^ ((4u * (unsigned)q + (lane >> 4)) & 7)) << 4);
-}
-__host__ __device__ inline bool wide_reads_past(int64_t row0, int MT, int64_t N, int cb, int nst) {
-    return (row0 + MT - 1) * cb + (int64_t)nst * 128 > N * cb;
-}
-__host__ __device__ inline unsigned wide_clamped_offset(unsigned lane, int q, int64_t row0, int64_t N, int cb, int over) {
-    const int64_t r = row0 + q * 8 + (int)(lane >> 3), gr = r < N ? r : N - 1;
-    int at = (int)(((lane & 7) ^ ((4u * (unsigned)q + (lane >> 4)) & 7)) << 4);
-    if (over > 0 && at > 112 - over) at = 112 - over;
-    return (unsigned)((gr - row0) * cb) + (unsigned)at;
+// Where the copies of train rows read, in bytes from the tile's first row (and the line's 128 bytes into it): copy q takes rows
+// 8 q + lane / 8, of each the chunk (lane % 8) ^ ((row / 2) % 8): 16 consecutive rows read together use all 64 banks.  EDGE: rows past
+// `last_row` re-read that one (masked later), chunks past `last_chunk` bytes re-read that one (the validation bytes there are zero).
+template <bool EDGE>
+__host__ __device__ inline unsigned wide_offset(unsigned lane, int q, int cb, unsigned last_row, unsigned last_chunk) {
+    unsigned row = (lane >> 3) * (unsigned)cb + 8u * (unsigned)q * (unsigned)cb, at = ((lane & 7) ^ ((4u * (unsigned)q + (lane >> 4)) & 7)) << 4;
+    if (EDGE) { row = row < last_row ? row : last_row; at = at < last_chunk ? at : last_chunk; }
+    return row + at;
 }
 
 // EDGE = false: every tile has MT rows that exist (the last one starts at N - MT and repeats rows of the tile before
-// it, with the same results) and rows are whole stages.  EDGE = true: fewer train rows than a tile, or rows that
-// end inside a stage, whose last tiles may not read past the store; the branch this takes per copy costs 10 % in the
-// 256 x 128 shape (2.42 against 2.20 ms, bfloat16 65536 x 512).
+// it, with the same results) and rows are whole lines.  EDGE = true: fewer train rows than a tile, or rows that
+// end inside a line.  The straight-line stage: see score_codes_kernel.
 template <class Sh, bool EDGE>
 __global__ void __launch_bounds__(64 * Sh::NW, Sh::NW / 4)
 score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
     constexpr bool BF16 = Sh::BITS == 16;
-    constexpr int WR = Sh::WR, WC = Sh::WC, WX = Sh::WX, NBUF = Sh::NBUF, NW = Sh::NW, MT = Sh::MT, VT = Sh::VT;
-    constexpr int TBYTES = Sh::TBYTES, VBYTES = Sh::VBYTES, BUF = Sh::BUF, VCP = Sh::VCP, TU = Sh::TU, VU = Sh::VU, LPW = Sh::LPW;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    constexpr int WR = Sh::WR, WC = Sh::WC, WX = Sh::WX, NT = Sh::NT, NV = Sh::NV, NW = Sh::NW, MT = Sh::MT, VT = Sh::VT;
+    constexpr int TBYTES = Sh::TBYTES, VBYTES = Sh::VBYTES, VCP = Sh::VCP, TU = Sh::TU, VU = Sh::VU;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];        // [NT][TBYTES], [NV][VBYTES]
     __shared__ unsigned int s_rowmax[MT];
     // XCD-aware decode: the vtiles workgroups of one train tile get ids 8 apart (same XCD, same L2)
     const int64_t id = blockIdx.x, jj = id >> 3;
@@ -126,55 +113,70 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
     for (int i = tid; i < MT; i += 64 * NW) s_rowmax[i] = 0u;
     const unsigned lds0 = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)smem);
 
-    // ---- copies, 1 KB each: TU of train rows (8 rows x 128 bytes) and VU of validation rows (linear) per wavefront and
-    // stage; past the end of the validation side a wavefront repeats its last copy, so that all count the same number.
-    // The address is a wave-uniform base plus a lane part that the copies share: the tiles fill the register file,
-    // and a spilled register is read back through the same counter as the copies.
-    const int T = a.C * w.nst;                            // stages of all checkpoints, one pipeline
-    const int over = EDGE ? w.nst * 128 - w.cb : 0;       // bytes of the last stage past the end of a train row
-    const bool clamped = EDGE && wide_reads_past(row0, MT, a.N, w.cb, w.nst);
-    const int q0 = wave * TU, v0 = wave * VU < VCP ? wave * VU : VCP - 1;     // first copy of either side
-    unsigned train_lane[2];                               // of copies of even and odd distance from q0
+    // ---- copies: TU of a line of train rows, VU of half a line's validation rows (linear) per wavefront; past the end of the
+    // validation side a wavefront repeats its last copy, so that all count the same number
+    const int nst = w.nst, T = a.C * nst;                 // lines per row, and of all checkpoints
+    const int over = nst * 128 - w.cb;                    // bytes of the last line past the end of a train row
+    const unsigned last_row = EDGE ? (unsigned)((a.N - 1 - row0 < MT ? a.N - 1 - row0 : MT) * w.cb) : 0u;
+    const int q0 = wave * TU;
+    unsigned train_lane[2];                               // of copies of even and odd distance from q0, beside the wave-uniform 8 q cb
 #pragma unroll
-    for (int e = 0; e < 2; ++e) train_lane[e] = wide_lane_offset((unsigned)lane, q0 + e, w.cb);
+    for (int e = 0; e < 2; ++e) train_lane[e] = wide_offset<false>((unsigned)lane, q0 + e, w.cb, 0, 0) - 8u * (unsigned)(q0 + e) * (unsigned)w.cb;
     const unsigned val_lane = (unsigned)(lane * 16);
-    int i_it = 0, i_ci = 0, i_s = 0, i_buf = 0;           // the next stage to request
-    const unsigned char *tb = a.tc[0] + row0 * w.cb;
-    const unsigned char *vb = w.vexp + (size_t)vt * w.nst * VBYTES;
-    auto copy = [&](int u) {
-        if (u >= TU) {
-            const int q = v0 + u - TU < VCP ? v0 + u - TU : VCP - 1;
-            global_to_lds16(vb + q * 1024, val_lane, lds0 + (unsigned)(i_buf * BUF + TBYTES + q * 1024));
-            return;
-        }
+    // the checkpoints' train rows: lane i holds the tile's first row of checkpoint i
+    const uint64_t tile_row = (uint64_t)(a.tc[lane < a.C ? lane : 0] + row0 * w.cb);
+    auto train_of = [&](int ci) {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)tile_row, ci);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(tile_row >> 32), ci);
+        return (const unsigned char *)(((uint64_t)hi << 32) | lo);
+    };
+    int t_it = 0, t_ci = 0, t_s = 0, t_slot = 0;          // the next line of train rows to request
+    int v_it = 0, v_s = 0, v_slot = 0;                    // and the next half line of validation rows
+    const unsigned char *tb = train_of(0);
+    const unsigned char *vb = w.vexp + (size_t)vt * (2 * nst) * VBYTES;
+    const size_t v_wrap = (size_t)(vtiles - 1) * (2 * nst) * VBYTES;
+    auto copy_train = [&](int u) {
         const int q = q0 + u;
-        const unsigned lds = lds0 + (unsigned)(i_buf * BUF + q * 1024);
-        if (!clamped) {
-            global_to_lds16(tb + (unsigned)(q * 8 * w.cb), train_lane[u & 1], lds);
-        } else {
-            unsigned l = (unsigned)lane;                  // opaque, so that this stays in its branch
+        const unsigned lds = lds0 + (unsigned)(t_slot * TBYTES + q * 1024);
+        if (EDGE) {
+            unsigned l = (unsigned)lane;                  // opaque: formed here, not kept in a register per copy
             asm volatile("" : "+v"(l));
-            global_to_lds16(tb, wide_clamped_offset(l, q, row0, a.N, w.cb, i_s == w.nst - 1 ? over : 0), lds);
+            global_to_lds16(tb, wide_offset<true>(l, q, w.cb, last_row, t_s == nst - 1 ? (unsigned)(112 - over) : 112u), lds);
+        } else {
+            global_to_lds16(tb + (unsigned)(q * 8 * w.cb), train_lane[u & 1], lds);
         }
     };
-    auto copy_next = [&]() {
-        tb += 128; vb += VBYTES; ++i_it;
-        if (++i_buf == NBUF) i_buf = 0;
-        if (++i_s == w.nst) {
-            i_s = 0;
-            if (++i_ci < a.C) { tb = a.tc[i_ci] + row0 * w.cb; vb = w.vexp + ((size_t)i_ci * vtiles + vt) * (size_t)w.nst * VBYTES; }
-        }
+    auto copy_val = [&](int u) {
+        const int at = wave * VU + u, q = VCP % (NW * VU) == 0 || at < VCP ? at : VCP - 1;
+        global_to_lds16(vb + q * 1024, val_lane, lds0 + (unsigned)(NT * TBYTES + v_slot * VBYTES + q * 1024));
+    };
+    auto next_train = [&]() {
+        const bool end = t_it + 1 >= T, wrap = !end && t_s + 1 == nst;
+        t_ci += wrap ? 1 : 0;
+        const unsigned char *first = train_of(t_ci);
+        tb = wrap ? first : tb + (end ? 0 : 128);
+        t_s = wrap ? 0 : t_s + (end ? 0 : 1);
+        ++t_it;
+        t_slot = t_slot + 1 == NT ? 0 : t_slot + 1;
+    };
+    auto next_val = [&]() {
+        const bool end = v_it + 1 >= 2 * T, wrap = !end && v_s + 1 == 2 * nst;
+        vb += (end ? 0 : VBYTES) + (wrap ? v_wrap : 0);
+        v_s = wrap ? 0 : v_s + (end ? 0 : 1);
+        ++v_it;
+        v_slot = v_slot + 1 == NV ? 0 : v_slot + 1;
     };
 
-    // ---- operand reads: the lane (row l32, half) takes chunk 2 ks + half; both sides share the lane's part of the address
-    const unsigned lane_base = (unsigned)(l32 * 128 + ((half ^ ((l32 >> 1) & 7)) << 4));
-    const unsigned a_base = (unsigned)(trow * 128), b_base = (unsigned)(TBYTES + vcol * 128);        // wave-uniform
-    i32x4 fa[WR], fb[2][WC];
-    auto load_a = [&](int b, int buf, int ks) {
-        fa[b] = *(const i32x4 *)(smem + ((lane_base ^ (ks << 5)) + (unsigned)(buf * BUF) + a_base) + b * 4096);
+    // ---- operands.  Train: the lane (row l32, half) takes chunk 2 * (K step of the line) + half; validation: 16 bytes at
+    // [K step of the half line][half][row].
+    const unsigned a_lane = (unsigned)(l32 * 128 + ((half ^ ((l32 >> 1) & 7)) << 4)), a_base = (unsigned)(trow * 128);
+    const unsigned b_lane = (unsigned)((half * VT + vcol + l32) * 16);
+    i32x4 fa[2][WR], fb[WC];
+    auto load_a = [&](int set, int b, int slot, int ks) {
+        fa[set][b] = *(const i32x4 *)(smem + (a_lane ^ (unsigned)(ks << 5)) + (unsigned)(slot * TBYTES) + a_base + b * 4096);
     };
-    auto load_b = [&](int c, int slot, int buf, int ks) {
-        fb[slot][c] = *(const i32x4 *)(smem + ((lane_base ^ (ks << 5)) + (unsigned)(buf * BUF) + b_base) + c * 4096);
+    auto load_b = [&](int c, int slot, int ks) {
+        fb[c] = *(const i32x4 *)(smem + NT * TBYTES + (unsigned)(slot * VBYTES) + b_lane + (2 * ks * VT + 32 * c) * 16);
     };
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };   // keeps the order below
 
@@ -186,19 +188,26 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) facc[b][c][v] = 0.0f;
 
-    for (int i = 0; i < NBUF && i < T; ++i) {
+    // The first requests, in the order in which the loop goes on: at the barrier of half line h validation rows h + NV, behind them
+    // (odd h) the line of train rows NT lines on from the one that is done.
+    for (int i = 0; i < NT; ++i) {
+        if (i == NT - 1)
+            for (int j = 0; j < NV; ++j) {
 #pragma unroll
-        for (int u = 0; u < LPW; ++u) copy(u);
-        copy_next();
+                for (int u = 0; u < VU; ++u) copy_val(u);
+                next_val();
+            }
+#pragma unroll
+        for (int u = 0; u < TU; ++u) copy_train(u);
+        next_train();
     }
-    if (NBUF <= T) wait_vmcnt<(NBUF - 1) * LPW>(); else wait_vmcnt<0>();
+    wait_vmcnt<(NV - 1) * VU + TU>();                     // the first line and half line
     __syncthreads();
 #pragma unroll
-    for (int c = 0; c < WC; ++c) load_b(c, 0, 0, 0);
+    for (int c = 0; c < WC; ++c) load_b(c, 0, 0);
 #pragma unroll
-    for (int b = 0; b < WR; ++b) load_a(b, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);                   // lgkmcnt(0): no read is outstanding at the head of the loop
-    int buf = 0, g = 0;
+    for (int b = 0; b < WR; ++b) load_a(0, b, 0, 0);
+    int tslot = 0, vslot = 0;
     for (int ci = 0; ci < a.C; ++ci) {
         typename WideAcc<BF16>::type acc[WR][WC];
 #pragma unroll
@@ -207,106 +216,52 @@ score_wide_kernel(ScoreArgs a, WidePrep w, int64_t ttiles, int vtiles) {
             for (int c = 0; c < WC; ++c)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[b][c][v] = 0;
-        for (int s = 0; s < w.nst; ++s, ++g) {
-            const int next = buf + 1 == NBUF ? 0 : buf + 1;
-            const bool more = g + 1 < T, refill = i_it < T;
-            // K step ks multiplies what the step before read; the train fragment of a row block is re-read as soon as
-            // its instructions are issued.  In the last step the stage's buffer has been read completely
-            // after the first instructions: there the barrier, and behind it the next stage's reads and the
-            // copies into the buffer.
+        for (int s = 0; s < nst; ++s) {
+            const int tnext = tslot + 1 == NT ? 0 : tslot + 1;
+            // Column block by column block: a validation fragment is requested again (for the next K step) as soon as its last
+            // instruction is issued; the train fragments of the next K step go to registers of their own.
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) {
-                const int cur = ks & 1, nxt = cur ^ 1;
-                const int lbuf = ks < 3 ? buf : next, lks = (ks + 1) & 3;
-                constexpr int K0 = WC - 1;                                      // instruction of the last step before the barrier
-                constexpr int SLOTS = WR * WC - K0;                             // instructions the copies are spread over
+            for (int k4 = 0; k4 < 4; ++k4) {                                    // K steps of the line: h = k4 / 2 the half line
+                const int h = k4 >> 1, cur = k4 & 1;
+                const bool last = k4 & 1;                                       // of its half line
+                const int vnext = vslot + 1 == NV ? 0 : vslot + 1;
+                const int rt = k4 == 3 ? tnext : tslot, rv = last ? vnext : vslot, ra = (k4 + 1) & 3, rb = last ? 0 : 1;   // the next K step's
+                constexpr int I = WR * WC, K0 = 1;                              // instructions of a K step; the last one's before the barrier
 #pragma unroll
-                for (int b = 0; b < WR; ++b) {
-#pragma unroll
-                    for (int c = 0; c < WC; ++c) {
-                        pin();
-                        acc[b][c] = wide_mma<BF16>(fa[b], fb[cur][c], acc[b][c]);
-                        pin();
-                        if (ks < 3 && b == 0) load_b(c, nxt, lbuf, lks);
-                        const int i = b * WC + c;
-                        if (ks == 3 && more && i >= K0) {
-                            if (i == K0) {
-                                // this wavefront's reads of the stage have returned and its share of the next
-                                // stage has landed; the barrier says so of all wavefronts
-                                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                                if (refill) wait_vmcnt<(NBUF - 2) * LPW>(); else wait_vmcnt<0>();
-                                __builtin_amdgcn_s_barrier();
-                                asm volatile("" ::: "memory");
-                                pin();
-#pragma unroll
-                                for (int q = 0; q < WC; ++q) load_b(q, nxt, lbuf, lks);
-                                pin();
-                            }
-                            if (refill) {
-#pragma unroll
-                                for (int u = 0; u < LPW; ++u)
-                                    if (u * SLOTS / LPW == i - K0) copy(u);
-                            }
-                        }
-                    }
+                for (int i = 0; i < I; ++i) {
+                    const int c = i / WR, b = i % WR;
                     pin();
-                    if (ks < 3 || more) load_a(b, lbuf, lks);
+                    acc[b][c] = wide_mma<BF16>(fa[cur][b], fb[c], acc[b][c]);
+                    asm volatile("" : "+v"(acc[b][c]) :: "memory");              // stays here, between the reads before and behind it
+                    pin();
+                    if (last && i == K0) {
+                        // this wavefront's reads of the half line (and line) have returned and its share of the next one has
+                        // landed; the barrier says so of all wavefronts.  Younger: validation rows of the half lines after it and,
+                        // with three lines in the ring or none needed now, a line of train rows.
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        if (h == 0 || NT == 3) wait_vmcnt<(NV - 2) * VU + TU>(); else wait_vmcnt<VU>();
+                        __builtin_amdgcn_s_barrier();
+                        asm volatile("" ::: "memory");
+                        pin();
+                    }
+                    if (last ? i >= K0 && i < K0 + WR : i < WR) load_a(cur ^ 1, last ? i - K0 : i, rt, ra);
+                    if (b == WR - 1) load_b(c, rv, rb);
+                    if (last && i >= K0) {
+                        const int n = VU + (h == 1 ? TU : 0);                   // copies, spread over the instructions behind the barrier
+#pragma unroll
+                        for (int u = 0; u < VU + TU; ++u)
+                            if (u < n && u * (I - K0) / n == i - K0) { if (u < VU) copy_val(u); else copy_train(u - VU); }
+                    }
                 }
+                if (last) { next_val(); vslot = vnext; }
             }
-            if (refill) copy_next();
-            pin();
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            pin();
-            buf = next;
+            next_train();
+            tslot = tnext;
         }
-        // checkpoint epilogue.  acc[b][c][v]: train row 32 b + 8 (v / 4) + 4 half + v % 4, val column 32 c + l32.
-        // Lane L holds rnorm of train rows trow + L and trow + 64 + L; rows are fetched by shuffle.
-        float rt_lane[(WR + 1) / 2];
-#pragma unroll
-        for (int q = 0; q < (WR + 1) / 2; ++q) {
-            int64_t r = row0 + trow + 64 * q + lane;
-            if (r > a.N - 1) r = a.N - 1;
-            rt_lane[q] = (BF16 && !a.tr[ci]) ? 1.0f : a.tr[ci][r];
-        }
-        int row_lane = 4 * half;                          // opaque: the 16 lane numbers below are formed here, not kept over the loop
-        asm volatile("" : "+v"(row_lane));
-        float wv[WC];
-#pragma unroll
-        for (int c = 0; c < WC; ++c) wv[c] = w.vw[ci * w.Mp + vt * VT + vcol + 32 * c + l32];
-#pragma unroll
-        for (int b = 0; b < WR; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float rt = __shfl(rt_lane[b >> 1], 32 * (b & 1) + 8 * (v >> 2) + row_lane + (v & 3), 64);
-#pragma unroll
-                for (int c = 0; c < WC; ++c) {
-                    const float D = (float)acc[b][c][v];
-                    facc[b][c][v] = __fadd_rn(facc[b][c][v], __fmul_rn(__fmul_rn(D, rt), wv[c]));
-                }
-            }
+        tile_add_checkpoint<WR, WC>(acc, 1.0f, a.tr[ci], row0 + trow, a.N, w.vw + ci * w.Mp + vt * VT + vcol, facc);
     }
-    // tile epilogue: optional full matrix, row maxima over this val tile
-#pragma unroll
-    for (int b = 0; b < WR; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int rloc = trow + 32 * b + 8 * (v >> 2) + 4 * half + (v & 3);
-            const int64_t r = row0 + rloc;
-            float m = neg_inf();
-#pragma unroll
-            for (int c = 0; c < WC; ++c) {
-                const int col = vt * VT + vcol + 32 * c + l32;
-                if (col < a.M) {
-                    m = fmaxf(m, facc[b][c][v]);
-                    if (a.full && r < a.N) a.full[r * a.M + col] = facc[b][c][v];
-                }
-            }
-            if (a.score) {
-#pragma unroll
-                for (int o = 16; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-                if (l32 == 0 && m > neg_inf()) atomicMax(&s_rowmax[rloc], f32_order_key(m));
-            }
-        }
+    wait_vmcnt<0>();                                      // no copy is under way when the workgroup gives its LDS back
+    tile_finish<WR, WC>(a, facc, row0, trow, vt * VT + vcol, s_rowmax);
     if (a.score) {
         __syncthreads();
         for (int i = tid; i < MT; i += 64 * NW)
@@ -336,8 +291,12 @@ static qless_status launch_wide_shape(const ScoreArgs &a, WidePrep w, bool prepa
     const int vtiles = w.Mp / Sh::VT;
     const int64_t ttiles = (a.N + Sh::MT - 1) / Sh::MT, grid = 8 * (int64_t)vtiles * ((ttiles + 7) / 8);
     if (grid > 0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
-    if (prepare)
-        hipLaunchKernelGGL(score_wide_prepare_kernel, dim3((unsigned)w.Mp, (unsigned)a.C), dim3(256), 0, st, a, w, Sh::VT, Sh::BITS == 16);
+    if (prepare) {
+        const unsigned rows32 = (unsigned)(w.Mp / 32);
+        unsigned parts = (512 + rows32 * (unsigned)a.C - 1) / (rows32 * (unsigned)a.C);      // two workgroups per compute unit
+        if (parts > (unsigned)w.nst) parts = (unsigned)w.nst;
+        hipLaunchKernelGGL(score_wide_prepare_kernel, dim3(rows32, (unsigned)a.C, parts), dim3(256), 0, st, a, w, Sh::VT, Sh::BITS == 16);
+    }
     if (a.N >= Sh::MT && w.cb % 128 == 0)
         hipLaunchKernelGGL((score_wide_kernel<Sh, false>), dim3((unsigned)grid), dim3(64 * Sh::NW), Sh::LDS, st, a, w, ttiles, vtiles);
     else
@@ -346,30 +305,37 @@ static qless_status launch_wide_shape(const ScoreArgs &a, WidePrep w, bool prepa
 }
 
 // The shape with the least padded work: rounds of one workgroup per compute unit, times the tile's pairs, times what a
-// pair costs in the shape (measured at N = 270 000, M = 285 and 1024, relative to the 96 x 64 wavefronts:
-// 256 x 128 6 %, 512 x 96 16 % more per pair -- more operand bytes per product).  The validation tiles of a train tile run
+// pair costs in the shape: 8 bits as measured with the kernel before this one (N = 270 000, M = 285 and 1024; 98 304 x 768 now takes 1103, 1129,
+// 1235 and 1314 us, relative to the padded pairs 1.00, 1.02, 1.12 and 1.19), bfloat16 65 536 x 512 and 98 304 x 768 (2020, 2153, 2136, 2561 and
+// 1066, 1092, 1193, 1292 us).  The validation tiles of a train tile run
 // on one XCD, so the rounds are those of the XCD with the most train tiles: 25 316 x 773 in tiles of 256 x 192 is 495
-// workgroups, but 65 of them on three of the XCDs, a third round (6016 codes of 4 bits: 202 us; 256 x 128: 169).
-static int choose_shape(int64_t N, int32_t M) {
-    static const struct { int mt, vt; double cost; } s[4] = {{192, 256, 1.0}, {256, 192, 1.0}, {256, 128, 1.06}, {512, 96, 1.16}};
+// workgroups, but 65 of them on three of the XCDs, a third round.
+static int choose_shape(int64_t N, int32_t M, bool bf16) {
+    static const struct { int mt, vt; double cost[2]; } s[4] = {{192, 256, {1.0, 1.0}}, {256, 192, {1.0, 1.03}}, {256, 128, {1.06, 1.14}}, {512, 96, {1.16, 1.22}}};
     const int64_t cus = (compute_units() + 7) / 8;                   // per XCD
     int best = 0;
     double least = 0;
     for (int i = 0; i < 4; ++i) {
         const int64_t ttiles = (N + s[i].mt - 1) / s[i].mt, tiles = (ttiles + 7) / 8 * ((M + s[i].vt - 1) / s[i].vt);
-        const double c = (double)((tiles + cus - 1) / cus) * s[i].mt * s[i].vt * s[i].cost;
+        const double c = (double)((tiles + cus - 1) / cus) * s[i].mt * s[i].vt * s[i].cost[bf16];
         if (i == 0 || c < least) { best = i; least = c; }
     }
     return best;
 }
 
+template <int BITS> struct Wide {
+    typedef WideShape<BITS, 3, 2, 2, 4, 3, 3> T192x256;
+    typedef WideShape<BITS, 2, 3, 4, 2, 3, 3> T256x192;
+    typedef WideShape<BITS, 2, 2, 4, 2, 3, 3> T256x128;
+    typedef WideShape<BITS, 2, 3, 8, 1, 2, 3> T512x96;
+};
 template <int BITS>
 static qless_status launch_wide_bits(const ScoreArgs &a, const WidePrep &w, int shape, bool prepare, hipStream_t st) {
     switch (shape) {
-        case 0: return launch_wide_shape<WideShape<BITS, 3, 2, 2, 4, 2>>(a, w, prepare, st);
-        case 1: return launch_wide_shape<WideShape<BITS, 2, 3, 4, 2, 2>>(a, w, prepare, st);
-        case 2: return launch_wide_shape<WideShape<BITS, 2, 2, 4, 2, 3>>(a, w, prepare, st);
-        default: return launch_wide_shape<WideShape<BITS, 2, 3, 8, 1, 2>>(a, w, prepare, st);
+        case 0: return launch_wide_shape<typename Wide<BITS>::T192x256>(a, w, prepare, st);
+        case 1: return launch_wide_shape<typename Wide<BITS>::T256x192>(a, w, prepare, st);
+        case 2: return launch_wide_shape<typename Wide<BITS>::T256x128>(a, w, prepare, st);
+        default: return launch_wide_shape<typename Wide<BITS>::T512x96>(a, w, prepare, st);
     }
 }
 
@@ -382,7 +348,7 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
     wide_offsets(rows, a.M, w.cb, a.C, &off_vw, &off_smax, &total);
     unsigned char *base = (unsigned char *)ws;
     w.vexp = base; w.vw = (float *)(base + off_vw); w.smax = (unsigned int *)(base + off_smax);
-    const int shape = choose_shape(rows, a.M);            // of plan_rows: the pre-pass is laid out for it
+    const int shape = choose_shape(rows, a.M, bits == 16);            // of plan_rows: the pre-pass is laid out for it
     qless_status rc;
     if (bits == 16) rc = launch_wide_bits<16>(a, w, shape, prepare, st);
     else rc = launch_wide_bits<8>(a, w, shape, prepare, st);
@@ -391,25 +357,27 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
     return launch_status();
 }
 
-template <class Sh>
-static int64_t wide_reach(int64_t N, int cb) {
+template <class Sh, bool EDGE>
+static int64_t wide_reach_edge(int64_t N, int cb) {
+    constexpr int MT = Sh::MT;
     const int nst = (cb + 127) / 128, over = nst * 128 - cb;
-    const int64_t ttiles = (N + Sh::MT - 1) / Sh::MT;
-    const bool edge = !(N >= Sh::MT && cb % 128 == 0);
+    const int64_t ttiles = (N + MT - 1) / MT;
     int64_t most = 0;
     for (int64_t tt = ttiles > 3 ? ttiles - 3 : 0; tt < ttiles; ++tt) {
-        const int64_t row0 = edge || tt * Sh::MT + Sh::MT <= N ? tt * Sh::MT : N - Sh::MT;
-        const bool clamped = edge && wide_reads_past(row0, Sh::MT, N, cb, nst);
+        const int64_t row0 = EDGE || tt * MT + MT <= N ? tt * MT : N - MT;
+        const unsigned last_row = (unsigned)((N - 1 - row0 < MT ? N - 1 - row0 : MT) * cb);
         for (int s = 0; s < nst; ++s)
             for (int q = 0; q < Sh::TCP; ++q)
                 for (unsigned lane = 0; lane < 64; ++lane) {
-                    const int64_t off = clamped ? (int64_t)wide_clamped_offset(lane, q, row0, N, cb, s == nst - 1 ? over : 0)
-                                                : (int64_t)q * 8 * cb + wide_lane_offset(lane, q, cb);
-                    const int64_t end = row0 * cb + (int64_t)s * 128 + off + 16;
+                    const int64_t end = row0 * cb + (int64_t)s * 128 + 16 + wide_offset<EDGE>(lane, q, cb, last_row, (unsigned)(112 - (s == nst - 1 ? over : 0)));
                     most = end > most ? end : most;
                 }
     }
     return most;
+}
+template <class Sh>
+static int64_t wide_reach(int64_t N, int cb) {
+    return N >= Sh::MT && cb % 128 == 0 ? wide_reach_edge<Sh, false>(N, cb) : wide_reach_edge<Sh, true>(N, cb);
 }
 
 }  // namespace qless
@@ -419,12 +387,12 @@ static int64_t wide_reach(int64_t N, int cb) {
 extern "C" int64_t qless_internal_wide_reach(int64_t N, int row_bytes, int shape) {
     using namespace qless;
     switch (shape) {
-        case 0: return wide_reach<WideShape<8, 3, 2, 2, 4, 2>>(N, row_bytes);
-        case 1: return wide_reach<WideShape<8, 2, 3, 4, 2, 2>>(N, row_bytes);
-        case 2: return wide_reach<WideShape<8, 2, 2, 4, 2, 3>>(N, row_bytes);
-        default: return wide_reach<WideShape<8, 2, 3, 8, 1, 2>>(N, row_bytes);
+        case 0: return wide_reach<Wide<8>::T192x256>(N, row_bytes);
+        case 1: return wide_reach<Wide<8>::T256x192>(N, row_bytes);
+        case 2: return wide_reach<Wide<8>::T256x128>(N, row_bytes);
+        default: return wide_reach<Wide<8>::T512x96>(N, row_bytes);
     }
 }
 
-// For the tests, host only: the tile shape that a call with N train rows and M validation vectors takes.
-extern "C" int qless_internal_wide_shape(int64_t N, int32_t M) { return qless::choose_shape(N, M); }
+// For the tests, host only: the tile shape that a call of 8-bit codes with N train rows and M validation vectors takes.
+extern "C" int qless_internal_wide_shape(int64_t N, int32_t M) { return qless::choose_shape(N, M, false); }
