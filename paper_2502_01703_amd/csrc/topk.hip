@@ -3,22 +3,21 @@
 //
 // Every example gets a 64-bit key  (order-preserving image of the fp32 score) << 32 | (2^32-1 - index);
 // keys are distinct and "larger key" is exactly "selected earlier".  Steps:
-//   1. radix-select the k_sel-th largest key in passes of 8 bits (keys are formed on the fly from
-//   the scores); the passes stop as soon as the bucket that holds the k_sel-th key is selected as a
-//   whole.  Up to 16384 scores one workgroup does all (up to 8) passes in a single launch (a launch
-//   costs more than such a pass; beyond that size the ~50 instructions per key and pass are too
-//   many for one compute unit).  Above that, one histogram launch for each of the four digits of
-//   the score, whose workgroups each first pick the digit of the pass before from its finished
-//   histogram (a 256-bin scan, cheaper than a launch of its own); if the threshold score T is then
+//   1. find the k_sel-th largest score.  Up to 16384 scores one workgroup holds all of them in registers and does this and the
+//   compaction in a single launch (topk_select_one_kernel); above that, one histogram launch for each of the three digits (10, 11 and
+//   11 bits) of the score, whose workgroups each first pick the digit of the pass before from its finished
+//   histogram (a scan of its bins, cheaper than a launch of its own); the passes stop as soon as the bucket that holds the
+//   k_sel-th key is selected as a whole.  If the threshold score T is then
 //   shared by more examples than are still to be taken, the r with the smallest indices are the
 //   first r in array order: a count of the examples with score T per 1024 examples and the sum of the
 //   counts before them (taken by the compaction itself, above 4096 such groups by a scan launch) give
 //   every such example its position among them;
 //   2. compact all selected keys (exactly k_sel of them; one atomic per workgroup and 1024 examples);
 //   3. order them, descending: up to 16384 selected keys by rank (every key counts the larger ones
-//   among all of them, k_sel^2 comparisons spread over the whole chip, and is written to the slot of
-//   its rank: two short launches); above that, a bitonic network (LDS spans of 4096 keys with global
+//   among all of them, k_sel^2 comparisons spread over the whole chip, and its index and score go to the slot of
+//   its rank: one launch); above that, a bitonic network (LDS spans of 4096 keys with global
 //   steps in between), then  4. decode indices and gather the scores.
+// Latency is all there is to save: what a launch more costs is 3 to 5 us.
 #include "common.h"
 #include <atomic>
 #include <mutex>
@@ -27,12 +26,14 @@ namespace qless {
 
 constexpr int kSortBlock = 4096;   // keys sorted per workgroup in LDS (32 KB)
 constexpr int kSortOne = 16384;    // most (padded) selected keys that are ordered by rank instead of sorted
-constexpr int kPasses = 4;         // 8-bit digits of the score half of the keys (histogram launches)
-constexpr int64_t kSelectSmallMax = 16384;   // scores one workgroup selects from in a single launch (top 5 % of 32768: 41 us, by the launches 33)
+constexpr int kPasses = 3;         // digits of the score half of the keys (histogram launches; four digits of 8 bits were a launch more)
+constexpr int kDigitBits[kPasses] = {10, 11, 11}, kDigitShift[kPasses] = {54, 43, 32}, kHistAt[kPasses] = {0, 1024, 3072};
+constexpr int kHistBins = 5120;
+constexpr int64_t kSelectOneMax = 16384;     // scores one workgroup selects from in a single launch (top 5 % of 32768: 26 - 49 us, by the launches 26 - 30)
 
 struct TopkPlan {
     int64_t padded;                // power of two >= k_sel (>= kSortBlock)
-    size_t off_sel, off_hist, off_state, off_rank, off_ties, total;
+    size_t off_sel, off_hist, off_state, off_ties, total;
     int64_t chunks;                // groups of 1024 examples
 };
 
@@ -43,14 +44,15 @@ static TopkPlan topk_plan(int64_t N, int64_t k_sel) {
     p.padded = pad;
     size_t o = 0;
     p.off_sel = o;   o += (size_t)pad * 8;
-    p.off_hist = o;  o += kPasses * 256 * 4;        // one histogram per pass
-    p.off_state = o; o += (kPasses + 1) * 32 + 32;  // state before each pass and after the last; compaction cursor
-    p.off_rank = o;  o += (size_t)pad * 4;          // ranks of the selected keys
+    p.off_hist = o;  o += 4096 + (size_t)pad * 4;   // one histogram per pass, 20 480 bytes
+    p.off_state = o; o += 192;                      // state before each pass and after the last; compaction cursor
     p.chunks = (N + 1023) / 1024;
     p.off_ties = o;  o += (size_t)(p.chunks + 1) * 4;   // examples at the threshold score per 1024 examples
     p.total = o;
     return p;
 }
+
+static_assert(kHistBins * 4 <= 4096 + kSortBlock * 4, "the histograms' share of the workspace");
 
 struct SelectState {
     unsigned long long prefix;     // high digits of the threshold found so far
@@ -76,142 +78,216 @@ __global__ void __launch_bounds__(256) topk_init_kernel(unsigned int *hist, Sele
         state[0].prefix = 0; state[0].remaining = k_sel; state[0].count = 0; state[0].done = 0;
         state[kPasses].count = 0;
     }
-    for (int p = 0; p < kPasses; ++p) hist[p * 256 + threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < kHistBins; i += 256) hist[i] = 0;
 }
 
-// Suffix sums over 256 bins and the digit that holds the remaining rank `rem` (walking from the top):
-// thread d < 256 passes its bin count; the thread of the chosen digit returns true, with the rank
-// left inside that bin in `left`.  `above` is LDS scratch of 257 entries.  All threads of the
-// workgroup call it (barriers inside).
-__device__ inline bool pick_digit(unsigned long long *above, unsigned int mine, unsigned long long rem,
-                                  unsigned long long &left) {
-    const int d = (int)threadIdx.x;
-    if (d < 256) above[d] = mine;
-    if (d == 0) above[256] = 0;
+// The digit that holds the remaining rank `rem`, walking the B bins of a finished histogram from the top, in a workgroup of 256 threads.
+// The thread of that digit returns it, with the rank left inside its bin and the bin's count; the others return -1.  If no bin
+// reaches the rank the digit is 0.  `part` is LDS scratch of four entries.  All threads call it.
+template <int B>
+__device__ inline int pick_digit(const unsigned int *bins, unsigned long long *part, unsigned long long rem, unsigned long long &left, unsigned int &count) {
+    constexpr int P = B / 256;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, top = B - 1 - P * (int)threadIdx.x;      // thread 0 has the highest bins
+    unsigned int c[P];
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int q = 0; q < P; ++q) { c[q] = bins[top - q]; sum += c[q]; }
+    unsigned long long upto = sum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long below = __shfl_up(upto, o, 64);
+        if (lane >= o) upto += below;
+    }
+    if (lane == 63) part[wave] = upto;
     __syncthreads();
-    for (int step = 1; step < 256; step <<= 1) {    // Hillis-Steele
-        const unsigned long long add = (d < 256 && d + step < 256) ? above[d + step] : 0ull;
-        __syncthreads();
-        if (d < 256) above[d] += add;
-        __syncthreads();
+    for (int q = 0; q < wave; ++q) upto += part[q];
+    unsigned long long before = upto - sum;
+    const bool last = threadIdx.x == 255;
+    if (before >= rem || (upto < rem && !last)) return -1;
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+        if (before + c[q] >= rem || (last && q == P - 1)) { left = rem - before; count = c[q]; return top - q; }
+        before += c[q];
     }
-    // the digit is the largest d with above[d] >= rem; if no bin reaches the rank it is 0
-    bool here = false;
-    if (d < 256) {
-        here = (above[d] >= rem && above[d + 1] < rem) || (d == 0 && above[0] < rem);
-        if (here) left = rem - above[d + 1];
-    }
-    return here;
+    return -1;
 }
 
-// All passes of the selection in one workgroup (small N).  A wavefront adds the digit of its first
-// matching lane once for all lanes that share it (the leading digits of scores are few), the other
-// lanes add their own.
+// Inclusive sum over the threads of a 1024-thread workgroup; `part` is LDS scratch of 16 entries.  All threads call it.
+__device__ inline unsigned int block_scan(unsigned int v, unsigned int *part) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned int below = __shfl_up(v, o, 64);
+        if (lane >= o) v += below;
+    }
+    __syncthreads();                                    // part may still be read from the call before
+    if (lane == 63) part[wave] = v;
+    __syncthreads();
+    unsigned int base = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) base += q < wave ? part[q] : 0u;
+    return v + base;
+}
+
+// Selection and compaction in one workgroup: thread t holds the keys of scores t, t + 1024, .., U of them, in registers.  The range
+// of keys that holds the k_sel-th largest is cut into 2048 equal bins, counted in LDS, until a bin is taken as a whole or holds one value:
+// two or three rounds for the scores of a datastore, whose keys lie close together (their leading bits, which a radix select starts
+// with, are the same for nearly all of them, so its first passes count into a handful of bins).  A range over most of the 32 bits (infinities,
+// NaN, both signs) puts nearly all keys into a few bins again: there the lanes that share the first one's bin are added at once.
+// Bound: latency (top 5 % of 16384, 8192 and 4096 scores 28.4, 21.4 and 19.1 us with up to eight radix passes and the compaction, ranks and output in
+// launches of their own, now 17.5, 12.8 and 13.5; all scores equal 58 -> 27 us).
+template <int U>
 __global__ void __launch_bounds__(1024)
-topk_select_small_kernel(const float *score, int64_t N, unsigned long long k_sel, SelectState *state) {
-    __shared__ unsigned int h[256];
-    __shared__ unsigned long long above[257];
-    __shared__ unsigned long long sh_prefix, sh_rem;
-    __shared__ int sh_done;
-    const int lane = threadIdx.x & 63;
-    unsigned long long prefix = 0, rem = k_sel;
-    constexpr int kU = 8;
-    const int64_t n_up = (N + 1024 * kU - 1) / (1024 * kU) * (1024 * kU);
-    for (int pass = 0; pass < 8; ++pass) {              // all eight digits of the 64-bit keys
-        if (threadIdx.x < 256) h[threadIdx.x] = 0;
-        if (threadIdx.x == 0) sh_done = 0;
+topk_select_one_kernel(const float *score, int N, unsigned int k_sel, unsigned long long *sel, int padded) {
+    __shared__ unsigned int hist[2048], part[16], lohi[32], ties[16 * U];
+    __shared__ unsigned int sh_bin, sh_left, sh_count;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t key[U], lo = 0xFFFFFFFFu, hi = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = u * 1024 + tid;
+        const float f = score[i < N ? i : N - 1];
+        key[u] = order_key(f);
+        lo = key[u] < lo ? key[u] : lo;
+        hi = key[u] > hi ? key[u] : hi;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint32_t l = (uint32_t)__shfl_xor((int)lo, o, 64), h = (uint32_t)__shfl_xor((int)hi, o, 64);
+        lo = l < lo ? l : lo;
+        hi = h > hi ? h : hi;
+    }
+    if (lane == 0) { lohi[wave] = lo; lohi[16 + wave] = hi; }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        lo = lohi[q] < lo ? lohi[q] : lo;
+        hi = lohi[16 + q] > hi ? lohi[16 + q] : hi;
+    }
+    int shift = lo == hi ? 0 : 32 - __builtin_clz(hi - lo) - 11;
+    if (shift < 0) shift = 0;
+    unsigned int rem = k_sel;
+    bool cut;                                           // the threshold score is shared by more examples than are still to be taken
+    for (;;) {                                          // uniform; every round narrows the range 2048-fold
+        hist[tid] = 0; hist[tid + 1024] = 0;
         __syncthreads();
-        const int shift = 56 - 8 * pass;
-        const unsigned long long himask = pass == 0 ? 0ull : (~0ull << (shift + 8));
-        for (int64_t base = 0; base < n_up; base += 1024 * kU) {  // same trip count for all lanes
-            float v[kU];
+        if (shift > 16) {
 #pragma unroll
-            for (int u = 0; u < kU; ++u) {                         // kU loads in flight per thread
-                const int64_t i = base + u * 1024 + threadIdx.x;
-                v[u] = i < N ? score[i] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                const int64_t i = base + u * 1024 + threadIdx.x;
-                bool match = false;
-                unsigned int d = 0;
-                if (i < N) {
-                    const unsigned long long key = make_key(v[u], i);
-                    match = ((key ^ prefix) & himask) == 0;
-                    d = (unsigned int)(key >> shift) & 0xFFu;
-                }
-                const unsigned long long act = __ballot(match);
+            for (int u = 0; u < U; ++u) {
+                const bool in = u * 1024 + tid < N && key[u] >= lo && key[u] <= hi;
+                const unsigned int bin = in ? (key[u] - lo) >> shift : 0u;
+                const unsigned long long act = __ballot(in);
                 if (act) {
                     const int leader = __ffsll((long long)act) - 1;
-                    const unsigned int d0 = (unsigned int)__builtin_amdgcn_readlane((int)d, leader);
-                    const unsigned long long same = __ballot(match && d == d0);
-                    if (lane == leader) atomicAdd(&h[d0], (unsigned int)__popcll(same));
-                    if (match && d != d0) atomicAdd(&h[d], 1u);
+                    const unsigned int b0 = (unsigned int)__builtin_amdgcn_readlane((int)bin, leader);
+                    const unsigned long long same = __ballot(in && bin == b0);
+                    if (lane == leader) atomicAdd(&hist[b0], (unsigned int)__popcll(same));
+                    if (in && bin != b0) atomicAdd(&hist[bin], 1u);
                 }
             }
+        } else {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (u * 1024 + tid < N && key[u] >= lo && key[u] <= hi) atomicAdd(&hist[(key[u] - lo) >> shift], 1u);
         }
         __syncthreads();
-        const unsigned int mine = threadIdx.x < 256 ? h[threadIdx.x] : 0u;
-        unsigned long long left = 0;
-        if (pick_digit(above, mine, rem, left)) {
-            sh_prefix = prefix | ((unsigned long long)threadIdx.x << shift);
-            sh_rem = left;
-            sh_done = left == (unsigned long long)mine;             // the whole bucket is selected
+        // bins from the top: thread t has 2047 - 2 t and the one below it
+        const unsigned int c0 = hist[2047 - 2 * tid], c1 = hist[2046 - 2 * tid];
+        const unsigned int upto = block_scan(c0 + c1, part), before = upto - c0 - c1;
+        if (before < rem && rem <= upto) {
+            const bool upper = rem <= before + c0;
+            sh_bin = upper ? 2047 - 2 * tid : 2046 - 2 * tid;
+            sh_left = rem - (upper ? before : before + c0);
+            sh_count = upper ? c0 : c1;
         }
         __syncthreads();
-        prefix = sh_prefix; rem = sh_rem;
-        const int done = sh_done;
+        lo += sh_bin << shift;
+        hi = lo + ((1u << shift) - 1u);
+        rem = sh_left;
+        cut = sh_count != rem;
+        if (!cut || shift == 0) break;
+        shift = shift > 11 ? shift - 11 : 0;
+    }
+    // taken: keys from lo on, or, where lo is a value that not all examples with it are taken of, keys above it and the first `rem` with it
+    unsigned long long take = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (u * 1024 + tid < N && (cut ? key[u] > lo : key[u] >= lo)) take |= 1ull << u;
+    if (cut) {                                          // positions in array order: by u, then wavefront, then lane
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned long long m = __ballot(u * 1024 + tid < N && key[u] == lo);
+            if (lane == 0) ties[u * 16 + wave] = (unsigned int)__popcll(m);
+        }
         __syncthreads();
-        if (done) break;
+        const unsigned int mine = tid < 16 * U ? ties[tid] : 0u, upto = block_scan(mine, part);
+        if (tid < 16 * U) ties[tid] = upto - mine;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool tie = u * 1024 + tid < N && key[u] == lo;
+            const unsigned long long m = __ballot(tie);
+            if (tie && ties[u * 16 + wave] + (unsigned int)__popcll(m & ((1ull << lane) - 1ull)) < rem) take |= 1ull << u;
+        }
     }
-    if (threadIdx.x == 0) {
-        state[kPasses].prefix = prefix; state[kPasses].remaining = rem; state[kPasses].count = 0; state[kPasses].done = 1;
-    }
+    const unsigned int mine = (unsigned int)__popcll(take);
+    unsigned int at = block_scan(mine, part) - mine;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (take >> u & 1) {
+            if (at < k_sel) sel[at] = ((unsigned long long)key[u] << 32) | (0xFFFFFFFFull - (unsigned long long)(u * 1024 + tid));
+            ++at;
+        }
+    for (int i = (int)k_sel + tid; i < padded; i += 1024) sel[i] = 0;     // padding sorts last (real keys are > 0)
 }
 
-// The state after the digit pick of pass `pass` (from the state before it and the pass's finished
+// The state after the digit pick of pass PASS (from the state before it and the pass's finished
 // histogram), computed by every thread of a 256-thread workgroup alike; workgroup 0 also records
-// it in state[pass + 1].  `above` and `sh` are LDS scratch.
-__device__ inline SelectState next_state(int pass, SelectState *state, const unsigned int *hist,
-                                         unsigned long long *above, SelectState *sh) {
-    const SelectState before = state[pass];
+// it in state[PASS + 1].  `part` and `sh` are LDS scratch.
+template <int PASS>
+__device__ inline SelectState next_state(SelectState *state, const unsigned int *hist, unsigned long long *part, SelectState *sh) {
+    const SelectState before = state[PASS];
     if (before.done) {                              // uniform
-        if (blockIdx.x == 0 && threadIdx.x == 0) { state[pass + 1].prefix = before.prefix; state[pass + 1].remaining = before.remaining; state[pass + 1].done = 1; }
+        if (blockIdx.x == 0 && threadIdx.x == 0) { state[PASS + 1].prefix = before.prefix; state[PASS + 1].remaining = before.remaining; state[PASS + 1].done = 1; }
         return before;
     }
-    const unsigned int mine = hist[pass * 256 + threadIdx.x];
     unsigned long long left = 0;
-    if (pick_digit(above, mine, before.remaining, left)) {
-        sh->prefix = before.prefix | ((unsigned long long)threadIdx.x << (56 - 8 * pass));
+    unsigned int count = 0;
+    const int digit = pick_digit<1 << kDigitBits[PASS]>(hist + kHistAt[PASS], part, before.remaining, left, count);
+    if (digit >= 0) {
+        sh->prefix = before.prefix | ((unsigned long long)digit << kDigitShift[PASS]);
         sh->remaining = left;
-        sh->done = left == (unsigned long long)mine;    // the whole bucket is selected: the prefix with zeros below is the threshold
+        sh->done = left == (unsigned long long)count;   // the whole bucket is selected: the prefix with zeros below is the threshold
     }
     __syncthreads();
     SelectState after = *sh;
     after.count = 0;
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) { state[pass + 1].prefix = after.prefix; state[pass + 1].remaining = after.remaining; state[pass + 1].done = after.done; }
+    if (blockIdx.x == 0 && threadIdx.x == 0) { state[PASS + 1].prefix = after.prefix; state[PASS + 1].remaining = after.remaining; state[PASS + 1].done = after.done; }
     return after;
 }
 
 constexpr int kHistPer = 8;                         // examples per thread and round of the histogram
-// histogram of digit `pass` (0 = most significant byte) over keys whose higher digits equal the prefix
+// histogram of digit PASS (0 = most significant) over keys whose higher digits equal the prefix
 // chosen so far; the pick of the pass before is done here first, by every workgroup for itself
+template <int PASS>
 __global__ void __launch_bounds__(256)
-topk_hist_kernel(const float *score, int64_t N, int pass, SelectState *state, unsigned int *hist) {
-    __shared__ unsigned int h[256];
-    __shared__ unsigned long long above[257];
+topk_hist_kernel(const float *score, int64_t N, SelectState *state, unsigned int *hist) {
+    constexpr int B = 1 << kDigitBits[PASS], shift = kDigitShift[PASS];
+    __shared__ unsigned int h[B];
+    __shared__ unsigned long long part[4];
     __shared__ SelectState sh;
-    const SelectState cur = pass == 0 ? state[0] : next_state(pass - 1, state, hist, above, &sh);
+    SelectState cur;
+    if constexpr (PASS == 0) cur = state[0];
+    else cur = next_state<PASS - 1>(state, hist, part, &sh);
     if (cur.done) return;                           // uniform
-    h[threadIdx.x] = 0;
+    for (int i = threadIdx.x; i < B; i += 256) h[i] = 0;
     __syncthreads();
     const unsigned long long prefix = cur.prefix;
-    const int shift = 56 - 8 * pass;
     // bits above the current digit: pass 0 has none (mask 0), later passes compare them all
-    const unsigned long long himask = pass == 0 ? 0ull : (~0ull << (shift + 8));
+    constexpr unsigned long long himask = PASS == 0 ? 0ull : (~0ull << (shift + kDigitBits[PASS]) % 64);
     // a workgroup takes kHistPer * 256 consecutive examples at a time (few workgroups: every one of them ends
-    // with up to 256 atomics on the same global bins), kHistPer loads in flight per thread
+    // with an atomic on every bin it has counted into), kHistPer loads in flight per thread
     for (int64_t c0 = (int64_t)blockIdx.x * (256 * kHistPer); c0 < N; c0 += (int64_t)gridDim.x * (256 * kHistPer)) {   // uniform
         float v[kHistPer];
 #pragma unroll
@@ -224,7 +300,7 @@ topk_hist_kernel(const float *score, int64_t N, int pass, SelectState *state, un
             const int64_t i = c0 + u * 256 + threadIdx.x;
             const unsigned long long key = make_key(v[u], i);
             const bool match = i < N && ((key ^ prefix) & himask) == 0;
-            const unsigned int d = (unsigned int)(key >> shift) & 0xFFu;
+            const unsigned int d = (unsigned int)(key >> shift) & (unsigned int)(B - 1);
             // the leading digits of scores are few: the lanes that share the digit of the first matching
             // lane are added at once, the others one by one
             const unsigned long long act = __ballot(match);
@@ -238,84 +314,28 @@ topk_hist_kernel(const float *score, int64_t N, int pass, SelectState *state, un
         }
     }
     __syncthreads();
-    if (h[threadIdx.x]) atomicAdd(&hist[pass * 256 + threadIdx.x], h[threadIdx.x]);
+    for (int i = threadIdx.x; i < B; i += 256)
+        if (h[i]) atomicAdd(&hist[kHistAt[PASS] + i], h[i]);
 }
 
 constexpr int kCompactPer = 4;                      // examples per thread and round
 constexpr int kChunk = 256 * kCompactPer;           // examples per round of a workgroup
 
-// After the last histogram: picks its digit; unless the threshold bucket is taken whole, counts the
-// examples whose score is the threshold score in every group of kChunk examples.
-__global__ void __launch_bounds__(256)
-topk_tie_count_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *hist,
-                      unsigned int *ties) {
-    __shared__ unsigned long long above[257];
-    __shared__ SelectState sh;
-    __shared__ unsigned int cnt;
-    const SelectState fin = next_state(kPasses - 1, state, hist, above, &sh);
-    if (fin.done) return;                           // uniform
-    const uint32_t T = (uint32_t)(fin.prefix >> 32);
-    for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < N; c0 += (int64_t)gridDim.x * kChunk) {
-        if (threadIdx.x == 0) cnt = 0;
-        __syncthreads();
-        unsigned int mine = 0;
-#pragma unroll
-        for (int u = 0; u < kCompactPer; ++u) {
-            const int64_t i = c0 + u * 256 + threadIdx.x;
-            const bool tie = i < N && order_key(score[i]) == T;
-            mine += (unsigned int)__popcll(__ballot(tie));
-        }
-        if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&cnt, mine);
-        __syncthreads();
-        if (threadIdx.x == 0) ties[c0 / kChunk] = cnt;
-        __syncthreads();
-    }
-}
-
-// One workgroup: exclusive scan, in place, of the per-group counts.
-__global__ void __launch_bounds__(1024)
-topk_tie_scan_kernel(const SelectState *state, unsigned int *ties, int64_t chunks) {
-    __shared__ unsigned int part[1024];
-    __shared__ unsigned int carry;
-    if (state[kPasses].done) return;                // written by the launch before
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int64_t b = 0; b < chunks; b += 1024) {
-        const int64_t c = b + threadIdx.x;
-        const unsigned int v = c < chunks ? ties[c] : 0u;
-        part[threadIdx.x] = v;
-        __syncthreads();
-        for (int step = 1; step < 1024; step <<= 1) {   // Hillis-Steele, inclusive
-            const unsigned int add = (int)threadIdx.x >= step ? part[threadIdx.x - step] : 0u;
-            __syncthreads();
-            part[threadIdx.x] += add;
-            __syncthreads();
-        }
-        const unsigned int base = carry;
-        if (c < chunks) ties[c] = base + part[threadIdx.x] - v;
-        __syncthreads();
-        if (threadIdx.x == 1023) carry = base + part[1023];
-        __syncthreads();
-    }
-}
-
 // The selected keys (exactly k_sel of them) are gathered in any order; the slots from k_sel to
-// padded and the ranks are cleared.  A workgroup takes kChunk consecutive examples at a time and one
+// padded are cleared.  A workgroup takes kChunk consecutive examples at a time and one
 // atomic for all it selects among them.  Selected: key >= threshold key when the selection ended
 // with a whole bucket; otherwise score above the threshold score T, or equal to it and among the
-// first `remaining` such examples in array order (`ties` holds how many precede each group).
-__global__ void __launch_bounds__(256)
-topk_compact_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *ties, int scanned,
-                    unsigned long long *sel, unsigned int *rank, int64_t k_sel, int64_t padded) {
+// first `remaining` such examples in array order (`ties` holds how many precede each group).  All threads of a 256-thread workgroup call it.
+__device__ inline void
+compact(const SelectState &fin, const float *score, int64_t N, unsigned int *cursor, const unsigned int *ties, int scanned,
+        unsigned long long *sel, int64_t k_sel, int64_t padded) {
     __shared__ unsigned int before[4];
     __shared__ unsigned int offs[4 * kCompactPer + 1];
     __shared__ unsigned int toffs[4 * kCompactPer];
-    const SelectState fin = state[kPasses];
     const bool by_position = !fin.done;             // uniform
     const unsigned long long thr = by_position ? (fin.prefix | 0xFFFFFFFFull) + 1ull : fin.prefix;   // T + 1 in the score half
     const bool none_above = by_position && thr == 0ull;     // T is the largest score key: nothing lies above it
     const uint32_t T = (uint32_t)(fin.prefix >> 32);
-    unsigned int *cursor = &state[kPasses].count;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t span = N > padded ? N : padded;
     for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < span; c0 += (int64_t)gridDim.x * kChunk) {   // uniform per workgroup
@@ -325,7 +345,6 @@ topk_compact_kernel(const float *score, int64_t N, SelectState *state, const uns
         for (int u = 0; u < kCompactPer; ++u) {
             const int64_t i = c0 + u * 256 + threadIdx.x;
             if (i >= k_sel && i < padded) sel[i] = 0;   // padding sorts last (real keys are > 0)
-            if (i < padded) rank[i] = 0;
             key[u] = 0; take[u] = false; tie[u] = false;
             if (i < N) {
                 key[u] = make_key(score[i], i);
@@ -385,54 +404,107 @@ topk_compact_kernel(const float *score, int64_t N, SelectState *state, const uns
     }
 }
 
-// Rank of every selected key = how many selected keys are larger (keys are distinct): workgroup
-// (x, y) counts, for its 256 * kRankPer keys, the larger ones among keys [y * seg, (y + 1) * seg),
-// staged in LDS 1024 at a time and read by all lanes at once (a broadcast).  k_sel^2 comparisons: for
-// k_sel <= kSortOne only.
-constexpr int kRankPer = 1;                         // keys per thread (two measured no faster)
+// After the last histogram: picks its digit; if the threshold bucket is taken whole (few scores are shared), compacts at once, so that the
+// launches behind it have nothing to do; else counts the examples whose score is the threshold score in every group of kChunk examples.
 __global__ void __launch_bounds__(256)
-topk_rank_kernel(const unsigned long long *sel, int64_t k_sel, int64_t seg, unsigned int *rank) {
-    __shared__ __attribute__((aligned(16))) unsigned long long tile[1024];
-    unsigned long long mine[kRankPer];
-    unsigned int cnt[kRankPer];
-#pragma unroll
-    for (int e = 0; e < kRankPer; ++e) {
-        const int64_t i = ((int64_t)blockIdx.x * kRankPer + e) * 256 + threadIdx.x;
-        mine[e] = i < k_sel ? sel[i] : ~0ull;
-        cnt[e] = 0;
+topk_finish_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *hist,
+                   unsigned int *ties, unsigned long long *sel, int64_t k_sel, int64_t padded) {
+    __shared__ unsigned long long part[4];
+    __shared__ SelectState sh;
+    __shared__ unsigned int cnt;
+    const SelectState fin = next_state<kPasses - 1>(state, hist, part, &sh);
+    if (fin.done) {                                 // uniform
+        compact(fin, score, N, &state[kPasses].count, nullptr, 0, sel, k_sel, padded);
+        return;
     }
-    const int64_t j0 = (int64_t)blockIdx.y * seg;
-    const int64_t j1 = j0 + seg < k_sel ? j0 + seg : k_sel;
-    for (int64_t jb = j0; jb < j1; jb += 1024) {
-        const int n = j1 - jb < 1024 ? (int)(j1 - jb) : 1024, up = (n + 15) & ~15;
+    const uint32_t T = (uint32_t)(fin.prefix >> 32);
+    for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < N; c0 += (int64_t)gridDim.x * kChunk) {
+        if (threadIdx.x == 0) cnt = 0;
         __syncthreads();
-        for (int t = threadIdx.x; t < up; t += 256) tile[t] = t < n ? sel[jb + t] : 0ull;   // 0 is below every key
-        __syncthreads();
-#pragma unroll 8
-        for (int t = 0; t < up; t += 2) {
-            const ulonglong2 pr = *(const ulonglong2 *)&tile[t];
+        unsigned int mine = 0;
 #pragma unroll
-            for (int e = 0; e < kRankPer; ++e) cnt[e] += (pr.x > mine[e]) + (pr.y > mine[e]);
+        for (int u = 0; u < kCompactPer; ++u) {
+            const int64_t i = c0 + u * 256 + threadIdx.x;
+            const bool tie = i < N && order_key(score[i]) == T;
+            mine += (unsigned int)__popcll(__ballot(tie));
         }
-    }
-#pragma unroll
-    for (int e = 0; e < kRankPer; ++e) {
-        const int64_t i = ((int64_t)blockIdx.x * kRankPer + e) * 256 + threadIdx.x;
-        if (i < k_sel && cnt[e]) atomicAdd(&rank[i], cnt[e]);
+        if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&cnt, mine);
+        __syncthreads();
+        if (threadIdx.x == 0) ties[c0 / kChunk] = cnt;
+        __syncthreads();
     }
 }
 
-// idx / val in rank order
+// One workgroup: exclusive scan, in place, of the per-group counts.
+__global__ void __launch_bounds__(1024)
+topk_tie_scan_kernel(const SelectState *state, unsigned int *ties, int64_t chunks) {
+    __shared__ unsigned int part[1024];
+    __shared__ unsigned int carry;
+    if (state[kPasses].done) return;                // written by the launch before
+    if (threadIdx.x == 0) carry = 0;
+    __syncthreads();
+    for (int64_t b = 0; b < chunks; b += 1024) {
+        const int64_t c = b + threadIdx.x;
+        const unsigned int v = c < chunks ? ties[c] : 0u;
+        part[threadIdx.x] = v;
+        __syncthreads();
+        for (int step = 1; step < 1024; step <<= 1) {   // Hillis-Steele, inclusive
+            const unsigned int add = (int)threadIdx.x >= step ? part[threadIdx.x - step] : 0u;
+            __syncthreads();
+            part[threadIdx.x] += add;
+            __syncthreads();
+        }
+        const unsigned int base = carry;
+        if (c < chunks) ties[c] = base + part[threadIdx.x] - v;
+        __syncthreads();
+        if (threadIdx.x == 1023) carry = base + part[1023];
+        __syncthreads();
+    }
+}
+
+// The compaction where the threshold score is shared by more examples than are still to be taken
 __global__ void __launch_bounds__(256)
-topk_scatter_kernel(const unsigned long long *sel, const unsigned int *rank, int64_t k_sel, const float *score,
-                    int64_t N, int64_t *idx, float *val) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= k_sel) return;
-    const int64_t i = (int64_t)(0xFFFFFFFFull - (sel[t] & 0xFFFFFFFFull));
-    const unsigned int r = rank[t];
-    if ((int64_t)r >= k_sel) return;                 // cannot happen with distinct keys
-    idx[r] = i;
-    if (val) val[r] = score[i < N ? i : N - 1];
+topk_compact_ties_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *ties, int scanned,
+                         unsigned long long *sel, int64_t k_sel, int64_t padded) {
+    const SelectState fin = state[kPasses];
+    if (fin.done) return;                           // uniform
+    compact(fin, score, N, &state[kPasses].count, ties, scanned, sel, k_sel, padded);
+}
+
+// Rank of every selected key = how many selected keys are larger (keys are distinct); its index and score go to the slot of that rank.
+// A workgroup ranks 32 keys, one per lane of a half wavefront: its 32 halves count the larger ones in a share each of all keys, staged in LDS
+// 4096 at a time and read by all lanes of a half at once (a broadcast), and the counts are joined in LDS.  k_sel^2 comparisons: for k_sel <=
+// kSortOne only.  (Two launches, counts joined by global atomics, then written out: 3276 of 65536 2 us more; 64 keys to a workgroup leave
+// half the chip idle there.)
+__global__ void __launch_bounds__(1024)
+topk_rank_kernel(const unsigned long long *sel, int k_sel, const float *score, int64_t N, int64_t *idx, float *val) {
+    __shared__ __attribute__((aligned(16))) unsigned long long tile[4096];
+    __shared__ unsigned int larger[32][32];
+    const int lane = threadIdx.x & 31, part = threadIdx.x >> 5, mine_at = (int)blockIdx.x * 32 + lane;
+    const unsigned long long mine = mine_at < k_sel ? sel[mine_at] : ~0ull;
+    unsigned int cnt = 0;
+    for (int jb = 0; jb < k_sel; jb += 4096) {
+        const int n = k_sel - jb < 4096 ? k_sel - jb : 4096, share = (n + 63) / 64 * 2;       // keys per half, a multiple of two
+        __syncthreads();
+        for (int t = threadIdx.x; t < 32 * share; t += 1024) tile[t] = t < n ? sel[jb + t] : 0ull;   // 0 is below every key
+        __syncthreads();
+        const int t0 = part * share;
+#pragma unroll 8
+        for (int t = 0; t < share; t += 2) {
+            const ulonglong2 pr = *(const ulonglong2 *)&tile[t0 + t];
+            cnt += (pr.x > mine) + (pr.y > mine);
+        }
+    }
+    larger[part][lane] = cnt;
+    __syncthreads();
+    if (part != 0 || mine_at >= k_sel) return;
+#pragma unroll
+    for (int q = 1; q < 32; ++q) cnt += larger[q][lane];
+    const int64_t i = (int64_t)(0xFFFFFFFFull - (mine & 0xFFFFFFFFull));
+    if (cnt >= (unsigned int)k_sel) return;          // cannot happen with distinct keys
+    idx[cnt] = i;
+    const uint32_t s = (uint32_t)(mine >> 32);          // the score's bits, but for the sign of a zero
+    if (val) val[cnt] = s == 0x80000000u ? score[i < N ? i : N - 1] : __uint_as_float(s & 0x80000000u ? s & 0x7FFFFFFFu : ~s);
 }
 
 // Bitonic network, descending.  Stage size kk (sub-sequence length), step jj (partner distance).
@@ -512,47 +584,33 @@ static qless_status topk_run(const float *score, int64_t N, int64_t k_sel, int64
     unsigned long long *sel = (unsigned long long *)(w + p.off_sel);
     unsigned int *hist = (unsigned int *)(w + p.off_hist);
     SelectState *state = (SelectState *)(w + p.off_state);
-    unsigned int *rank = (unsigned int *)(w + p.off_rank);
     unsigned int *ties = (unsigned int *)(w + p.off_ties);
 
     auto blocks_for = [](int64_t n) { int64_t b = (n + 255) / 256; if (b < 1) b = 1; if (b > 2048) b = 2048; return (unsigned)b; };
-    const bool small = N <= kSelectSmallMax;
-    if (small) {
-        hipLaunchKernelGGL(topk_select_small_kernel, dim3(1), dim3(1024), 0, st, score, N, (unsigned long long)k_sel, state);
+    if (N <= kSelectOneMax) {
+        const auto one = N <= 4096 ? topk_select_one_kernel<4> : (N <= 8192 ? topk_select_one_kernel<8> : topk_select_one_kernel<16>);
+        hipLaunchKernelGGL(one, dim3(1), dim3(1024), 0, st, score, (int)N, (unsigned int)k_sel, sel, (int)p.padded);
     } else {
         hipLaunchKernelGGL(topk_init_kernel, dim3(1), dim3(256), 0, st, hist, state, (unsigned long long)k_sel);
         int64_t hblocks = (N + 256 * kHistPer - 1) / (256 * kHistPer);
         if (hblocks > 2048) hblocks = 2048;
-        for (int pass = 0; pass < kPasses; ++pass)
-            hipLaunchKernelGGL(topk_hist_kernel, dim3((unsigned)hblocks), dim3(256), 0, st, score, N, pass, state, hist);
-    }
-    const int64_t span = N > p.padded ? N : p.padded;
-    int64_t cblocks = (span + kChunk - 1) / kChunk;
-    if (cblocks > 2048) cblocks = 2048;
-    // up to 2^22 scores (4096 groups of 1024) the compaction sums the counts of the groups before its own itself: a launch less
-    const bool scan = p.chunks > 4096;
-    if (!small) {
-        int64_t tblocks = (N + kChunk - 1) / kChunk;
-        if (tblocks > 2048) tblocks = 2048;
-        hipLaunchKernelGGL(topk_tie_count_kernel, dim3((unsigned)tblocks), dim3(256), 0, st, score, N, state,
-                           (const unsigned int *)hist, ties);
+        hipLaunchKernelGGL(topk_hist_kernel<0>, dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist);
+        hipLaunchKernelGGL(topk_hist_kernel<1>, dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist);
+        hipLaunchKernelGGL(topk_hist_kernel<2>, dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist);
+        const int64_t span = N > p.padded ? N : p.padded;
+        int64_t cblocks = (span + kChunk - 1) / kChunk;
+        if (cblocks > 2048) cblocks = 2048;
+        // up to 2^22 scores (4096 groups of 1024) the compaction sums the counts of the groups before its own itself: a launch less
+        const bool scan = p.chunks > 4096;
+        hipLaunchKernelGGL(topk_finish_kernel, dim3((unsigned)cblocks), dim3(256), 0, st, score, N, state,
+                           (const unsigned int *)hist, ties, sel, k_sel, p.padded);
         if (scan) hipLaunchKernelGGL(topk_tie_scan_kernel, dim3(1), dim3(1024), 0, st, (const SelectState *)state, ties, p.chunks);
+        hipLaunchKernelGGL(topk_compact_ties_kernel, dim3((unsigned)cblocks), dim3(256), 0, st, score, N, state,
+                           (const unsigned int *)ties, scan ? 1 : 0, sel, k_sel, p.padded);
     }
-    hipLaunchKernelGGL(topk_compact_kernel, dim3((unsigned)cblocks), dim3(256), 0, st, score, N, state,
-                       (const unsigned int *)ties, scan ? 1 : 0, sel, rank, k_sel, p.padded);
     if (p.padded <= kSortOne) {
-        // few selected keys: rank every key among all of them, then write in rank order
-        const unsigned kb = (unsigned)((k_sel + 255) / 256);
-        // keys per workgroup and segment: a segment is one chain of LDS broadcasts (1024 keys: 13 us), so few selected keys are
-        // cut into short segments, down to 64 keys, as long as there are not far more workgroups than the chip holds
-        // (409 of 8192: 13 -> 2 us, 3276 of 65536: 14 -> 4 us); many keys keep 1024 and fewer atomics
-        int64_t seg = 1024;
-        while (seg > 64 && ((k_sel + 255) / 256) * ((k_sel + seg / 2 - 1) / (seg / 2)) <= 1024) seg >>= 1;
-        const unsigned rb = (unsigned)((k_sel + 256 * kRankPer - 1) / (256 * kRankPer));
-        hipLaunchKernelGGL(topk_rank_kernel, dim3(rb, (unsigned)((k_sel + seg - 1) / seg)), dim3(256), 0, st,
-                           (const unsigned long long *)sel, k_sel, seg, rank);
-        hipLaunchKernelGGL(topk_scatter_kernel, dim3(kb), dim3(256), 0, st, (const unsigned long long *)sel,
-                           (const unsigned int *)rank, k_sel, score, N, idx, val);
+        hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)((k_sel + 31) / 32)), dim3(1024), 0, st, (const unsigned long long *)sel,
+                           (int)k_sel, score, N, idx, val);
         return launch_status();
     }
     // many selected keys: sort them, descending, with a bitonic network
@@ -627,7 +685,7 @@ extern "C" qless_status qless_topk_noalloc(const float *score, int64_t N, int64_
     const qless_status rs = topk_scratch_address(&ws);
     if (rs != QLESS_OK) return rs;
     // every word of the workspace that a launch reads is written earlier in the same call (init /
-    // select kernels clear histograms, states and the cursor; the compaction clears padding and ranks;
+    // select kernels clear histograms, states and the cursor; the compaction clears padding;
     // the tie counts are written before they are scanned), so nothing of the call before survives
     return topk_run(score, N, k_sel, idx, val, ws, (hipStream_t)stream);
 }
