@@ -173,35 +173,67 @@ score_split_kernel(ScoreArgs a, int cb, int parts, int per, uint32_t *planes) {
     }
 }
 
-// The parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.  ROWS train rows per workgroup of four
-// wavefronts: one each (up to 64 columns), or all on one row (with a row per wavefront 1800 x 145 x 4 took 27 us instead of 22).
+// One pair's influence: the parts of four checkpoints' sums at a time, all requested before the first is used (the additions stay in the
+// order of the parts and of the checkpoints).
+__device__ inline float split_pair(const ScoreArgs &a, int parts, const uint32_t *planes, size_t plane, int bf16, int64_t z, int c) {
+    float acc = 0.0f;
+    const uint32_t *p = planes + (size_t)z * a.M + c;
+    for (int c0 = 0; c0 < a.C; c0 += 4) {
+        float rt[4], wv[4], D[4];
+        uint32_t d[4];
+        const int live = a.C - c0 < 4 ? a.C - c0 : 4;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int ci = u < live ? c0 + u : c0;
+            rt[u] = a.tr[ci] ? a.tr[ci][z] : 1.0f;
+            wv[u] = bf16 ? a.eta[ci] : __fmul_rn(a.eta[ci], a.vr[ci][c]);
+            d[u] = p[(size_t)(ci - c0) * parts * plane];
+            D[u] = __uint_as_float(d[u]);
+        }
+        int s = 1;
+        for (; s + 2 <= parts; s += 2) {
+            uint32_t t[4][2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v) t[u][v] = p[((size_t)(u < live ? u : 0) * parts + s + v) * plane];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                D[u] = __fadd_rn(__fadd_rn(D[u], __uint_as_float(t[u][0])), __uint_as_float(t[u][1]));
+                d[u] += t[u][0] + t[u][1];
+            }
+        }
+        if (s < parts) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t t = p[((size_t)(u < live ? u : 0) * parts + s) * plane];
+                D[u] = __fadd_rn(D[u], __uint_as_float(t));
+                d[u] += t;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (u < live) acc = __fadd_rn(acc, __fmul_rn(__fmul_rn(bf16 ? D[u] : (float)(int)d[u], rt[u]), wv[u]));
+        p += 4 * (size_t)parts * plane;
+    }
+    return acc;
+}
+
+// The parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.  What it takes is the time of its loads one
+// behind the other, so they go out together and every thread has one column (up to 1024): with a walk of 256 threads over the columns and
+// one load at a time 64 x 512 x 4 took 13.5 us at 1 bit, so 5.9 (with the sums 8 bits 47 -> 21 us, bfloat16 51 -> 26).  ROWS train rows per workgroup of four wavefronts: one each (up to 64 columns), or
+// all wavefronts on one row (with a row per wavefront 1800 x 145 x 4 took 27 us instead of 22).
 template <int ROWS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(ROWS == 1 ? 1024 : 256)
 score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf16, float none) {
-    __shared__ float wave_best[4];
+    __shared__ float wave_best[16];
     const int wave = threadIdx.x >> 6;
     const int64_t z = ROWS == 1 ? blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
     const size_t plane = (size_t)a.N * (size_t)a.M;
     if (ROWS > 1 && z >= a.N) return;                // (no barrier below then)
     float best = neg_inf();
-    for (int c = ROWS == 1 ? threadIdx.x : threadIdx.x & 63; c < a.M; c += ROWS == 1 ? 256 : 64) {
-        float acc = 0.0f;
-        const uint32_t *p = planes + (size_t)z * a.M + c;
-        for (int ci = 0; ci < a.C; ++ci) {
-            float D;
-            if (bf16) {
-                D = __uint_as_float(p[0]);
-                for (int s = 1; s < parts; ++s) D += __uint_as_float(p[s * plane]);
-            } else {
-                int d = 0;
-                for (int s = 0; s < parts; ++s) d += (int)p[s * plane];
-                D = (float)d;
-            }
-            p += parts * plane;
-            const float rt = a.tr[ci] ? a.tr[ci][z] : 1.0f;
-            const float wv = bf16 ? a.eta[ci] : __fmul_rn(a.eta[ci], a.vr[ci][c]);
-            acc = __fadd_rn(acc, __fmul_rn(__fmul_rn(D, rt), wv));
-        }
+    for (int c = ROWS == 1 ? threadIdx.x : threadIdx.x & 63; c < a.M; c += ROWS == 1 ? blockDim.x : 64) {
+        const float acc = split_pair(a, parts, planes, plane, bf16, z, c);
         if (a.full) a.full[z * a.M + c] = acc;
         best = fmaxf(best, acc);
     }
@@ -211,15 +243,18 @@ score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf
     if (ROWS == 1) {
         if ((threadIdx.x & 63) == 0) wave_best[wave] = best;
         __syncthreads();
-        best = fmaxf(fmaxf(wave_best[0], wave_best[1]), fmaxf(wave_best[2], wave_best[3]));
+        if (threadIdx.x) return;
+        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) best = fmaxf(best, wave_best[w]);
     }
-    if (threadIdx.x == (ROWS == 1 ? 0 : wave * 64)) a.score[z] = best > neg_inf() ? best : none;
+    if ((threadIdx.x & 63) == 0) a.score[z] = best > neg_inf() ? best : none;
 }
 qless_status launch_split_finish(const ScoreArgs &a, int parts, const uint32_t *planes, bool bf16, float none, hipStream_t st) {
     if (a.M <= 64 && a.N >= 1024)
         hipLaunchKernelGGL(score_split_finish_kernel<4>, dim3((unsigned)((a.N + 3) / 4)), dim3(256), 0, st, a, parts, planes, bf16, none);
-    else
-        hipLaunchKernelGGL(score_split_finish_kernel<1>, dim3((unsigned)a.N), dim3(256), 0, st, a, parts, planes, bf16, none);
+    else {
+        const int threads = a.M >= 1024 ? 1024 : (a.M + 63) / 64 * 64;
+        hipLaunchKernelGGL(score_split_finish_kernel<1>, dim3((unsigned)a.N), dim3(threads), 0, st, a, parts, planes, bf16, none);
+    }
     return launch_status();
 }
 

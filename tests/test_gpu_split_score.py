@@ -49,6 +49,13 @@ def test_split_codes_bit_exact(bits, N, M, k, C):
     assert torch.equal(Q.score(tc, tr, vc, vr, _eta(C), k, bits), got)
 
 
+# a thread per column up to 1024 of them, a walk above; checkpoints by fours, parts by twos, with every remainder
+@pytest.mark.parametrize("bits,N,M,k,C", [(1, 3, 1023, 8192, 5), (8, 2, 1024, 4096, 7), (4, 2, 1025, 4096, 9), (2, 3, 2049, 2048, 6), (8, 70, 257, 1024, 1),
+                                          (8, 70, 64, 3072, 3), (4, 5, 65, 8192, 8)])
+def test_split_columns_and_checkpoints(bits, N, M, k, C):
+    test_split_codes_bit_exact(bits, N, M, k, C)
+
+
 @pytest.mark.parametrize("N,M,k,C", [(64, 100, 8192, 4), (1, 3, 4096, 2), (130, 65, 192, 16), (33, 9, 16384, 1)])
 def test_split_bfloat16(N, M, k, C):
     _say("split bfloat16 N=%d M=%d k=%d C=%d" % (N, M, k, C))
