@@ -3,16 +3,15 @@
 //
 // Every example gets a 64-bit key  (order-preserving image of the fp32 score) << 32 | (2^32-1 - index);
 // keys are distinct and "larger key" is exactly "selected earlier".  Steps:
-//   1. find the k_sel-th largest score.  Up to 16384 scores one workgroup holds all of them in registers and does this and the
-//   compaction in a single launch (topk_select_one_kernel); above that, one histogram launch for each of the three digits (10, 11 and
-//   11 bits) of the score, whose workgroups each first pick the digit of the pass before from its finished
-//   histogram (a scan of its bins, cheaper than a launch of its own); the passes stop as soon as the bucket that holds the
-//   k_sel-th key is selected as a whole.  If the threshold score T is then
-//   shared by more examples than are still to be taken, the r with the smallest indices are the
-//   first r in array order: a count of the examples with score T per 1024 examples and the sum of the
-//   counts before them (taken by the compaction itself, above 4096 such groups by a scan launch) give
-//   every such example its position among them;
-//   2. compact all selected keys (exactly k_sel of them; one atomic per workgroup and 1024 examples);
+//   1. find the k_sel-th largest score, to a digit that leaves few keys too many.  Up to 16384 scores one workgroup holds all of them in
+//   registers and does this and the compaction in a single launch (topk_select_one_kernel); above that, one histogram launch for each of
+//   the three digits (10, 11 and 11 bits) of the score, whose workgroups each first pick the digit of the pass before from its finished
+//   histogram (a scan of its bins, cheaper than a launch of its own); the passes stop as soon as the keys from the bucket of
+//   the k_sel-th key on are no more than the ordering takes along (it drops those behind the k_sel-th).  If the threshold score T is
+//   shared by more examples than that, the r with the smallest indices are the first r in array order: a count of the examples with
+//   score T per 1024 examples and the sum of the counts before them (taken where it is needed, above 4096 such groups by a scan
+//   launch) give every such example its position among them, and that is its place behind all keys above T;
+//   2. compact the keys above the threshold (one atomic per workgroup and 1024 examples);
 //   3. order them, descending: up to 16384 selected keys by rank (every key counts the larger ones
 //   among all of them, k_sel^2 comparisons spread over the whole chip, and its index and score go to the slot of
 //   its rank: one launch); above that, a bitonic network (LDS spans of 4096 keys with global
@@ -58,8 +57,8 @@ struct SelectState {
     unsigned long long prefix;     // high digits of the threshold found so far
     unsigned long long remaining;  // rank still to locate inside the current prefix bucket
     unsigned int count;            // compaction cursor (of the last state only)
-    unsigned int done;             // the threshold is final: later passes return at once
-    unsigned long long pad_;       // 32 bytes per state
+    unsigned int done;             // the threshold is final (the keys from `prefix` on are compacted): later passes return at once
+    unsigned long long take;       // keys that the ordering is given before the examples at the threshold score: 32 bytes per state
 };
 
 __device__ inline uint32_t order_key(float f) {
@@ -72,26 +71,45 @@ __device__ inline unsigned long long make_key(float sc, int64_t i) {
     return ((unsigned long long)order_key(sc) << 32) | (0xFFFFFFFFull - (unsigned long long)i);
 }
 
-// state[0] = nothing chosen yet; all histograms and the compaction cursor (state[kPasses].count) cleared
-__global__ void __launch_bounds__(256) topk_init_kernel(unsigned int *hist, SelectState *state, unsigned long long k_sel) {
+// state[0] = nothing chosen yet; the histograms from bin `from` on and the compaction cursor (state[kPasses].count) cleared by a workgroup
+__device__ inline void clear_states(unsigned int *hist, int from, SelectState *state, unsigned long long k_sel) {
     if (threadIdx.x == 0) {
-        state[0].prefix = 0; state[0].remaining = k_sel; state[0].count = 0; state[0].done = 0;
+        state[0].prefix = 0; state[0].remaining = k_sel; state[0].count = 0; state[0].done = 0; state[0].take = 0;
         state[kPasses].count = 0;
     }
-    for (int i = threadIdx.x; i < kHistBins; i += 256) hist[i] = 0;
+    for (int i = from + threadIdx.x; i < kHistBins; i += blockDim.x) hist[i] = 0;
+}
+__global__ void __launch_bounds__(256) topk_init_kernel(unsigned int *hist, SelectState *state, unsigned long long k_sel) {
+    clear_states(hist, 0, state, k_sel);
 }
 
 // The digit that holds the remaining rank `rem`, walking the B bins of a finished histogram from the top, in a workgroup of 256 threads.
+// Of the first digit there may be `parts` histograms of 16-bit counts instead, one of each workgroup, to be added.
 // The thread of that digit returns it, with the rank left inside its bin and the bin's count; the others return -1.  If no bin
 // reaches the rank the digit is 0.  `part` is LDS scratch of four entries.  All threads call it.
 template <int B>
-__device__ inline int pick_digit(const unsigned int *bins, unsigned long long *part, unsigned long long rem, unsigned long long &left, unsigned int &count) {
+__device__ inline int pick_digit(const unsigned int *bins, int parts, unsigned long long *part, unsigned long long rem, unsigned long long &left, unsigned int &count) {
     constexpr int P = B / 256;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, top = B - 1 - P * (int)threadIdx.x;      // thread 0 has the highest bins
     unsigned int c[P];
     unsigned long long sum = 0;
+    if (P == 4 && parts) {                              // uniform
 #pragma unroll
-    for (int q = 0; q < P; ++q) { c[q] = bins[top - q]; sum += c[q]; }
+        for (int q = 0; q < P; ++q) c[q] = 0;
+        for (int w0 = 0; w0 < parts; w0 += 8) {
+            uint2 t[8];
+#pragma unroll
+            for (int w = 0; w < 8; ++w) t[w] = *(const uint2 *)((const unsigned short *)bins + (w0 + w < parts ? w0 + w : 0) * B + top - 3);
+#pragma unroll
+            for (int w = 0; w < 8; ++w)
+                if (w0 + w < parts) { c[0] += t[w].y >> 16; c[1] += t[w].y & 0xFFFFu; c[2] += t[w].x >> 16; c[3] += t[w].x & 0xFFFFu; }
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < P; ++q) c[q] = bins[top - q];
+    }
+#pragma unroll
+    for (int q = 0; q < P; ++q) sum += c[q];
     unsigned long long upto = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -245,59 +263,66 @@ topk_select_one_kernel(const float *score, int N, unsigned int k_sel, unsigned l
 // histogram), computed by every thread of a 256-thread workgroup alike; workgroup 0 also records
 // it in state[PASS + 1].  `part` and `sh` are LDS scratch.
 template <int PASS>
-__device__ inline SelectState next_state(SelectState *state, const unsigned int *hist, unsigned long long *part, SelectState *sh) {
+__device__ inline SelectState next_state(SelectState *state, const unsigned int *bins, int parts, unsigned int extra, unsigned long long *part, SelectState *sh) {
     const SelectState before = state[PASS];
     if (before.done) {                              // uniform
-        if (blockIdx.x == 0 && threadIdx.x == 0) { state[PASS + 1].prefix = before.prefix; state[PASS + 1].remaining = before.remaining; state[PASS + 1].done = 1; }
+        if (blockIdx.x == 0 && threadIdx.x == 0) { state[PASS + 1].prefix = before.prefix; state[PASS + 1].remaining = before.remaining; state[PASS + 1].done = 1; state[PASS + 1].take = before.take; }
         return before;
     }
     unsigned long long left = 0;
     unsigned int count = 0;
-    const int digit = pick_digit<1 << kDigitBits[PASS]>(hist + kHistAt[PASS], part, before.remaining, left, count);
+    const int digit = pick_digit<1 << kDigitBits[PASS]>(bins, parts, part, before.remaining, left, count);
     if (digit >= 0) {
         sh->prefix = before.prefix | ((unsigned long long)digit << kDigitShift[PASS]);
         sh->remaining = left;
-        sh->done = left == (unsigned long long)count;   // the whole bucket is selected: the prefix with zeros below is the threshold
+        // at most `extra` keys of the bucket are not wanted: all of it is taken, the prefix with zeros below is the threshold
+        sh->done = count - left <= (unsigned long long)extra;
+        sh->take = before.take + before.remaining - left + (sh->done ? count : 0u);
     }
     __syncthreads();
     SelectState after = *sh;
     after.count = 0;
     __syncthreads();
-    if (blockIdx.x == 0 && threadIdx.x == 0) { state[PASS + 1].prefix = after.prefix; state[PASS + 1].remaining = after.remaining; state[PASS + 1].done = after.done; }
+    if (blockIdx.x == 0 && threadIdx.x == 0) { state[PASS + 1].prefix = after.prefix; state[PASS + 1].remaining = after.remaining; state[PASS + 1].done = after.done; state[PASS + 1].take = after.take; }
     return after;
 }
 
-constexpr int kHistPer = 8;                         // examples per thread and round of the histogram
-// histogram of digit PASS (0 = most significant) over keys whose higher digits equal the prefix
-// chosen so far; the pick of the pass before is done here first, by every workgroup for itself
-template <int PASS>
-__global__ void __launch_bounds__(256)
-topk_hist_kernel(const float *score, int64_t N, SelectState *state, unsigned int *hist) {
-    constexpr int B = 1 << kDigitBits[PASS], shift = kDigitShift[PASS];
+// Histogram of digit PASS (0 = most significant) over keys whose higher digits equal the prefix chosen so far; the pick of the pass before
+// is done here first, by every workgroup for itself.  With PARTS there are few workgroups in the first pass: each stores a histogram of its
+// own (16-bit counts, in the place of the selected keys, that the second pass adds), so that nothing has to be cleared by a launch before
+// it, and the first one clears what the launches behind it count into.
+template <int PASS, bool PARTS>
+__global__ void __launch_bounds__(PASS == 0 && PARTS ? 1024 : 256)
+topk_hist_kernel(const float *score, int64_t N, SelectState *state, unsigned int *hist, unsigned int *parts, int nparts, unsigned int extra,
+                 unsigned long long k_sel) {
+    constexpr int B = 1 << kDigitBits[PASS], shift = kDigitShift[PASS], T = PASS == 0 && PARTS ? 1024 : 256, PER = PASS == 0 && PARTS ? 4 : 8;
     __shared__ unsigned int h[B];
     __shared__ unsigned long long part[4];
     __shared__ SelectState sh;
     SelectState cur;
-    if constexpr (PASS == 0) cur = state[0];
-    else cur = next_state<PASS - 1>(state, hist, part, &sh);
+    if constexpr (PASS == 0) {
+        if (PARTS) { cur.prefix = 0; cur.done = 0; if (blockIdx.x == 0) clear_states(hist, kHistAt[1], state, k_sel); }
+        else cur = state[0];
+    } else if constexpr (PASS == 1 && PARTS) cur = next_state<0>(state, parts, nparts, extra, part, &sh);
+    else cur = next_state<PASS - 1>(state, hist + kHistAt[PASS - 1], 0, extra, part, &sh);
     if (cur.done) return;                           // uniform
-    for (int i = threadIdx.x; i < B; i += 256) h[i] = 0;
+    for (int i = threadIdx.x; i < B; i += T) h[i] = 0;
     __syncthreads();
     const unsigned long long prefix = cur.prefix;
     // bits above the current digit: pass 0 has none (mask 0), later passes compare them all
     constexpr unsigned long long himask = PASS == 0 ? 0ull : (~0ull << (shift + kDigitBits[PASS]) % 64);
-    // a workgroup takes kHistPer * 256 consecutive examples at a time (few workgroups: every one of them ends
-    // with an atomic on every bin it has counted into), kHistPer loads in flight per thread
-    for (int64_t c0 = (int64_t)blockIdx.x * (256 * kHistPer); c0 < N; c0 += (int64_t)gridDim.x * (256 * kHistPer)) {   // uniform
-        float v[kHistPer];
+    // a workgroup takes PER * T consecutive examples at a time (few workgroups: every one of them ends
+    // with an atomic on every bin it has counted into), PER loads in flight per thread
+    for (int64_t c0 = (int64_t)blockIdx.x * (T * PER); c0 < N; c0 += (int64_t)gridDim.x * (T * PER)) {   // uniform
+        float v[PER];
 #pragma unroll
-        for (int u = 0; u < kHistPer; ++u) {
-            const int64_t i = c0 + u * 256 + threadIdx.x;
+        for (int u = 0; u < PER; ++u) {
+            const int64_t i = c0 + u * T + threadIdx.x;
             v[u] = i < N ? score[i] : 0.0f;
         }
 #pragma unroll
-        for (int u = 0; u < kHistPer; ++u) {
-            const int64_t i = c0 + u * 256 + threadIdx.x;
+        for (int u = 0; u < PER; ++u) {
+            const int64_t i = c0 + u * T + threadIdx.x;
             const unsigned long long key = make_key(v[u], i);
             const bool match = i < N && ((key ^ prefix) & himask) == 0;
             const unsigned int d = (unsigned int)(key >> shift) & (unsigned int)(B - 1);
@@ -314,124 +339,72 @@ topk_hist_kernel(const float *score, int64_t N, SelectState *state, unsigned int
         }
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < B; i += 256)
-        if (h[i]) atomicAdd(&hist[kHistAt[PASS] + i], h[i]);
+    if (PASS == 0 && PARTS) {
+        for (int i = threadIdx.x; i < B / 2; i += T) parts[blockIdx.x * (B / 2) + i] = h[2 * i] | h[2 * i + 1] << 16;
+    } else {
+        for (int i = threadIdx.x; i < B; i += T)
+            if (h[i]) atomicAdd(&hist[kHistAt[PASS] + i], h[i]);
+    }
 }
 
 constexpr int kCompactPer = 4;                      // examples per thread and round
 constexpr int kChunk = 256 * kCompactPer;           // examples per round of a workgroup
 
-// The selected keys (exactly k_sel of them) are gathered in any order; the slots from k_sel to
-// padded are cleared.  A workgroup takes kChunk consecutive examples at a time and one
-// atomic for all it selects among them.  Selected: key >= threshold key when the selection ended
-// with a whole bucket; otherwise score above the threshold score T, or equal to it and among the
-// first `remaining` such examples in array order (`ties` holds how many precede each group).  All threads of a 256-thread workgroup call it.
-__device__ inline void
-compact(const SelectState &fin, const float *score, int64_t N, unsigned int *cursor, const unsigned int *ties, int scanned,
-        unsigned long long *sel, int64_t k_sel, int64_t padded) {
-    __shared__ unsigned int before[4];
+// After the last histogram: picks its digit and gathers the keys above the threshold (or from it on, if its bucket is taken whole) in any
+// order; the slots behind what is ordered are cleared up to `padded`.  A workgroup takes kChunk consecutive examples at a time
+// and one atomic for all it selects among them.  If the threshold score's examples are taken by position, those of each group are counted.
+__global__ void __launch_bounds__(256)
+topk_finish_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *hist, unsigned int extra,
+                   unsigned int *ties, unsigned long long *sel, int64_t k_sel, int64_t slots, int64_t padded) {
+    __shared__ unsigned long long part[4];
+    __shared__ SelectState sh;
     __shared__ unsigned int offs[4 * kCompactPer + 1];
-    __shared__ unsigned int toffs[4 * kCompactPer];
+    __shared__ unsigned int cnt;
+    const SelectState fin = next_state<kPasses - 1>(state, hist + kHistAt[kPasses - 1], 0, extra, part, &sh);
     const bool by_position = !fin.done;             // uniform
     const unsigned long long thr = by_position ? (fin.prefix | 0xFFFFFFFFull) + 1ull : fin.prefix;   // T + 1 in the score half
     const bool none_above = by_position && thr == 0ull;     // T is the largest score key: nothing lies above it
     const uint32_t T = (uint32_t)(fin.prefix >> 32);
+    const int64_t used = by_position ? k_sel : (int64_t)fin.take;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t span = N > padded ? N : padded;
     for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < span; c0 += (int64_t)gridDim.x * kChunk) {   // uniform per workgroup
-        unsigned long long key[kCompactPer], mask[kCompactPer], tmask[kCompactPer];
-        bool take[kCompactPer], tie[kCompactPer];
+        unsigned long long key[kCompactPer], mask[kCompactPer];
+        bool take[kCompactPer];
+        unsigned int same = 0;
+        if (threadIdx.x == 0) cnt = 0;
 #pragma unroll
         for (int u = 0; u < kCompactPer; ++u) {
             const int64_t i = c0 + u * 256 + threadIdx.x;
-            if (i >= k_sel && i < padded) sel[i] = 0;   // padding sorts last (real keys are > 0)
-            key[u] = 0; take[u] = false; tie[u] = false;
+            if (i >= used && i < padded) sel[i] = 0;   // padding sorts last (real keys are > 0)
+            key[u] = 0; take[u] = false;
+            bool tie = false;
             if (i < N) {
                 key[u] = make_key(score[i], i);
                 take[u] = !none_above && key[u] >= thr;
-                tie[u] = by_position && (uint32_t)(key[u] >> 32) == T;
+                tie = by_position && (uint32_t)(key[u] >> 32) == T;
             }
-        }
-        if (by_position) {
-            // position of every example with the threshold score among all of them, in array order
-            // (element u * 256 + 64 * wave + lane of the group: order by u, then wave, then lane)
-#pragma unroll
-            for (int u = 0; u < kCompactPer; ++u) {
-                tmask[u] = __ballot(tie[u]);
-                if (lane == 0) toffs[u * 4 + wave] = (unsigned int)__popcll(tmask[u]);
-            }
-            // ties in the groups before this one: from the scan, or summed here
-            if (!scanned && c0 < N) {
-                unsigned int mine = 0;
-                for (int64_t g = threadIdx.x; g < c0 / kChunk; g += 256) mine += ties[g];
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o, 64);
-                if (lane == 0) before[wave] = mine;
-            }
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                unsigned int run = c0 >= N ? 0u : (scanned ? ties[c0 / kChunk] : before[0] + before[1] + before[2] + before[3]);
-                for (int q = 0; q < 4 * kCompactPer; ++q) { const unsigned int v = toffs[q]; toffs[q] = run; run += v; }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < kCompactPer; ++u) {
-                const unsigned long long pos = (unsigned long long)toffs[u * 4 + wave] +
-                                               (unsigned long long)__popcll(tmask[u] & ((1ull << lane) - 1ull));
-                if (tie[u] && pos < fin.remaining) take[u] = true;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kCompactPer; ++u) {
             mask[u] = __ballot(take[u]);
+            same += (unsigned int)__popcll(__ballot(tie));
             if (lane == 0) offs[wave * kCompactPer + u] = (unsigned int)__popcll(mask[u]);
         }
         __syncthreads();
+        if (lane == 0 && same) atomicAdd(&cnt, same);
         if (threadIdx.x == 0) {                      // exclusive prefix over the 16 counts, then one atomic
             unsigned int run = 0;
             for (int q = 0; q < 4 * kCompactPer; ++q) { const unsigned int v = offs[q]; offs[q] = run; run += v; }
-            offs[4 * kCompactPer] = run ? atomicAdd(cursor, run) : 0u;
+            offs[4 * kCompactPer] = run ? atomicAdd(&state[kPasses].count, run) : 0u;
         }
         __syncthreads();
+        if (by_position && threadIdx.x == 0 && c0 < N) ties[c0 / kChunk] = cnt;
         const unsigned int wgbase = offs[4 * kCompactPer];
 #pragma unroll
         for (int u = 0; u < kCompactPer; ++u) {
             const unsigned int pos = wgbase + offs[wave * kCompactPer + u] +
                                      (unsigned int)__popcll(mask[u] & ((1ull << lane) - 1ull));
-            if (take[u] && (int64_t)pos < k_sel) sel[pos] = key[u];
+            if (take[u] && (int64_t)pos < slots) sel[pos] = key[u];
         }
-        __syncthreads();                             // offs and toffs are reused by the next round
-    }
-}
-
-// After the last histogram: picks its digit; if the threshold bucket is taken whole (few scores are shared), compacts at once, so that the
-// launches behind it have nothing to do; else counts the examples whose score is the threshold score in every group of kChunk examples.
-__global__ void __launch_bounds__(256)
-topk_finish_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *hist,
-                   unsigned int *ties, unsigned long long *sel, int64_t k_sel, int64_t padded) {
-    __shared__ unsigned long long part[4];
-    __shared__ SelectState sh;
-    __shared__ unsigned int cnt;
-    const SelectState fin = next_state<kPasses - 1>(state, hist, part, &sh);
-    if (fin.done) {                                 // uniform
-        compact(fin, score, N, &state[kPasses].count, nullptr, 0, sel, k_sel, padded);
-        return;
-    }
-    const uint32_t T = (uint32_t)(fin.prefix >> 32);
-    for (int64_t c0 = (int64_t)blockIdx.x * kChunk; c0 < N; c0 += (int64_t)gridDim.x * kChunk) {
-        if (threadIdx.x == 0) cnt = 0;
-        __syncthreads();
-        unsigned int mine = 0;
-#pragma unroll
-        for (int u = 0; u < kCompactPer; ++u) {
-            const int64_t i = c0 + u * 256 + threadIdx.x;
-            const bool tie = i < N && order_key(score[i]) == T;
-            mine += (unsigned int)__popcll(__ballot(tie));
-        }
-        if ((threadIdx.x & 63) == 0 && mine) atomicAdd(&cnt, mine);
-        __syncthreads();
-        if (threadIdx.x == 0) ties[c0 / kChunk] = cnt;
-        __syncthreads();
+        __syncthreads();                             // offs and cnt are reused by the next round
     }
 }
 
@@ -462,13 +435,43 @@ topk_tie_scan_kernel(const SelectState *state, unsigned int *ties, int64_t chunk
     }
 }
 
-// The compaction where the threshold score is shared by more examples than are still to be taken
-__global__ void __launch_bounds__(256)
-topk_compact_ties_kernel(const float *score, int64_t N, SelectState *state, const unsigned int *ties, int scanned,
-                         unsigned long long *sel, int64_t k_sel, int64_t padded) {
+// The first `remaining` examples with the threshold score, in array order: place(position, index, score) for each, by the workgroups of 1024
+// threads of a grid.  `ties` holds the counts per group of kChunk examples, summed over the groups before it (scanned) or not.
+template <class F>
+__device__ inline void each_tie(const SelectState &fin, const float *score, int64_t N, const unsigned int *ties, int scanned, F place) {
+    __shared__ unsigned int part[16];
+    __shared__ unsigned int base;
+    static_assert(kChunk == 1024, "one example per thread");
+    const uint32_t T = (uint32_t)(fin.prefix >> 32);
+    const int64_t chunks = (N + kChunk - 1) / kChunk;
+    for (int64_t c = blockIdx.x; c < chunks; c += gridDim.x) {     // uniform
+        if (threadIdx.x == 0) base = scanned ? ties[c] : 0u;
+        __syncthreads();
+        if (!scanned) {
+            unsigned int mine = 0;
+            for (int64_t g = threadIdx.x; g < c; g += 1024) mine += ties[g];
+            if (mine) atomicAdd(&base, mine);
+        }
+        __syncthreads();
+        const unsigned long long first = base;
+        if (first >= fin.remaining) return;          // uniform; later groups have more before them
+        const int64_t i = c * kChunk + threadIdx.x;
+        const float f = score[i < N ? i : N - 1];
+        const bool tie = i < N && order_key(f) == T;
+        const unsigned long long pos = first + block_scan(tie ? 1u : 0u, part) - 1ull;
+        if (tie && pos < fin.remaining) place((int64_t)pos, i, f);
+    }
+}
+
+// Where the selected keys are sorted: the examples with the threshold score behind those above it
+__global__ void __launch_bounds__(1024)
+topk_ties_kernel(const float *score, int64_t N, const SelectState *state, const unsigned int *ties, int scanned,
+                 unsigned long long *sel, int64_t k_sel) {
     const SelectState fin = state[kPasses];
     if (fin.done) return;                           // uniform
-    compact(fin, score, N, &state[kPasses].count, ties, scanned, sel, k_sel, padded);
+    each_tie(fin, score, N, ties, scanned, [&](int64_t pos, int64_t i, float f) {
+        if ((int64_t)fin.take + pos < k_sel) sel[fin.take + pos] = make_key(f, i);
+    });
 }
 
 // Rank of every selected key = how many selected keys are larger (keys are distinct); its index and score go to the slot of that rank.
@@ -476,35 +479,56 @@ topk_compact_ties_kernel(const float *score, int64_t N, SelectState *state, cons
 // 4096 at a time and read by all lanes of a half at once (a broadcast), and the counts are joined in LDS.  k_sel^2 comparisons: for k_sel <=
 // kSortOne only.  (Two launches, counts joined by global atomics, then written out: 3276 of 65536 2 us more; 64 keys to a workgroup leave
 // half the chip idle there.)
-__global__ void __launch_bounds__(1024)
-topk_rank_kernel(const unsigned long long *sel, int k_sel, const float *score, int64_t N, int64_t *idx, float *val) {
+// With a state (of a selection by launches) it says how many keys there are: those that a bucket held behind the k_sel-th are dropped, and
+// examples with the threshold score that are taken by position go behind the others, without a rank.
+// (Eight wavefronts per SIMD, two workgroups per compute unit: with one scalar register too many for that 16384 keys took 34 us instead of 27.)
+__global__ void __launch_bounds__(1024, 8)
+topk_rank_kernel(const unsigned long long *sel, int k_sel, int slots, const SelectState *state, const unsigned int *ties, int scanned,
+                 const float *score, int64_t N, int64_t *idx, float *val) {
     __shared__ __attribute__((aligned(16))) unsigned long long tile[4096];
     __shared__ unsigned int larger[32][32];
     const int lane = threadIdx.x & 31, part = threadIdx.x >> 5, mine_at = (int)blockIdx.x * 32 + lane;
-    const unsigned long long mine = mine_at < k_sel ? sel[mine_at] : ~0ull;
-    unsigned int cnt = 0;
-    for (int jb = 0; jb < k_sel; jb += 4096) {
-        const int n = k_sel - jb < 4096 ? k_sel - jb : 4096, share = (n + 63) / 64 * 2;       // keys per half, a multiple of two
-        __syncthreads();
-        for (int t = threadIdx.x; t < 32 * share; t += 1024) tile[t] = t < n ? sel[jb + t] : 0ull;   // 0 is below every key
-        __syncthreads();
-        const int t0 = part * share;
+    SelectState fin;
+    int keys = k_sel;
+    if (state) {
+        fin = state[kPasses];
+        keys = fin.take < (unsigned long long)slots ? (int)fin.take : slots;
+    }
+    if ((int)blockIdx.x * 32 < keys) {              // uniform
+        const unsigned long long mine = mine_at < keys ? sel[mine_at] : ~0ull;
+        unsigned int cnt = 0;
+        for (int jb = 0; jb < keys; jb += 4096) {
+            const int n = keys - jb < 4096 ? keys - jb : 4096, share = (n + 63) / 64 * 2;     // keys per half, a multiple of two
+            __syncthreads();
+            for (int t = threadIdx.x; t < 32 * share; t += 1024) tile[t] = t < n ? sel[jb + t] : 0ull;   // 0 is below every key
+            __syncthreads();
+            const int t0 = part * share;
 #pragma unroll 8
-        for (int t = 0; t < share; t += 2) {
-            const ulonglong2 pr = *(const ulonglong2 *)&tile[t0 + t];
-            cnt += (pr.x > mine) + (pr.y > mine);
+            for (int t = 0; t < share; t += 2) {
+                const ulonglong2 pr = *(const ulonglong2 *)&tile[t0 + t];
+                cnt += (pr.x > mine) + (pr.y > mine);
+            }
+        }
+        larger[part][lane] = cnt;
+        __syncthreads();
+        if (part == 0 && mine_at < keys) {
+#pragma unroll
+            for (int q = 1; q < 32; ++q) cnt += larger[q][lane];
+            const int64_t i = (int64_t)(0xFFFFFFFFull - (mine & 0xFFFFFFFFull));
+            if (cnt < (unsigned int)k_sel) {
+                idx[cnt] = i;
+                const uint32_t s = (uint32_t)(mine >> 32);          // the score's bits, but for the sign of a zero
+                if (val) val[cnt] = s == 0x80000000u ? score[i < N ? i : N - 1] : __uint_as_float(s & 0x80000000u ? s & 0x7FFFFFFFu : ~s);
+            }
         }
     }
-    larger[part][lane] = cnt;
-    __syncthreads();
-    if (part != 0 || mine_at >= k_sel) return;
-#pragma unroll
-    for (int q = 1; q < 32; ++q) cnt += larger[q][lane];
-    const int64_t i = (int64_t)(0xFFFFFFFFull - (mine & 0xFFFFFFFFull));
-    if (cnt >= (unsigned int)k_sel) return;          // cannot happen with distinct keys
-    idx[cnt] = i;
-    const uint32_t s = (uint32_t)(mine >> 32);          // the score's bits, but for the sign of a zero
-    if (val) val[cnt] = s == 0x80000000u ? score[i < N ? i : N - 1] : __uint_as_float(s & 0x80000000u ? s & 0x7FFFFFFFu : ~s);
+    if (!state || fin.done) return;                 // uniform
+    each_tie(fin, score, N, ties, scanned, [&](int64_t pos, int64_t i, float f) {
+        const int64_t at = keys + pos;
+        if (at >= k_sel) return;
+        idx[at] = i;
+        if (val) val[at] = f;
+    });
 }
 
 // Bitonic network, descending.  Stage size kk (sub-sequence length), step jj (partner distance).
@@ -587,30 +611,50 @@ static qless_status topk_run(const float *score, int64_t N, int64_t k_sel, int64
     unsigned int *ties = (unsigned int *)(w + p.off_ties);
 
     auto blocks_for = [](int64_t n) { int64_t b = (n + 255) / 256; if (b < 1) b = 1; if (b > 2048) b = 2048; return (unsigned)b; };
-    if (N <= kSelectOneMax) {
-        const auto one = N <= 4096 ? topk_select_one_kernel<4> : (N <= 8192 ? topk_select_one_kernel<8> : topk_select_one_kernel<16>);
-        hipLaunchKernelGGL(one, dim3(1), dim3(1024), 0, st, score, (int)N, (unsigned int)k_sel, sel, (int)p.padded);
+    const bool ranked = p.padded <= kSortOne, one = N <= kSelectOneMax;
+    // up to 2^22 scores (4096 groups of 1024) the counts of the groups before one are summed where they are needed: a launch less
+    const bool scan = p.chunks > 4096;
+    // keys behind the k_sel-th that are ordered with the others, so that fewer digits tell: ranking takes the square of the keys, sorting the padded number
+    int64_t extra = ranked && k_sel / 16 > 256 ? k_sel / 16 : 256;
+    if (!ranked || extra > p.padded - k_sel) extra = p.padded - k_sel;
+    if (one) {
+        const auto select = N <= 4096 ? topk_select_one_kernel<4> : (N <= 8192 ? topk_select_one_kernel<8> : topk_select_one_kernel<16>);
+        hipLaunchKernelGGL(select, dim3(1), dim3(1024), 0, st, score, (int)N, (unsigned int)k_sel, sel, (int)p.padded);
     } else {
-        hipLaunchKernelGGL(topk_init_kernel, dim3(1), dim3(256), 0, st, hist, state, (unsigned long long)k_sel);
-        int64_t hblocks = (N + 256 * kHistPer - 1) / (256 * kHistPer);
+        const unsigned long long want = (unsigned long long)k_sel;
+        const unsigned ex = (unsigned)extra;
+        // a histogram per workgroup of the first pass (2 KB, where the selected keys go later) if that leaves none more than two rounds of
+        // 4096 scores, so that its counts fit 16 bits and few are added; else by atomics into one that a launch clears (first two passes of
+        // 65536 scores: that launch, 3.8 and 5.1 us; without it 4.4 and 6.4)
+        int64_t nparts = (N + 8191) / 8192;
+        if (nparts > p.padded / 256) nparts = p.padded / 256;
+        unsigned int *parts = (unsigned int *)sel;
+        int64_t hblocks = (N + 2047) / 2048;
         if (hblocks > 2048) hblocks = 2048;
-        hipLaunchKernelGGL(topk_hist_kernel<0>, dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist);
-        hipLaunchKernelGGL(topk_hist_kernel<1>, dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist);
-        hipLaunchKernelGGL(topk_hist_kernel<2>, dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist);
-        const int64_t span = N > p.padded ? N : p.padded;
+        if (N <= nparts * 8192) {
+            hipLaunchKernelGGL((topk_hist_kernel<0, true>), dim3((unsigned)nparts), dim3(1024), 0, st, score, N, state, hist, parts, 0, ex, want);
+            hipLaunchKernelGGL((topk_hist_kernel<1, true>), dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist, parts, (int)nparts, ex, want);
+        } else {
+            hipLaunchKernelGGL(topk_init_kernel, dim3(1), dim3(256), 0, st, hist, state, want);
+            hipLaunchKernelGGL((topk_hist_kernel<0, false>), dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist, parts, 0, ex, want);
+            hipLaunchKernelGGL((topk_hist_kernel<1, false>), dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist, parts, 0, ex, want);
+        }
+        hipLaunchKernelGGL((topk_hist_kernel<2, false>), dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist, parts, 0, ex, want);
+        const int64_t clear = ranked ? 0 : p.padded, span = N > clear ? N : clear;
         int64_t cblocks = (span + kChunk - 1) / kChunk;
         if (cblocks > 2048) cblocks = 2048;
-        // up to 2^22 scores (4096 groups of 1024) the compaction sums the counts of the groups before its own itself: a launch less
-        const bool scan = p.chunks > 4096;
         hipLaunchKernelGGL(topk_finish_kernel, dim3((unsigned)cblocks), dim3(256), 0, st, score, N, state,
-                           (const unsigned int *)hist, ties, sel, k_sel, p.padded);
+                           (const unsigned int *)hist, ex, ties, sel, k_sel, p.padded, clear);
         if (scan) hipLaunchKernelGGL(topk_tie_scan_kernel, dim3(1), dim3(1024), 0, st, (const SelectState *)state, ties, p.chunks);
-        hipLaunchKernelGGL(topk_compact_ties_kernel, dim3((unsigned)cblocks), dim3(256), 0, st, score, N, state,
-                           (const unsigned int *)ties, scan ? 1 : 0, sel, k_sel, p.padded);
+        if (!ranked) hipLaunchKernelGGL(topk_ties_kernel, dim3((unsigned)(p.chunks < 512 ? p.chunks : 512)), dim3(1024), 0, st, score, N,
+                                        (const SelectState *)state, (const unsigned int *)ties, scan ? 1 : 0, sel, k_sel);
     }
-    if (p.padded <= kSortOne) {
-        hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)((k_sel + 31) / 32)), dim3(1024), 0, st, (const unsigned long long *)sel,
-                           (int)k_sel, score, N, idx, val);
+    if (ranked) {
+        const int64_t most = one ? k_sel : k_sel + extra;
+        int64_t rblocks = (most + 31) / 32;
+        if (!one && rblocks < p.chunks) rblocks = p.chunks < 256 ? p.chunks : (rblocks > 256 ? rblocks : 256);     // (groups of examples with the threshold score)
+        hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)rblocks), dim3(1024), 0, st, (const unsigned long long *)sel, (int)k_sel, (int)p.padded,
+                           one ? (const SelectState *)nullptr : (const SelectState *)state, (const unsigned int *)ties, scan ? 1 : 0, score, N, idx, val);
         return launch_status();
     }
     // many selected keys: sort them, descending, with a bitonic network
@@ -684,7 +728,7 @@ extern "C" qless_status qless_topk_noalloc(const float *score, int64_t N, int64_
     void *ws = nullptr;
     const qless_status rs = topk_scratch_address(&ws);
     if (rs != QLESS_OK) return rs;
-    // every word of the workspace that a launch reads is written earlier in the same call (init /
+    // every word of the workspace that a launch reads is written earlier in the same call (the first launch /
     // select kernels clear histograms, states and the cursor; the compaction clears padding;
     // the tie counts are written before they are scanned), so nothing of the call before survives
     return topk_run(score, N, k_sel, idx, val, ws, (hipStream_t)stream);
