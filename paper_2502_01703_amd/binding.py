@@ -83,7 +83,8 @@ def init():
 
 
 def _stream():
-    return _vp(torch.cuda.current_stream().cuda_stream)
+    # the current stream's handle itself: the Stream object around it costs 2.5 us of every call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _check(status, what):
@@ -99,9 +100,7 @@ def _dtype_code(t):
     raise TypeError("gradients must be float32 or bfloat16")
 
 
-def _ws(nbytes, device, ws=None):
-    if ws is not None:
-        return ws
+def _ws(nbytes, device):
     return torch.empty(max(int(nbytes), 16), dtype=torch.uint8, device=device)
 
 
@@ -118,24 +117,24 @@ def project(G, k, kind=RADEMACHER, seed=0, d_offset=0, out=None, accumulate=Fals
         out = torch.empty(n, k, dtype=torch.float32, device=G.device)
     assert out.is_cuda and out.dtype == torch.float32 and out.stride(1) == 1
     ldG = G.stride(0) if n > 1 else max(d, G.stride(0))
-    w = _ws(project_workspace(n, d, k), G.device, ws)
-    _check(lib().qless_project(_vp(G.data_ptr()), _dtype_code(G), n, d, ldG, d_offset, k, kind, seed,
-                               int(accumulate), _vp(out.data_ptr()),
+    w = _ws(project_workspace(n, d, k), G.device) if ws is None else ws
+    _check(lib().qless_project(G.data_ptr(), _dtype_code(G), n, d, ldG, d_offset, k, kind, seed,
+                               int(accumulate), out.data_ptr(),
                                out.stride(0) if n > 1 else max(k, out.stride(0)),
-                               _vp(w.data_ptr()), w.numel(), _stream()), "qless_project")
+                               w.data_ptr(), w.numel(), _stream()), "qless_project")
     return out
 
 
 def generator_words(seed, m0, nrows, w0, nwords, salt=0, device="cuda"):
     out = torch.empty(nrows, nwords, dtype=torch.int32, device=device)
-    _check(lib().qless_generator_words(seed, m0, nrows, w0, nwords, salt, _vp(out.data_ptr()), _stream()),
+    _check(lib().qless_generator_words(seed, m0, nrows, w0, nwords, salt, out.data_ptr(), _stream()),
            "qless_generator_words")
     return out
 
 
 def gaussian_table():
     buf = (_c.c_float * 256)()
-    _check(lib().qless_gaussian_table(_c.cast(buf, _vp)), "qless_gaussian_table")
+    _check(lib().qless_gaussian_table(buf), "qless_gaussian_table")
     return torch.tensor(list(buf), dtype=torch.float32)
 
 
@@ -156,8 +155,8 @@ def quantize(P, bits, codes=None, S=None, rnorm=None, absmean=False):
     if rnorm is None:
         rnorm = torch.empty(n, dtype=torch.float32, device=dev)
     fn = lib().qless_quantize_absmean if absmean else lib().qless_quantize
-    _check(fn(_vp(P.data_ptr()), P.stride(0) if n > 1 else max(k, P.stride(0)), n, k, bits,
-              _vp(codes.data_ptr()), _vp(S.data_ptr()), _vp(rnorm.data_ptr()), _stream()),
+    _check(fn(P.data_ptr(), P.stride(0) if n > 1 else max(k, P.stride(0)), n, k, bits,
+              codes.data_ptr(), S.data_ptr(), rnorm.data_ptr(), _stream()),
            "qless_quantize_absmean" if absmean else "qless_quantize")
     return codes, S, rnorm
 
@@ -172,11 +171,11 @@ def project_quantize(G, k, bits, kind=RADEMACHER, seed=0, d_offset=0, want_P=Fal
     rnorm = torch.empty(n, dtype=torch.float32, device=dev)
     P = torch.empty(n, k, dtype=torch.float32, device=dev) if want_P else None
     ldG = G.stride(0) if n > 1 else max(d, G.stride(0))
-    w = _ws(project_workspace(n, d, k), dev, ws)
-    _check(lib().qless_project_quantize(_vp(G.data_ptr()), _dtype_code(G), n, d, ldG, d_offset, k, kind, seed,
-                                        bits, _vp(codes.data_ptr()), _vp(S.data_ptr()), _vp(rnorm.data_ptr()),
-                                        _vp(P.data_ptr()) if want_P else None, k,
-                                        _vp(w.data_ptr()), w.numel(), _stream()), "qless_project_quantize")
+    w = _ws(project_workspace(n, d, k), dev) if ws is None else ws
+    _check(lib().qless_project_quantize(G.data_ptr(), _dtype_code(G), n, d, ldG, d_offset, k, kind, seed,
+                                        bits, codes.data_ptr(), S.data_ptr(), rnorm.data_ptr(),
+                                        P.data_ptr() if want_P else None, k,
+                                        w.data_ptr(), w.numel(), _stream()), "qless_project_quantize")
     return (codes, S, rnorm, P) if want_P else (codes, S, rnorm)
 
 
@@ -198,12 +197,12 @@ def project_quantize_slice(G, k, d_offset, P, first, last, bits=1, kind=RADEMACH
     ldG = G.stride(0) if n > 1 else max(d, G.stride(0))
     ldP = P.stride(0) if n > 1 else max(k, P.stride(0))
     ldO = 0 if P_other is None else (P_other.stride(0) if n > 1 else max(k, P_other.stride(0)))
-    w = _ws(project_workspace(n, d, k), dev, ws)
+    w = _ws(project_workspace(n, d, k), dev) if ws is None else ws
     _check(lib().qless_project_quantize_slice(
-        _vp(G.data_ptr()), _dtype_code(G), n, d, ldG, d_offset, k, kind, seed, int(first), int(last),
-        _vp(P.data_ptr()), ldP, _vp(P_other.data_ptr()) if P_other is not None else None, ldO, bits,
-        _vp(codes.data_ptr()) if last else None, _vp(S.data_ptr()) if last else None,
-        _vp(rnorm.data_ptr()) if last else None, _vp(w.data_ptr()), w.numel(), _stream()),
+        G.data_ptr(), _dtype_code(G), n, d, ldG, d_offset, k, kind, seed, int(first), int(last),
+        P.data_ptr(), ldP, P_other.data_ptr() if P_other is not None else None, ldO, bits,
+        codes.data_ptr() if last else None, S.data_ptr() if last else None,
+        rnorm.data_ptr() if last else None, w.data_ptr(), w.numel(), _stream()),
         "qless_project_quantize_slice")
     return (codes, S, rnorm) if last else None
 
@@ -232,12 +231,12 @@ def score(train_codes, train_rnorm, val_codes, val_rnorm, eta, k, bits, want_sco
     if want_full and full_out is None:
         full_out = torch.empty(N, M, dtype=torch.float32, device=dev)
     eta_arr = (_c.c_float * C)(*[float(e) for e in eta])
-    w = _ws(score_workspace(N, M, k, bits, C), dev, ws)
+    w = _ws(score_workspace(N, M, k, bits, C), dev) if ws is None else ws
     _check(lib().qless_score(_ptr_array(train_codes), _ptr_array(train_rnorm), _ptr_array(val_codes),
-                             _ptr_array(val_rnorm), _c.cast(eta_arr, _vp), C, N, M, k, bits,
-                             _vp(score_out.data_ptr()) if score_out is not None else None,
-                             _vp(full_out.data_ptr()) if full_out is not None else None,
-                             _vp(w.data_ptr()), w.numel(), _stream()), "qless_score")
+                             _ptr_array(val_rnorm), eta_arr, C, N, M, k, bits,
+                             score_out.data_ptr() if score_out is not None else None,
+                             full_out.data_ptr() if full_out is not None else None,
+                             w.data_ptr(), w.numel(), _stream()), "qless_score")
     if want_score and want_full:
         return score_out, full_out
     return score_out if want_score else full_out
@@ -250,8 +249,8 @@ def normalize16(P, out=None):
     if out is None:
         out = torch.empty(n, k, dtype=torch.bfloat16, device=P.device)
     assert out.is_cuda and out.dtype == torch.bfloat16 and out.is_contiguous()
-    _check(lib().qless_normalize16(_vp(P.data_ptr()), P.stride(0) if n > 1 else max(k, P.stride(0)), n, k,
-                                   _vp(out.data_ptr()), _stream()), "qless_normalize16")
+    _check(lib().qless_normalize16(P.data_ptr(), P.stride(0) if n > 1 else max(k, P.stride(0)), n, k,
+                                   out.data_ptr(), _stream()), "qless_normalize16")
     return out
 
 
@@ -271,11 +270,11 @@ def score16(train16, val16, eta, want_score=True, want_full=False, ws=None):
     score_out = torch.empty(N, dtype=torch.float32, device=dev) if want_score else None
     full_out = torch.empty(N, M, dtype=torch.float32, device=dev) if want_full else None
     eta_arr = (_c.c_float * C)(*[float(e) for e in eta])
-    w = _ws(score16_workspace(N, M, k, C), dev, ws)
-    _check(lib().qless_score16(_ptr_array(train16), _ptr_array(val16), _c.cast(eta_arr, _vp), C, N, M, k,
-                               _vp(score_out.data_ptr()) if want_score else None,
-                               _vp(full_out.data_ptr()) if want_full else None,
-                               _vp(w.data_ptr()), w.numel(), _stream()), "qless_score16")
+    w = _ws(score16_workspace(N, M, k, C), dev) if ws is None else ws
+    _check(lib().qless_score16(_ptr_array(train16), _ptr_array(val16), eta_arr, C, N, M, k,
+                               score_out.data_ptr() if want_score else None,
+                               full_out.data_ptr() if want_full else None,
+                               w.data_ptr(), w.numel(), _stream()), "qless_score16")
     if want_score and want_full:
         return score_out, full_out
     return score_out if want_score else full_out
@@ -298,12 +297,12 @@ def score_mixed(train_codes, train_rnorm, val16, eta, k, bits, want_score=True, 
     score_out = torch.empty(N, dtype=torch.float32, device=dev) if want_score else None
     full_out = torch.empty(N, M, dtype=torch.float32, device=dev) if want_full else None
     eta_arr = (_c.c_float * C)(*[float(e) for e in eta])
-    w = _ws(score_mixed_workspace(N, M, k, bits, C), dev, ws)
+    w = _ws(score_mixed_workspace(N, M, k, bits, C), dev) if ws is None else ws
     _check(lib().qless_score_mixed(_ptr_array(train_codes), _ptr_array(train_rnorm), _ptr_array(val16),
-                                   _c.cast(eta_arr, _vp), C, N, M, k, bits,
-                                   _vp(score_out.data_ptr()) if want_score else None,
-                                   _vp(full_out.data_ptr()) if want_full else None,
-                                   _vp(w.data_ptr()), w.numel(), _stream()), "qless_score_mixed")
+                                   eta_arr, C, N, M, k, bits,
+                                   score_out.data_ptr() if want_score else None,
+                                   full_out.data_ptr() if want_full else None,
+                                   w.data_ptr(), w.numel(), _stream()), "qless_score_mixed")
     if want_score and want_full:
         return score_out, full_out
     return score_out if want_score else full_out
@@ -320,9 +319,9 @@ def topk(score_vec, k_sel, want_val=True, ws=None):
     dev = score_vec.device
     idx = torch.empty(k_sel, dtype=torch.int64, device=dev)
     val = torch.empty(k_sel, dtype=torch.float32, device=dev) if want_val else None
-    w = _ws(topk_workspace(N, k_sel), dev, ws)
-    _check(lib().qless_topk(_vp(score_vec.data_ptr()), N, k_sel, _vp(idx.data_ptr()),
-                            _vp(val.data_ptr()) if want_val else None, _vp(w.data_ptr()), w.numel(),
+    w = _ws(topk_workspace(N, k_sel), dev) if ws is None else ws
+    _check(lib().qless_topk(score_vec.data_ptr(), N, k_sel, idx.data_ptr(),
+                            val.data_ptr() if want_val else None, w.data_ptr(), w.numel(),
                             _stream()), "qless_topk")
     return (idx, val) if want_val else idx
 
@@ -333,8 +332,8 @@ def topk_noalloc(score_vec, idx, val=None):
     assert score_vec.is_cuda and score_vec.dtype == torch.float32 and score_vec.is_contiguous()
     assert idx.is_cuda and idx.dtype == torch.int64 and idx.is_contiguous()
     assert val is None or (val.is_cuda and val.dtype == torch.float32 and val.numel() == idx.numel())
-    _check(lib().qless_topk_noalloc(_vp(score_vec.data_ptr()), score_vec.numel(), idx.numel(),
-                                    _vp(idx.data_ptr()), _vp(val.data_ptr()) if val is not None else None,
+    _check(lib().qless_topk_noalloc(score_vec.data_ptr(), score_vec.numel(), idx.numel(),
+                                    idx.data_ptr(), val.data_ptr() if val is not None else None,
                                     _stream()), "qless_topk_noalloc")
     return idx, val
 
@@ -349,8 +348,8 @@ def aggregate(full, group_end, mode=AGG_MAX, out=None):
     ge = (_c.c_int32 * len(group_end))(*[int(g) for g in group_end])
     if out is None:
         out = torch.empty(N, len(group_end), dtype=torch.float32, device=full.device)
-    _check(lib().qless_aggregate(_vp(full.data_ptr()), N, M, _c.cast(ge, _vp), len(group_end), mode,
-                                 _vp(out.data_ptr()), _stream()), "qless_aggregate")
+    _check(lib().qless_aggregate(full.data_ptr(), N, M, ge, len(group_end), mode,
+                                 out.data_ptr(), _stream()), "qless_aggregate")
     return out
 
 
@@ -369,9 +368,9 @@ def score_groups(train_codes, train_rnorm, val_codes, val_rnorm, eta, k, bits, g
     if out is None:
         out = torch.empty(N, T, dtype=torch.float32, device=dev)
     eta_arr = (_c.c_float * C)(*[float(e) for e in eta])
-    w = _ws(score_groups_workspace(N, M, k, bits, C), dev, ws)
+    w = _ws(score_groups_workspace(N, M, k, bits, C), dev) if ws is None else ws
     _check(lib().qless_score_groups(_ptr_array(train_codes), _ptr_array(train_rnorm), _ptr_array(val_codes),
-                                    _ptr_array(val_rnorm), _c.cast(eta_arr, _vp), C, N, M, k, bits,
-                                    _c.cast(ge, _vp), T, mode, _vp(out.data_ptr()), _vp(w.data_ptr()), w.numel(),
+                                    _ptr_array(val_rnorm), eta_arr, C, N, M, k, bits,
+                                    ge, T, mode, out.data_ptr(), w.data_ptr(), w.numel(),
                                     _stream()), "qless_score_groups")
     return out
