@@ -51,6 +51,18 @@ __device__ inline int quant1(float p, float scale, float alpha) {
     return (int)r;
 }
 
+template <int U>
+__device__ inline void add_planes(float4 &f, const float *p, size_t plane) {
+    float4 t[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) t[u] = *(const float4 *)(p + (size_t)u * plane);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        f.x = __fadd_rn(f.x, t[u].x); f.y = __fadd_rn(f.y, t[u].y);
+        f.z = __fadd_rn(f.z, t[u].z); f.w = __fadd_rn(f.w, t[u].w);
+    }
+}
+
 // Element ownership: thread t owns, for each group g, the E consecutive elements starting at
 // g * 256 * E + t * E with E = 4: one dword of codes (8-bit), one 16-bit word (4-bit) or one
 // nibble of plane bits OR-combined over 8 neighbouring lanes into a 32-bit plane word (2-/1-bit).
@@ -63,7 +75,7 @@ __device__ inline int quant1(float p, float scale, float alpha) {
 // SUM = false is the plain matrix (one plane): no loop, so a thread's loads go out back to back.
 // With an accumulator row `acc` the value is acc[m] + (that sum), and with a second one, `oth`, oth[m] is
 // added last (the sliced datastore build: slices accumulated in call order, two accumulators joined).
-template <int E, bool SUM>
+template <int E, bool SUM, int FLY = 4>
 __device__ inline void load_elems(const float *p, int base, int32_t k, bool vec, int nsplit, size_t plane,
                                   float (&v)[E], const float *acc = nullptr, const float *oth = nullptr) {
     const bool in = base < k;
@@ -73,22 +85,11 @@ __device__ inline void load_elems(const float *p, int base, int32_t k, bool vec,
 #pragma unroll
         for (int e = 0; e < E; e += 4) {
             float4 f = *(const float4 *)(p + b + e);
-            int s = 1;
-            for (; s + 4 <= nsplit; s += 4) {          // four planes in flight, added in plane order
-                float4 t[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) t[u] = *(const float4 *)(p + (size_t)(s + u) * plane + b + e);
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    f.x = __fadd_rn(f.x, t[u].x); f.y = __fadd_rn(f.y, t[u].y);
-                    f.z = __fadd_rn(f.z, t[u].z); f.w = __fadd_rn(f.w, t[u].w);
-                }
-            }
-            for (; s < nsplit; ++s) {
-                const float4 t = *(const float4 *)(p + (size_t)s * plane + b + e);
-                f.x = __fadd_rn(f.x, t.x); f.y = __fadd_rn(f.y, t.y);
-                f.z = __fadd_rn(f.z, t.z); f.w = __fadd_rn(f.w, t.w);
-            }
+            int s = 1;                                 // FLY planes in flight, added in plane order
+            for (; s + FLY <= nsplit; s += FLY) add_planes<FLY>(f, p + (size_t)s * plane + b + e, plane);
+            if (FLY > 4 && s + 4 <= nsplit) { add_planes<4>(f, p + (size_t)s * plane + b + e, plane); s += 4; }
+            if (s + 2 <= nsplit) { add_planes<2>(f, p + (size_t)s * plane + b + e, plane); s += 2; }
+            if (s < nsplit) add_planes<1>(f, p + (size_t)s * plane + b + e, plane);
             if (SUM && acc) {
                 const float4 t = *(const float4 *)(acc + b + e);
                 f.x = __fadd_rn(t.x, f.x); f.y = __fadd_rn(t.y, f.y);
@@ -184,18 +185,23 @@ __device__ inline void emit_elems(const float (&v)[E], int base, int32_t k, floa
 // MEAN selects the absmean variant (Sec. 5): the scale is 1 / mean|g| instead of alpha / max|g|, with
 // the mean taken in fixed point (32 fractional bits below the binary exponent of the row maximum), so
 // that it does not depend on the order of the additions.
-template <int BITS, int NG, bool SUM, bool MEAN = false>   // NG > 0: the row fits NG register groups per thread; NG == 0: re-read it
-__global__ void __launch_bounds__(kQThreads)
+// The sums of a projection's planes: there is a workgroup per row, and few rows leave most of the chip idle, so what counts is how many
+// loads a row has in flight: 1024 threads and eight planes at a time (the rest by four, two and one), where 256 threads and four planes were
+// before.  With the projection, 37 rows of 300000 into 4096 columns 108 -> 101 us, one of 400000 into 8192 148 -> 135, 20 of 50000 into 32768 181 -> 132.
+// Up to 1024 and 2048 columns 256 and 512 threads cover the row; more stand idle (1900 rows of 1088 5 us slower).
+template <int BITS, int NG, bool SUM, bool MEAN = false, int T = kQThreads>   // NG > 0: the row fits NG register groups per thread; NG == 0: re-read it
+__global__ void __launch_bounds__(T)
 quantize_kernel(const float *__restrict__ P, int64_t ldP, int32_t k, unsigned char *__restrict__ codes,
                 float *__restrict__ S_out, float *__restrict__ rnorm_out, int vec, int nsplit, size_t plane,
                 float *keep, int64_t ldK, const float *accum = nullptr, int64_t ldA = 0,
                 const float *other = nullptr, int64_t ldO = 0) {
     constexpr int E = 4;
-    constexpr int GROUP = kQThreads * E;
+    constexpr int WAVES = T / 64, FLY = SUM ? 8 : 4;
+    constexpr int GROUP = T * E;
     constexpr bool CACHED = NG > 0;
     constexpr int MAXG = CACHED ? NG : 1;
-    __shared__ float s_max[4];
-    __shared__ uint32_t s_sum[4];
+    __shared__ float s_max[WAVES];
+    __shared__ uint32_t s_sum[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t row = blockIdx.x;
     const float *p = P + row * ldP;
@@ -210,7 +216,7 @@ quantize_kernel(const float *__restrict__ P, int64_t ldP, int32_t k, unsigned ch
 #pragma unroll
         for (int g = 0; g < MAXG; ++g) {
             if (g < ngroups) {
-                load_elems<E, SUM>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[g], arow, orow);
+                load_elems<E, SUM, FLY>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[g], arow, orow);
                 if (SUM) keep_elems<E>(krow, g * GROUP + tid * E, k, vec != 0, reg[g]);
 #pragma unroll
                 for (int e = 0; e < E; ++e) amax = fmaxf(amax, fabsf(reg[g][e]));
@@ -218,7 +224,7 @@ quantize_kernel(const float *__restrict__ P, int64_t ldP, int32_t k, unsigned ch
         }
     } else {
         for (int g = 0; g < ngroups; ++g) {
-            load_elems<E, SUM>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[0], arow, orow);
+            load_elems<E, SUM, FLY>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[0], arow, orow);
             if (SUM) keep_elems<E>(krow, g * GROUP + tid * E, k, vec != 0, reg[0]);
 #pragma unroll
             for (int e = 0; e < E; ++e) amax = fmaxf(amax, fabsf(reg[0][e]));
@@ -227,10 +233,13 @@ quantize_kernel(const float *__restrict__ P, int64_t ldP, int32_t k, unsigned ch
     amax = wave_max(amax);
     if (lane == 0) s_max[wave] = amax;
     __syncthreads();
-    float S = fmaxf(fmaxf(s_max[0], s_max[1]), fmaxf(s_max[2], s_max[3]));
+    float S = s_max[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) S = fmaxf(S, s_max[w]);
     const float alpha = (float)((1 << (BITS - 1)) - 1);
     float scale = (BITS > 1 && S > 0.0f) ? __fdiv_rn(alpha, S) : 0.0f;
     if (MEAN) {
+        static_assert(!MEAN || WAVES == 4, "");
         __shared__ unsigned long long s_abs[4];
         int ex = 0;
         (void)frexpf(S, &ex);                                  // max|g| = f 2^ex, f in [0.5, 1)
@@ -245,7 +254,7 @@ quantize_kernel(const float *__restrict__ P, int64_t ldP, int32_t k, unsigned ch
                     }
             } else {
                 for (int g = 0; g < ngroups; ++g) {
-                    load_elems<E, SUM>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[0], arow, orow);
+                    load_elems<E, SUM, FLY>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[0], arow, orow);
 #pragma unroll
                     for (int e = 0; e < E; ++e) u += (uint32_t)ldexpf(fabsf(reg[0][e]), 32 - ex);
                 }
@@ -267,7 +276,7 @@ quantize_kernel(const float *__restrict__ P, int64_t ldP, int32_t k, unsigned ch
             if (g < ngroups) emit_elems<BITS, E>(reg[g], g * GROUP + tid * E, k, scale, alpha, crow, lane, n2);
     } else {
         for (int g = 0; g < ngroups; ++g) {
-            load_elems<E, SUM>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[0], arow, orow);
+            load_elems<E, SUM, FLY>(p, g * GROUP + tid * E, k, vec != 0, nsplit, plane, reg[0], arow, orow);
             emit_elems<BITS, E>(reg[0], g * GROUP + tid * E, k, scale, alpha, crow, lane, n2);
         }
     }
@@ -282,7 +291,9 @@ quantize_kernel(const float *__restrict__ P, int64_t ldP, int32_t k, unsigned ch
     if (lane == 0) s_sum[wave] = n2;
     __syncthreads();
     if (tid == 0) {
-        const unsigned long long tot = (unsigned long long)s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+        unsigned long long tot = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) tot += s_sum[w];
         S_out[row] = S;
         rnorm_out[row] = tot ? (float)(1.0 / sqrt((double)tot)) : 0.0f;
     }
@@ -369,11 +380,14 @@ static void launch_quantize(const float *P, int64_t ldP, int nsplit, size_t plan
         const float *ap = accum ? accum + r0 * ldA : nullptr, *op = other ? other + r0 * ldO : nullptr;
         unsigned char *c = (unsigned char *)codes + r0 * ((int64_t)k * BITS / 8);
 #define QLESS_QB(NG) do { \
-            if (sum) hipLaunchKernelGGL((quantize_kernel<BITS, NG, true>), dim3((unsigned)rows), dim3(kQThreads), 0, st, \
+            if (sum) hipLaunchKernelGGL((quantize_kernel<BITS, (NG + 3) / 4, true, false, NG == 1 || NG == 2 ? NG * kQThreads : 4 * kQThreads>), dim3((unsigned)rows), \
+                                        dim3(NG == 1 || NG == 2 ? NG * kQThreads : 4 * kQThreads), 0, st, \
                                         p, ldP, k, c, S + r0, rnorm + r0, vec, nsplit, plane, kp, ldK, ap, ldA, op, ldO); \
             else hipLaunchKernelGGL((quantize_kernel<BITS, NG, false>), dim3((unsigned)rows), dim3(kQThreads), 0, st, \
                                     p, ldP, k, c, S + r0, rnorm + r0, vec, nsplit, plane, kp, ldK); } while (0)
-        if (groups <= 4) QLESS_QB(4);
+        if (groups == 1 && sum) QLESS_QB(1);
+        else if (groups == 2 && sum) QLESS_QB(2);
+        else if (groups <= 4) QLESS_QB(4);
         else if (groups <= 8) QLESS_QB(8);
         else if (groups <= 16) QLESS_QB(16);
         else QLESS_QB(0);
