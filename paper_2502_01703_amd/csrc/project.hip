@@ -20,6 +20,7 @@
 // ((h << s) & 0x88888888) | 0x22222222 places in the sign position of eight FP4 (E2M1) codes
 // of +-1.0 for K-step s; V_CVT_SCALEF32_PK_BF16_FP4 expands them to packed bf16 +-1.0, two
 // elements per instruction.
+#include <type_traits>
 #include "common.h"
 
 namespace qless {
@@ -521,7 +522,7 @@ template <int NR, int NX> struct NarrowShape {
 };
 
 template <ProjectInput IN, bool GAUSS, int NR, int NX>
-__global__ void __launch_bounds__(kWaves * 64, 2)
+__global__ void __launch_bounds__(kWaves * 64, NR == 1 ? 4 : 2)      // (wavefronts per SIMD: two workgroups of 16-row tiles)
 project_narrow_kernel(ProjectArgs a, GaussTable gt) {
     using Sh = NarrowShape<NR, NX>;
     constexpr int NK = Sh::NK, KB = kNarrowCols / 16, kSubBytes = Sh::kSubBytes, kStage = Sh::kStage;
@@ -543,7 +544,8 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
     const int64_t c_begin = (int64_t)split * a.stages_per_split * kStageD;
     int64_t c_end = c_begin + a.stages_per_split * kStageD;
     if (c_end > a.d_len) c_end = a.d_len;
-    const int nsub = (int)((c_end - c_begin + kStageD - 1) / kStageD), nstages = (nsub + NK - 1) / NK;
+    const int nsub = __builtin_amdgcn_readfirstlane((int)((c_end - c_begin + kStageD - 1) / kStageD)), nstages = (nsub + NK - 1) / NK;
+    const int nfull = __builtin_amdgcn_readfirstlane((int)((c_end - c_begin) / kStageD));      // sub-stages that are whole
 
     unsigned char *smem = lds + (GAUSS ? kGaussBytes : 0);
     const uint32_t lane4 = (uint32_t)lane * 4u;
@@ -562,24 +564,49 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) acc[r][kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-    // ---- staging through registers: 16-byte chunks of the stage, [sub-stage][row][chunk]
+    // ---- staging through registers, two stages ahead (but see below): chunks of eight elements of the stage, [sub-stage][row][chunk], as they are in
+    // memory.  Every stage requests the same loads without a branch (one would make the wait for a stage a wait for all of them): rows past
+    // the last one re-read it (never stored), sub-stages that are not whole the last whole one; what is left of a row there is read element
+    // by element where the stage is written to LDS.  (One stage ahead, with the end of the rows told apart by every load: fp32, 32 x 262144 -> 4096
+    // 90 us, now 72, 16 x 300000 -> 8192 114, now 103, 1024 x 16384 -> 512 35.6, now 32.4; bf16 at odd offsets 1 x 400000 -> 8192 131, now 125.)
     constexpr int kThreads = kWaves * 64, kChunks = kStage / 16, kPer = (kChunks + kThreads - 1) / kThreads;
-    uint4 regs[DIRECT ? 1 : kPer];
-    auto fetch = [&](int s) {
+    constexpr int kElem = IN == kStagedF32 ? 4 : 2, kRegs = kElem / 2;
+    // Gaussian bf16 tiles of 16 rows stay one stage ahead: their stages take longer than a load (two ahead, in twice the code, 1 x 100000 -> 8192 96 -> 98 us).
+    constexpr bool TWO = !(GAUSS && IN == kStagedBf16 && NR == 1);
+    uint4 regs[TWO ? 2 : 1][DIRECT ? 1 : kPer][kRegs];
+    struct Chunk { int at, sub; int64_t row, cc; };
+    auto chunk = [&](int i) {                      // thread's chunk i of a stage (past the last one: its first again, not written)
+        const int c = kChunks % kThreads == 0 || tid + kThreads * i < kChunks ? tid + kThreads * i : tid;
+        const int64_t row = row0 + c / 16 % Sh::kRows;
+        return Chunk{c, __builtin_amdgcn_readfirstlane(c / (kSubBytes / 16)), row < a.n ? row : a.n - 1, (int64_t)(c & 15) * 8};
+    };
+    auto fetch = [&](int set, int s) {             // (nfull > 0)
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const int c = tid + kThreads * i;
-            const int sub = c / (kSubBytes / 16), r = c / 16 % Sh::kRows, cc = c & 15;
-            const int64_t row = row0 + r, col = c_begin + ((int64_t)s * NK + sub) * kStageD + cc * 8;
-            const uint4 v = c < kChunks ? load_chunk<IN>(a, row, col, c_end) : make_uint4(0, 0, 0, 0);
-            regs[DIRECT ? 0 : i] = v;
+            const Chunk c = chunk(i);
+            const int q = s * NK + c.sub < nfull ? s * NK + c.sub : nfull - 1;
+            const unsigned char *p = (const unsigned char *)a.G + (c.row * a.ldG + c_begin + (int64_t)q * kStageD + c.cc) * kElem;
+#pragma unroll
+            for (int e = 0; e < kRegs; ++e) regs[set][DIRECT ? 0 : i][e] = load_any(p + 16 * e);
         }
     };
-    auto commit = [&](int buf) {
+    auto commit = [&](int set, int buf, int s) {
 #pragma unroll
         for (int i = 0; i < kPer; ++i) {
-            const int c = tid + kThreads * i, r = c >> 4, cc = c & 15;         // r counts rows over all sub-stages: r % 16 is the row's
-            if (c < kChunks) *(uint4 *)(smem + buf * kStage + r * 256 + ((cc ^ (r & 15)) << 4)) = regs[DIRECT ? 0 : i];
+            const Chunk c = chunk(i);
+            const int r = c.at >> 4, cc = c.at & 15;                            // r counts rows over all sub-stages: r % 16 is the row's
+            uint4 o;
+            if (s * NK + c.sub < nfull) {                                       // wave-uniform
+                const uint4 (&v)[kRegs] = regs[set][DIRECT ? 0 : i];
+                o = v[0];
+                if constexpr (kElem == 4) {
+                    auto f = [](uint32_t x) { return __uint_as_float(x); };
+                    o = make_uint4(pack2_bf16(f(v[0].x), f(v[0].y)), pack2_bf16(f(v[0].z), f(v[0].w)), pack2_bf16(f(v[1].x), f(v[1].y)), pack2_bf16(f(v[1].z), f(v[1].w)));
+                }
+            } else {
+                o = load_chunk<IN>(a, c.row, c_begin + ((int64_t)s * NK + c.sub) * kStageD + c.cc, c_end);
+            }
+            if (tid + kThreads * i < kChunks) *(uint4 *)(smem + buf * kStage + r * 256 + ((cc ^ (r & 15)) << 4)) = o;
         }
     };
     // ---- asynchronous copies of 1 KB (4 rows); past the end of a stage a wavefront repeats its last copy, past the end
@@ -614,8 +641,8 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
         for (int s = 0; s < RING - 1; ++s)
             if (s < nstages) issue(s);
     } else {
-        fetch(0);
-        commit(0);
+        if (nfull > 0) { fetch(0, 0); if (TWO) fetch(TWO ? 1 : 0, 1); }
+        commit(0, 0, 0);
         __syncthreads();
     }
 
@@ -623,14 +650,14 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
     asm volatile("" : "+v"(fp4_one));
     GaussRaw raw;
     GaussWords next;
-    for (int s = 0; s < nstages; ++s) {
-        const int buf = DIRECT ? s % RING : (s & 1);
+    auto stage = [&](int s, auto odd, auto only) { // odd: s % 2 where staged; only: there is no other one
+        const int buf = DIRECT ? s % RING : (int)odd;
         if (DIRECT) {
             if (s + RING - 2 < nstages) wait_vmcnt<(RING - 2) * kCopies>(); else wait_vmcnt<0>();
             __syncthreads();
             if (s + RING - 1 < nstages) issue(s + RING - 1);
-        } else if (s + 1 < nstages) {
-            fetch(s + 1);
+        } else if (!only) {
+            if constexpr (TWO) fetch(odd, s + 2); else fetch(0, s + 1);
         }
         const int sub = s * NK + wk;
         if (sub < nsub) {                                                       // wave-uniform
@@ -675,8 +702,24 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
             }
         }
         if (!DIRECT) {
-            if (s + 1 < nstages) commit(buf ^ 1);
+            if (!only && s + 1 < nstages) commit(TWO ? odd ^ 1 : 0, odd ^ 1, s + 1);
             __syncthreads();
+        }
+    };
+    typedef std::integral_constant<int, 0> Even;
+    typedef std::integral_constant<int, 1> Odd;
+    if (DIRECT) {
+        for (int s = 0; s < nstages; ++s) stage(s, Even(), std::false_type());
+    } else if (nfull == 0) {
+        stage(0, Even(), std::true_type());
+    } else if (!TWO) {
+        for (int s = 0; s < nstages; ++s) stage(s, s & 1, std::false_type());
+    } else {
+        for (int s = 0;;) {                        // the register sets by name
+            stage(s, Even(), std::false_type());
+            if (++s >= nstages) break;
+            stage(s, Odd(), std::false_type());
+            if (++s >= nstages) break;
         }
     }
     if (NK > 1) {

@@ -114,3 +114,16 @@ def test_staged_and_direct_agree():
         ca, cb = Q.project_quantize(A, 1024, 4, seed=9), Q.quantize(Q.project(B, 1024, seed=9), 4)
         for x, y in zip(ca, cb):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("kind", [Q.RADEMACHER, Q.GAUSSIAN])
+@pytest.mark.parametrize("n", [3, 17, 47])
+def test_staged_ends(kind, n):
+    """Rows staged through registers two stages ahead: slices of no, one and several whole sub-stages, with and without a rest."""
+    _say("staged rows n=%d kind=%d" % (n, kind))
+    for whole in (0, 1, 2, 3, 4, 5, 8):
+        for rest in (0, 1, 127):
+            d = 128 * whole + rest
+            if d:
+                _check(_gradients(n, d, 1, 1, torch.bfloat16, d), 192, kind, 13)
+                _check(_gradients(n, d, 0, 0, torch.float32, d), 576, kind, 13)
