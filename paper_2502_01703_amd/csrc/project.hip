@@ -164,6 +164,25 @@ __device__ inline uint4 load_chunk(const ProjectArgs &a, int64_t row, int64_t co
     return v;
 }
 
+// The same eight elements as they are in memory, of a row and columns that exist (no branch), and packed where they are written to LDS
+template <ProjectInput IN>
+struct RawChunk {
+    static constexpr int kElem = IN == kStagedF32 ? 4 : 2, kRegs = kElem / 2;
+    uint4 v[kRegs];
+    __device__ inline void load(const ProjectArgs &a, int64_t row, int64_t col) {
+        const unsigned char *p = (const unsigned char *)a.G + (row * a.ldG + col) * kElem;
+#pragma unroll
+        for (int e = 0; e < kRegs; ++e) v[e] = load_any(p + 16 * e);
+    }
+    __device__ inline uint4 packed() const {
+        if constexpr (kElem == 2) return v[0];
+        else {
+            auto two = [](uint32_t x, uint32_t y) { return pack2_bf16(__uint_as_float(x), __uint_as_float(y)); };
+            return make_uint4(two(v[0].x, v[0].y), two(v[0].z, v[0].w), two(v[1].x, v[1].y), two(v[1].z, v[1].w));
+        }
+    }
+};
+
 union Frag { bf16x8 v; bf16x2 p[4]; uint4 u; uint32_t w[4]; uint16_t h[8]; };
 
 // DIRECT: gradient tiles go global -> LDS asynchronously (no VGPR staging) into a ring of kRing
@@ -271,25 +290,28 @@ project_kernel(ProjectArgs a, GaussTable gt) {
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[nb][kb][v] = 0.0f;
 
-    // staging (register path): kTileRows rows x 16 chunks of 8 columns; thread handles chunks tid + kThreads*i
+    // staging (register path): kTileRows rows x 16 chunks of 8 columns; thread handles chunks tid + kThreads*i, one stage ahead, requested
+    // without a branch (fp32 with a branch and a conversion behind every load: 128 x 131072 -> 8192 210 us, now 192, Gaussian 306, now 276;
+    // 500 x 100000 -> 2048 178, now 152)
     constexpr int kThreads = kWaves * 64;
     constexpr int kChunksPerThread = kTileRows * (kStageD / 8) / kThreads;
-    uint4 stage_regs[DIRECT ? 1 : kChunksPerThread];
-    auto fetch = [&](int s) {
-        const int64_t cs = c_begin + (int64_t)s * kStageD;
+    const int nfull = __builtin_amdgcn_readfirstlane((int)((c_end - c_begin) / kStageD));      // stages that are whole
+    RawChunk<IN> stage_regs[DIRECT ? 1 : kChunksPerThread];
+    auto staged_row = [&](int i) { const int64_t row = row0 + ((tid + kThreads * i) >> 4); return row < a.n ? row : a.n - 1; };   // (never stored)
+    auto fetch = [&](int s) {                      // (nfull > 0)
+        const int64_t cs = c_begin + (int64_t)(s < nfull ? s : nfull - 1) * kStageD;
 #pragma unroll
-        for (int i = 0; i < kChunksPerThread; ++i) {
-            int c = tid + kThreads * i;
-            int r = c >> 4, cc = c & 15;
-            stage_regs[DIRECT ? 0 : i] = load_chunk<IN>(a, row0 + r, cs + cc * 8, c_end);
-        }
+        for (int i = 0; i < kChunksPerThread; ++i) stage_regs[DIRECT ? 0 : i].load(a, staged_row(i), cs + (tid & 15) * 8);
     };
-    auto commit = [&](int buf) {
+    auto commit = [&](int buf, int s) {
 #pragma unroll
         for (int i = 0; i < kChunksPerThread; ++i) {
             int c = tid + kThreads * i;
             int r = c >> 4, cc = c & 15;
-            *(uint4 *)(smem + buf * kStageBytes + r * kLdsStride + cc * 16) = stage_regs[DIRECT ? 0 : i];
+            uint4 o;
+            if (s < nfull) o = stage_regs[DIRECT ? 0 : i].packed();
+            else o = load_chunk<IN>(a, staged_row(i), c_begin + (int64_t)s * kStageD + cc * 8, c_end);
+            *(uint4 *)(smem + buf * kStageBytes + r * kLdsStride + cc * 16) = o;
         }
     };
 
@@ -351,8 +373,8 @@ project_kernel(ProjectArgs a, GaussTable gt) {
                 if (s < nstages) issue(s);
             if (nstages >= RING) wait_vmcnt<(RING - 1) * kCopies>(); else wait_vmcnt<0>();
         } else {
-            fetch(0);
-            commit(0);
+            if (nfull > 0) fetch(0);
+            commit(0, 0);
         }
         __syncthreads();                           // stage 0 and the table visible to all waves
         Frag ag[2][NB];
@@ -377,7 +399,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
                         // stage s + 1 is the oldest copy group in flight; RING - 2 younger ones may stay outstanding
                         if (s + RING - 1 < nstages) wait_vmcnt<(RING - 2) * kCopies>(); else wait_vmcnt<0>();
                     } else if (s + 1 < nstages) {
-                        commit(nbuf);
+                        commit(nbuf, s + 1);
                     }
                     __syncthreads();
                     if (DIRECT && s + RING < nstages) issue(buf);
@@ -414,8 +436,8 @@ project_kernel(ProjectArgs a, GaussTable gt) {
         for (int s = 0; s < RING - 1; ++s)
             if (s < nstages) issue(s);
     } else {
-        fetch(0);
-        commit(0);
+        if (nfull > 0) fetch(0);
+        commit(0, 0);
         __syncthreads();
     }
 
@@ -467,7 +489,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
             }
         }
         if (!DIRECT) {
-            if (s + 1 < nstages) commit(buf ^ 1);
+            if (s + 1 < nstages) commit(buf ^ 1, s + 1);
             __syncthreads();
         }
     }
@@ -570,10 +592,9 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
     // by element where the stage is written to LDS.  (One stage ahead, with the end of the rows told apart by every load: fp32, 32 x 262144 -> 4096
     // 90 us, now 72, 16 x 300000 -> 8192 114, now 103, 1024 x 16384 -> 512 35.6, now 32.4; bf16 at odd offsets 1 x 400000 -> 8192 131, now 125.)
     constexpr int kThreads = kWaves * 64, kChunks = kStage / 16, kPer = (kChunks + kThreads - 1) / kThreads;
-    constexpr int kElem = IN == kStagedF32 ? 4 : 2, kRegs = kElem / 2;
     // Gaussian bf16 tiles of 16 rows stay one stage ahead: their stages take longer than a load (two ahead, in twice the code, 1 x 100000 -> 8192 96 -> 98 us).
     constexpr bool TWO = !(GAUSS && IN == kStagedBf16 && NR == 1);
-    uint4 regs[TWO ? 2 : 1][DIRECT ? 1 : kPer][kRegs];
+    RawChunk<IN> regs[TWO ? 2 : 1][DIRECT ? 1 : kPer];
     struct Chunk { int at, sub; int64_t row, cc; };
     auto chunk = [&](int i) {                      // thread's chunk i of a stage (past the last one: its first again, not written)
         const int c = kChunks % kThreads == 0 || tid + kThreads * i < kChunks ? tid + kThreads * i : tid;
@@ -585,9 +606,7 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
         for (int i = 0; i < kPer; ++i) {
             const Chunk c = chunk(i);
             const int q = s * NK + c.sub < nfull ? s * NK + c.sub : nfull - 1;
-            const unsigned char *p = (const unsigned char *)a.G + (c.row * a.ldG + c_begin + (int64_t)q * kStageD + c.cc) * kElem;
-#pragma unroll
-            for (int e = 0; e < kRegs; ++e) regs[set][DIRECT ? 0 : i][e] = load_any(p + 16 * e);
+            regs[set][DIRECT ? 0 : i].load(a, c.row, c_begin + (int64_t)q * kStageD + c.cc);
         }
     };
     auto commit = [&](int set, int buf, int s) {
@@ -596,16 +615,8 @@ project_narrow_kernel(ProjectArgs a, GaussTable gt) {
             const Chunk c = chunk(i);
             const int r = c.at >> 4, cc = c.at & 15;                            // r counts rows over all sub-stages: r % 16 is the row's
             uint4 o;
-            if (s * NK + c.sub < nfull) {                                       // wave-uniform
-                const uint4 (&v)[kRegs] = regs[set][DIRECT ? 0 : i];
-                o = v[0];
-                if constexpr (kElem == 4) {
-                    auto f = [](uint32_t x) { return __uint_as_float(x); };
-                    o = make_uint4(pack2_bf16(f(v[0].x), f(v[0].y)), pack2_bf16(f(v[0].z), f(v[0].w)), pack2_bf16(f(v[1].x), f(v[1].y)), pack2_bf16(f(v[1].z), f(v[1].w)));
-                }
-            } else {
-                o = load_chunk<IN>(a, c.row, c_begin + ((int64_t)s * NK + c.sub) * kStageD + c.cc, c_end);
-            }
+            if (s * NK + c.sub < nfull) o = regs[set][DIRECT ? 0 : i].packed();                 // wave-uniform
+            else o = load_chunk<IN>(a, c.row, c_begin + ((int64_t)s * NK + c.sub) * kStageD + c.cc, c_end);
             if (tid + kThreads * i < kChunks) *(uint4 *)(smem + buf * kStage + r * 256 + ((cc ^ (r & 15)) << 4)) = o;
         }
     };

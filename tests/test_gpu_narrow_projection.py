@@ -117,7 +117,7 @@ def test_staged_and_direct_agree():
 
 
 @pytest.mark.parametrize("kind", [Q.RADEMACHER, Q.GAUSSIAN])
-@pytest.mark.parametrize("n", [3, 17, 47])
+@pytest.mark.parametrize("n", [3, 17, 47, 130, 700])
 def test_staged_ends(kind, n):
     """Rows staged through registers two stages ahead: slices of no, one and several whole sub-stages, with and without a rest."""
     _say("staged rows n=%d kind=%d" % (n, kind))
