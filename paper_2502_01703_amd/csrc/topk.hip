@@ -152,6 +152,8 @@ __device__ inline unsigned int block_scan(unsigned int v, unsigned int *part) {
 // two or three rounds for the scores of a datastore, whose keys lie close together (their leading bits, which a radix select starts
 // with, are the same for nearly all of them, so its first passes count into a handful of bins).  A range over most of the 32 bits (infinities,
 // NaN, both signs) puts nearly all keys into a few bins again: there the lanes that share the first one's bin are added at once.
+// The bins start at the smallest key, so the last one may end past the largest: the range that is kept ends there (without that the end wrapped
+// past 2^32 for NaN of bits 0x7FE00000 and above, whose keys are the last 2^21, and the rounds behind it counted nothing).
 // Bound: latency (top 5 % of 16384, 8192 and 4096 scores 28.4, 21.4 and 19.1 us with up to eight radix passes and the compaction, ranks and output in
 // launches of their own, now 17.5, 12.8 and 13.5; all scores equal 58 -> 27 us).
 template <int U>
@@ -220,7 +222,8 @@ topk_select_one_kernel(const float *score, int N, unsigned int k_sel, unsigned l
         }
         __syncthreads();
         lo += sh_bin << shift;
-        hi = lo + ((1u << shift) - 1u);
+        const uint32_t width = (1u << shift) - 1u;          // the bin's, which may reach past `hi` and past 2^32
+        hi = hi - lo < width ? hi : lo + width;
         rem = sh_left;
         cut = sh_count != rem;
         if (!cut || shift == 0) break;

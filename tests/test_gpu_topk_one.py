@@ -43,3 +43,24 @@ def test_topk_one_workgroup(kind):
             idx, val = Q.topk(dev, k_sel)
             np.testing.assert_array_equal(idx.cpu().numpy(), order[:k_sel])
             np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), s[order[:k_sel]].view(np.uint32))
+
+
+@pytest.mark.parametrize("payload", [0x7FFFFFFF, 0x7FF00000, 0x7FE00001, 0x7FE00000, 0x7FDFFFFF, 0xFFFFFFFF, 0x7F800001])
+def test_topk_one_workgroup_nan_payloads(payload):
+    """NaN whose keys are the first or last of the 32 bits, among scores of both signs and beside the lowest key: the bin that holds the threshold
+    may end past 2^32, and is cut again where fewer of them are wanted than it holds."""
+    print("[case] top-k, one workgroup, NaN %08X" % payload, flush=True)
+    for N in (33, 300, 2000, 4096, 8192, 16384):
+        for same in (2, 10, 20):
+            for lowest in (False, True):
+                s = _scores("distinct", N)
+                r = np.random.default_rng(N + same)
+                at = r.permutation(N)
+                s.view(np.uint32)[at[:same]] = payload
+                if lowest:
+                    s.view(np.uint32)[at[same]] = 0xFFFFFFFF
+                dev, order = torch.from_numpy(s).to("cuda"), _order(s)
+                for k_sel in sorted({1, same // 2, same - 1, same, same + 1, N // 2, N - 1}):
+                    idx, val = Q.topk(dev, k_sel)
+                    np.testing.assert_array_equal(idx.cpu().numpy(), order[:k_sel])
+                    np.testing.assert_array_equal(val.cpu().numpy().view(np.uint32), s[order[:k_sel]].view(np.uint32))
