@@ -602,6 +602,12 @@ extern "C" size_t qless_topk_workspace(int64_t N, int64_t k_sel) {
     return topk_plan(N, k_sel).total;
 }
 
+// Histograms of the first pass that its workgroups store one by one; 0: counted by atomics into one.  Every workgroup of the second pass reads
+// all of them, so they are few whatever N is, and fit where any selection's keys go.  Top 5 % with them and without: 16385 scores 20.9 and 22.0 us, 65536
+// 24.6 and 26.3, 131072 30.8 and 29.6, 270000 47.3 and 47.4, 10^6 (123 of them) 137 and 129, 10^7 (1221) 625 and 390.
+constexpr int kFirstParts = kSortBlock * 8 / 2048;
+static int first_pass_parts(int64_t N) { return N <= kFirstParts * (int64_t)8192 ? (int)((N + 8191) / 8192) : 0; }
+
 // Enqueues the whole selection on `st`; `ws` holds at least topk_plan(N, k_sel).total bytes, 8-byte
 // aligned; 1 <= k_sel <= N < 2^32, all pointers checked by the caller.
 static qless_status topk_run(const float *score, int64_t N, int64_t k_sel, int64_t *idx, float *val,
@@ -626,17 +632,15 @@ static qless_status topk_run(const float *score, int64_t N, int64_t k_sel, int64
     } else {
         const unsigned long long want = (unsigned long long)k_sel;
         const unsigned ex = (unsigned)extra;
-        // a histogram per workgroup of the first pass (2 KB, where the selected keys go later) if that leaves none more than two rounds of
-        // 4096 scores, so that its counts fit 16 bits and few are added; else by atomics into one that a launch clears (first two passes of
-        // 65536 scores: that launch, 3.8 and 5.1 us; without it 4.4 and 6.4)
-        int64_t nparts = (N + 8191) / 8192;
-        if (nparts > p.padded / 256) nparts = p.padded / 256;
+        // a histogram per workgroup of the first pass (2 KB, where the selected keys go later), of two rounds of 4096 scores at most so that its
+        // counts fit 16 bits; else by atomics into one that a launch clears
+        const int nparts = first_pass_parts(N);
         unsigned int *parts = (unsigned int *)sel;
         int64_t hblocks = (N + 2047) / 2048;
         if (hblocks > 2048) hblocks = 2048;
-        if (N <= nparts * 8192) {
+        if (nparts) {
             hipLaunchKernelGGL((topk_hist_kernel<0, true>), dim3((unsigned)nparts), dim3(1024), 0, st, score, N, state, hist, parts, 0, ex, want);
-            hipLaunchKernelGGL((topk_hist_kernel<1, true>), dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist, parts, (int)nparts, ex, want);
+            hipLaunchKernelGGL((topk_hist_kernel<1, true>), dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist, parts, nparts, ex, want);
         } else {
             hipLaunchKernelGGL(topk_init_kernel, dim3(1), dim3(256), 0, st, hist, state, want);
             hipLaunchKernelGGL((topk_hist_kernel<0, false>), dim3((unsigned)hblocks), dim3(256), 0, st, score, N, state, hist, parts, 0, ex, want);
@@ -736,3 +740,6 @@ extern "C" qless_status qless_topk_noalloc(const float *score, int64_t N, int64_
     // the tie counts are written before they are scanned), so nothing of the call before survives
     return topk_run(score, N, k_sel, idx, val, ws, (hipStream_t)stream);
 }
+
+// For the tests, host only: the histograms that every workgroup of the second pass reads in a selection from N scores by launches.
+extern "C" int qless_internal_topk_parts(int64_t N) { return first_pass_parts(N); }
