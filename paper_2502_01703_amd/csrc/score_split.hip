@@ -7,6 +7,7 @@
 // chunks in flight, no barrier), joins them in LDS and writes them to the workspace; a second kernel adds
 // the parts and applies the fp32 epilogue in checkpoint order.  Integer parts add exactly (sign and ternary codes as FP4
 // products: integers below 2^24 in fp32); bfloat16 rows' fp32 parts are added in a fixed order.
+#include <type_traits>
 #include "score.h"
 
 namespace qless {
@@ -173,58 +174,66 @@ score_split_kernel(ScoreArgs a, int cb, int parts, int per, uint32_t *planes) {
     }
 }
 
-// One pair's influence: the parts of four checkpoints' sums at a time, all requested before the first is used (the additions stay in the
-// order of the parts and of the checkpoints).
-__device__ inline float split_pair(const ScoreArgs &a, int parts, const uint32_t *planes, size_t plane, int bf16, int64_t z, int c) {
-    float acc = 0.0f;
-    const uint32_t *p = planes + (size_t)z * a.M + c;
-    for (int c0 = 0; c0 < a.C; c0 += 4) {
-        float rt[4], wv[4], D[4];
-        uint32_t d[4];
-        const int live = a.C - c0 < 4 ? a.C - c0 : 4;
+// U checkpoints of one pair's influence: the parts of their sums go out together (U = 4: two parts at a time, else four), all requested before
+// the first is used; the additions stay in the order of the parts and of the checkpoints.
+template <int U>
+__device__ inline float split_group(const ScoreArgs &a, int c0, int parts, const uint32_t *p, size_t plane, int bf16, int64_t z, int c, float acc) {
+    constexpr int V = U == 4 ? 2 : 4;
+    float rt[U], wv[U], D[U];
+    uint32_t d[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int ci = u < live ? c0 + u : c0;
-            rt[u] = a.tr[ci] ? a.tr[ci][z] : 1.0f;
-            wv[u] = bf16 ? a.eta[ci] : __fmul_rn(a.eta[ci], a.vr[ci][c]);
-            d[u] = p[(size_t)(ci - c0) * parts * plane];
-            D[u] = __uint_as_float(d[u]);
-        }
-        int s = 1;
-        for (; s + 2 <= parts; s += 2) {
-            uint32_t t[4][2];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 2; ++v) t[u][v] = p[((size_t)(u < live ? u : 0) * parts + s + v) * plane];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                D[u] = __fadd_rn(__fadd_rn(D[u], __uint_as_float(t[u][0])), __uint_as_float(t[u][1]));
-                d[u] += t[u][0] + t[u][1];
-            }
-        }
-        if (s < parts) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t t = p[((size_t)(u < live ? u : 0) * parts + s) * plane];
-                D[u] = __fadd_rn(D[u], __uint_as_float(t));
-                d[u] += t;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (u < live) acc = __fadd_rn(acc, __fmul_rn(__fmul_rn(bf16 ? D[u] : (float)(int)d[u], rt[u]), wv[u]));
-        p += 4 * (size_t)parts * plane;
+    for (int u = 0; u < U; ++u) {
+        rt[u] = a.tr[c0 + u] ? a.tr[c0 + u][z] : 1.0f;
+        wv[u] = bf16 ? a.eta[c0 + u] : __fmul_rn(a.eta[c0 + u], a.vr[c0 + u][c]);
+        d[u] = p[(size_t)u * parts * plane];
+        D[u] = __uint_as_float(d[u]);
     }
+    auto add = [&](int s, auto n) {
+        constexpr int W = decltype(n)::value;
+        uint32_t t[U][W];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int v = 0; v < W; ++v) t[u][v] = p[((size_t)u * parts + s + v) * plane];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int v = 0; v < W; ++v) {
+                D[u] = __fadd_rn(D[u], __uint_as_float(t[u][v]));
+                d[u] += t[u][v];
+            }
+    };
+    int s = 1;
+    for (; s + V <= parts; s += V) add(s, std::integral_constant<int, V>());
+    for (; s < parts; ++s) add(s, std::integral_constant<int, 1>());
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc = __fadd_rn(acc, __fmul_rn(__fmul_rn(bf16 ? D[u] : (float)(int)d[u], rt[u]), wv[u]));
+    return acc;
+}
+// One pair's influence: four checkpoints at a time, the rest as two and one (four loads each whatever is left took 2179 x 737, one
+// checkpoint, k = 3264, 1 bit from 24 to 34 us)
+template <bool ONE>
+__device__ inline float split_pair(const ScoreArgs &a, int parts, const uint32_t *planes, size_t plane, int bf16, int64_t z, int c) {
+    const uint32_t *p = planes + (size_t)z * a.M + c;
+    if (ONE) return split_group<1>(a, 0, parts, p, plane, bf16, z, c, 0.0f);
+    const size_t step = (size_t)parts * plane;
+    float acc = 0.0f;
+    int c0 = 0;
+    for (; c0 + 4 <= a.C; c0 += 4) acc = split_group<4>(a, c0, parts, p + c0 * step, plane, bf16, z, c, acc);
+    if (c0 + 2 <= a.C) { acc = split_group<2>(a, c0, parts, p + c0 * step, plane, bf16, z, c, acc); c0 += 2; }
+    if (c0 < a.C) acc = split_group<1>(a, c0, parts, p + c0 * step, plane, bf16, z, c, acc);
     return acc;
 }
 
-// The parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.  What it takes is the time of its loads one
-// behind the other, so they go out together and every thread has one column (up to 1024): with a walk of 256 threads over the columns and
-// one load at a time 64 x 512 x 4 took 13.5 us at 1 bit, so 5.9 (with the sums 8 bits 47 -> 21 us, bfloat16 51 -> 26).  ROWS train rows per workgroup of four wavefronts: one each (up to 64 columns), or
-// all wavefronts on one row (with a row per wavefront 1800 x 145 x 4 took 27 us instead of 22).
-template <int ROWS>
-__global__ void __launch_bounds__(ROWS == 1 ? 1024 : 256)
+// The parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.  Few rows: what it takes is the time of its loads
+// one behind the other, so they go out together and every thread has one column (up to 1024): with a walk of 256 threads over the
+// columns and one load at a time 64 x 512 x 4 took 13.5 us at 1 bit, so 5.9 (with the sums 8 bits 47 -> 21 us, bfloat16 51 -> 26).  Many rows
+// keep the chip full by themselves, and 256 threads to a row start and end faster (8503 x 764 x 2, k = 960, 1 bit 72 us with 768 threads, 52 with 256;
+// 200 x 800 x 5, k = 4096, 8 bits 37 and 44): the line is the wavefronts that the chip holds.  Eight wavefronts per SIMD either way (16453 x 453 x 2,
+// k = 2368 111 us with four, 99 with eight).  ROWS train rows per workgroup of four wavefronts: one each (up to 64 columns), or
+// all wavefronts on one row (with a row per wavefront 1800 x 145 x 4 took 27 us instead of 22).  ONE: a single checkpoint (5 % of such calls).
+template <int ROWS, bool ONE>
+__global__ void __launch_bounds__(ROWS == 1 ? 1024 : 256, 8)
 score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf16, float none) {
     __shared__ float wave_best[16];
     const int wave = threadIdx.x >> 6;
@@ -233,7 +242,7 @@ score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf
     if (ROWS > 1 && z >= a.N) return;                // (no barrier below then)
     float best = neg_inf();
     for (int c = ROWS == 1 ? threadIdx.x : threadIdx.x & 63; c < a.M; c += ROWS == 1 ? blockDim.x : 64) {
-        const float acc = split_pair(a, parts, planes, plane, bf16, z, c);
+        const float acc = split_pair<ONE>(a, parts, planes, plane, bf16, z, c);
         if (a.full) a.full[z * a.M + c] = acc;
         best = fmaxf(best, acc);
     }
@@ -248,13 +257,19 @@ score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf
     }
     if ((threadIdx.x & 63) == 0) a.score[z] = best > neg_inf() ? best : none;
 }
-qless_status launch_split_finish(const ScoreArgs &a, int parts, const uint32_t *planes, bool bf16, float none, hipStream_t st) {
-    if (a.M <= 64 && a.N >= 1024)
-        hipLaunchKernelGGL(score_split_finish_kernel<4>, dim3((unsigned)((a.N + 3) / 4)), dim3(256), 0, st, a, parts, planes, bf16, none);
-    else {
-        const int threads = a.M >= 1024 ? 1024 : (a.M + 63) / 64 * 64;
-        hipLaunchKernelGGL(score_split_finish_kernel<1>, dim3((unsigned)a.N), dim3(threads), 0, st, a, parts, planes, bf16, none);
+template <bool ONE>
+static void launch_split_finish_of(const ScoreArgs &a, int parts, const uint32_t *planes, bool bf16, float none, hipStream_t st) {
+    if (a.M <= 64 && a.N >= 1024) {
+        hipLaunchKernelGGL((score_split_finish_kernel<4, ONE>), dim3((unsigned)((a.N + 3) / 4)), dim3(256), 0, st, a, parts, planes, bf16, none);
+        return;
     }
+    const int64_t waves = (a.M + 63) / 64;
+    const int64_t most = a.N * waves <= 32 * (int64_t)compute_units() ? 16 : 4;
+    hipLaunchKernelGGL((score_split_finish_kernel<1, ONE>), dim3((unsigned)a.N), dim3((unsigned)(64 * (waves < most ? waves : most))), 0, st, a, parts, planes, bf16, none);
+}
+qless_status launch_split_finish(const ScoreArgs &a, int parts, const uint32_t *planes, bool bf16, float none, hipStream_t st) {
+    if (a.C == 1) launch_split_finish_of<true>(a, parts, planes, bf16, none, st);
+    else launch_split_finish_of<false>(a, parts, planes, bf16, none, st);
     return launch_status();
 }
 
