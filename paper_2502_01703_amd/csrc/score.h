@@ -36,12 +36,14 @@ void launch_score_finish(unsigned int *smax, int64_t N, float *score, hipStream_
 // score_wide.hip: 8-bit codes and bfloat16 rows (bits = 16) against more than 64 validation vectors.
 size_t wide_workspace(int64_t N, int32_t M, int64_t row_bytes, int C);
 // prepare = false: the workspace still holds the pre-pass of an earlier launch with the same validation
-// side, laid out for plan_rows >= a.N train rows (the finish kernel leaves the row maxima cleared)
-qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st, bool prepare = true, int64_t plan_rows = 0);
+// side, laid out for plan_rows >= a.N train rows (the finish kernel leaves the row maxima cleared).  shape: of the tile (here and below,
+// for the tests; otherwise the one that serves the call best)
+qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st, bool prepare = true, int64_t plan_rows = 0,
+                         int shape = -1);
 
 // score_codes.hip: 4-bit codes against more than 64 validation vectors.
 size_t codes_workspace(int64_t N, int32_t M, int64_t row_bytes, int C);
-qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st);
+qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st, int shape = -1);
 
 // score_fp4.hip: 1- and 2-bit codes (k a multiple of 128) against more than 64 validation vectors.
 // use_fp4: whether it serves a call faster than the 128 x 64 tiles of score.hip; share: with the planes of a call whose checkpoints
@@ -49,6 +51,8 @@ qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st);
 bool use_fp4(int64_t N, int32_t M, int32_t k, int bits, int C);
 size_t fp4_workspace(int64_t N, int32_t M, int32_t k, int bits, int C, bool share);
 qless_status launch_fp4(const ScoreArgs &a, int bits, void *ws, size_t ws_bytes, hipStream_t st);
+size_t fp4_workspace_as(int64_t N, int32_t M, int32_t k, int C, int parts);
+qless_status launch_fp4_as(const ScoreArgs &a, int bits, int shape, int parts, void *ws, hipStream_t st);
 
 // score_split.hip: few pairs (bits = 16: bfloat16 rows).  use_split: whether the path serves a call faster than the others.
 // Rows hold at least 16 bytes (16 per plane for the ternary codes).

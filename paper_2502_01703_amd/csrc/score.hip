@@ -1988,3 +1988,31 @@ extern "C" qless_status qless_score16(const void *const *train16, const void *co
     if (use_split(N, M, a.k, 16, C) && ws_bytes >= split_workspace(N, M, a.k, 16, C)) return launch_split(a, 16, no_score(kScoreTiles), ws, (hipStream_t)stream);
     return launch_mfma<8, true>(a, ws, ws_bytes, (hipStream_t)stream);
 }
+
+// For the tests: qless_score (bits = 16: qless_score16 of rows of k elements, without norms) of more than 64 validation vectors by the tile kernel of the width,
+// in tile shape `shape` of its table and, at 1 and 2 bits, with the K of a checkpoint shared out over `parts` workgroups (0: one workgroup
+// walks all checkpoints), so that the edges of a shape are reached whatever sizes it is chosen for.
+extern "C" size_t qless_internal_score_as_workspace(int64_t N, int32_t M, int32_t k, int bits, int C, int parts) {
+    if (bits <= 2) return fp4_workspace_as(N, M, k, C, parts);
+    return bits == 4 ? codes_workspace(N, M, k / 2, C) : wide_workspace(N, M, (int64_t)k * bits / 8, C);
+}
+extern "C" qless_status qless_internal_score_as(int shape, int parts, const void *const *train_codes, const float *const *train_rnorm,
+                                                const void *const *val_codes, const float *const *val_rnorm, const float *eta, int C, int64_t N,
+                                                int32_t M, int32_t k, int bits, float *score, float *full, void *ws, size_t ws_bytes, void *stream) {
+    if (!train_codes || !val_codes || !eta || (bits != 16 && (!train_rnorm || !val_rnorm))) return QLESS_ERR_INVALID_ARG;
+    if (C < 1 || C > QLESS_MAX_CHECKPOINTS || N < 1 || N > (int64_t)0x7FFFFFFF || M < 65 || k < 64 || k % 64 != 0 || k > 65536 || (!score && !full)) return QLESS_ERR_INVALID_ARG;
+    if (!(valid_bits(bits) || (bits == 16 && k <= 32768)) || shape < 0 || shape > (bits == 4 ? 2 : 3) + (bits <= 2 ? 3 : 0) || (bits > 2 && parts)) return QLESS_ERR_UNSUPPORTED;
+    if (!ws || (uintptr_t)ws % 16 || ws_bytes < qless_internal_score_as_workspace(N, M, k, bits, C, parts)) return QLESS_ERR_WORKSPACE;
+    ScoreArgs a{};
+    for (int i = 0; i < C; ++i) {
+        if ((uintptr_t)val_codes[i] % 16 || (uintptr_t)train_codes[i] % 16) return QLESS_ERR_INVALID_ARG;
+        a.tc[i] = (const unsigned char *)train_codes[i]; a.vc[i] = (const unsigned char *)val_codes[i];
+        a.tr[i] = bits == 16 ? nullptr : train_rnorm[i]; a.vr[i] = bits == 16 ? nullptr : val_rnorm[i]; a.eta[i] = eta[i];
+    }
+    a.C = C; a.N = N; a.M = M; a.k = bits == 16 ? 2 * k : k; a.score = score; a.full = full;
+    const qless_status ready = device_ready();
+    if (ready != QLESS_OK) return ready;
+    if (bits <= 2) return launch_fp4_as(a, bits, shape, parts, ws, (hipStream_t)stream);
+    if (bits == 4) return launch_codes(a, ws, (hipStream_t)stream, shape);
+    return launch_wide(a, bits, ws, (hipStream_t)stream, true, 0, shape);
+}

@@ -398,7 +398,7 @@ static int choose_codes_shape(int64_t N, int32_t M) {
     return best;
 }
 
-qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st) {
+qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st, int shape) {
     CodesPrep w{};
     w.cb = a.k / 2;
     w.nst = (w.cb + 127) / 128;
@@ -407,7 +407,7 @@ qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st) {
     unsigned char *base = (unsigned char *)ws;
     w.vexp = base; w.vw = (float *)(base + off_vw); w.vbias = (float *)(base + off_bias); w.smax = (unsigned int *)(base + off_smax);
     qless_status rc;
-    switch (choose_codes_shape(a.N, a.M)) {
+    switch (shape < 0 ? choose_codes_shape(a.N, a.M) : shape) {
         case 0: rc = launch_codes_shape<Codes256x192>(a, w, st); break;
         case 1: rc = launch_codes_shape<Codes256x128>(a, w, st); break;
         default: rc = launch_codes_shape<Codes512x96>(a, w, st); break;

@@ -428,12 +428,10 @@ bool use_fp4(int64_t N, int32_t M, int32_t k, int bits, int C) {
     return fp4_plan(N, M, k, bits, C, true).us + 8.0 < 17.0 + (double)((k + 511) / 512) * C * (1.15 + (crowd < 0.65 ? crowd : 0.65));
 }
 
-qless_status launch_fp4(const ScoreArgs &a, int bits, void *ws, size_t ws_bytes, hipStream_t st) {
+static qless_status launch_fp4_plan(const ScoreArgs &a, int bits, const Fp4Plan &p, void *ws, hipStream_t st) {
     Fp4Prep w{};
     w.cb = a.k / 8 * bits;
     w.nst = (a.k + 511) / 512;
-    // (a workspace laid out for a larger call may be too small for the planes: one workgroup walks all checkpoints then)
-    const Fp4Plan p = fp4_plan(a.N, a.M, a.k, bits, a.C, ws_bytes >= fp4_workspace(a.N, a.M, a.k, bits, a.C, true));
     size_t off_vw, off_bias, off_smax, off_planes, total;
     fp4_offsets(a.N, a.M, a.k, a.C, p.parts, &off_vw, &off_bias, &off_smax, &off_planes, &total);
     unsigned char *base = (unsigned char *)ws;
@@ -453,6 +451,22 @@ qless_status launch_fp4(const ScoreArgs &a, int bits, void *ws, size_t ws_bytes,
     if (p.parts) return launch_split_finish(a, p.parts, sp.planes, false, nan_below_all(), st);
     if (a.score) launch_score_finish(w.smax, a.N, a.score, st);
     return launch_status();
+}
+
+qless_status launch_fp4(const ScoreArgs &a, int bits, void *ws, size_t ws_bytes, hipStream_t st) {
+    // (a workspace laid out for a larger call may be too small for the planes: one workgroup walks all checkpoints then)
+    return launch_fp4_plan(a, bits, fp4_plan(a.N, a.M, a.k, bits, a.C, ws_bytes >= fp4_workspace(a.N, a.M, a.k, bits, a.C, true)), ws, st);
+}
+
+size_t fp4_workspace_as(int64_t N, int32_t M, int32_t k, int C, int parts) {
+    size_t v, b, s, p, t;
+    fp4_offsets(N, M, k, C, parts, &v, &b, &s, &p, &t);
+    return t;
+}
+qless_status launch_fp4_as(const ScoreArgs &a, int bits, int shape, int parts, void *ws, hipStream_t st) {
+    const int nst = (a.k + 511) / 512, per = parts ? (nst + parts - 1) / parts : nst;
+    if (shape < 0 || shape >= kFp4Shapes || kFp4Cost[shape].bits != bits || a.k % 128 != 0 || parts < 0 || (parts && (nst + per - 1) / per != parts)) return QLESS_ERR_UNSUPPORTED;
+    return launch_fp4_plan(a, bits, Fp4Plan{shape, parts, per, 0}, ws, st);
 }
 
 }  // namespace qless

@@ -339,7 +339,7 @@ static qless_status launch_wide_bits(const ScoreArgs &a, const WidePrep &w, int 
     }
 }
 
-qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st, bool prepare, int64_t plan_rows) {
+qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st, bool prepare, int64_t plan_rows, int shape) {
     const int64_t rows = plan_rows > 0 ? plan_rows : a.N;
     WidePrep w{};
     w.cb = bits == 16 ? a.k : a.k * bits / 8;
@@ -348,7 +348,7 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
     wide_offsets(rows, a.M, w.cb, a.C, &off_vw, &off_smax, &total);
     unsigned char *base = (unsigned char *)ws;
     w.vexp = base; w.vw = (float *)(base + off_vw); w.smax = (unsigned int *)(base + off_smax);
-    const int shape = choose_shape(rows, a.M, bits == 16);            // of plan_rows: the pre-pass is laid out for it
+    if (shape < 0) shape = choose_shape(rows, a.M, bits == 16);       // of plan_rows: the pre-pass is laid out for it
     qless_status rc;
     if (bits == 16) rc = launch_wide_bits<16>(a, w, shape, prepare, st);
     else rc = launch_wide_bits<8>(a, w, shape, prepare, st);

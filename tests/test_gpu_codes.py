@@ -5,18 +5,12 @@ import pytest
 import torch
 
 import oracle
+from named_tiles import score_as
 from paper_2502_01703_amd import binding as Q
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
 ETA = [1.0, -0.5, 0.25]
-SHAPES = ((256, 192), (256, 128), (512, 96))
-
-
-def _shape(N, M):
-    f = Q.lib().qless_internal_codes_shape
-    f.restype, f.argtypes = Q._c.c_int, [Q._i64, Q._i32]
-    return SHAPES[f(N, M)]
 
 
 def _bits(a):
@@ -41,10 +35,12 @@ def _codes(rows, k, C, seed, extreme):
     return [o[0] for o in out], [o[1] for o in out]
 
 
-def _check(N, M, k, C, extreme=0):
+def _check(N, M, k, C, extreme=0, tile=None):
+    """The named tile, or what qless_score takes."""
     tc, tr = _codes(N, k, C, N + k, extreme)
     vc, vr = _codes(M, k, C, M + k + 1, extreme)
-    got, full = Q.score(tc, tr, vc, vr, ETA[:C], k, 4, want_full=True)
+    public = Q.score(tc, tr, vc, vr, ETA[:C], k, 4)
+    got, full = score_as(tile, 0, tc, tr, vc, vr, ETA[:C], k, 4) if tile else Q.score(tc, tr, vc, vr, ETA[:C], k, 4, want_full=True)
     r = {0, N // 2, N - 1}
     for h in (256, 512):
         for m in (h, N // h * h):
@@ -57,7 +53,8 @@ def _check(N, M, k, C, extreme=0):
     np.testing.assert_array_equal(_bits(got[pick].cpu().numpy()), _bits(ref))
     np.testing.assert_array_equal(_bits(full[pick].cpu().numpy()), _bits(ref_full))
     assert torch.equal(full.amax(1), got)
-    assert torch.equal(Q.score(tc, tr, vc, vr, ETA[:C], k, 4), got)
+    assert torch.equal(public, got)
+    assert tile is None or torch.equal(score_as(tile, 0, tc, tr, vc, vr, ETA[:C], k, 4, want_full=False)[0], got)
 
 
 # k: rows of a quarter, half and three quarters of a line, of one line, of lines and a quarter, of as many lines as the rings hold and one
@@ -68,9 +65,8 @@ def _check(N, M, k, C, extreme=0):
     (32770, 128, 64, 2, (256, 128)), (131072, 96, 256, 2, (512, 96)), (130561, 95, 64, 1, (512, 96)), (131071, 96, 576, 2, (512, 96)),
     (130900, 90, 1024, 1, (512, 96)), (200, 16500, 64, 1, None), (255, 16400, 128, 1, None)])
 def test_every_shape(N, M, k, C, shape):
-    _ = shape is None or _shape(N, M) == shape or pytest.fail("this size takes %s" % (_shape(N, M),))
     print("[case] codes N=%d M=%d k=%d C=%d" % (N, M, k, C), flush=True)
-    _check(N, M, k, C)
+    _check(N, M, k, C, tile=shape)
 
 
 # the longest rows with the largest codes: sums next to 2^24 units

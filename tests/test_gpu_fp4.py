@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import oracle
+from named_tiles import score_as
 from paper_2502_01703_amd import binding as Q
 
 pytestmark = pytest.mark.gpu
@@ -35,10 +36,17 @@ def _store(rows, k, C, bits, seed):
     return [o[0] for o in out], [o[2] for o in out]
 
 
-def _check(N, M, k, bits, C, ws=None):
+def _check(N, M, k, bits, C, tile=None, parts=0, ws=None):
+    """The named tile, or what qless_score takes."""
     tc, tr = _store(N, k, C, bits, N + k)
     vc, vr = _store(M, k, C, bits, M + k + 1)
-    got, full = Q.score(tc, tr, vc, vr, ETA[:C], k, bits, want_full=True, ws=ws)
+    public = Q.score(tc, tr, vc, vr, ETA[:C], k, bits, ws=ws)
+    if tile:
+        got, full = score_as(tile, parts, tc, tr, vc, vr, ETA[:C], k, bits)
+        again = score_as(tile, parts, tc, tr, vc, vr, ETA[:C], k, bits, want_full=False)[0]
+    else:
+        got, full = Q.score(tc, tr, vc, vr, ETA[:C], k, bits, want_full=True, ws=ws)
+        again = public
     r = {0, N // 2, N - 1}
     for h in (256, 384, 512):
         for m in (h, N // h * h):
@@ -51,10 +59,10 @@ def _check(N, M, k, bits, C, ws=None):
     np.testing.assert_array_equal(_bits(got[pick].cpu().numpy()), _bits(ref))
     np.testing.assert_array_equal(_bits(full[pick].cpu().numpy()), _bits(ref_full))
     assert torch.equal(full.amax(1), got)
-    assert torch.equal(Q.score(tc, tr, vc, vr, ETA[:C], k, bits, ws=ws), got)
+    assert torch.equal(again, got) and torch.equal(public, got)
 
 
-# bits, N, M, k, C, rows and columns of the tile, parts per checkpoint (0: one workgroup walks all checkpoints).  Whole tiles and pieces, rows and
+# bits, N, M, k, C, rows and columns of the tile, parts per checkpoint (0: one workgroup walks all checkpoints), or what the call takes.  Whole tiles and pieces, rows and
 # columns that end inside a tile, rows that end inside a piece, fewer rows than a tile, one piece and as many as the ring holds and more
 @pytest.mark.parametrize("bits,N,M,k,C,plan", [
     (1, 22413, 488, 512, 1, (384, 128, 0)), (1, 41643, 219, 128, 2, (384, 128, 0)), (1, 39446, 193, 512, 1, (512, 96, 0)),
@@ -67,10 +75,8 @@ def _check(N, M, k, bits, C, ws=None):
     (2, 591, 522, 1024, 3, (256, 128, 1)), (2, 624, 495, 640, 3, (256, 128, 1)), (2, 323, 74, 1024, 2, (256, 128, 2)), (2, 305, 67, 640, 2, (256, 128, 2)),
     (2, 8192, 256, 4096, 4, (256, 128, 1))])
 def test_every_shape(bits, N, M, k, C, plan):
-    p = _plan(N, M, k, bits, C)
-    assert p[4] and (plan is None or tuple(p[:3]) == plan), p
     print("[case] fp4 bits=%d N=%d M=%d k=%d C=%d" % (bits, N, M, k, C), flush=True)
-    _check(N, M, k, bits, C)
+    _check(N, M, k, bits, C, *((plan[:2], plan[2]) if plan else ()))
 
 
 def test_workspace_laid_out_for_a_larger_call():
@@ -88,7 +94,6 @@ def test_rows_without_finite_norms():
     tc, tr = _store(N, k, C, bits, 1)
     vc, vr = _store(M, k, C, bits, 2)
     tr[0][5], tr[0][7] = float("nan"), float("inf")
-    shared = Q.score(tc, tr, vc, vr, ETA[:C], k, bits)
-    small = torch.empty(Q.score_workspace(50000, M, k, bits, C), dtype=torch.uint8, device=DEV)      # (without planes)
-    assert small.numel() < Q.score_workspace(N, M, k, bits, C)
-    assert torch.equal(shared.view(torch.int32), Q.score(tc, tr, vc, vr, ETA[:C], k, bits, ws=small).view(torch.int32))
+    public = Q.score(tc, tr, vc, vr, ETA[:C], k, bits)
+    for parts in (0, 1, 3):
+        assert torch.equal(score_as((256, 128), parts, tc, tr, vc, vr, ETA[:C], k, bits)[0].view(torch.int32), public.view(torch.int32))

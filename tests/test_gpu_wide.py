@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import oracle
+from named_tiles import SHAPES, score_as
 from paper_2502_01703_amd import binding as Q
 
 pytestmark = pytest.mark.gpu
@@ -123,3 +124,31 @@ def test_wide_rows_shorter_than_a_stage(N, M):
     np.testing.assert_array_equal(_bits(got[pick].cpu().numpy()), _bits(ref))
     np.testing.assert_array_equal(_bits(full[pick].cpu().numpy()), _bits(ref_full))
     assert torch.equal(full.amax(1), got)
+
+
+# whole tiles, one row less and one more, fewer rows than a tile; rows that end inside a line, of one line, of as many as the ring holds and more
+@pytest.mark.parametrize("bits", [8, 16])
+@pytest.mark.parametrize("tile", SHAPES[8])
+def test_wide_shapes(tile, bits):
+    h, w = tile
+    for N, M, k, C in ((8 * h, w + 1, 128, 1), (8 * h - 1, 2 * w, 192, 3), (9 * h + 1, max(w - 1, 65), 512, 2), (h + 2, w, 832, 2), (h - 1, 65, 64, 1)):
+        _say("wide tile %dx%d bits=%d N=%d M=%d k=%d C=%d" % (tile + (bits, N, M, k, C)))
+        if bits == 8:
+            tc, tr = _store(N, k, C, 8, N + k)
+            vc, vr = _store(M, k, C, 8, M + k)
+            want, want_full = Q.score(tc, tr, vc, vr, ETA[:C], k, 8, want_full=True)
+            got, full = score_as(tile, 0, tc, tr, vc, vr, ETA[:C], k, 8)
+            assert torch.equal(got, want) and torch.equal(full, want_full)
+            ref = oracle.score([t[-40:].cpu().numpy() for t in tc], [t[-40:].cpu().numpy() for t in tr], [v.cpu().numpy() for v in vc],
+                               [v.cpu().numpy() for v in vr], ETA[:C], k, 8)
+            np.testing.assert_array_equal(_bits(got[-40:].cpu().numpy()), _bits(ref[0] if isinstance(ref, tuple) else ref))
+        else:
+            g = torch.Generator(device=DEV)
+            g.manual_seed(N)
+            t16 = [Q.normalize16(torch.randn(N, k, generator=g, device=DEV)) for _ in range(C)]
+            v16 = [Q.normalize16(torch.randn(M, k, generator=g, device=DEV)) for _ in range(C)]
+            got, full = score_as(tile, 0, t16, None, v16, None, ETA[:C], k, 16)
+            ref = sum(e * (t.double() @ v.double().t()) for e, t, v in zip(ETA, t16, v16))
+            # fp32 sums of at most k / 16 chained additions of exact products of unit rows (|sum| <= 1): far inside C 2^-17
+            assert (full.double() - ref).abs().max() <= C * 2.0 ** -17
+        assert torch.equal(full.amax(1), got)
