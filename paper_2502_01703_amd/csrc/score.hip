@@ -1817,7 +1817,7 @@ extern "C" size_t qless_score_workspace(int64_t N, int32_t M, int32_t k, int bit
     if (N < 0 || M < 1 || k <= 0 || C < 1 || !valid_bits(bits)) return 0;
     const size_t need = score_base_workspace(N, M, k, bits, C);
     size_t split = score_splits(N, M, k, bits, C) ? split_workspace(N, M, (int64_t)k * bits / 8, bits, C) : 0;
-    if (!split && N > 0 && bits <= 2 && M > 64 && score_path(bits, M, k, C) == kScoreTiles) split = fp4_workspace(N, M, k, bits, C, true);
+    if (!split && N > 0 && bits <= 2 && M > 64 && score_path(bits, M, k, C) == kScoreTiles && use_fp4(N, M, k, bits, C)) split = fp4_workspace(N, M, k, bits, C, true);
     return split > need ? split : need;
 }
 

@@ -328,13 +328,15 @@ score_fp4_kernel(ScoreArgs a, Fp4Prep w, int64_t ttiles, int vtiles, Fp4Parts sp
     }
 }
 
-// ---- shapes.  piece_us: microseconds per piece (512 codes) of a round with a tile on every compute unit, measured at N = 270 000, k = 8192, C = 4,
-// M = 288 and 1024 (1 bit, M = 1024: 3.20, 3.27, 3.41 and 3.37 ms in the table's order, M = 288 1.23, 0.97, 1.18 and 1.28; 2 bits 3.60, 3.99 and
-// 3.73, and 1.34, 1.58 and 1.55).
-struct Fp4Cost { int bits, mt, vt; double piece_us; };
+// ---- shapes.  Microseconds of a round with a tile on every compute unit: per piece (512 codes), per checkpoint (its epilogue) and whatever its length.  These and
+// the other figures of fp4_plan and use_fp4 are fitted to 760 random calls (N = 256 .. 270 000, M = 65 .. 1024, k = 128 .. 16384, C = 1 .. 6), each run with every shape and
+// number of parts and, where the store is small, with the 128 x 64 tiles: the chosen kernel is 0.4 % (1 bit) and 0.9 % (2 bits) behind the fastest on small stores, the
+// chosen shape and parts 0.5 and 0.4 % in all, and no call but for 1 % of them more than 2 % slower than before this kernel (with prices from one k and C and
+// none for an epilogue 32 and 9 %, 2.1 and 2.9 %, and a tenth of the small stores slower).
+struct Fp4Cost { int bits, mt, vt; double piece_us, checkpoint_us, round_us; };
 constexpr int kFp4Shapes = 7;
-constexpr Fp4Cost kFp4Cost[kFp4Shapes] = {{1, 384, 128, 2.20}, {1, 512, 96, 2.15}, {1, 256, 192, 2.05}, {1, 256, 128, 1.52},
-                                          {2, 256, 192, 2.20}, {2, 256, 128, 1.83}, {2, 384, 128, 2.60}};
+constexpr Fp4Cost kFp4Cost[kFp4Shapes] = {{1, 384, 128, 1.85, 2.35, 6.5}, {1, 512, 96, 1.85, 1.55, 6.5}, {1, 256, 192, 1.80, 1.60, 6.5}, {1, 256, 128, 1.38, 1.25, 5.3},
+                                          {2, 256, 192, 2.08, 2.00, 6.8}, {2, 256, 128, 1.76, 1.30, 5.6}, {2, 384, 128, 2.34, 3.00, 7.4}};
 template <class Sh> constexpr bool fp4_is(const Fp4Cost &c) { return Sh::BITS == c.bits && Sh::MT == c.mt && Sh::VT == c.vt; }
 typedef Fp4Shape<1, 3, 2, 4, 2, 3> Fp4Signs384x128;
 typedef Fp4Shape<1, 2, 3, 8, 1, 3> Fp4Signs512x96;
@@ -365,9 +367,10 @@ static Fp4Plan fp4_plan(int64_t N, int32_t M, int32_t k, int bits, int C, bool s
             if (parts == last) continue;
             last = parts;
             const int64_t wgs = tiles * (parts ? (int64_t)parts * C : 1);
-            double us = (double)((wgs + cus - 1) / cus) * ((double)per * (parts ? 1 : C) * c.piece_us + 5.0);
+            const double round = parts ? per * c.piece_us * 1.08 + c.round_us - 1.0 : C * (per * c.piece_us + c.checkpoint_us) + c.round_us;
             const double bytes = (double)C * parts * (double)N * (double)M * 4;
-            if (parts) us += 5.0 + bytes * 2 / 4e6 + (double)N * 0.3e-3;
+            double us = (double)((wgs + cus - 1) / cus) * round;
+            if (parts) us += 3.5 + 0.5e-6 * (bytes < 20e6 ? bytes : 10e6 + 0.5 * bytes) + (double)N * 0.2e-3;
             if (bytes > (double)((size_t)256 << 20)) continue;
             if (best.shape < 0 || us < best.us) best = Fp4Plan{i, parts, per, us};
         }
@@ -417,15 +420,15 @@ static qless_status launch_fp4_shape(const ScoreArgs &a, Fp4Prep w, const Fp4Par
     return QLESS_OK;
 }
 
-// The 128 x 64 tiles of a small datastore (few enough for the chip to hold all of them) take about 17 us and 1.15 us per piece of a workgroup
-// with one of them on a compute unit, up to 1.8 with two; this path about 8 us and what its plan says (80 random calls with 512 .. 20 000 rows:
-// 8192 x 256 x 4, k = 16384, 2 bits 158 against 86 us, 5646 x 498 x 6, k = 4096 99 against 89, 4440 x 251 x 6, k = 1152 35 against 44).
+// The 128 x 64 tiles of a small datastore (few enough for the chip to hold all of them) take 9.2 us, 1.2 per piece of a workgroup with one of them on every
+// compute unit, 1.4 to 1.6 with two on some or all, and an epilogue per checkpoint; this path 7.8 us and what its plan says (843 x 1024 x 6, k = 256, 1 bit 18.7 against
+// 29.8 us, 3931 x 320 x 1, k = 4096 20.4 and 25.4; 2 bits 8192 x 256 x 4, k = 16384 158 and 86).
 bool use_fp4(int64_t N, int32_t M, int32_t k, int bits, int C) {
     const int64_t cus = compute_units();
     if (((N + 255) / 256) * ((M + 127) / 128) * 2 > cus) return true;
     const int64_t tiles = ((N + 127) / 128) * ((M + 63) / 64);
-    const double crowd = tiles <= cus ? 0.0 : 1.3 * (double)(tiles - cus) / (double)cus;
-    return fp4_plan(N, M, k, bits, C, true).us + 8.0 < 17.0 + (double)((k + 511) / 512) * C * (1.15 + (crowd < 0.65 ? crowd : 0.65));
+    const double piece = tiles <= cus ? 1.2 : 1.4 + 0.2 * (tiles >= 2 * cus ? 1.0 : (double)(tiles - cus) / (double)cus);
+    return fp4_plan(N, M, k, bits, C, true).us + 7.8 < 9.2 + C * ((k + 511) / 512 * piece + (bits == 1 ? 0.5 : 2.1));
 }
 
 static qless_status launch_fp4_plan(const ScoreArgs &a, int bits, const Fp4Plan &p, void *ws, hipStream_t st) {
