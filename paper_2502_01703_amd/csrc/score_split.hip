@@ -174,11 +174,11 @@ score_split_kernel(ScoreArgs a, int cb, int parts, int per, uint32_t *planes) {
     }
 }
 
-// U checkpoints of one pair's influence: the parts of their sums go out together (U = 4: two parts at a time, else four), all requested before
+// U checkpoints of one pair's influence: the parts of their sums go out together (two at a time, four of one or two checkpoints), all requested before
 // the first is used; the additions stay in the order of the parts and of the checkpoints.
 template <int U>
 __device__ inline float split_group(const ScoreArgs &a, int c0, int parts, const uint32_t *p, size_t plane, int bf16, int64_t z, int c, float acc) {
-    constexpr int V = U == 4 ? 2 : 4;
+    constexpr int V = U > 2 ? 2 : 4;
     float rt[U], wv[U], D[U];
     uint32_t d[U];
 #pragma unroll
@@ -210,7 +210,7 @@ __device__ inline float split_group(const ScoreArgs &a, int c0, int parts, const
     for (int u = 0; u < U; ++u) acc = __fadd_rn(acc, __fmul_rn(__fmul_rn(bf16 ? D[u] : (float)(int)d[u], rt[u]), wv[u]));
     return acc;
 }
-// One pair's influence: four checkpoints at a time, the rest as two and one (four loads each whatever is left took 2179 x 737, one
+// One pair's influence: four checkpoints at a time, the rest together (four loads each whatever is left took 2179 x 737, one
 // checkpoint, k = 3264, 1 bit from 24 to 34 us)
 template <bool ONE>
 __device__ inline float split_pair(const ScoreArgs &a, int parts, const uint32_t *planes, size_t plane, int bf16, int64_t z, int c) {
@@ -220,9 +220,11 @@ __device__ inline float split_pair(const ScoreArgs &a, int parts, const uint32_t
     float acc = 0.0f;
     int c0 = 0;
     for (; c0 + 4 <= a.C; c0 += 4) acc = split_group<4>(a, c0, parts, p + c0 * step, plane, bf16, z, c, acc);
-    if (c0 + 2 <= a.C) { acc = split_group<2>(a, c0, parts, p + c0 * step, plane, bf16, z, c, acc); c0 += 2; }
-    if (c0 < a.C) acc = split_group<1>(a, c0, parts, p + c0 * step, plane, bf16, z, c, acc);
-    return acc;
+    const int rest = a.C - c0;
+    p += c0 * step;
+    if (rest == 3) return split_group<3>(a, c0, parts, p, plane, bf16, z, c, acc);
+    if (rest == 2) return split_group<2>(a, c0, parts, p, plane, bf16, z, c, acc);
+    return rest ? split_group<1>(a, c0, parts, p, plane, bf16, z, c, acc) : acc;
 }
 
 // The parts of every pair added, the epilogue of Eq.(6),(7) in checkpoint order, row maximum.  Few rows: what it takes is the time of its loads

@@ -50,7 +50,7 @@ def test_split_codes_bit_exact(bits, N, M, k, C):
 
 
 # a thread per column up to 1024 of them, a walk above, and by 256 threads where the rows fill the chip (8192 wavefronts, one more, and one column
-# more than 256); checkpoints by four, two and one, parts by two and four, with every remainder
+# more than 256); checkpoints by four and what is left, parts by two and four, with every remainder
 @pytest.mark.parametrize("bits,N,M,k,C", [(1, 3, 1023, 8192, 5), (8, 2, 1024, 4096, 7), (4, 2, 1025, 4096, 9), (2, 3, 2049, 2048, 6), (8, 70, 257, 1024, 1),
                                           (8, 70, 64, 3072, 3), (4, 5, 65, 8192, 8), (1, 819, 640, 8192, 3), (1, 820, 640, 8192, 6), (1, 1639, 257, 8192, 1),
                                           (8, 33, 70, 16384, 1), (8, 33, 70, 16384, 2), (1, 1025, 64, 8192, 1), (1, 1027, 60, 8192, 7)])
