@@ -304,21 +304,27 @@ static qless_status launch_wide_shape(const ScoreArgs &a, WidePrep w, bool prepa
     return QLESS_OK;
 }
 
-// The shape with the least padded work: rounds of one workgroup per compute unit, times the tile's pairs, times what a
-// pair costs in the shape: 8 bits as measured with the kernel before this one (N = 270 000, M = 285 and 1024; 98 304 x 768 now takes 1103, 1129,
-// 1235 and 1314 us, relative to the padded pairs 1.00, 1.02, 1.12 and 1.19), bfloat16 65 536 x 512 and 98 304 x 768 (2020, 2153, 2136, 2561 and
-// 1066, 1092, 1193, 1292 us).  The validation tiles of a train tile run
+// The shape with the fastest rounds of one workgroup per compute unit.  A round takes so many microseconds per line of the rows, per checkpoint (its epilogue) and
+// whatever its length, 8-bit codes and bfloat16 rows each: fitted to 115 and 170 random calls (N = 500 .. 270 000, M = 65 .. 1024, k = 64 .. 16384, C = 1 .. 6),
+// each run with all four shapes.  Over these and another 98 and 140 the chosen one is 0.3 and 0.1 % behind the fastest, 10 and 5 % at most (with one price per
+// padded pair, of the kernel before this one at 8 bits, 1.2 and 0.7 %, 16 and 15 %; two calls of the 523 are 8 and 10 % slower for it): short rows want few
+// epilogues, 29 863 x 832 x 3, k = 128 bfloat16 66.8 us in 192 x 256 tiles, 59.4 in 256 x 192; long ones
+// the 192 x 256 tiles: 65 536 x 512 x 4, k = 8192 2020 and 2153 us).  The validation tiles of a train tile run
 // on one XCD, so the rounds are those of the XCD with the most train tiles: 25 316 x 773 in tiles of 256 x 192 is 495
 // workgroups, but 65 of them on three of the XCDs, a third round.
-static int choose_shape(int64_t N, int32_t M, bool bf16) {
-    static const struct { int mt, vt; double cost[2]; } s[4] = {{192, 256, {1.0, 1.0}}, {256, 192, {1.0, 1.03}}, {256, 128, {1.06, 1.14}}, {512, 96, {1.16, 1.22}}};
+struct WidePrice { int mt, vt; struct { double line, checkpoint, round; } us[2]; };
+constexpr int kWideShapes = 4;
+constexpr WidePrice kWidePrice[kWideShapes] = {{192, 256, {{1.164, 2.05, 8.6}, {0.985, 3.40, 9.0}}}, {256, 192, {{1.204, 1.85, 8.0}, {1.047, 1.60, 8.35}}},
+                                               {256, 128, {{0.945, 1.48, 5.5}, {0.805, 1.17, 6.2}}}, {512, 96, {{1.504, 1.65, 7.7}, {1.400, 1.22, 8.6}}}};
+static int choose_shape(int64_t N, int32_t M, int lines, int C, bool bf16) {
     const int64_t cus = (compute_units() + 7) / 8;                   // per XCD
     int best = 0;
     double least = 0;
-    for (int i = 0; i < 4; ++i) {
-        const int64_t ttiles = (N + s[i].mt - 1) / s[i].mt, tiles = (ttiles + 7) / 8 * ((M + s[i].vt - 1) / s[i].vt);
-        const double c = (double)((tiles + cus - 1) / cus) * s[i].mt * s[i].vt * s[i].cost[bf16];
-        if (i == 0 || c < least) { best = i; least = c; }
+    for (int i = 0; i < kWideShapes; ++i) {
+        const WidePrice &s = kWidePrice[i];
+        const int64_t ttiles = (N + s.mt - 1) / s.mt, tiles = (ttiles + 7) / 8 * ((M + s.vt - 1) / s.vt);
+        const double us = (double)((tiles + cus - 1) / cus) * (C * (lines * s.us[bf16].line + s.us[bf16].checkpoint) + s.us[bf16].round);
+        if (i == 0 || us < least) { best = i; least = us; }
     }
     return best;
 }
@@ -348,7 +354,7 @@ qless_status launch_wide(const ScoreArgs &a, int bits, void *ws, hipStream_t st,
     wide_offsets(rows, a.M, w.cb, a.C, &off_vw, &off_smax, &total);
     unsigned char *base = (unsigned char *)ws;
     w.vexp = base; w.vw = (float *)(base + off_vw); w.smax = (unsigned int *)(base + off_smax);
-    if (shape < 0) shape = choose_shape(rows, a.M, bits == 16);       // of plan_rows: the pre-pass is laid out for it
+    if (shape < 0) shape = choose_shape(rows, a.M, w.nst, a.C, bits == 16);       // of plan_rows: the pre-pass is laid out for it
     qless_status rc;
     if (bits == 16) rc = launch_wide_bits<16>(a, w, shape, prepare, st);
     else rc = launch_wide_bits<8>(a, w, shape, prepare, st);
@@ -394,5 +400,11 @@ extern "C" int64_t qless_internal_wide_reach(int64_t N, int row_bytes, int shape
     }
 }
 
-// For the tests, host only: the tile shape that a call of 8-bit codes with N train rows and M validation vectors takes.
-extern "C" int qless_internal_wide_shape(int64_t N, int32_t M) { return qless::choose_shape(N, M, false); }
+// For the tests, host only: the tile shape that a call takes (rows of row_bytes: 8-bit codes or, bf16 != 0, bfloat16), and the price of a round of a shape.
+extern "C" int qless_internal_wide_shape(int64_t N, int32_t M, int64_t row_bytes, int C, int bf16) {
+    return qless::choose_shape(N, M, (int)((row_bytes + 127) / 128), C, bf16 != 0);
+}
+extern "C" double qless_internal_wide_round(int shape, int64_t row_bytes, int C, int bf16) {
+    const auto &p = qless::kWidePrice[shape].us[bf16 != 0];
+    return C * ((double)((row_bytes + 127) / 128) * p.line + p.checkpoint) + p.round;
+}
