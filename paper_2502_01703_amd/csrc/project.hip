@@ -292,16 +292,21 @@ project_kernel(ProjectArgs a, GaussTable gt) {
 
     // staging (register path): kTileRows rows x 16 chunks of 8 columns; thread handles chunks tid + kThreads*i, one stage ahead, requested
     // without a branch (fp32 with a branch and a conversion behind every load: 128 x 131072 -> 8192 210 us, now 192, Gaussian 306, now 276;
-    // 500 x 100000 -> 2048 178, now 152)
+    // 500 x 100000 -> 2048 178, now 152).  The Rademacher tiles of 128 rows have no registers for that (8 and, fp32, 30 spilled: 128 x 4 044 256 -> 1088 fp32
+    // 1793 -> 1871 us, 349 x 1 118 053 -> 512 521 -> 581, bf16 337 -> 351) and keep packed chunks.
+    constexpr bool RAW = GAUSS || NB == 2;
     constexpr int kThreads = kWaves * 64;
     constexpr int kChunksPerThread = kTileRows * (kStageD / 8) / kThreads;
     const int nfull = __builtin_amdgcn_readfirstlane((int)((c_end - c_begin) / kStageD));      // stages that are whole
-    RawChunk<IN> stage_regs[DIRECT ? 1 : kChunksPerThread];
+    std::conditional_t<RAW, RawChunk<IN>, uint4> stage_regs[DIRECT ? 1 : kChunksPerThread];
     auto staged_row = [&](int i) { const int64_t row = row0 + ((tid + kThreads * i) >> 4); return row < a.n ? row : a.n - 1; };   // (never stored)
-    auto fetch = [&](int s) {                      // (nfull > 0)
-        const int64_t cs = c_begin + (int64_t)(s < nfull ? s : nfull - 1) * kStageD;
+    auto fetch = [&](int s) {                      // (RAW: nfull > 0)
+        const int64_t cs = c_begin + (int64_t)(!RAW || s < nfull ? s : nfull - 1) * kStageD;
 #pragma unroll
-        for (int i = 0; i < kChunksPerThread; ++i) stage_regs[DIRECT ? 0 : i].load(a, staged_row(i), cs + (tid & 15) * 8);
+        for (int i = 0; i < kChunksPerThread; ++i) {
+            if constexpr (RAW) stage_regs[DIRECT ? 0 : i].load(a, staged_row(i), cs + (tid & 15) * 8);
+            else stage_regs[DIRECT ? 0 : i] = load_chunk<IN>(a, row0 + ((tid + kThreads * i) >> 4), cs + (tid & 15) * 8, c_end);
+        }
     };
     auto commit = [&](int buf, int s) {
 #pragma unroll
@@ -309,7 +314,8 @@ project_kernel(ProjectArgs a, GaussTable gt) {
             int c = tid + kThreads * i;
             int r = c >> 4, cc = c & 15;
             uint4 o;
-            if (s < nfull) o = stage_regs[DIRECT ? 0 : i].packed();
+            if constexpr (!RAW) o = stage_regs[DIRECT ? 0 : i];
+            else if (s < nfull) o = stage_regs[DIRECT ? 0 : i].packed();
             else o = load_chunk<IN>(a, staged_row(i), c_begin + (int64_t)s * kStageD + cc * 8, c_end);
             *(uint4 *)(smem + buf * kStageBytes + r * kLdsStride + cc * 16) = o;
         }
@@ -436,7 +442,7 @@ project_kernel(ProjectArgs a, GaussTable gt) {
         for (int s = 0; s < RING - 1; ++s)
             if (s < nstages) issue(s);
     } else {
-        if (nfull > 0) fetch(0);
+        if (!RAW || nfull > 0) fetch(0);
         commit(0, 0);
         __syncthreads();
     }
