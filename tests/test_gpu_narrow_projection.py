@@ -38,12 +38,17 @@ def _check(G, k, kind, seed):
     return got
 
 
-def _tile(n, d, k, kind, dtype):
+def _plan(n, d, k, kind, dtype):
+    """Rows and columns of the tile, d-slices, stages per slice."""
     plan = Q.lib().qless_internal_project_plan
     plan.restype, plan.argtypes = None, [Q._i64, Q._i64, Q._i32, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
     out = (ctypes.c_int64 * 5)()
     plan(n, d, k, int(kind == Q.GAUSSIAN), int(dtype == torch.float32), ctypes.cast(out, ctypes.c_void_p))
-    return out[0], out[1]
+    return tuple(out[:4])
+
+
+def _tile(n, d, k, kind, dtype):
+    return _plan(n, d, k, kind, dtype)[:2]
 
 
 # (tile) -> {(kind, fp32): [(n, stages of 128 columns, k), ...]}
@@ -81,8 +86,8 @@ def test_every_tile(tile):
 def test_gaussian_ring(n, stages, per, tile):
     """Slices of fewer, as many and more stages than the ring holds: its first fill, its last stages and the look-ups past the end."""
     _say("Gaussian ring n=%d stages=%d" % (n, stages))
-    assert _tile(n, 128 * stages, 8256, Q.GAUSSIAN, torch.bfloat16) == tile
     for dtype, d, pad, lead in ((torch.bfloat16, 128 * stages, 0, 0), (torch.float32, 128 * stages - 3, 1, 0)):
+        assert _plan(n, d, 8256, Q.GAUSSIAN, dtype) == tile + (stages // per, per)
         _check(_gradients(n, d, pad, lead, dtype, n + d), 8256, Q.GAUSSIAN, 11)
 
 
