@@ -82,9 +82,14 @@ def init():
     _check(lib().qless_init(), "qless_init")
 
 
+# the current stream's handle itself: the Stream object around it costs 2.5 us of every call (torch does not promise this function)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    # the current stream's handle itself: the Stream object around it costs 2.5 us of every call
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check(status, what):
