@@ -385,14 +385,16 @@ static qless_status launch_codes_shape(const ScoreArgs &a, CodesPrep w, hipStrea
 // The shape whose rounds cost least: the rounds of the XCD that gets the most train tiles (all validation tiles of a train tile run on
 // one), times a tile's pairs, times what a pair costs in the shape: at N = 270 000, k = 8192, C = 4 the 256 x 192 tiles take 5.81 and 2.13 ms for
 // M = 1024 and 285 (1152 and 384 columns), 256 x 128 6.25 and 2.49 (1024 and 384), 512 x 96 6.19 and 1.96 (1056 and 288).
+struct CodesCost { int mt, vt; double pair; };
+constexpr CodesCost kCodesCost[3] = {{256, 192, 1.0}, {256, 128, 1.19}, {512, 96, 1.19}};
 static int choose_codes_shape(int64_t N, int32_t M) {
-    static const struct { int mt, vt; double cost; } s[3] = {{256, 192, 1.0}, {256, 128, 1.19}, {512, 96, 1.19}};
     const int64_t cus = (compute_units() + 7) / 8;                   // per XCD
     int best = 0;
     double least = 0;
     for (int i = 0; i < 3; ++i) {
-        const int64_t tiles = ((N + s[i].mt - 1) / s[i].mt + 7) / 8 * ((M + s[i].vt - 1) / s[i].vt);
-        const double c = (double)((tiles + cus - 1) / cus) * s[i].mt * s[i].vt * s[i].cost;
+        const CodesCost &s = kCodesCost[i];
+        const int64_t tiles = ((N + s.mt - 1) / s.mt + 7) / 8 * ((M + s.vt - 1) / s.vt);
+        const double c = (double)((tiles + cus - 1) / cus) * s.mt * s.vt * s.pair;
         if (i == 0 || c < least) { best = i; least = c; }
     }
     return best;
@@ -444,7 +446,8 @@ static int64_t codes_reach(int64_t N, int cb) {
 }  // namespace qless
 
 // For the tests, host only: the end of the last byte of the train rows that any copy of tile shape `shape` (256 x 192, 256 x 128,
-// 512 x 96) reads (at most N * row_bytes), from the kernel's own address arithmetic; and the shape that a call takes.
+// 512 x 96) reads (at most N * row_bytes), from the kernel's own address arithmetic; the shape that a call takes, and what a pair
+// costs in a shape.
 extern "C" int64_t qless_internal_codes_reach(int64_t N, int row_bytes, int shape) {
     using namespace qless;
     switch (shape) {
@@ -454,3 +457,4 @@ extern "C" int64_t qless_internal_codes_reach(int64_t N, int row_bytes, int shap
     }
 }
 extern "C" int qless_internal_codes_shape(int64_t N, int32_t M) { return qless::choose_codes_shape(N, M); }
+extern "C" double qless_internal_codes_pair(int shape) { return qless::kCodesCost[shape].pair; }
