@@ -184,8 +184,11 @@ qless_status qless_project_quantize_slice(const void *G, qless_dtype dt, int64_t
  *              bytes (0 for the configurations that need none).  It holds the validation codes
  *              as the tiled matrix-core paths stage them and the running row maxima; for sign codes
  *              against 17 .. 192 validation vectors a bit-permuted copy of the validation codes and
- *              their per-row counts; for few pairs partial dot products (at most 256 MB; a workspace
- *              laid out for more train rows serves such a call by the other paths if it cannot hold them);
+ *              their per-row counts; for few pairs, and for 1- and 2-bit calls against more than 64 validation vectors
+ *              whose few tiles share out their checkpoints, partial dot products, 4 N M bytes per checkpoint and part.
+ *              These are most of the answer where they occur (at most 256 MB, where the rest is a few MB); a workspace
+ *              that cannot hold them but the rest, such as one laid out for more train rows, serves the call without
+ *              them, with the same bits and in more time;
  *              the path that streams bit-plane codes against at most 16 validation vectors leaves it
  *              untouched, unless the checkpoints are scored in groups of
  *              launches (their validation rows do not all fit in LDS): then it carries N x 16 fp32
