@@ -2001,7 +2001,7 @@ extern "C" qless_status qless_internal_score_as(int shape, int parts, const void
                                                 int32_t M, int32_t k, int bits, float *score, float *full, void *ws, size_t ws_bytes, void *stream) {
     if (!train_codes || !val_codes || !eta || (bits != 16 && (!train_rnorm || !val_rnorm))) return QLESS_ERR_INVALID_ARG;
     if (C < 1 || C > QLESS_MAX_CHECKPOINTS || N < 1 || N > (int64_t)0x7FFFFFFF || M < 65 || k < 64 || k % 64 != 0 || k > 65536 || (!score && !full)) return QLESS_ERR_INVALID_ARG;
-    if (!(valid_bits(bits) || (bits == 16 && k <= 32768)) || shape < 0 || shape > (bits == 4 ? 2 : 3) + (bits <= 2 ? 3 : 0) || (bits > 2 && parts)) return QLESS_ERR_UNSUPPORTED;
+    if (!(valid_bits(bits) || (bits == 16 && k <= 32768)) || shape < 0 || shape > (bits <= 2 ? 6 : 3) || (bits > 2 && parts)) return QLESS_ERR_UNSUPPORTED;
     if (!ws || (uintptr_t)ws % 16 || ws_bytes < qless_internal_score_as_workspace(N, M, k, bits, C, parts)) return QLESS_ERR_WORKSPACE;
     ScoreArgs a{};
     for (int i = 0; i < C; ++i) {

@@ -10,7 +10,7 @@
 //     in a three-input operation (fp6_train).  The int8 form took six for eight codes and two instructions for their products.
 //   * The pre-pass writes the validation codes as FP6 numbers in that order, and the sum of a row: sum (q + 8) v - 8 sum v starts
 //     from an accumulator of -8 sum v.  Units of 1/64: |15 * 8 + 8 * 8| * 65536 < 2^24.
-//   * Tiles of 256 x 192, 256 x 128 or 512 x 96, eight wavefronts of 64 x 96 or 64 x 64: an unpacked train fragment feeds three (two)
+//   * Tiles of 256 x 192, 256 x 128, 512 x 96 or 192 x 256, eight wavefronts of 64 x 96, 64 x 64 or 96 x 64: an unpacked train fragment feeds three (two)
 //     matrix instructions.
 //   * Two rings: a line (128 bytes, 256 codes) of every train row of the tile in a ring of three (512 rows: two), half as many codes of
 //     every validation row in a ring of three, both filled asynchronously.  Train rows come from HBM and may take two lines' time,
@@ -37,11 +37,11 @@ struct CodesPrep {                             // workspace views (device pointe
     int32_t Mp, cb, nst;                       // padded validation rows, bytes and lines per train row
 };
 
-// A wavefront owns 2 x WC accumulators of 32 x 32, WY x WX wavefronts make a tile; NT lines of train rows in their ring.
-template <int WC_, int WY_, int WX_, int NT_>
+// A wavefront owns WR x WC accumulators of 32 x 32, WY x WX wavefronts make a tile; NT lines of train rows in their ring.
+template <int WR_, int WC_, int WY_, int WX_, int NT_>
 struct CodesShape {
-    static constexpr int WC = WC_, WY = WY_, WX = WX_, NT = NT_, NV = 3, NW = WY * WX;
-    static constexpr int MT = 64 * WY, VT = 32 * WC * WX;
+    static constexpr int WR = WR_, WC = WC_, WY = WY_, WX = WX_, NT = NT_, NV = 3, NW = WY * WX;
+    static constexpr int MT = 32 * WR * WY, VT = 32 * WC * WX;
     static constexpr int TBYTES = MT * 128, V16 = 4 * VT * 16, VBYTES = 4 * VT * 24;      // a line of train rows, half a line's validation rows
     static constexpr int TCP = TBYTES / 1024, VCP = VBYTES / 1024;              // 1 KB copies
     static constexpr int TU = TCP / NW, VU = (VCP + NW - 1) / NW;               // per wavefront
@@ -143,7 +143,7 @@ __host__ __device__ inline unsigned codes_offset(unsigned lane_row, unsigned lan
 template <class Sh, bool EDGE>
 __global__ void __launch_bounds__(64 * Sh::NW, Sh::NW / 4)
 score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
-    constexpr int WC = Sh::WC, WX = Sh::WX, NT = Sh::NT, NV = Sh::NV, NW = Sh::NW, MT = Sh::MT, VT = Sh::VT;
+    constexpr int WR = Sh::WR, WC = Sh::WC, WX = Sh::WX, NT = Sh::NT, NV = Sh::NV, NW = Sh::NW, MT = Sh::MT, VT = Sh::VT;
     constexpr int TBYTES = Sh::TBYTES, VBYTES = Sh::VBYTES, VCP = Sh::VCP, TU = Sh::TU, VU = Sh::VU;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];        // [NT][TBYTES], [NV][VBYTES]
     __shared__ unsigned int s_rowmax[MT];
@@ -154,7 +154,7 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
     if (tt >= ttiles) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    const int trow = wave / WX * 64, vcol = wave % WX * 32 * WC;                // this wavefront's corner inside the tile
+    const int trow = wave / WX * 32 * WR, vcol = wave % WX * 32 * WC;                // this wavefront's corner inside the tile
     const int64_t row0 = EDGE || tt * MT + MT <= a.N ? tt * MT : a.N - MT;
     for (int i = tid; i < MT; i += 64 * NW) s_rowmax[i] = 0u;
     const unsigned lds0 = (unsigned)(uintptr_t)((__attribute__((address_space(3))) unsigned char *)smem);
@@ -217,8 +217,8 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
     // [K step of the half line][half][row].
     const unsigned a_lane = (unsigned)(l32 * 128) + ((half ^ codes_swizzle((unsigned)l32)) << 4), a_base = (unsigned)(trow * 128);
     const unsigned b_lane = (unsigned)((half * VT + vcol + l32) * 8);
-    i32x4 fa[2];
-    i32x8 ua[2], fb[WC];
+    i32x4 fa[WR];
+    i32x8 ua[WR], fb[WC];
     auto load_a = [&](int b, int slot, int ks) {
         fa[b] = *(const i32x4 *)(smem + (a_lane ^ (unsigned)(ks << 5)) + (unsigned)(slot * TBYTES) + a_base + b * 4096);
     };
@@ -242,9 +242,9 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
     };
     auto pin = []() { __builtin_amdgcn_sched_barrier(0); };   // keeps the order below
 
-    float facc[2][WC][16];
+    float facc[WR][WC][16];
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < WR; ++b)
 #pragma unroll
         for (int c = 0; c < WC; ++c)
 #pragma unroll
@@ -267,25 +267,25 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < WC; ++c) load_b(c, 0, 0);
-    load_a(0, 0, 0);
-    load_a(1, 0, 0);
+#pragma unroll
+    for (int b = 0; b < WR; ++b) load_a(b, 0, 0);
     unpack(0, 0); unpack(0, 1);
     int tslot = 0, vslot = 0;
     for (int ci = 0; ci < a.C; ++ci) {
-        f32x16 acc[2][WC];
+        f32x16 acc[WR][WC];
 #pragma unroll
         for (int c = 0; c < WC; ++c) {
             const float start = w.vbias[ci * w.Mp + vt * VT + vcol + 32 * c + l32];
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < WR; ++b)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[b][c][v] = start;
         }
         for (int s = 0; s < nst; ++s) {
             const int tnext = tslot + 1 == NT ? 0 : tslot + 1;
-            // Column block by column block, both row blocks: a validation fragment is requested again (for the next K step) as soon
-            // as its second instruction is issued, four instructions before its next use; block 0 of the train rows is unpacked
-            // between its last instruction and the next K step's first, block 1 behind that one.  (Behind the very last line:
+            // Column block by column block, all row blocks: a validation fragment is requested again (for the next K step) as soon
+            // as its last instruction is issued, several instructions before its next use; block 0 of the train rows is unpacked
+            // between its last instruction and the next K step's first, the others each behind the one before.  (Behind the very last line:
             // whatever the rings hold, not used.)
 #pragma unroll
             for (int k4 = 0; k4 < 4; ++k4) {                                    // K steps of the line: h = k4 / 2 the half line
@@ -293,33 +293,28 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
                 const bool last = k4 & 1;                                       // of its half line
                 const int vnext = vslot + 1 == NV ? 0 : vslot + 1;
                 const int rt = k4 == 3 ? tnext : tslot, rv = last ? vnext : vslot, ra = (k4 + 1) & 3, rb = last ? 0 : 1;   // the next K step's
-                constexpr int I = 2 * WC, K0 = 1;                               // instructions of a K step; the last one's before the barrier
+                constexpr int I = WR * WC, K0 = 1;                               // instructions of a K step; the last one's before the barrier
 #pragma unroll
                 for (int i = 0; i < I; ++i) {
-                    const int c = i >> 1, b = i & 1;
+                    const int c = i / WR, b = i % WR;
                     pin();
                     acc[b][c] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ua[b], fb[c], acc[b][c], 2, 2, 0, 127, 0, 127);
                     asm volatile("" : "+v"(acc[b][c]) :: "memory");              // stays here, between the reads before and behind it
                     pin();
-                    if (i == 0) {
-                        unpack(1, 0); unpack(1, 1);
-                        if (!last) load_a(0, rt, ra);
+                    if (i + 1 < WR) { unpack(i + 1, 0); unpack(i + 1, 1); }
+                    if (last && i == K0) {
+                        // this wavefront's reads of the half line (and line) have returned and its share of the next one has
+                        // landed; the barrier says so of all wavefronts.  Younger: validation rows of the half line after it and,
+                        // with three lines in the ring or none needed now, a line of train rows.
+                        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                        if (h == 0 || NT == 3) wait_vmcnt<VU + TU>(); else wait_vmcnt<VU>();
+                        __builtin_amdgcn_s_barrier();
+                        asm volatile("" ::: "memory");
+                        pin();
+                        load_a(0, rt, ra);
                     }
-                    if (i == K0) {
-                        if (last) {
-                            // this wavefront's reads of the half line (and line) have returned and its share of the next one has
-                            // landed; the barrier says so of all wavefronts.  Younger: validation rows of the half line after it and,
-                            // with three lines in the ring or none needed now, a line of train rows.
-                            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-                            if (h == 0 || NT == 3) wait_vmcnt<VU + TU>(); else wait_vmcnt<VU>();
-                            __builtin_amdgcn_s_barrier();
-                            asm volatile("" ::: "memory");
-                            pin();
-                            load_a(0, rt, ra);
-                        }
-                        load_a(1, rt, ra);
-                    }
-                    if (b == 1) load_b(c, rv, rb);
+                    if (i < WR && !(last && i < K0)) load_a(i, rt, ra);          // (unpacked by now)
+                    if (b == WR - 1) load_b(c, rv, rb);
                     if (i >= I - 2) { pin(); unpack(0, i - (I - 2)); }
                     if (last && i >= K0) {
                         const int n = VU + (h == 1 ? TU : 0);                   // copies, spread over the instructions behind the barrier
@@ -333,10 +328,10 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
             next_train();
             tslot = tnext;
         }
-        tile_add_checkpoint<2, WC>(acc, 64.0f, a.tr[ci], row0 + trow, a.N, w.vw + ci * w.Mp + vt * VT + vcol, facc);      // acc = D / 64
+        tile_add_checkpoint<WR, WC>(acc, 64.0f, a.tr[ci], row0 + trow, a.N, w.vw + ci * w.Mp + vt * VT + vcol, facc);      // acc = D / 64
     }
     wait_vmcnt<0>();                                      // no copy is under way when the workgroup gives its LDS back
-    tile_finish<2, WC>(a, facc, row0, trow, vt * VT + vcol, s_rowmax);
+    tile_finish<WR, WC>(a, facc, row0, trow, vt * VT + vcol, s_rowmax);
     if (a.score) {
         __syncthreads();
         for (int i = tid; i < MT; i += 64 * NW)
@@ -344,10 +339,10 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
     }
 }
 
-// Padded validation rows: at most M + 191.
+// Padded validation rows: at most M + 255.
 static void codes_offsets(int64_t N, int32_t M, int64_t cb, int C, size_t *off_vw, size_t *off_bias, size_t *off_smax, size_t *total) {
     auto up = [](size_t o) { return (o + 255) & ~(size_t)255; };
-    const size_t rows = (size_t)(M + 191);
+    const size_t rows = (size_t)(M + 255);
     *off_vw = up((size_t)C * rows * (size_t)((cb + 127) / 128 * 192));
     *off_bias = up(*off_vw + (size_t)C * rows * 4);
     *off_smax = up(*off_bias + (size_t)C * rows * 4);
@@ -359,9 +354,10 @@ size_t codes_workspace(int64_t N, int32_t M, int64_t row_bytes, int C) {
     return t;
 }
 
-typedef CodesShape<3, 4, 2, 3> Codes256x192;
-typedef CodesShape<2, 4, 2, 3> Codes256x128;
-typedef CodesShape<3, 8, 1, 2> Codes512x96;
+typedef CodesShape<2, 3, 4, 2, 3> Codes256x192;
+typedef CodesShape<2, 2, 4, 2, 3> Codes256x128;
+typedef CodesShape<2, 3, 8, 1, 2> Codes512x96;
+typedef CodesShape<3, 2, 2, 4, 3> Codes192x256;
 
 template <class Sh>
 static qless_status launch_codes_shape(const ScoreArgs &a, CodesPrep w, hipStream_t st) {
@@ -382,20 +378,23 @@ static qless_status launch_codes_shape(const ScoreArgs &a, CodesPrep w, hipStrea
     return QLESS_OK;
 }
 
-// The shape whose rounds cost least: the rounds of the XCD that gets the most train tiles (all validation tiles of a train tile run on
-// one), times a tile's pairs, times what a pair costs in the shape: at N = 270 000, k = 8192, C = 4 the 256 x 192 tiles take 5.81 and 2.13 ms for
-// M = 1024 and 285 (1152 and 384 columns), 256 x 128 6.25 and 2.49 (1024 and 384), 512 x 96 6.19 and 1.96 (1056 and 288).
-struct CodesCost { int mt, vt; double pair; };
-constexpr CodesCost kCodesCost[3] = {{256, 192, 1.0}, {256, 128, 1.19}, {512, 96, 1.19}};
-static int choose_codes_shape(int64_t N, int32_t M) {
+// The shape with the fastest rounds, those of the XCD that gets the most train tiles (all validation tiles of a train tile run on
+// one).  A round takes so many microseconds per line of the rows, per checkpoint (its epilogue) and whatever its length, fitted to 389 random calls (N = 1500 ..
+// 270 000, M = 65 .. 1024, k = 64 .. 16384, C = 1 .. 6), each run with every shape: the chosen one is 0.3 % behind the fastest (without the 192 x 256 tiles and with one price per padded
+// pair 1.2 %, 32 % at most: 11 979 x 985 x 5, k = 5952 in tiles of 256 rows is 36 workgroups on most XCDs, a second round, 349 us; in 192 x 256 tiles 32, 254 us).
+struct CodesPrice { int mt, vt; double line, checkpoint, round; };
+constexpr int kCodesShapes = 4;
+constexpr CodesPrice kCodesPrice[kCodesShapes] = {{256, 192, 1.55, 2.2, 8.3}, {256, 128, 1.34, 1.4, 5.7}, {512, 96, 1.76, 2.1, 8.4}, {192, 256, 1.65, 3.1, 8.3}};
+static double codes_round(int shape, int lines, int C) { return C * (lines * kCodesPrice[shape].line + kCodesPrice[shape].checkpoint) + kCodesPrice[shape].round; }
+static int choose_codes_shape(int64_t N, int32_t M, int lines, int C) {
     const int64_t cus = (compute_units() + 7) / 8;                   // per XCD
     int best = 0;
     double least = 0;
-    for (int i = 0; i < 3; ++i) {
-        const CodesCost &s = kCodesCost[i];
+    for (int i = 0; i < kCodesShapes; ++i) {
+        const CodesPrice &s = kCodesPrice[i];
         const int64_t tiles = ((N + s.mt - 1) / s.mt + 7) / 8 * ((M + s.vt - 1) / s.vt);
-        const double c = (double)((tiles + cus - 1) / cus) * s.mt * s.vt * s.pair;
-        if (i == 0 || c < least) { best = i; least = c; }
+        const double us = (double)((tiles + cus - 1) / cus) * codes_round(i, lines, C);
+        if (i == 0 || us < least) { best = i; least = us; }
     }
     return best;
 }
@@ -409,10 +408,11 @@ qless_status launch_codes(const ScoreArgs &a, void *ws, hipStream_t st, int shap
     unsigned char *base = (unsigned char *)ws;
     w.vexp = base; w.vw = (float *)(base + off_vw); w.vbias = (float *)(base + off_bias); w.smax = (unsigned int *)(base + off_smax);
     qless_status rc;
-    switch (shape < 0 ? choose_codes_shape(a.N, a.M) : shape) {
+    switch (shape < 0 ? choose_codes_shape(a.N, a.M, w.nst, a.C) : shape) {
         case 0: rc = launch_codes_shape<Codes256x192>(a, w, st); break;
         case 1: rc = launch_codes_shape<Codes256x128>(a, w, st); break;
-        default: rc = launch_codes_shape<Codes512x96>(a, w, st); break;
+        case 2: rc = launch_codes_shape<Codes512x96>(a, w, st); break;
+        default: rc = launch_codes_shape<Codes192x256>(a, w, st); break;
     }
     if (rc != QLESS_OK) return rc;
     if (a.score) launch_score_finish(w.smax, a.N, a.score, st);
@@ -445,16 +445,16 @@ static int64_t codes_reach(int64_t N, int cb) {
 
 }  // namespace qless
 
-// For the tests, host only: the end of the last byte of the train rows that any copy of tile shape `shape` (256 x 192, 256 x 128,
-// 512 x 96) reads (at most N * row_bytes), from the kernel's own address arithmetic; the shape that a call takes, and what a pair
-// costs in a shape.
+// For the tests, host only: the end of the last byte of the train rows that any copy of tile shape `shape` (of the table above) reads (at most
+// N * row_bytes), from the kernel's own address arithmetic; the shape that a call takes, and the price of a round of a shape.
 extern "C" int64_t qless_internal_codes_reach(int64_t N, int row_bytes, int shape) {
     using namespace qless;
     switch (shape) {
         case 0: return codes_reach<Codes256x192>(N, row_bytes);
         case 1: return codes_reach<Codes256x128>(N, row_bytes);
-        default: return codes_reach<Codes512x96>(N, row_bytes);
+        case 2: return codes_reach<Codes512x96>(N, row_bytes);
+        default: return codes_reach<Codes192x256>(N, row_bytes);
     }
 }
-extern "C" int qless_internal_codes_shape(int64_t N, int32_t M) { return qless::choose_codes_shape(N, M); }
-extern "C" double qless_internal_codes_pair(int shape) { return qless::kCodesCost[shape].pair; }
+extern "C" int qless_internal_codes_shape(int64_t N, int32_t M, int64_t row_bytes, int C) { return qless::choose_codes_shape(N, M, (int)((row_bytes + 127) / 128), C); }
+extern "C" double qless_internal_codes_round(int shape, int64_t row_bytes, int C) { return qless::codes_round(shape, (int)((row_bytes + 127) / 128), C); }

@@ -4,7 +4,7 @@ import torch
 from paper_2502_01703_amd import binding as Q
 
 # train rows x validation rows, in the order of the kernels' tables
-SHAPES = {1: ((384, 128), (512, 96), (256, 192), (256, 128)), 2: ((256, 192), (256, 128), (384, 128)), 4: ((256, 192), (256, 128), (512, 96)),
+SHAPES = {1: ((384, 128), (512, 96), (256, 192), (256, 128)), 2: ((256, 192), (256, 128), (384, 128)), 4: ((256, 192), (256, 128), (512, 96), (192, 256)),
           8: ((192, 256), (256, 192), (256, 128), (512, 96))}
 SHAPES[16] = SHAPES[8]
 
