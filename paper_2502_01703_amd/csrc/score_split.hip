@@ -233,7 +233,7 @@ __device__ inline float split_pair(const ScoreArgs &a, int parts, const uint32_t
 // keep the chip full by themselves, and 256 threads to a row start and end faster (8503 x 764 x 2, k = 960, 1 bit 72 us with 768 threads, 52 with 256;
 // 200 x 800 x 5, k = 4096, 8 bits 37 and 44): the line is the wavefronts that the chip holds.  Eight wavefronts per SIMD either way (16453 x 453 x 2,
 // k = 2368 111 us with four, 99 with eight).  ROWS train rows per workgroup of four wavefronts: one each (up to 64 columns), or
-// all wavefronts on one row (with a row per wavefront 1800 x 145 x 4 took 27 us instead of 22).  ONE: a single checkpoint (5 % of such calls).
+// all wavefronts on one row (with a row per wavefront 1800 x 145 x 4 took 27 us instead of 22).  ONE: a single checkpoint, whose calls that makes 5 % faster.
 template <int ROWS, bool ONE>
 __global__ void __launch_bounds__(ROWS == 1 ? 1024 : 256, 8)
 score_split_finish_kernel(ScoreArgs a, int parts, const uint32_t *planes, int bf16, float none) {
