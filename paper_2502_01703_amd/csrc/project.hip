@@ -1031,3 +1031,13 @@ extern "C" void qless_internal_project_plan(int64_t n, int64_t d_len, int32_t k,
     out[0] = kTileCost[p.shape].rows; out[1] = kTileCost[p.shape].cols;
     out[2] = p.nsplit; out[3] = p.stages_per_split; out[4] = (int64_t)p.ws_bytes;
 }
+
+// For the tests: bytes of scratch memory (spilled registers) per lane of the Rademacher kernel of 64- or 128-row tiles whose rows pass through
+// registers; -1 if the device does not say.
+extern "C" int qless_internal_project_scratch(int rows, int fp32) {
+    using namespace qless;
+    const void *fn = rows == 128 ? (fp32 ? (const void *)project_kernel<kStagedF32, false, 4> : (const void *)project_kernel<kStagedBf16, false, 4>)
+                                 : (fp32 ? (const void *)project_kernel<kStagedF32, false, 2> : (const void *)project_kernel<kStagedBf16, false, 2>);
+    hipFuncAttributes at{};
+    return hipFuncGetAttributes(&at, fn) == hipSuccess ? (int)at.localSizeBytes : -1;
+}
