@@ -331,7 +331,7 @@ score_fp4_kernel(ScoreArgs a, Fp4Prep w, int64_t ttiles, int vtiles, Fp4Parts sp
 // ---- shapes.  Microseconds of a round with a tile on every compute unit: per piece (512 codes), per checkpoint (its epilogue) and whatever its length.  These and
 // the other figures of fp4_plan and use_fp4 are fitted to 760 random calls (N = 256 .. 270 000, M = 65 .. 1024, k = 128 .. 16384, C = 1 .. 6), each run with every shape and
 // number of parts and, where the store is small, with the 128 x 64 tiles: the chosen kernel is 0.4 % (1 bit) and 0.9 % (2 bits) behind the fastest on small stores, the
-// chosen shape and parts 0.5 and 0.4 % in all, and no call but for 1 % of them more than 2 % slower than before this kernel (with prices from one k and C and
+// chosen shape and parts 0.5 and 0.4 % in all; on another 118 small stores 1.4 %, and none of these more than 3 % slower than before this kernel (with prices from one k and C and
 // none for an epilogue 32 and 9 %, 2.1 and 2.9 %, and a tenth of the small stores slower).
 struct Fp4Cost { int bits, mt, vt; double piece_us, checkpoint_us, round_us; };
 constexpr int kFp4Shapes = 7;
