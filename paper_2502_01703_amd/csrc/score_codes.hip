@@ -339,10 +339,11 @@ score_codes_kernel(ScoreArgs a, CodesPrep w, int64_t ttiles, int vtiles) {
     }
 }
 
-// Padded validation rows: at most M + 255.
+// Padded validation rows: at most M + 191 (a shape that pads more does not serve the call).
+constexpr int kCodesPad = 191;
 static void codes_offsets(int64_t N, int32_t M, int64_t cb, int C, size_t *off_vw, size_t *off_bias, size_t *off_smax, size_t *total) {
     auto up = [](size_t o) { return (o + 255) & ~(size_t)255; };
-    const size_t rows = (size_t)(M + 255);
+    const size_t rows = (size_t)(M + kCodesPad);
     *off_vw = up((size_t)C * rows * (size_t)((cb + 127) / 128 * 192));
     *off_bias = up(*off_vw + (size_t)C * rows * 4);
     *off_smax = up(*off_bias + (size_t)C * rows * 4);
@@ -364,6 +365,7 @@ static qless_status launch_codes_shape(const ScoreArgs &a, CodesPrep w, hipStrea
     QLESS_LDS_KERNEL((score_codes_kernel<Sh, false>), Sh::LDS);
     QLESS_LDS_KERNEL((score_codes_kernel<Sh, true>), Sh::LDS);
     w.Mp = (a.M + Sh::VT - 1) / Sh::VT * Sh::VT;
+    if (w.Mp > a.M + kCodesPad) return QLESS_ERR_UNSUPPORTED;
     const int vtiles = w.Mp / Sh::VT;
     const int64_t ttiles = (a.N + Sh::MT - 1) / Sh::MT, grid = 8 * (int64_t)vtiles * ((ttiles + 7) / 8);
     if (grid > 0x7FFFFFFF) return QLESS_ERR_UNSUPPORTED;
@@ -392,6 +394,7 @@ static int choose_codes_shape(int64_t N, int32_t M, int lines, int C) {
     double least = 0;
     for (int i = 0; i < kCodesShapes; ++i) {
         const CodesPrice &s = kCodesPrice[i];
+        if ((M + s.vt - 1) / s.vt * s.vt > M + kCodesPad) continue;      // (the first shape never pads more)
         const int64_t tiles = ((N + s.mt - 1) / s.mt + 7) / 8 * ((M + s.vt - 1) / s.vt);
         const double us = (double)((tiles + cus - 1) / cus) * codes_round(i, lines, C);
         if (i == 0 || us < least) { best = i; least = us; }

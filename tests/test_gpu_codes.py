@@ -63,7 +63,7 @@ def _check(N, M, k, C, extreme=0, tile=None):
     (33024, 192, 64, 1, (256, 192)), (33025, 191, 128, 2, (256, 192)), (65537, 380, 192, 1, (256, 192)), (49151, 192, 512, 3, (256, 192)),
     (33026, 192, 832, 2, (256, 192)), (33025, 128, 256, 1, (256, 128)), (32769, 127, 320, 3, (256, 128)), (33024, 65, 768, 2, (256, 128)),
     (32770, 128, 64, 2, (256, 128)), (131072, 96, 256, 2, (512, 96)), (130561, 95, 64, 1, (512, 96)), (131071, 96, 576, 2, (512, 96)),
-    (130900, 90, 1024, 1, (512, 96)), (33024, 256, 64, 1, (192, 256)), (33025, 255, 128, 2, (192, 256)), (33023, 300, 192, 1, (192, 256)),
+    (130900, 90, 1024, 1, (512, 96)), (33024, 256, 64, 1, (192, 256)), (33025, 255, 128, 2, (192, 256)), (33023, 330, 192, 1, (192, 256)),
     (12287, 256, 512, 3, (192, 256)), (12289, 512, 832, 2, (192, 256)), (190, 256, 256, 1, (192, 256)), (193, 65, 1024, 2, (192, 256)), (200, 16500, 64, 1, None), (255, 16400, 128, 1, None)])
 def test_every_shape(N, M, k, C, shape):
     print("[case] codes N=%d M=%d k=%d C=%d" % (N, M, k, C), flush=True)
